@@ -1,24 +1,33 @@
 // Block scores, block softmax and block selection (Sec. 4.1, "Predicting Block Masks" and
-// "Selecting Blocks"), all in float64.  Two kernels:
+// "Selecting Blocks"), all in float64.
 //
-// logits_kernel: one workgroup computes R consecutive query-block rows of one head,
-//     logits[I][J] = scale * <q_pool[I], k_pool[J]>,
-//   four lanes sharing one J (16 dims each).  Every k_pool element is loaded once per workgroup and
-//   used for all R rows: k_pool of a head is re-read by every workgroup from L2, and that traffic is
-//   what bounds this step.  The logits go to a caller-provided workspace [heads, nb_q, nb_k].
+// Scores.  logits[I][J] = scale * <q_pool[I], k_pool[J]> on v_mfma_f64_16x16x4: a wave keeps 16 query
+//   rows (A operand) in registers and meets 16 key blocks (B operand) per 16 instructions.  Lane
+//   (i = lane%16, g = lane/16) holds dims 16g .. 16g+15 of row i of either operand, i.e. the contraction
+//   runs over the dims in the order s, 16+s, 32+s, 48+s for s = 0..15 and every lane loads 128
+//   consecutive bytes.  Accumulator register r of the lane is (row g + 4r, column i).
 //
-// select_kernel: one WAVE per row, the whole row in registers (lane l holds blocks l, l+64, ...),
-//   no LDS and no barriers.  The ranked prefix the method keeps is found without sorting:
-//   with key(p) = the bit pattern of p (monotone for p >= 0) and, for a threshold key C,
+// Selection.  One WAVE per row, the whole row in registers (lane l holds blocks l, l+64, ...).  The
+//   ranked prefix the method keeps is found without sorting: with key(p) = the bit pattern of p
+//   (monotone for p >= 0) and, for a threshold key C,
 //       M(C) = sum of p over {key >= C},   cnt(C) = number of blocks with key >= C,
 //   the block at which the ranked cumulative mass first reaches tau is the one with key
 //       T = max{C : cnt(C) >= 1 and M(C) >= tau},
-//   found by bisection over the key range [key(p_min), key(p_max)] (each step one wave-wide sum);
-//   the bisection stops as soon as one block is left in the window.  Blocks above T are kept;
-//   blocks that tie with T are kept in ascending block order while the running mass is below tau.
-//   The top-k floor is the same search with the predicate cnt(C) >= k.  The sums are taken in a
-//   fixed order (lane-local in ascending block order, then a butterfly), so results are
-//   deterministic; adding non-negative terms in a fixed order is monotone, which the bisection needs.
+//   found by bisection over the key range [key(p_min), key(p_max)].  Steps over the whole row are
+//   taken only until 64 blocks are left in the window; those are then put one to a lane and the rest of
+//   the steps cost one value per lane.  It stops as soon as one block is left in the window.
+//   Blocks above T are kept; blocks that tie with T are kept in ascending block order while the
+//   running mass is below tau.  The top-k floor is the same search with the predicate cnt(C) >= k.
+//   The sums are taken in a fixed order (lane-local in ascending block order, then a butterfly), so
+//   results are deterministic; adding non-negative terms in a fixed order is monotone, which the
+//   bisection needs.
+//
+// Two ways to launch.  Up to 512 key blocks one kernel does both: a workgroup of 16 waves computes the
+//   scores of 16 rows into LDS (64 KB at 512 key blocks, so two workgroups share a CU) and each wave then
+//   selects one of the rows.  Longer rows go through the workspace, [heads, nb_q, nb_k] float64, because
+//   16 of them do not fit the LDS.
+#include <type_traits>
+
 #include "bsga_internal.h"
 
 namespace bsga {
@@ -27,87 +36,99 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kD = 64;
+constexpr int kFusedRows = 16;       // rows (= waves) of a workgroup of the fused kernel
+constexpr int kFusedMaxBlocks = 512;
 
-template <int R>
-__global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restrict__ q_pool,
-                                                          const double* __restrict__ k_pool, int nb_q, int nb_k,
-                                                          double score_scale, double* __restrict__ logits) {
-  const int I0 = blockIdx.x * R;
-  const int h = blockIdx.y;
-  const int t = threadIdx.x;
-  // lane quarter qd of a group of four handles the 16-byte chunks qd, qd+4, ..., qd+28 of a row
-  const int qd = t & 3;
-  double2 qv[R][8];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int I = min(I0 + r, nb_q - 1);  // rows past the end repeat the last row and are not stored
-    const double2* qrow = reinterpret_cast<const double2*>(q_pool + (int64_t(h) * nb_q + I) * kD);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) qv[r][i] = qrow[4 * i + qd];
-  }
-  const double2* kbase = reinterpret_cast<const double2*>(k_pool + int64_t(h) * nb_k * kD);
-  for (int j0 = 0; j0 < nb_k; j0 += kThreads / 4) {
-    const int J = j0 + (t >> 2);
-    double acc[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = 0.0;
-    if (J < nb_k) {
-      const double2* krow = kbase + int64_t(J) * (kD / 2);
-      double2 kv[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) kv[i] = krow[4 * i + qd];
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[r] = fma(qv[r][i].x, kv[i].x, fma(qv[r][i].y, kv[i].y, acc[r]));
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      acc[r] += __shfl_xor(acc[r], 1);
-      acc[r] += __shfl_xor(acc[r], 2);
-      if (qd == 0 && J < nb_k && I0 + r < nb_q)
-        logits[(int64_t(h) * nb_q + I0 + r) * nb_k + J] = score_scale * acc[r];
-    }
-  }
-}
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-__device__ inline double wave_sum_all(double v) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
-  return v;  // the butterfly leaves the same bits in every lane
-}
-__device__ inline int wave_sum_all(int v) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
+// ---- wave-wide reductions over DPP and row swaps (no LDS round trips) -----------------------------
+// Six steps pair up lanes 1, 2, 4, 8, 16 and 32 apart (the mirrors do 4 and 8: lanes of a quad, then of
+// half a row, already agree); every lane ends with the same bits.
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_all(T v, Op op) {
+  static_assert(sizeof(T) == 8, "64-bit values");
+  auto step = [&](auto ctrl) {
+    const uint2 x = __builtin_bit_cast(uint2, v);
+    const uint2 y = make_uint2(
+        static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x.x), decltype(ctrl)::value, 0xf, 0xf, false)),
+        static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x.y), decltype(ctrl)::value, 0xf, 0xf, false)));
+    v = op(v, __builtin_bit_cast(T, y));
+  };
+  step(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  step(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  step(std::integral_constant<int, 0x141>{});  // row_half_mirror
+  step(std::integral_constant<int, 0x140>{});  // row_mirror
+  {
+    const uint2 x = __builtin_bit_cast(uint2, v);
+    const auto lo = __builtin_amdgcn_permlane16_swap(x.x, x.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(x.y, x.y, false, false);
+    v = op(__builtin_bit_cast(T, make_uint2(lo[0], hi[0])), __builtin_bit_cast(T, make_uint2(lo[1], hi[1])));
+  }
+  {
+    const uint2 x = __builtin_bit_cast(uint2, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap(x.x, x.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(x.y, x.y, false, false);
+    v = op(__builtin_bit_cast(T, make_uint2(lo[0], hi[0])), __builtin_bit_cast(T, make_uint2(lo[1], hi[1])));
+  }
   return v;
 }
-__device__ inline uint64_t uniform64(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
+__device__ __forceinline__ double wave_sum(double v) {
+  return wave_all(v, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ double wave_max(double v) {
+  return wave_all(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ __forceinline__ double wave_min(double v) {
+  return wave_all(v, [](double a, double b) { return fmin(a, b); });
+}
+__device__ __forceinline__ uint64_t uniform_key(double v) {
+  const uint2 x = __builtin_bit_cast(uint2, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(x.x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(x.y);
   return (uint64_t(hi) << 32) | lo;
+}
+__device__ __forceinline__ double key_value(uint64_t key) { return __longlong_as_double(static_cast<long long>(key)); }
+__device__ __forceinline__ int votes(bool b) { return static_cast<int>(__popcll(__ballot(b))); }
+
+// exp(x) for x <= 0 (NaN stays NaN): x = n ln2 + r with |r| <= ln2 / 2, ln2 split in two so that n * hi is
+// exact, then the Taylor series to r^13 / 13! (the next term is below 2^-57 of the result) and a
+// scaling by 2^n.  Largest error against 80-bit exp over 4 million arguments in [-700, 0]: 0.87 units in the
+// last place.
+__device__ __forceinline__ double exp_nonpos(double x) {
+  const double t = x < -800.0 ? -800.0 : x;  // e^-800 is 0 in float64; keeps n finite for -inf
+  const double n = __builtin_rint(t * 1.4426950408889634074);
+  double r = fma(n, -6.93147180369123816490e-01, t);
+  r = fma(n, -1.90821492927058770002e-10, r);
+  double e = 1.0 / 6227020800.0;
+  e = fma(e, r, 1.0 / 479001600.0);
+  e = fma(e, r, 1.0 / 39916800.0);
+  e = fma(e, r, 1.0 / 3628800.0);
+  e = fma(e, r, 1.0 / 362880.0);
+  e = fma(e, r, 1.0 / 40320.0);
+  e = fma(e, r, 1.0 / 5040.0);
+  e = fma(e, r, 1.0 / 720.0);
+  e = fma(e, r, 1.0 / 120.0);
+  e = fma(e, r, 1.0 / 24.0);
+  e = fma(e, r, 1.0 / 6.0);
+  e = fma(e, r, 0.5);
+  e = fma(e, r, 1.0);
+  e = fma(e, r, 1.0);
+  return __builtin_amdgcn_ldexp(e, static_cast<int>(n));
 }
 
 // Threshold search.  MASS: largest C with cnt(C) >= 1 and M(C) >= tau; otherwise largest C with
 // cnt(C) >= k_target.  Requires the predicate to hold at key_min.  Returns the threshold key T and
-// n_gt = cnt(T+1), mass_gt = M(T+1), ties = number of blocks whose key equals T.
+// n_gt = cnt(T+1), mass_gt = M(T+1), ties = number of blocks whose key equals T.  Blocks that take no
+// part hold a negative p.  `lot`: 64 doubles of LDS of this wave's own.
 template <int E, bool MASS>
-__device__ inline uint64_t find_threshold(const double (&p)[E], uint64_t key_min, uint64_t key_max, int nb_k,
-                                          double tau, int k_target, int& n_gt, double& mass_gt, int& ties) {
+__device__ __forceinline__ uint64_t find_threshold(const double (&p)[E], uint64_t key_min, uint64_t key_max, int nb_ranked,
+                                                   double tau, int k_target, double* lot, int& n_gt, double& mass_gt,
+                                                   int& ties) {
   uint64_t lo = key_min, hi = key_max + 1;
-  int cnt_lo = nb_k, cnt_hi = 0;
+  int cnt_lo = nb_ranked, cnt_hi = 0;
   double mass_hi = 0.0;
-  while (cnt_lo - cnt_hi > 1 && hi - lo > 1) {
-    const uint64_t mid = lo + ((hi - lo) >> 1);
-    double s = 0.0;
-    int c = 0;
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-      const bool ge = static_cast<uint64_t>(__double_as_longlong(p[r])) >= mid;  // padding has key 0 < mid
-      s += ge ? p[r] : 0.0;
-      c += ge ? 1 : 0;
-    }
-    c = __builtin_amdgcn_readfirstlane(wave_sum_all(c));
-    const double m = wave_sum_all(s);
+  auto decide = [&](uint64_t mid, int c, double m) {
     const bool holds = MASS ? (c >= 1 && m >= tau) : (c >= k_target);
     if (__builtin_amdgcn_readfirstlane(holds ? 1 : 0)) {
       lo = mid;
@@ -117,21 +138,51 @@ __device__ inline uint64_t find_threshold(const double (&p)[E], uint64_t key_min
       cnt_hi = c;
       mass_hi = m;
     }
-  }
-  uint64_t T = lo;
-  if (hi - lo > 1) {  // one block left in [lo, hi): its key is the threshold
-    uint64_t best = 0;
+  };
+  while (cnt_lo - cnt_hi > 64 && hi - lo > 1) {
+    const uint64_t mid = lo + ((hi - lo) >> 1);  // > 0, so negative p never count
+    const double at = key_value(mid);
+    double s = 0.0;
+    int c = 0;
 #pragma unroll
     for (int r = 0; r < E; ++r) {
-      const uint64_t key = static_cast<uint64_t>(__double_as_longlong(p[r]));
-      if (key >= lo && key < hi) best = key;
+      const bool ge = p[r] >= at;
+      if constexpr (MASS) s += ge ? p[r] : 0.0;
+      c += votes(ge);
     }
+    if constexpr (MASS) s = wave_sum(s);
+    decide(mid, c, s);
+  }
+  uint64_t T = lo;
+  if (hi - lo > 1) {
+    // at most 64 blocks are left in [lo, hi): one to a lane, in ascending block order
+    const int lane = static_cast<int>(threadIdx.x & 63);
+    const double lo_v = key_value(lo), hi_v = key_value(hi);
+    int n = 0;
+    lot[lane] = -1.0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint64_t other = static_cast<uint64_t>(__shfl_xor(static_cast<long long>(best), o));
-      best = best > other ? best : other;
+    for (int r = 0; r < E; ++r) {
+      const bool in = p[r] >= lo_v && p[r] < hi_v;
+      const unsigned long long b = __ballot(in);
+      if (in) lot[n + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(b), 0))] = p[r];
+      n += static_cast<int>(__popcll(b));
     }
-    T = uniform64(best);
+    const double x = lot[lane];
+    const int cnt_base = cnt_hi;
+    const double mass_base = mass_hi;
+    while (cnt_lo - cnt_hi > 1 && hi - lo > 1) {
+      const uint64_t mid = lo + ((hi - lo) >> 1);
+      const bool ge = x >= key_value(mid);
+      decide(mid, cnt_base + votes(ge), MASS ? mass_base + wave_sum(ge ? x : 0.0) : 0.0);
+    }
+    T = lo;
+    if (hi - lo > 1) {  // one block left in [lo, hi): its key is the threshold
+      const unsigned long long b = __ballot(x >= key_value(lo) && x < key_value(hi));
+      const int src = b != 0 ? __builtin_ctzll(b) : 0;
+      const uint2 w = __builtin_bit_cast(uint2, x);
+      const uint32_t wl = __builtin_amdgcn_readlane(w.x, src), wh = __builtin_amdgcn_readlane(w.y, src);
+      T = (uint64_t(wh) << 32) | wl;
+    }
   }
   n_gt = cnt_hi;
   mass_gt = mass_hi;
@@ -139,87 +190,91 @@ __device__ inline uint64_t find_threshold(const double (&p)[E], uint64_t key_min
   return T;
 }
 
-template <int E>
-__global__ __launch_bounds__(kThreads) void select_kernel(
-    const double* __restrict__ logits, int nb_q, int nb_k, int64_t rows, double tau, double one_minus_rho,
-    const uint8_t* __restrict__ force_q, const uint8_t* __restrict__ force_k, uint32_t* __restrict__ mask_bits,
-    int32_t* __restrict__ kv_idx, int32_t* __restrict__ kv_cnt, int idx_stride) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6);  // = head * nb_q + I
-  if (row >= rows) return;  // whole wave; the kernel has no barriers
-  const int I = static_cast<int>(row % nb_q);
-  const double* lrow = logits + row * nb_k;
+// What the selection of one row needs besides its logits.
+struct SelectArgs {
+  int nb_q, nb_k;
+  double tau, one_minus_rho;
+  const uint8_t* force_q;
+  const uint8_t* force_k;
+  uint32_t* mask_bits;
+  int32_t* kv_idx;
+  int32_t* kv_cnt;
+  int idx_stride;
+};
 
+// One wave selects row `row` = head * nb_q + I of which `lrow` holds the nb_k logits (global or LDS).
+template <int E, typename Ptr>
+__device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const SelectArgs& a, double* lot) {
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  const int nb_k = a.nb_k;
+  const double tau = a.tau;
   // ---- softmax over the ranked blocks: p[r] belongs to block J = 64 r + lane.  Padding (J >= nb_k)
-  // and blocks with force_k[J] == 2 (always kept, not ranked) get p = 0 and take no part below.
+  // and blocks with force_k[J] == 2 (always kept, not ranked) get p = -1 and take no part below.
   double p[E];
-  unsigned long long ranked[(E + 63) / 64] = {};  // bit r: block 64 r + lane is ranked
+  uint32_t ranked[(E + 31) / 32] = {};  // bit r: block 64 r + lane is ranked
   double mx = -INFINITY;
+  int nb_ranked = 0;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int J = r * 64 + lane;
     bool rk = J < nb_k;
-    if (rk && force_k != nullptr) rk = force_k[J] != 2;
-    if (rk) ranked[r >> 6] |= 1ull << (r & 63);
     p[r] = rk ? lrow[J] : -INFINITY;
+    if (a.force_k != nullptr) {
+      rk = rk && a.force_k[min(J, nb_k - 1)] != 2;
+      p[r] = rk ? p[r] : -INFINITY;
+    }
+    ranked[r / 32] |= rk ? 1u << (r % 32) : 0u;
+    nb_ranked += votes(rk);
     mx = fmax(mx, p[r]);
   }
+  mx = wave_max(mx);
+  // (opaque: the compiler would otherwise keep one scalar register pair per slot alive instead of the bits)
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) mx = fmax(mx, __shfl_xor(mx, o));
-  int my_ranked = 0;
-#pragma unroll
-  for (int w = 0; w < (E + 63) / 64; ++w) my_ranked += __popcll(ranked[w]);
-  const int nb_ranked = __builtin_amdgcn_readfirstlane(wave_sum_all(my_ranked));
+  for (int w = 0; w < (E + 31) / 32; ++w) asm("" : "+v"(ranked[w]));
   double z = 0.0;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    p[r] = ((ranked[r >> 6] >> (r & 63)) & 1) ? exp(p[r] - mx) : 0.0;
-    z += p[r];
+    const bool rk = (ranked[r / 32] >> (r % 32)) & 1;
+    const double e = exp_nonpos(p[r] - mx);
+    p[r] = rk ? e : -1.0;
+    z += rk ? e : 0.0;
   }
-  z = wave_sum_all(z);
-  double total = 0.0;
+  z = wave_sum(z);
+  // p = e / z, rounded as the division rounds it: with the rounded reciprocal of z one correction of
+  // the quotient by its exact remainder suffices (Markstein)
+  const double rz = 1.0 / z;
+  double total = 0.0, p_min = INFINITY, p_max = 0.0;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    p[r] = ((ranked[r >> 6] >> (r & 63)) & 1) ? p[r] / z : 0.0;
-    total += p[r];
+    const bool rk = !(p[r] < 0.0);
+    const double q0 = p[r] * rz;
+    const double q1 = fma(fma(-q0, z, p[r]), rz, q0);
+    p[r] = rk ? q1 : -1.0;
+    const double add = rk ? q1 : 0.0;
+    total += add;
+    p_max = fmax(p_max, add);
+    p_min = fmin(p_min, rk ? q1 : INFINITY);
   }
-  total = wave_sum_all(total);
+  total = wave_sum(total);
   // smallest and largest key among the ranked blocks: the range the bisection works on
-  uint64_t key_min = ~0ull, key_max = 0;
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const uint64_t key = static_cast<uint64_t>(__double_as_longlong(p[r]));
-    if ((ranked[r >> 6] >> (r & 63)) & 1) {
-      key_min = key < key_min ? key : key_min;
-      key_max = key > key_max ? key : key_max;
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t a = static_cast<uint64_t>(__shfl_xor(static_cast<long long>(key_min), o));
-    const uint64_t b = static_cast<uint64_t>(__shfl_xor(static_cast<long long>(key_max), o));
-    key_min = a < key_min ? a : key_min;
-    key_max = b > key_max ? b : key_max;
-  }
-  key_min = uniform64(key_min);
-  key_max = uniform64(key_max);
+  const uint64_t key_min = uniform_key(wave_min(p_min)), key_max = uniform_key(wave_max(p_max));
 
   // ---- threshold ----------------------------------------------------------------------------
   // k = floor(B (1 - rho)) in binary64 as the definition is written, B = number of ranked blocks
-  const int k_floor = static_cast<int>(floor(static_cast<double>(nb_ranked) * one_minus_rho));
+  const int k_floor = static_cast<int>(floor(static_cast<double>(nb_ranked) * a.one_minus_rho));
   const int k_target = min(nb_ranked, max(k_floor, 1));
   // tau >= 1 keeps every block by definition (the summed mass may round to 1.0 before blocks of
   // negligible mass are counted); so does a mass that never gets to tau, and a row with nothing ranked
   const bool keep_all = tau >= 1.0 || !(total >= tau) || nb_ranked == 0;
   uint64_t T = 0;
-  int n_ties = 0;
+  int n_ties = 0, ties = 0;
   if (!keep_all) {
-    int n_gt, ties;
+    int n_gt;
     double mass_gt;
     int n_cdf = 1;  // tau <= 0: the first ranked block already covers it (top-k only selection)
     if (tau > 0.0) {
-      T = find_threshold<E, true>(p, key_min, key_max, nb_ranked, tau, 0, n_gt, mass_gt, ties);
-      const double pt = __longlong_as_double(static_cast<long long>(T));
+      T = find_threshold<E, true>(p, key_min, key_max, nb_ranked, tau, 0, lot, n_gt, mass_gt, ties);
+      const double pt = key_value(T);
       double run = mass_gt;
       n_ties = 0;
       do {
@@ -229,49 +284,138 @@ __global__ __launch_bounds__(kThreads) void select_kernel(
       n_cdf = n_gt + n_ties;
     }
     if (n_cdf < k_target || !(tau > 0.0)) {  // the top-k floor decides
-      T = find_threshold<E, false>(p, key_min, key_max, nb_ranked, tau, k_target, n_gt, mass_gt, ties);
+      T = find_threshold<E, false>(p, key_min, key_max, nb_ranked, tau, k_target, lot, n_gt, mass_gt, ties);
       n_ties = k_target - n_gt;
     }
   }
-  const bool whole_row = force_q != nullptr && force_q[I] != 0;
+  const bool whole_row = a.force_q != nullptr && a.force_q[I] != 0;
+  const double cut = key_value(T);  // 0 when everything is kept
+  const bool some_ties = n_ties < ties;
 
   // ---- emit: 64 blocks per step = two mask words; ties are ranked by block index ---------------
   const int words = (nb_k + 31) >> 5;
-  const unsigned long long below = (1ull << lane) - 1ull;
   int running = 0, tie_run = 0;
+  int l = lane;
+  asm("" : "+v"(l));  // opaque, for the same reason as above
+  auto before = [](unsigned long long b) {  // lanes below this one that voted
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(b), 0)));
+  };
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     if (r * 64 < nb_k) {  // uniform
-      const int J = r * 64 + lane;
+      const int J = r * 64 + l;
       const bool valid = J < nb_k;
-      const uint64_t key = static_cast<uint64_t>(__double_as_longlong(p[r]));
-      const bool rk = (ranked[r >> 6] >> (r & 63)) & 1;
-      const bool tied = rk && key == T;
-      const unsigned long long tb = __ballot(tied);
-      const int tie_idx = tie_run + __popcll(tb & below);
-      bool f = rk && (keep_all || key > T || (tied && tie_idx < n_ties));
+      bool f = !(p[r] < cut);  // NaN counts as kept: only rows that keep everything can hold one
+      if (some_ties) {
+        const bool tied = p[r] == cut;
+        const unsigned long long tb = __ballot(tied);
+        f = f && !(tied && tie_run + before(tb) >= n_ties);
+        tie_run += static_cast<int>(__popcll(tb));
+      }
       f = f || whole_row;
-      if (valid && force_k != nullptr) f = f || force_k[J] != 0;
+      if (a.force_k != nullptr) f = f || a.force_k[min(J, nb_k - 1)] != 0;
       f = f && valid;
       const unsigned long long bal = __ballot(f);
-      if (mask_bits != nullptr && lane < 2 && 2 * r + lane < words)
-        mask_bits[row * words + 2 * r + lane] = static_cast<uint32_t>(lane == 0 ? bal : (bal >> 32));
-      if (f && kv_idx != nullptr) kv_idx[row * idx_stride + running + __popcll(bal & below)] = J;
-      running += __popcll(bal);
-      tie_run += __popcll(tb);
+      if (a.mask_bits != nullptr && l < 2 && 2 * r + l < words)
+        a.mask_bits[row * words + 2 * r + l] = static_cast<uint32_t>(l == 0 ? bal : (bal >> 32));
+      if (f && a.kv_idx != nullptr) a.kv_idx[row * a.idx_stride + running + before(bal)] = J;
+      running += static_cast<int>(__popcll(bal));
     }
   }
-  if (lane == 0 && kv_cnt != nullptr) kv_cnt[row] = running;
+  if (lane == 0 && a.kv_cnt != nullptr) a.kv_cnt[row] = running;
+}
+
+// 16 rows of pooled vectors as an MFMA operand: rows first + lane%16 (the last row stands in for rows past
+// the end; its products are not stored)
+__device__ __forceinline__ void load_rows(double (&x)[16], const double* __restrict__ pool, int first, int n) {
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  const int row = min(first + (lane & 15), n - 1);
+  const f64x2* src = reinterpret_cast<const f64x2*>(pool + int64_t(row) * kD + (lane >> 4) * 16);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const f64x2 v = src[i];
+    x[2 * i] = v[0];
+    x[2 * i + 1] = v[1];
+  }
+}
+__device__ __forceinline__ f64x4 products(const double (&a)[16], const double (&b)[16]) {
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+  return acc;
+}
+
+// Logits of 32 query rows against 256 key blocks per workgroup (64 per wave).  Bound by the 8 bytes it
+// writes per logit: 762 MB at 2440 x 2440 blocks and 16 heads.  The version before it (vector fp64, four
+// rows per workgroup, every key row read by every workgroup) was bound by re-reading the keys from L2.
+constexpr int kLogitRows = 32, kLogitCols = 256;
+__global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restrict__ q_pool, const double* __restrict__ k_pool,
+                                                          int nb_q, int nb_k, double score_scale, double* __restrict__ logits) {
+  const int h = blockIdx.z;
+  const int I0 = blockIdx.y * kLogitRows;
+  const int lane = threadIdx.x & 63;
+  const int J0 = blockIdx.x * kLogitCols + (threadIdx.x >> 6) * 64;
+  if (J0 >= nb_k) return;  // whole wave; the kernel has no barriers
+  const double* qh = q_pool + int64_t(h) * nb_q * kD;
+  const double* kh = k_pool + int64_t(h) * nb_k * kD;
+  double a[2][16];
+  load_rows(a[0], qh, I0, nb_q);
+  load_rows(a[1], qh, I0 + 16, nb_q);
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) {
+    const int J = J0 + ct * 16 + (lane & 15);
+    double b[16];
+    load_rows(b, kh, J0 + ct * 16, nb_k);
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const f64x4 acc = products(a[rt], b);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int I = I0 + rt * 16 + (lane >> 4) + 4 * r;
+        if (I < nb_q && J < nb_k) logits[(int64_t(h) * nb_q + I) * nb_k + J] = score_scale * acc[r];
+      }
+    }
+  }
 }
 
 template <int E>
-void launch_select_rows(const double* logits, int heads, int nb_q, int nb_k, double tau, double one_minus_rho,
-                        const uint8_t* force_q, const uint8_t* force_k, uint32_t* mask_bits, int32_t* kv_idx,
-                        int32_t* kv_cnt, int idx_stride, hipStream_t stream) {
-  const int64_t rows = int64_t(heads) * nb_q;
-  hipLaunchKernelGGL(select_kernel<E>, dim3(static_cast<unsigned>((rows + kWaves - 1) / kWaves)), dim3(kThreads), 0,
-                     stream, logits, nb_q, nb_k, rows, tau, one_minus_rho, force_q, force_k, mask_bits, kv_idx, kv_cnt,
-                     idx_stride);
+__global__ __launch_bounds__(kThreads) void select_kernel(const double* __restrict__ logits, int64_t rows, SelectArgs args) {
+  __shared__ double lot[kWaves][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = int64_t(blockIdx.x) * kWaves + wave;  // = head * nb_q + I
+  if (row >= rows) return;  // whole wave; the kernel has no barriers
+  select_row<E>(logits + row * args.nb_k, row, static_cast<int>(row % args.nb_q), args, lot[wave]);
+}
+
+// Scores and selection of 16 rows of one head; LDS: [16][stride] logits, then 64 doubles per wave.
+template <int E>
+__global__ __launch_bounds__(kFusedRows * 64) void score_select_kernel(const double* __restrict__ q_pool,
+                                                                       const double* __restrict__ k_pool,
+                                                                       double score_scale, SelectArgs args) {
+  extern __shared__ __align__(16) double rows_lds[];
+  const int h = blockIdx.y;
+  const int I0 = blockIdx.x * kFusedRows;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int stride = args.nb_k | 1;  // odd: the four rows a lane group writes fall into different banks
+  const double* kh = k_pool + int64_t(h) * args.nb_k * kD;
+  if (wave * 16 < args.nb_k) {
+    double a[16];
+    load_rows(a, q_pool + int64_t(h) * args.nb_q * kD, I0, args.nb_q);
+    for (int c0 = wave * 16; c0 < args.nb_k; c0 += kFusedRows * 16) {
+      double b[16];
+      load_rows(b, kh, c0, args.nb_k);
+      const f64x4 acc = products(a, b);
+      const int J = c0 + (lane & 15);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (J < args.nb_k) rows_lds[((lane >> 4) + 4 * r) * stride + J] = score_scale * acc[r];
+    }
+  }
+  __syncthreads();
+  const int I = I0 + wave;
+  if (I >= args.nb_q) return;  // whole wave, after the only barrier
+  select_row<E>(rows_lds + wave * stride, int64_t(h) * args.nb_q + I, I, args, rows_lds + kFusedRows * stride + wave * 64);
 }
 
 }  // namespace
@@ -283,20 +427,26 @@ size_t select_workspace_bytes(int heads, int nb_q, int nb_k) {
 int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_q, int nb_k, double score_scale,
                   double tau, double one_minus_rho, const uint8_t* force_q, const uint8_t* force_k, uint32_t* mask_bits,
                   int32_t* kv_idx, int32_t* kv_cnt, int idx_stride, void* workspace, hipStream_t stream) {
-  double* logits = static_cast<double*>(workspace);
-  constexpr int R = 4;
-  hipLaunchKernelGGL(logits_kernel<R>, dim3((nb_q + R - 1) / R, heads), dim3(kThreads), 0, stream, q_pool, k_pool,
-                     nb_q, nb_k, score_scale, logits);
-  if (int rc = check_hip(hipGetLastError(), "bsga_select_blocks (logits) launch")) return rc;
+  const SelectArgs args = {nb_q, nb_k, tau, one_minus_rho, force_q, force_k, mask_bits, kv_idx, kv_cnt, idx_stride};
   // per-lane register tile: the smallest instantiation that holds ceil(nb_k / 64) blocks per lane
   const int e = (nb_k + 63) / 64;
-#define BSGA_SELECT_CASE(E_)                                                                                     \
-  if (e <= E_) {                                                                                                 \
-    launch_select_rows<E_>(logits, heads, nb_q, nb_k, tau, one_minus_rho, force_q, force_k, mask_bits, kv_idx, kv_cnt, \
-                           idx_stride, stream);                                                                  \
+  if (nb_k <= kFusedMaxBlocks) {
+    const dim3 grid(static_cast<unsigned>(ceil_div(nb_q, kFusedRows)), heads), blk(kFusedRows * 64);
+    const size_t lds = (size_t(kFusedRows) * (nb_k | 1) + kFusedRows * 64) * sizeof(double);
+    if (e <= 4) hipLaunchKernelGGL(score_select_kernel<4>, grid, blk, lds, stream, q_pool, k_pool, score_scale, args);
+    else hipLaunchKernelGGL(score_select_kernel<8>, grid, blk, lds, stream, q_pool, k_pool, score_scale, args);
+    return check_hip(hipGetLastError(), "bsga_select_blocks launch");
+  }
+  double* logits = static_cast<double*>(workspace);
+  const dim3 lgrid(static_cast<unsigned>(ceil_div(nb_k, kLogitCols)), static_cast<unsigned>(ceil_div(nb_q, kLogitRows)), heads);
+  hipLaunchKernelGGL(logits_kernel, lgrid, dim3(kThreads), 0, stream, q_pool, k_pool, nb_q, nb_k, score_scale, logits);
+  if (int rc = check_hip(hipGetLastError(), "bsga_select_blocks (logits) launch")) return rc;
+  const int64_t rows = int64_t(heads) * nb_q;
+  const dim3 grid(static_cast<unsigned>(ceil_div(rows, kWaves)));
+#define BSGA_SELECT_CASE(E_)                                                                                  \
+  if (e <= E_) {                                                                                              \
+    hipLaunchKernelGGL(select_kernel<E_>, grid, dim3(kThreads), 0, stream, logits, rows, args);               \
   } else
-  BSGA_SELECT_CASE(4)
-  BSGA_SELECT_CASE(8)
   BSGA_SELECT_CASE(12)
   BSGA_SELECT_CASE(20)
   BSGA_SELECT_CASE(28)
