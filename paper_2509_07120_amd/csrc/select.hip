@@ -3,9 +3,10 @@
 //
 // Scores.  logits[I][J] = scale * <q_pool[I], k_pool[J]> on v_mfma_f64_16x16x4: a wave keeps 16 query
 //   rows (A operand) in registers and meets 16 key blocks (B operand) per 16 instructions.  Lane
-//   (i = lane%16, g = lane/16) holds dims 16g .. 16g+15 of row i of either operand, i.e. the contraction
-//   runs over the dims in the order s, 16+s, 32+s, 48+s for s = 0..15 and every lane loads 128
-//   consecutive bytes.  Accumulator register r of the lane is (row g + 4r, column i).
+//   (i = lane%16, g = lane/16) holds dims 8c + 2g and 8c + 2g + 1, c = 0..7, of row i of either operand: a
+//   16-byte load then covers 64 consecutive bytes of 16 rows.  (With 16 consecutive dims to a lane every
+//   load touches 64 cache lines.)
+//   Accumulator register r of the lane is (row g + 4r, column i).
 //
 // Selection.  One WAVE per row, the whole row in registers (lane l holds blocks l, l+64, ...).  The
 //   ranked prefix the method keeps is found without sorting: with key(p) = the bit pattern of p
@@ -20,7 +21,9 @@
 //   running mass is below tau.  The top-k floor is the same search with the predicate cnt(C) >= k.
 //   The sums are taken in a fixed order (lane-local in ascending block order, then a butterfly), so
 //   results are deterministic; adding non-negative terms in a fixed order is monotone, which the
-//   bisection needs.
+//   bisection needs.  Bound by vector issue: about 65 instructions per slot, a third of them the
+//   exponential.  2440 blocks x 39,040 rows: 320 us (1209 us when every step ran over the whole row and every
+//   reduction over six LDS permutes); four waves per SIMD up to 40 slots.
 //
 // Two ways to launch.  Up to 512 key blocks one kernel does both: a workgroup of 16 waves computes the
 //   scores of 16 rows into LDS (64 KB at 512 key blocks, so two workgroups share a CU) and each wave then
@@ -149,6 +152,7 @@ __device__ __forceinline__ uint64_t find_threshold(const double (&p)[E], uint64_
       const bool ge = p[r] >= at;
       if constexpr (MASS) s += ge ? p[r] : 0.0;
       c += votes(ge);
+      if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // bounds the scalar registers that hold votes
     }
     if constexpr (MASS) s = wave_sum(s);
     decide(mid, c, s);
@@ -166,6 +170,7 @@ __device__ __forceinline__ uint64_t find_threshold(const double (&p)[E], uint64_
       const unsigned long long b = __ballot(in);
       if (in) lot[n + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(b), 0))] = p[r];
       n += static_cast<int>(__popcll(b));
+      if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     const double x = lot[lane];
     const int cnt_base = cnt_hi;
@@ -203,7 +208,8 @@ struct SelectArgs {
 };
 
 // One wave selects row `row` = head * nb_q + I of which `lrow` holds the nb_k logits (global or LDS).
-template <int E, typename Ptr>
+// FULL: slots 0 .. FULL-1 are known to be whole (64 * FULL <= nb_k); FORCE: force_q or force_k is given.
+template <int E, int FULL, bool FORCE, typename Ptr>
 __device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const SelectArgs& a, double* lot) {
   const int lane = static_cast<int>(threadIdx.x & 63);
   const int nb_k = a.nb_k;
@@ -213,51 +219,68 @@ __device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const S
   double p[E];
   uint32_t ranked[(E + 31) / 32] = {};  // bit r: block 64 r + lane is ranked
   double mx = -INFINITY;
-  int nb_ranked = 0;
+  int nb_ranked = FORCE ? 0 : nb_k;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int J = r * 64 + lane;
-    bool rk = J < nb_k;
-    p[r] = rk ? lrow[J] : -INFINITY;
-    if (a.force_k != nullptr) {
-      rk = rk && a.force_k[min(J, nb_k - 1)] != 2;
+    if constexpr (!FORCE) {
+      p[r] = r < FULL ? lrow[J] : lrow[min(J, nb_k - 1)];
+      if (r >= FULL) p[r] = J < nb_k ? p[r] : -INFINITY;
+    } else {
+      bool rk = J < nb_k;
+      const int Jc = min(J, nb_k - 1);
+      if (a.force_k != nullptr) rk = rk && a.force_k[Jc] != 2;
+      p[r] = lrow[Jc];
       p[r] = rk ? p[r] : -INFINITY;
+      ranked[r / 32] |= rk ? 1u << (r % 32) : 0u;
+      nb_ranked += votes(rk);
     }
-    ranked[r / 32] |= rk ? 1u << (r % 32) : 0u;
-    nb_ranked += votes(rk);
     mx = fmax(mx, p[r]);
   }
   mx = wave_max(mx);
-  // (opaque: the compiler would otherwise keep one scalar register pair per slot alive instead of the bits)
+  // opaque: the compiler would otherwise keep one scalar register pair per slot alive instead of
+  // comparing again
 #pragma unroll
   for (int w = 0; w < (E + 31) / 32; ++w) asm("" : "+v"(ranked[w]));
+  int l = lane;
+  asm("" : "+v"(l));
   double z = 0.0;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const bool rk = (ranked[r / 32] >> (r % 32)) & 1;
-    const double e = exp_nonpos(p[r] - mx);
-    p[r] = rk ? e : -1.0;
-    z += rk ? e : 0.0;
+    p[r] = exp_nonpos(p[r] - mx);
+    if constexpr (FORCE) p[r] = (ranked[r / 32] >> (r % 32)) & 1 ? p[r] : -1.0;
+    else if (r >= FULL) p[r] = r * 64 + l < nb_k ? p[r] : -1.0;
+    z += (!FORCE && r < FULL) ? p[r] : (p[r] < 0.0 ? 0.0 : p[r]);
+    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // bounds the registers that hold comparisons
   }
   z = wave_sum(z);
   // p = e / z, rounded as the division rounds it: with the rounded reciprocal of z one correction of
   // the quotient by its exact remainder suffices (Markstein)
   const double rz = 1.0 / z;
-  double total = 0.0, p_min = INFINITY, p_max = 0.0;
+  auto over_z = [&](double e) {
+    const double q0 = e * rz;
+    return fma(fma(-q0, z, e), rz, q0);
+  };
+  double total = 0.0, p_min = INFINITY;
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const bool rk = !(p[r] < 0.0);
-    const double q0 = p[r] * rz;
-    const double q1 = fma(fma(-q0, z, p[r]), rz, q0);
-    p[r] = rk ? q1 : -1.0;
-    const double add = rk ? q1 : 0.0;
-    total += add;
-    p_max = fmax(p_max, add);
-    p_min = fmin(p_min, rk ? q1 : INFINITY);
+    const double q = over_z(p[r]);
+    if (!FORCE && r < FULL) {
+      p[r] = q;
+      total += q;
+      p_min = fmin(p_min, q);
+    } else {
+      const bool out = p[r] < 0.0;
+      p[r] = out ? -1.0 : q;
+      total += out ? 0.0 : q;
+      p_min = fmin(p_min, out ? INFINITY : q);
+    }
+    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
   }
   total = wave_sum(total);
-  // smallest and largest key among the ranked blocks: the range the bisection works on
-  const uint64_t key_min = uniform_key(wave_min(p_min)), key_max = uniform_key(wave_max(p_max));
+  // smallest and largest key among the ranked blocks: the range the bisection works on.  The largest
+  // exponential is exp(0) = 1.
+  const uint64_t key_min = uniform_key(wave_min(p_min)), key_max = uniform_key(over_z(1.0));
 
   // ---- threshold ----------------------------------------------------------------------------
   // k = floor(B (1 - rho)) in binary64 as the definition is written, B = number of ranked blocks
@@ -288,52 +311,60 @@ __device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const S
       n_ties = k_target - n_gt;
     }
   }
-  const bool whole_row = a.force_q != nullptr && a.force_q[I] != 0;
   const double cut = key_value(T);  // 0 when everything is kept
   const bool some_ties = n_ties < ties;
 
-  // ---- emit: 64 blocks per step = two mask words; ties are ranked by block index ---------------
+  // ---- emit: 64 blocks per slot = two mask words; ties are ranked by block index ---------------
   const int words = (nb_k + 31) >> 5;
+  const bool whole_row = FORCE && a.force_q != nullptr && a.force_q[I] != 0;
+  int32_t* const idx_row = a.kv_idx != nullptr ? a.kv_idx + row * a.idx_stride : nullptr;
   int running = 0, tie_run = 0;
-  int l = lane;
-  asm("" : "+v"(l));  // opaque, for the same reason as above
-  auto before = [](unsigned long long b) {  // lanes below this one that voted
-    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(b), 0)));
+  auto rank = [](unsigned long long b, int first) {  // first + lanes below this one that voted
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(b >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(b), first)));
   };
+  uint32_t word[(E + 31) / 32] = {};  // mask word 64 w + lane
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    if (r * 64 < nb_k) {  // uniform
-      const int J = r * 64 + l;
-      const bool valid = J < nb_k;
-      bool f = !(p[r] < cut);  // NaN counts as kept: only rows that keep everything can hold one
-      if (some_ties) {
-        const bool tied = p[r] == cut;
-        const unsigned long long tb = __ballot(tied);
-        f = f && !(tied && tie_run + before(tb) >= n_ties);
-        tie_run += static_cast<int>(__popcll(tb));
-      }
+    const int J = r * 64 + l;
+    asm("" : "+v"(l));  // (each slot's J is made when it is needed)
+    // padding never passes (p = -1, cut >= 0); NaN does: only a row that keeps everything can hold one
+    bool f = !(p[r] < cut);
+    if (some_ties) {
+      const bool tied = p[r] == cut;
+      const unsigned long long tb = __ballot(tied);
+      f = f && !(tied && rank(tb, tie_run) >= n_ties);
+      tie_run += static_cast<int>(__popcll(tb));
+    }
+    if constexpr (FORCE) {
       f = f || whole_row;
       if (a.force_k != nullptr) f = f || a.force_k[min(J, nb_k - 1)] != 0;
-      f = f && valid;
-      const unsigned long long bal = __ballot(f);
-      if (a.mask_bits != nullptr && l < 2 && 2 * r + l < words)
-        a.mask_bits[row * words + 2 * r + l] = static_cast<uint32_t>(l == 0 ? bal : (bal >> 32));
-      if (f && a.kv_idx != nullptr) a.kv_idx[row * a.idx_stride + running + before(bal)] = J;
-      running += static_cast<int>(__popcll(bal));
+      f = f && J < nb_k;
     }
+    const unsigned long long bal = __ballot(f);
+    asm("v_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
+        : "+v"(word[r / 32])
+        : "s"(static_cast<unsigned>(bal)), "s"(static_cast<unsigned>(bal >> 32)), "n"(2 * (r % 32)), "n"(2 * (r % 32) + 1));
+    if (f && idx_row != nullptr) idx_row[rank(bal, running)] = J;
+    running += static_cast<int>(__popcll(bal));
+    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
   }
-  if (lane == 0 && a.kv_cnt != nullptr) a.kv_cnt[row] = running;
+  if (a.mask_bits != nullptr) {
+#pragma unroll
+    for (int w = 0; w < (E + 31) / 32; ++w)
+      if (w * 64 + l < words) a.mask_bits[row * words + w * 64 + l] = word[w];
+  }
+  if (l == 0 && a.kv_cnt != nullptr) a.kv_cnt[row] = running;
 }
 
-// 16 rows of pooled vectors as an MFMA operand: rows first + lane%16 (the last row stands in for rows past
-// the end; its products are not stored)
-__device__ __forceinline__ void load_rows(double (&x)[16], const double* __restrict__ pool, int first, int n) {
+// One row of pooled vectors per lane of a 16-lane group, as an MFMA operand (the last row stands in for rows
+// past the end; its products are not stored).
+__device__ __forceinline__ void load_rows(double (&x)[16], const double* __restrict__ pool, int row, int n) {
   const int lane = static_cast<int>(threadIdx.x & 63);
-  const int row = min(first + (lane & 15), n - 1);
-  const f64x2* src = reinterpret_cast<const f64x2*>(pool + int64_t(row) * kD + (lane >> 4) * 16);
+  const f64x2* src = reinterpret_cast<const f64x2*>(pool + int64_t(min(row, n - 1)) * kD + (lane >> 4) * 2);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const f64x2 v = src[i];
+    const f64x2 v = src[4 * i];
     x[2 * i] = v[0];
     x[2 * i + 1] = v[1];
   }
@@ -345,50 +376,65 @@ __device__ __forceinline__ f64x4 products(const double (&a)[16], const double (&
   return acc;
 }
 
-// Logits of 32 query rows against 256 key blocks per workgroup (64 per wave).  Bound by the 8 bytes it
-// writes per logit: 762 MB at 2440 x 2440 blocks and 16 heads.  The version before it (vector fp64, four
-// rows per workgroup, every key row read by every workgroup) was bound by re-reading the keys from L2.
-constexpr int kLogitRows = 32, kLogitCols = 256;
+// Logits of 48 query rows against 128 key blocks per wave, four waves of a workgroup below each other.
+// Column 2i of a pair of column tiles comes from the first, column 2i + 1 from the second, so a lane holds
+// two neighbours and 16 lanes store 256 consecutive bytes (8-byte aligned: nb_k may be odd).  The stores bypass
+// the L2, which holds the key rows all workgroups share: at 2440 x 2440 blocks and 16 heads (762 MB
+// written, 12.2 GFLOP) 250 us, 349 us with plain stores; a plain fill of the same buffer takes 157 us and the
+// products alone 230 us.  32 rows per wave: 312 us, 64 rows: 313 us.  The version before this one (vector
+// fp64, four rows per workgroup, every key row read by each) took 810 us.
+constexpr int kLogitRowTiles = 3, kLogitCols = 128, kLogitRows = 4 * 16 * kLogitRowTiles;
 __global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restrict__ q_pool, const double* __restrict__ k_pool,
                                                           int nb_q, int nb_k, double score_scale, double* __restrict__ logits) {
+  typedef double f64x2_at8 __attribute__((ext_vector_type(2), aligned(8)));
   const int h = blockIdx.z;
-  const int I0 = blockIdx.y * kLogitRows;
   const int lane = threadIdx.x & 63;
-  const int J0 = blockIdx.x * kLogitCols + (threadIdx.x >> 6) * 64;
-  if (J0 >= nb_k) return;  // whole wave; the kernel has no barriers
+  const int i16 = lane & 15;
+  const int I0 = blockIdx.y * kLogitRows + (threadIdx.x >> 6) * 16 * kLogitRowTiles;
+  const int J0 = blockIdx.x * kLogitCols;
+  if (I0 >= nb_q) return;  // whole wave; the kernel has no barriers
   const double* qh = q_pool + int64_t(h) * nb_q * kD;
   const double* kh = k_pool + int64_t(h) * nb_k * kD;
-  double a[2][16];
-  load_rows(a[0], qh, I0, nb_q);
-  load_rows(a[1], qh, I0 + 16, nb_q);
+  double a[kLogitRowTiles][16], b[2][16];
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const int J = J0 + ct * 16 + (lane & 15);
-    double b[16];
-    load_rows(b, kh, J0 + ct * 16, nb_k);
+  for (int rt = 0; rt < kLogitRowTiles; ++rt) load_rows(a[rt], qh, I0 + rt * 16 + i16, nb_q);
+  load_rows(b[0], kh, J0 + 2 * i16, nb_k);
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const f64x4 acc = products(a[rt], b);
+  for (int cp = 0; cp < kLogitCols / 32; ++cp) {
+    const int J = J0 + cp * 32 + 2 * i16;
+    f64x4 even[kLogitRowTiles], odd[kLogitRowTiles];
+    load_rows(b[1], kh, J + 1, nb_k);
+#pragma unroll
+    for (int rt = 0; rt < kLogitRowTiles; ++rt) even[rt] = products(a[rt], b[0]);
+    if (cp + 1 < kLogitCols / 32) load_rows(b[0], kh, J + 32, nb_k);
+#pragma unroll
+    for (int rt = 0; rt < kLogitRowTiles; ++rt) odd[rt] = products(a[rt], b[1]);
+#pragma unroll
+    for (int rt = 0; rt < kLogitRowTiles; ++rt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int I = I0 + rt * 16 + (lane >> 4) + 4 * r;
-        if (I < nb_q && J < nb_k) logits[(int64_t(h) * nb_q + I) * nb_k + J] = score_scale * acc[r];
+        if (I >= nb_q) continue;
+        double* dst = logits + (int64_t(h) * nb_q + I) * nb_k + J;
+        if (J + 1 < nb_k)
+          __builtin_nontemporal_store(f64x2_at8{score_scale * even[rt][r], score_scale * odd[rt][r]}, reinterpret_cast<f64x2_at8*>(dst));
+        else if (J < nb_k)
+          __builtin_nontemporal_store(score_scale * even[rt][r], dst);
       }
-    }
   }
 }
 
-template <int E>
-__global__ __launch_bounds__(kThreads) void select_kernel(const double* __restrict__ logits, int64_t rows, SelectArgs args) {
+template <int E, int FULL, bool FORCE>
+__global__ __launch_bounds__(kThreads, E <= 40 ? 4 : 1) void select_kernel(const double* __restrict__ logits, int64_t rows, SelectArgs args) {
   __shared__ double lot[kWaves][64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row = int64_t(blockIdx.x) * kWaves + wave;  // = head * nb_q + I
   if (row >= rows) return;  // whole wave; the kernel has no barriers
-  select_row<E>(logits + row * args.nb_k, row, static_cast<int>(row % args.nb_q), args, lot[wave]);
+  select_row<E, FULL, FORCE>(logits + row * args.nb_k, row, static_cast<int>(row % args.nb_q), args, lot[wave]);
 }
 
 // Scores and selection of 16 rows of one head; LDS: [16][stride] logits, then 64 doubles per wave.
-template <int E>
+template <int E, int FULL, bool FORCE>
 __global__ __launch_bounds__(kFusedRows * 64) void score_select_kernel(const double* __restrict__ q_pool,
                                                                        const double* __restrict__ k_pool,
                                                                        double score_scale, SelectArgs args) {
@@ -401,10 +447,10 @@ __global__ __launch_bounds__(kFusedRows * 64) void score_select_kernel(const dou
   const double* kh = k_pool + int64_t(h) * args.nb_k * kD;
   if (wave * 16 < args.nb_k) {
     double a[16];
-    load_rows(a, q_pool + int64_t(h) * args.nb_q * kD, I0, args.nb_q);
+    load_rows(a, q_pool + int64_t(h) * args.nb_q * kD, I0 + (lane & 15), args.nb_q);
     for (int c0 = wave * 16; c0 < args.nb_k; c0 += kFusedRows * 16) {
       double b[16];
-      load_rows(b, kh, c0, args.nb_k);
+      load_rows(b, kh, c0 + (lane & 15), args.nb_k);
       const f64x4 acc = products(a, b);
       const int J = c0 + (lane & 15);
 #pragma unroll
@@ -415,7 +461,7 @@ __global__ __launch_bounds__(kFusedRows * 64) void score_select_kernel(const dou
   __syncthreads();
   const int I = I0 + wave;
   if (I >= args.nb_q) return;  // whole wave, after the only barrier
-  select_row<E>(rows_lds + wave * stride, int64_t(h) * args.nb_q + I, I, args, rows_lds + kFusedRows * stride + wave * 64);
+  select_row<E, FULL, FORCE>(rows_lds + wave * stride, int64_t(h) * args.nb_q + I, I, args, rows_lds + kFusedRows * stride + wave * 64);
 }
 
 }  // namespace
@@ -428,13 +474,16 @@ int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_
                   double tau, double one_minus_rho, const uint8_t* force_q, const uint8_t* force_k, uint32_t* mask_bits,
                   int32_t* kv_idx, int32_t* kv_cnt, int idx_stride, void* workspace, hipStream_t stream) {
   const SelectArgs args = {nb_q, nb_k, tau, one_minus_rho, force_q, force_k, mask_bits, kv_idx, kv_cnt, idx_stride};
-  // per-lane register tile: the smallest instantiation that holds ceil(nb_k / 64) blocks per lane
+  const bool force = force_q != nullptr || force_k != nullptr;
+  // per-lane register tile: the smallest instantiation that holds ceil(nb_k / 64) blocks per lane; nb_k is
+  // above the one before it, whose slots are therefore whole
   const int e = (nb_k + 63) / 64;
   if (nb_k <= kFusedMaxBlocks) {
     const dim3 grid(static_cast<unsigned>(ceil_div(nb_q, kFusedRows)), heads), blk(kFusedRows * 64);
     const size_t lds = (size_t(kFusedRows) * (nb_k | 1) + kFusedRows * 64) * sizeof(double);
-    if (e <= 4) hipLaunchKernelGGL(score_select_kernel<4>, grid, blk, lds, stream, q_pool, k_pool, score_scale, args);
-    else hipLaunchKernelGGL(score_select_kernel<8>, grid, blk, lds, stream, q_pool, k_pool, score_scale, args);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, blk, lds, stream, q_pool, k_pool, score_scale, args); };
+    if (e <= 4) launch(force ? score_select_kernel<4, 0, true> : score_select_kernel<4, 0, false>);
+    else launch(force ? score_select_kernel<8, 4, true> : score_select_kernel<8, 4, false>);
     return check_hip(hipGetLastError(), "bsga_select_blocks launch");
   }
   double* logits = static_cast<double*>(workspace);
@@ -443,18 +492,17 @@ int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_
   if (int rc = check_hip(hipGetLastError(), "bsga_select_blocks (logits) launch")) return rc;
   const int64_t rows = int64_t(heads) * nb_q;
   const dim3 grid(static_cast<unsigned>(ceil_div(rows, kWaves)));
-#define BSGA_SELECT_CASE(E_)                                                                                  \
-  if (e <= E_) {                                                                                              \
-    hipLaunchKernelGGL(select_kernel<E_>, grid, dim3(kThreads), 0, stream, logits, rows, args);               \
-  } else
-  BSGA_SELECT_CASE(12)
-  BSGA_SELECT_CASE(20)
-  BSGA_SELECT_CASE(28)
-  BSGA_SELECT_CASE(40)
-  BSGA_SELECT_CASE(52)
-  BSGA_SELECT_CASE(64)
-  BSGA_SELECT_CASE(96)
-  BSGA_SELECT_CASE(128) { return fail(BSGA_ERR_UNSUPPORTED, "bsga_select_blocks: nb_k = %d exceeds 8192", nb_k); }
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, logits, rows, args); };
+#define BSGA_SELECT_CASE(E_, FULL_) \
+  if (e <= E_) launch(force ? select_kernel<E_, FULL_, true> : select_kernel<E_, FULL_, false>); else
+  BSGA_SELECT_CASE(12, 8)
+  BSGA_SELECT_CASE(20, 12)
+  BSGA_SELECT_CASE(28, 20)
+  BSGA_SELECT_CASE(40, 28)
+  BSGA_SELECT_CASE(52, 40)
+  BSGA_SELECT_CASE(64, 52)
+  BSGA_SELECT_CASE(96, 64)
+  BSGA_SELECT_CASE(128, 96) { return fail(BSGA_ERR_UNSUPPORTED, "bsga_select_blocks: nb_k = %d exceeds 8192", nb_k); }
 #undef BSGA_SELECT_CASE
   return check_hip(hipGetLastError(), "bsga_select_blocks launch");
 }
