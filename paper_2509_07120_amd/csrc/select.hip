@@ -342,9 +342,9 @@ __device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const S
       f = f && J < nb_k;
     }
     const unsigned long long bal = __ballot(f);
-    asm("v_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
-        : "+v"(word[r / 32])
-        : "s"(static_cast<unsigned>(bal)), "s"(static_cast<unsigned>(bal >> 32)), "n"(2 * (r % 32)), "n"(2 * (r % 32) + 1));
+    word[r / 32] = l == 2 * (r % 32) ? static_cast<uint32_t>(bal) : word[r / 32];
+    word[r / 32] = l == 2 * (r % 32) + 1 ? static_cast<uint32_t>(bal >> 32) : word[r / 32];
+    asm volatile("" : "+v"(word[r / 32]));  // here, not from 2 E saved scalars at the end
     if (f && idx_row != nullptr) idx_row[rank(bal, running)] = J;
     running += static_cast<int>(__popcll(bal));
     if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);

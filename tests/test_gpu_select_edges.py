@@ -64,7 +64,7 @@ def test_ties_larger_than_a_wave(B, nbk):
         _check(B, qp, kp, tau, rho, 0.125)
 
 
-@pytest.mark.parametrize("nbk", [130, 700])
+@pytest.mark.parametrize("nbk", [130, 700, 1300, 2500, 5000, 8192])
 def test_unranked_and_forced_columns(B, nbk):
     rng = np.random.default_rng(nbk)
     qp = rng.standard_normal((2, 20, 64))
