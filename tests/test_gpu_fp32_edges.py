@@ -21,11 +21,12 @@ def B():
 
 
 @pytest.mark.parametrize("b", [64, 128])
+@pytest.mark.parametrize("wide", [False, True])  # 32 or 64 rows to a workgroup: chosen by the number of workgroups
 @pytest.mark.parametrize("N,n_first", [(1, 1), (31, 31), (32, 32), (33, 33), (63, 63), (64, 64), (65, 65), (97, 97),
                                        (128, 128), (129, 129), (161, 161), (500, 500), (500, 129), (300, 31), (641, 609)])
-def test_units_and_pieces(B, b, N, n_first):
+def test_units_and_pieces(B, b, wide, N, n_first):
     rng = np.random.default_rng(N * 1000 + b)
-    H = 3
+    H = max(3, 200 // (len(O.block_ranges(N, b, n_first)) * (b // 64))) if wide else 3
     q, k, v = (rng.standard_normal((H, N, 64)).astype(np.float32) for _ in range(3))
     nb = len(O.block_ranges(N, b, n_first))
     mask = rng.random((H, nb, nb)) < 0.6
