@@ -127,12 +127,14 @@ int bsga_gather_tokens(const void* src, int dtype, int heads, int64_t n_src, int
                        const int32_t* index, int64_t n_dst, void* dst, void* stream);
 
 /*
- * Bytes of device workspace bsga_sparse_attn needs for this shape (bsga_dense_attn uses 16 bytes
- * of one and accepts NULL).  Q, K and V are read in place and all intermediates stay on chip; the
- * workspace holds the launch order of the (head, query block) rows, heaviest first, and the counter
- * through which the last rows of a large launch are handed out at run time (4 bytes per row, sized
- * for block 64 and a split sequence, plus 128 bytes per head and 16 bytes; 0 for fp32 and for invalid
- * arguments).
+ * Bytes of device workspace for a bf16 attention call of this shape (0 for fp32 and for invalid arguments).
+ * Q, K and V are read in place; the workspace holds the launch order of the (head, query block) rows,
+ * heaviest first, and the counter through which the last rows of a large launch are handed out at run
+ * time: 4 bytes per row, sized for block 64 and a split sequence, plus 128 bytes per head and 16 bytes.  That
+ * much a workspace must have.  For sequences above 4032 tokens with heads * ceil(n_tokens/128) < 1024 the
+ * answer also counts 35 MB of partial results, with which a call of few long rows shares rows between
+ * workgroups; a call given less than that computes every row in one workgroup (same results up to the
+ * order of fp32 sums).  bsga_dense_attn needs none and accepts NULL.
  */
 size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int head_dim);
 
@@ -145,8 +147,8 @@ size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int hea
  *   kv_idx   [heads, nb, idx_stride] int32, each row's kept key blocks: distinct, in [0, nb);
  *   kv_cnt   [heads, nb] int32, 1 <= count <= nb (a row with count 0 yields zeros, lse = -inf)
  *   lse      nullable [heads, n_tokens] float32: natural-log sum-exp of each row's kept logits
- *   workspace, workspace_bytes: device scratch of at least bsga_attn_workspace_bytes(...) bytes;
- *            contents are overwritten; calls sharing one workspace must be stream-ordered.  May be
+ *   workspace, workspace_bytes: device scratch of bsga_attn_workspace_bytes(...) bytes (see there for
+ *            the least); overwritten; calls sharing one workspace must be stream-ordered.  May be
  *            NULL: the query blocks are then launched in index order instead of heaviest first,
  *            and every row is tied to the workgroup of its number (same results; a longer tail when
  *            row lengths differ a lot, and a few per cent slower on large shapes because the XCDs of
@@ -172,7 +174,7 @@ int bsga_sparse_attn(const void* q, const void* k, const void* v, int dtype, int
  * lives in a buffer built into the library (bsga_noalloc_scratch_bytes() bytes of device memory per
  * GPU, held from the first call on that GPU until the process ends).  The call allocates and frees
  * nothing and clears nothing with a memset.  Shapes whose launch order does not fit, i.e.
- * bsga_attn_workspace_bytes(...) > bsga_noalloc_scratch_bytes(), return BSGA_ERR_UNSUPPORTED (the
+ * the least workspace of bsga_attn_workspace_bytes above bsga_noalloc_scratch_bytes(), return BSGA_ERR_UNSUPPORTED (the
  * buffer holds heads * (ceil(n_tokens/64) + 33) + 4 <= 524288 words: e.g. 16 heads x 2 million
  * tokens).  All calls on one GPU share the one buffer and each overwrites it: calls that overlap in
  * time on the same GPU (different streams, or different threads) race; order them on one stream.
@@ -220,7 +222,8 @@ int bsga_sparse_attn_split(const void* q, const void* k, const void* v, int dtyp
  * Dense attention baseline  (Sec. 4.1, Eq. (1)): softmax(softmax_scale * Q K^T) V per head.
  * Same tensors and numerics as bsga_sparse_attn, every key visible.  workspace: NULL, or at least
  * 16 bytes (16-byte aligned; a smaller or misaligned one is ignored) for the counter that hands out
- * the last rows of a large launch at run time; overwritten; stream-ordered like the others.
+ * the last rows of a large launch at run time, or bsga_attn_workspace_bytes(...) bytes for the sharing of
+ * few long rows as well; overwritten; stream-ordered like the others.
  */
 int bsga_dense_attn(const void* q, const void* k, const void* v, int dtype, int heads,
                     int64_t n_tokens, int head_dim, float softmax_scale, void* out, float* lse,

@@ -253,14 +253,83 @@ struct Tile {
   unsigned oa, ob;  // byte offsets of the blocks' first keys inside the head (filled in by fix())
 };
 
+// Launches of few long rows (STREAM, see shares_rows() for which).  With one workgroup per row such a launch
+// leaves much of the chip idle: 100 rows keep 100 CUs busy, and 688 rows of unequal length end with a few long
+// ones.  Instead the key tiles of all rows, in order, are cut into equal pieces, one per workgroup that the
+// chip holds (at least kMinQuota tiles each), and a workgroup walks its piece: the end of one row, whole rows,
+// the start of another.
+// A row that several workgroups share is summed by the last of them to finish (weights have reference 0
+// everywhere, so partial sums just add up): every one leaves its unnormalised output and row sums in the
+// workspace and counts itself in; the one that completes the count reads them all, in piece order, so the
+// result does not depend on who came last.  Nobody waits for anybody.
+// Workspace of a launch: the table below, then two partial results per workgroup.
+constexpr int kStreamMaxRows = 1024;     // rows of such a launch are fewer
+constexpr int kStreamMaxPlaces = 1024;   // workgroups: 2 x 256 (blocks of 128 rows), 4 x 256 (blocks of 64)
+constexpr int kMinQuota = 4;
+struct StreamTable {
+  int quota, used, pad[14];
+  int start_row[kStreamMaxPlaces];   // workgroup w starts at tile start_tile[w] of row start_row[w]
+  int start_tile[kStreamMaxPlaces];
+  int arrived[kStreamMaxRows];       // pieces of the row that are done
+};
+constexpr size_t kStreamPartialWords = 66 * 64;  // per 64 query rows: 64 accumulators and 2 row sums of 64 lanes
+static_assert(kStreamBytes >= sizeof(StreamTable) + 2 * 1024 * kStreamPartialWords * sizeof(float), "workspace of a STREAM launch");
+
+// Partial results go between XCDs within a launch, so they are stored through to and loaded from the level that
+// the XCDs share (cache bit sc1, device scope).  A store is waited for before the counter tells of it.  (A
+// fence of device scope instead writes back and drops the whole L2 for every wave: 43 -> 207 us for one
+// frame; atomic loads, one waited for after the other: 142 us.)
+constexpr int kDeviceScope = 1 << 4;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(float* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, kStreamPartialWords * sizeof(float), 0x00020000);
+}
+
+// One workgroup, one thread per row: prefix sums of the rows' tiles, then each row writes the pieces that
+// start in it.  An empty row counts one tile, so that somebody writes its zeros.
+__global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32_t* __restrict__ kv_cnt, int rows, int nbk,
+                                                                     int per_tile, int places, StreamTable* __restrict__ tab) {
+  __shared__ int wave_sum[kStreamMaxRows / 64];
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  int tiles = 0;
+  if (t < rows) {
+    const int cnt = kv_cnt != nullptr ? min(max(kv_cnt[t], 0), nbk) : nbk;
+    tiles = max(1, (cnt + per_tile - 1) / per_tile);
+    tab->arrived[t] = 0;
+  }
+  int end = tiles;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(end, o);
+    if (lane >= o) end += x;
+  }
+  if (lane == 63) wave_sum[t >> 6] = end;
+  __syncthreads();
+  int total = 0;
+  for (int w = 0; w < kStreamMaxRows / 64; ++w) {
+    end += w < (t >> 6) ? wave_sum[w] : 0;
+    total += wave_sum[w];
+  }
+  const int quota = max(kMinQuota, (total + places - 1) / places);
+  const int begin = end - tiles;
+  for (int w = (begin + quota - 1) / quota; w * quota < end; ++w) {
+    tab->start_row[w] = t;
+    tab->start_tile[w] = w * quota - begin;
+  }
+  if (t == 0) {
+    tab->quota = quota;
+    tab->used = (total + quota - 1) / quota;
+  }
+}
+
 // B: query rows per workgroup = keys per LDS tile.  KB: size of the key blocks the index list refers
-// to, B or B/2.
-template <int B, int KB>
+// to, B or B/2.  STREAM: rows are shared out by tiles, see above.
+template <int B, int KB, bool STREAM>
 __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
     const int32_t* __restrict__ kv_cnt, const int32_t* __restrict__ order, int idx_stride, int64_t n_tokens, int nb,
-    int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int* __restrict__ next_row) {
+    int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int* __restrict__ next_row,
+    StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
   constexpr bool HALF = KB != B;          // two listed key blocks per tile
   constexpr int WQ = B / 64;              // waves along queries (64 rows each)
@@ -278,32 +347,9 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int g = lane >> 5;
   const int qi = wave % WQ;
   const int kh = wave / WQ;
-  // Which (head, query block) row this workgroup computes.  Workgroup number w of the grid runs on
-  // XCD w % 8, whatever the XCDs' speeds, and the chip holds 512 workgroups at a time, 64 per XCD.
-  //  - The first n_static workgroups take positions of the launch order by their number.  Inside each
-  //    full group of 512 consecutive workgroups the positions are dealt out so that an XCD gets 64
-  //    consecutive ones: rows that are neighbours in the order, whose lists tend to overlap, then
-  //    share one L2 instead of being spread over all eight.
-  //  - The other workgroups (there are more of them than rows left) take the remaining positions
-  //    first come, first served, through one atomic counter, and leave at once when none is left.
-  //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
-  //    through with its static share early thus takes more of the remaining rows than a slow one.
-  const int64_t total = int64_t(heads) * nb;
-  const int64_t w = int64_t(blockIdx.y) * nb + blockIdx.x;
-  int64_t pos;
-  if (w < n_static) {
-    const int r = static_cast<int>(w & 511);
-    pos = (w - r) + 512 <= n_static ? (w - r) + (r & 7) * 64 + (r >> 3) : w;
-  } else {
-    int* slot = reinterpret_cast<int*>(smem);
-    if (tid == 0) *slot = atomicAdd(next_row, 1);
-    __syncthreads();
-    const int t = __builtin_amdgcn_readfirstlane(*slot);
-    __syncthreads();  // the slot lies where the first K tile goes
-    if (t >= total - n_static) return;  // the whole workgroup leaves, before any other barrier
-    pos = n_static + t;
-  }
-  const int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
+  // One row, or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
+  // this is number `me`.
+  auto run = [&](int64_t row, int tile0, int tile1, int w0, int w1, int me) {
   const int h = static_cast<int>(min(max(row / nb, int64_t(0)), int64_t(heads - 1)));
   const int I = static_cast<int>(min(max(row - int64_t(h) * nb, int64_t(0)), int64_t(nb - 1)));
   const int64_t head_bytes = int64_t(h) * n_tokens * 128;
@@ -384,9 +430,17 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   float l_run[2];  // this lane's share of the row sums
 
   const bool dense = kv_idx == nullptr;
-  const int count = dense ? nbk : min(max(kv_cnt[rowid], 0), nbk);  // listed key blocks
-  const int ntiles = HALF ? (count + 1) >> 1 : count;
-  const int32_t* my_idx = dense ? nullptr : kv_idx + rowid * idx_stride;
+  constexpr int PER = HALF ? 2 : 1;  // list entries per tile
+  const int count_row = dense ? nbk : min(max(kv_cnt[rowid], 0), nbk);  // listed key blocks of the row
+  int count = count_row;                        // of them, those of the tiles this workgroup takes,
+  int ntiles = HALF ? (count + 1) >> 1 : count;  // the number of these tiles
+  int first = 0;                                // and the first one
+  auto take_tiles = [&](int t0, int t1) {
+    first = t0;
+    ntiles = min(t1, (count_row + PER - 1) / PER) - t0;
+    count = min(count_row - t0 * PER, ntiles * PER);
+  };
+  if constexpr (STREAM) take_tiles(tile0, tile1);
   // key block J: first token and number of tokens.  Blocks of the first segment (J < nbk1) tile
   // tokens [0, n_first), the others tokens [n_first, n_tokens); the last block of each may be ragged.
   auto key_start = [&](int J) { return J < seg.nbk1 ? J * KB : seg.n_first + (J - seg.nbk1) * KB; };
@@ -399,14 +453,21 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // past the end it repeats the last tile) and hands back the unchecked entries; the caller keeps
   // them for a tile before fix() turns them into block numbers, so nothing waits for the load.
   typedef const int32_t __attribute__((address_space(4))) * const_idx_ptr;
-  const const_idx_ptr cidx = (const_idx_ptr)my_idx;
+  const const_idx_ptr cidx = dense ? (const_idx_ptr) nullptr : (const_idx_ptr)(kv_idx + rowid * idx_stride);
   auto raw_at = [&](int it) -> Tile {
-    if (dense) return Tile{min(it, nbk - 1), -1, 0u, 0u};
-    constexpr int PER = HALF ? 2 : 1;  // list entries per tile
-    const int e = min(it, ntiles - 1) * PER;
-    Tile t{cidx[e], -1, 0u, 0u};
-    if constexpr (HALF) t.b = cidx[min(e + 1, count - 1)];
-    return t;
+    if constexpr (STREAM) {
+      if (dense) return Tile{min(first + it, nbk - 1), -1, 0u, 0u};
+      const int e = first * PER + min(it, ntiles - 1) * PER;
+      Tile t{cidx[e], -1, 0u, 0u};
+      if constexpr (HALF) t.b = cidx[min(e + 1, first * PER + count - 1)];
+      return t;
+    } else {
+      if (dense) return Tile{min(it, nbk - 1), -1, 0u, 0u};
+      const int e = min(it, ntiles - 1) * PER;
+      Tile t{cidx[e], -1, 0u, 0u};
+      if constexpr (HALF) t.b = cidx[min(e + 1, count - 1)];
+      return t;
+    }
   };
   // An absent second half gets an offset past the end of the head's buffer: the bounds check of
   // the loads then zero-fills it.
@@ -883,19 +944,93 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         }
         float l = l_run[b2] * a0 + l1 * a1;
         l += xor32(l);
-        if constexpr (!SAFE) bad = bad || !(l >= 0x1p-80f && l <= 0x1p100f);
         lt[b2] = l;
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
+          for (int i = 0; i < 16; ++i)
             o[db][b2][i] = o[db][b2][i] * a0 + park[((db * 2 + b2) * 16 + i) * 64 + lane] * a1;
-            if constexpr (!SAFE) bad = bad || !(fabsf(o[db][b2][i]) < INFINITY);
+      }
+    }
+    if constexpr (STREAM && !SAFE) {
+      if (w1 > w0) {  // uniform: a row of several workgroups
+        float* const partials = reinterpret_cast<float*>(tab + 1);
+        // a workgroup has at most two parts of rows: the end of one and the start of another
+        // per 64 query rows: accumulators four to a lane, [16][64 lanes][4], then the row sums [2][64 lanes]
+        auto slot = [&](int w) { return partial_rsrc(partials + ((2 * int64_t(w) + (w == w0)) * WQ + qi) * kStreamPartialWords); };
+        if (kh == 0) {
+          const auto dst = slot(me);
+#pragma unroll
+          for (int b2 = 0; b2 < 2; ++b2) {
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+              for (int r4 = 0; r4 < 4; ++r4) {
+                const f32x16& x = o[db][b2];
+                const f32x4 y = {x[4 * r4], x[4 * r4 + 1], x[4 * r4 + 2], x[4 * r4 + 3]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, y), dst, lane * 16,
+                                                       ((db * 2 + b2) * 4 + r4) * 1024, kDeviceScope);
+              }
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lt[b2]), dst, lane * 4, 16384 + b2 * 256, kDeviceScope);
           }
+        }
+        __builtin_amdgcn_s_waitcnt(0);  // this part has arrived where every XCD sees it ...
+        __syncthreads();                // ... before it is counted
+        if (tid == 0) *flag = atomicAdd(&tab->arrived[row], 1);
+        __syncthreads();
+        const int before = __builtin_amdgcn_readfirstlane(*flag);
+        __syncthreads();
+        if (before != w1 - w0) return false;  // somebody is still at it
+        if (tid == 0) *flag = 0;
+        if (kh == 0) {
+#pragma unroll
+          for (int b2 = 0; b2 < 2; ++b2) {
+            lt[b2] = 0.f;
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) o[db][b2][i] = 0.f;
+          }
+          for (int w = w0; w <= w1; ++w) {
+            const auto src = slot(w);
+            f32x4 y[2][2][4];
+            float ly[2];
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2) {
+#pragma unroll
+              for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                  y[db][b2][r4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                                src, lane * 16, ((db * 2 + b2) * 4 + r4) * 1024, kDeviceScope));
+              ly[b2] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, lane * 4, 16384 + b2 * 256, kDeviceScope));
+            }
+            __builtin_amdgcn_sched_barrier(0);  // all of them in flight before the first is added
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2) {
+#pragma unroll
+              for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[db][b2][i] += y[db][b2][i >> 2][i & 3];
+              lt[b2] += ly[b2];
+            }
+          }
+        }
+        __syncthreads();  // the cleared flag
       }
     }
     if constexpr (!SAFE) {
-      if (count <= 0) bad = false;  // an empty row is zeros by definition, not a range problem
+      if (kh == 0) {
+#pragma unroll
+        for (int b2 = 0; b2 < 2; ++b2) {
+          bad = bad || !(lt[b2] >= 0x1p-80f && lt[b2] <= 0x1p100f);
+#pragma unroll
+          for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bad = bad || !(fabsf(o[db][b2][i]) < INFINITY);
+        }
+      }
+      if (count_row <= 0) bad = false;  // an empty row is zeros by definition, not a range problem
       if (bad) *flag = 1;
       __syncthreads();
       const bool any_bad = *flag != 0;
@@ -927,11 +1062,81 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   };
 
   if (pass(std::false_type{})) {
+    if constexpr (STREAM) take_tiles(0, 1 << 30);  // the whole row, whoever had its parts
     pass(std::true_type{});
   }
+  };  // run
+
+  if constexpr (STREAM) {
+    // consecutive pieces to one XCD (workgroup w runs on XCD w % 8), as for whole rows
+    const int w = static_cast<int>(blockIdx.x), places = static_cast<int>(gridDim.x);
+    const int me = (w & 7) * (places >> 3) + (w >> 3);
+    if (me >= tab->used) return;  // the whole workgroup, before any barrier
+    const int quota = tab->quota;
+    const int rows = heads * nb;
+    int row = __builtin_amdgcn_readfirstlane(tab->start_row[me]);
+    int tile = __builtin_amdgcn_readfirstlane(tab->start_tile[me]);
+    int done = 0;
+    while (done < quota && row < rows) {
+      const int cnt = kv_cnt != nullptr ? min(max(kv_cnt[row], 0), nbk) : nbk;
+      const int tiles = __builtin_amdgcn_readfirstlane(max(1, HALF ? (cnt + 1) >> 1 : cnt));
+      const int take = min(quota - done, tiles - tile);
+      const int begin = me * quota + done - tile;  // the row's first tile, counted over all rows
+      run(row, tile, tile + take, begin / quota, (begin + tiles - 1) / quota, me);
+      done += take;
+      tile = 0;
+      ++row;
+      __syncthreads();  // the next row's loads overwrite what the end of this one reads
+    }
+    return;
+  }
+  // Which (head, query block) row this workgroup computes.  Workgroup number w of the grid runs on
+  // XCD w % 8, whatever the XCDs' speeds, and the chip holds 512 workgroups at a time, 64 per XCD.
+  //  - The first n_static workgroups take positions of the launch order by their number.  Inside each
+  //    full group of 512 consecutive workgroups the positions are dealt out so that an XCD gets 64
+  //    consecutive ones: rows that are neighbours in the order, whose lists tend to overlap, then
+  //    share one L2 instead of being spread over all eight.
+  //  - The other workgroups (there are more of them than rows left) take the remaining positions
+  //    first come, first served, through one atomic counter, and leave at once when none is left.
+  //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
+  //    through with its static share early thus takes more of the remaining rows than a slow one.
+  const int64_t total = int64_t(heads) * nb;
+  const int64_t w = int64_t(blockIdx.y) * nb + blockIdx.x;
+  int64_t pos;
+  if (w < n_static) {
+    const int r = static_cast<int>(w & 511);
+    pos = (w - r) + 512 <= n_static ? (w - r) + (r & 7) * 64 + (r >> 3) : w;
+  } else {
+    int* slot = reinterpret_cast<int*>(smem);
+    if (tid == 0) *slot = atomicAdd(next_row, 1);
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(*slot);
+    __syncthreads();  // the slot lies where the first K tile goes
+    if (t >= total - n_static) return;  // the whole workgroup leaves, before any other barrier
+    pos = n_static + t;
+  }
+  const int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
+  run(row, 0, 0, 0, 0, 0);
 }
 
 }  // namespace
+
+// Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
+// partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
+// idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
+//  - Blocks of 64 (two waves per workgroup, four workgroups to fill a CU): 108 rows of 108 tiles 82 / 35 us
+//    (31 / 28), 344 of 344 328 / 175 (103 / 57), 688 of 344 337 / 304 (112 / 91), 520 of 65 69 / 60 (30 / 31);
+//    688 of 43 51 / 54 (25 / 32), 864 of 108 126 / 128 (47 / 51).
+//  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
+//    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
+//    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
+//    82 / 81 (36 / 39).
+static bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
+  if (rows >= kStreamMaxRows) return false;
+  if (block == 64) return rows <= 700 && tiles >= 64;
+  const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
+  return (idle && rows * tiles >= 50 * 512) || (!dense && rows * tiles >= 200 * 512);
+}
 
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
@@ -985,20 +1190,32 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t lds64 = 4 * 64 * 128, lds128 = 4 * 128 * 128;
   if (getenv("BSGA_DEBUG") != nullptr) {
     int n64 = -1, n128 = -1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64>, 128, lds64);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128>, 256, lds128);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false>, 128, lds64);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false>, 256, lds128);
     fprintf(stderr, "[bsga] attention occupancy (workgroups per CU): block 64 -> %d, block 128 -> %d\n", n64, n128);
   }
-  if (block == 64) {
-    hipLaunchKernelGGL((attn_bf16_kernel<64, 64>), grid, dim3(128), lds64, stream, qp, kp, vp, op, lse, kv_idx,
-                       kv_cnt, order, idx_stride, n_tokens, nb, nbk, scale_log2, seg, heads, n_static, next_row);
-  } else if (block_k == 128) {
-    hipLaunchKernelGGL((attn_bf16_kernel<128, 128>), grid, dim3(256), lds128, stream, qp, kp, vp, op, lse, kv_idx,
-                       kv_cnt, order, idx_stride, n_tokens, nb, nbk, scale_log2, seg, heads, n_static, next_row);
-  } else {
-    hipLaunchKernelGGL((attn_bf16_kernel<128, 64>), grid, dim3(256), lds128, stream, qp, kp, vp, op, lse, kv_idx,
-                       kv_cnt, order, idx_stride, n_tokens, nb, nbk, scale_log2, seg, heads, n_static, next_row);
+  auto launch = [&](auto kernel, dim3 g, int threads, size_t lds, StreamTable* tab) {
+    hipLaunchKernelGGL(kernel, g, dim3(threads), lds, stream, qp, kp, vp, op, lse, kv_idx, kv_cnt, order, idx_stride,
+                       n_tokens, nb, nbk, scale_log2, seg, heads, n_static, next_row, tab);
+  };
+  const size_t order_bytes = attn_order_bytes(heads, n_tokens);
+  if (!big && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&
+      shares_rows(rows, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
+      attn_workspace_granted() >= order_bytes + kStreamBytes + 256) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
+    StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
+    const int places = block == 64 ? 1024 : 512;
+    hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, static_cast<int>(rows), nbk,
+                       block_k == block ? 1 : 2, places, tab);
+    if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true>, dim3(places), 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true>, dim3(places), 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true>, dim3(places), 256, lds128, tab);
+    return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
+  if (block == 64) launch(attn_bf16_kernel<64, 64, false>, grid, 128, lds64, nullptr);
+  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false>, grid, 256, lds128, nullptr);
+  else launch(attn_bf16_kernel<128, 64, false>, grid, 256, lds128, nullptr);
   return check_hip(hipGetLastError(), "bsga bf16 attention launch");
 }
 

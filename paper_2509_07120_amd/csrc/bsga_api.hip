@@ -53,14 +53,14 @@ static int check_block(const char* fn, int block) {
   return BSGA_OK;
 }
 
+// What an attention call cannot do without if it is given a workspace at all.  Q, K and V are read in place;
+// the launch order is the only scratch of a large call.
 static size_t attn_workspace(int dtype, int heads, int64_t n_tokens) {
-  // Q, K and V are read in place and every intermediate stays on chip; the only scratch is the
-  // launch order of the (head, query block) rows of the sparse bf16 kernel: one int32 per row, sized
-  // for the smaller block size (plus one block for a split sequence), plus a [32 classes][heads] table.
-  if (dtype != BSGA_BF16) return 0;
-  return (static_cast<size_t>(heads) * static_cast<size_t>(ceil_div(n_tokens, 64) + 1) + 32u * static_cast<size_t>(heads) + 4u) *
-         sizeof(int32_t);
+  return dtype == BSGA_BF16 ? attn_order_bytes(heads, n_tokens) : 0;
 }
+
+static thread_local size_t g_attn_granted = 0;
+size_t attn_workspace_granted() { return g_attn_granted; }
 
 static int attn_common(const char* fn, const void* q, const void* k, const void* v, int dtype, int heads,
                        int64_t n_tokens, int64_t n_first, int head_dim, int block, int block_k, float softmax_scale,
@@ -98,6 +98,7 @@ static int attn_common(const char* fn, const void* q, const void* k, const void*
   }
   // the dense kernel uses a workspace, if it gets one, for one counter (balancing rows across the XCDs)
   if (!kv_idx && workspace && (workspace_bytes < 16 || !aligned16(workspace))) workspace = nullptr;
+  g_attn_granted = workspace ? workspace_bytes : 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == BSGA_BF16)
     return launch_attn_bf16(q, k, v, heads, n_tokens, n_first, block, block_k, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse,
@@ -222,7 +223,9 @@ int bsga_gather_tokens(const void* src, int dtype, int heads, int64_t n_src, int
 
 size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int head_dim) {
   if ((dtype != BSGA_BF16 && dtype != BSGA_FP32) || heads < 1 || n_tokens < 1 || head_dim != 64) return 0;
-  return attn_workspace(dtype, heads, n_tokens);
+  const size_t order = attn_workspace(dtype, heads, n_tokens);
+  // 256 more to align the partial results
+  return order > 0 && attn_stream_shape(heads, n_tokens) ? order + kStreamBytes + 256 : order;
 }
 
 int bsga_sparse_attn(const void* q, const void* k, const void* v, int dtype, int heads, int64_t n_tokens,

@@ -24,6 +24,24 @@ inline int64_t split_blocks(int64_t n_tokens, int64_t n_first, int64_t block) {
   return ceil_div(n_first, block) + ceil_div(n_tokens - n_first, block);
 }
 
+// Scratch of the bf16 attention kernels.  Every call may use the launch order of the (head, query block)
+// rows: one int32 per row, sized for the smaller block size (plus one block for a split sequence), plus a
+// [32 classes][heads] table.
+inline size_t attn_order_bytes(int heads, int64_t n_tokens) {
+  return (static_cast<size_t>(heads) * static_cast<size_t>(ceil_div(n_tokens, 64) + 1) + 32u * static_cast<size_t>(heads) + 4u) *
+         sizeof(int32_t);
+}
+// Calls of few rows share rows between workgroups and then need room for partial results, whatever the
+// number of rows: two of 33 KB for each of 512 workgroups, and a table.  Up to 4032 tokens (63 blocks of 64) a
+// row is too short to be worth sharing.
+constexpr size_t kStreamBytes = 2 * 512 * (2 * 66 * 64 * sizeof(float)) + (size_t(1) << 14);
+inline bool attn_stream_shape(int heads, int64_t n_tokens) {
+  return n_tokens > 4032 && static_cast<int64_t>(heads) * ceil_div(n_tokens, 128) < 1024;
+}
+// Bytes of the workspace of the attention call that this thread is making (a call may come with less than
+// bsga_attn_workspace_bytes, down to the launch order alone).
+size_t attn_workspace_granted();
+
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);
