@@ -126,16 +126,37 @@ __device__ __forceinline__ int order_class(int cnt, int nb) {  // class 0 holds 
   return (kOrderClasses - 1) - static_cast<int>((int64_t(c) * (kOrderClasses - 1)) / nb);
 }
 
-__global__ __launch_bounds__(256) void order_hist_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nbk,
+// kept count of unit I of head h: of row I, or (pair) of the longer of rows 2I and 2I + 1
+__device__ __forceinline__ int unit_count(const int32_t* __restrict__ kv_cnt, int h, int nb, int I, bool pair) {
+  const int32_t* c = kv_cnt + int64_t(h) * nb;
+  return pair ? max(c[2 * I], c[min(2 * I + 1, nb - 1)]) : c[I];
+}
+
+// Below: nu = units (rows, or pairs of rows) per head.
+__global__ __launch_bounds__(256) void order_hist_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
                                                          int heads, int32_t* __restrict__ table) {
   __shared__ int bins[kOrderClasses];
   const int h = blockIdx.x;
   const int t = threadIdx.x;
   if (t < kOrderClasses) bins[t] = 0;
   __syncthreads();
-  for (int I = t; I < nb; I += 256) atomicAdd(&bins[order_class(kv_cnt[int64_t(h) * nb + I], nbk)], 1);
+  for (int I = t; I < nu; I += 256) atomicAdd(&bins[order_class(unit_count(kv_cnt, h, nb, I, pair), nbk)], 1);
   __syncthreads();
   if (t < kOrderClasses) table[int64_t(t) * heads + h] = bins[t];
+}
+
+// The first class whose lower bound (31 - c) / 31 is below 1.4 x the mean kept fraction; total(c) = units of class c.
+template <typename Total>
+__device__ __forceinline__ int bulk_class(Total&& total) {
+  double rows = 0.0, mass = 0.0;  // mass: kept fraction at the middle of each class
+  for (int c = 0; c < kOrderClasses; ++c) {
+    rows += static_cast<double>(total(c));
+    mass += static_cast<double>(total(c)) * (kOrderClasses - 1 - c + 0.5) / (kOrderClasses - 1);
+  }
+  const double mean = rows > 0.0 ? mass / rows : 1.0;
+  int c = 0;
+  while (c < kOrderClasses - 1 && static_cast<double>(kOrderClasses - 1 - c) / (kOrderClasses - 1) >= 1.4 * mean) ++c;
+  return c;
 }
 
 // One workgroup.  Finds the first class c_bulk whose lower bound (31 - c) / 31 is below 1.4 x the
@@ -151,14 +172,7 @@ __global__ __launch_bounds__(256) void order_merge_kernel(int32_t* __restrict__ 
     atomicAdd(reinterpret_cast<unsigned long long*>(&total[i / heads]), static_cast<unsigned long long>(table[i]));
   __syncthreads();
   if (t == 0) {
-    double rows = 0.0, mass = 0.0;  // mass: kept fraction at the middle of each class
-    for (int c = 0; c < kOrderClasses; ++c) {
-      rows += static_cast<double>(total[c]);
-      mass += static_cast<double>(total[c]) * (kOrderClasses - 1 - c + 0.5) / (kOrderClasses - 1);
-    }
-    const double mean = rows > 0.0 ? mass / rows : 1.0;
-    int c = 0;
-    while (c < kOrderClasses - 1 && static_cast<double>(kOrderClasses - 1 - c) / (kOrderClasses - 1) >= 1.4 * mean) ++c;
+    const int c = bulk_class([&](int i) { return total[i]; });
     c_bulk = c;
     table[int64_t(kOrderClasses) * heads] = c;
     table[int64_t(kOrderClasses) * heads + 1] = 0;  // the attention kernel's counter of rows handed out at run time
@@ -201,8 +215,8 @@ __global__ __launch_bounds__(1024) void order_scan_kernel(int32_t* __restrict__ 
   }
 }
 
-__global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nbk,
-                                                          int heads, const int32_t* __restrict__ table,
+__global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu,
+                                                          bool pair, int nbk, int heads, const int32_t* __restrict__ table,
                                                           int32_t* __restrict__ order) {
   __shared__ int next[kOrderClasses];
   __shared__ int wave_bulk[4];
@@ -212,9 +226,9 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
   const int c_bulk = table[int64_t(kOrderClasses) * heads];
   __syncthreads();
   int bulk_next = next[c_bulk];  // every thread keeps its own copy of the bulk group's fill position
-  for (int base = 0; base < nb; base += 256) {
+  for (int base = 0; base < nu; base += 256) {
     const int I = base + t;
-    const int cls = I < nb ? min(order_class(kv_cnt[int64_t(h) * nb + I], nbk), c_bulk) : -1;
+    const int cls = I < nu ? min(order_class(unit_count(kv_cnt, h, nb, I, pair), nbk), c_bulk) : -1;
     // the bulk group keeps the natural order of its rows: rank of this row among the chunk's bulk rows
     const bool bulk = cls == c_bulk;
     const unsigned long long vote = __ballot(bulk);
@@ -226,10 +240,66 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
       before += w < (t >> 6) ? wave_bulk[w] : 0;
       chunk += wave_bulk[w];
     }
-    if (bulk) order[bulk_next + before + below] = h * nb + I;
-    else if (cls >= 0) order[atomicAdd(&next[cls], 1)] = h * nb + I;
+    if (bulk) order[bulk_next + before + below] = h * nu + I;
+    else if (cls >= 0) order[atomicAdd(&next[cls], 1)] = h * nu + I;
     bulk_next += chunk;
     __syncthreads();
+  }
+}
+
+// The whole launch order in one workgroup, for up to kOrderOneMax units: about 7 us, where the four kernels above
+// take 5 us each whatever the size (a fifth of an 8-frame layer at high sparsity).  The units of a thread are consecutive, so the bulk class keeps its order.
+constexpr int kOrderOneMax = 8192;
+__global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
+                                                         int heads, int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
+  constexpr int MAX = kOrderOneMax / 1024;
+  __shared__ int total[kOrderClasses], next[kOrderClasses];
+  __shared__ int c_bulk_s, wave_bulk[16];
+  const int t = threadIdx.x;
+  const int units = heads * nu;
+  const int per = (units + 1023) >> 10;
+  if (t < kOrderClasses) total[t] = 0;
+  __syncthreads();
+  int cls[MAX];
+#pragma unroll
+  for (int i = 0; i < MAX; ++i) {
+    const int u = t * per + i;
+    cls[i] = -1;
+    if (i < per && u < units) {
+      const int h = u / nu;
+      cls[i] = order_class(unit_count(kv_cnt, h, nb, u - h * nu, pair), nbk);
+      atomicAdd(&total[cls[i]], 1);
+    }
+  }
+  __syncthreads();
+  if (t == 0) {
+    const int c_bulk = bulk_class([&](int c) { return total[c]; });
+    int at = 0;
+    for (int c = 0; c <= c_bulk; ++c) {
+      next[c] = at;
+      at += total[c];
+    }
+    c_bulk_s = c_bulk;
+    *next_row = 0;  // the attention kernel's counter of rows handed out at run time
+  }
+  __syncthreads();
+  const int c_bulk = c_bulk_s;
+  int bulk = 0;
+#pragma unroll
+  for (int i = 0; i < MAX; ++i) bulk += cls[i] >= c_bulk;
+  int upto = bulk;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(upto, o);
+    if ((t & 63) >= o) upto += x;
+  }
+  if ((t & 63) == 63) wave_bulk[t >> 6] = upto;
+  __syncthreads();
+  int pos = next[c_bulk] + upto - bulk;
+  for (int w = 0; w < (t >> 6); ++w) pos += wave_bulk[w];
+#pragma unroll
+  for (int i = 0; i < MAX; ++i) {
+    if (cls[i] >= c_bulk) order[pos++] = t * per + i;
+    else if (cls[i] >= 0) order[atomicAdd(&next[cls[i]], 1)] = t * per + i;
   }
 }
 
@@ -323,7 +393,16 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 
 // B: query rows per workgroup = keys per LDS tile.  KB: size of the key blocks the index list refers
 // to, B or B/2.  STREAM: rows are shared out by tiles, see above.
-template <int B, int KB, bool STREAM>
+//
+// PAIR: the workgroup's 128 query rows are two blocks of 64 with a list each (KB = 64).  Tiles of two key
+// blocks that both lists name go through the pipelined loop of the 128-row kernel, which a workgroup of one
+// block of 64 cannot use (half the products per key loaded, and as many barriers and loads per tile); then a
+// tile holds one key block of the first list alone and one of the second alone, and each wave takes
+// half the keys of its own.  The two lists are sorted into these three in LDS (bit sets, then a scan), so they
+// may come in any order; kPairMaxBlocks key blocks fit beside the tiles with two workgroups to a CU.
+// 2,752 rows of 172 blocks, nine tenths kept: 515 -> 442 us; 5,504 of 344 1,900 -> 1,550.
+constexpr int kPairMaxBlocks = 4096;
+template <int B, int KB, bool STREAM, bool PAIR>
 __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
@@ -331,6 +410,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int* __restrict__ next_row,
     StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
+  static_assert(!PAIR || (B == 128 && KB == 64 && !STREAM), "pairs of blocks of 64");
+  constexpr int QB = PAIR ? 64 : B;       // query block size
   constexpr bool HALF = KB != B;          // two listed key blocks per tile
   constexpr int WQ = B / 64;              // waves along queries (64 rows each)
   constexpr int KW = B / 2;               // keys per wave per tile
@@ -347,17 +428,22 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int g = lane >> 5;
   const int qi = wave % WQ;
   const int kh = wave / WQ;
-  // One row, or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
+  const int units = PAIR ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
+
+  // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
   // this is number `me`.
   auto run = [&](int64_t row, int tile0, int tile1, int w0, int w1, int me) {
-  const int h = static_cast<int>(min(max(row / nb, int64_t(0)), int64_t(heads - 1)));
-  const int I = static_cast<int>(min(max(row - int64_t(h) * nb, int64_t(0)), int64_t(nb - 1)));
+  const int h = static_cast<int>(min(max(row / units, int64_t(0)), int64_t(heads - 1)));
+  const int u_in_head = static_cast<int>(min(max(row - int64_t(h) * units, int64_t(0)), int64_t(units - 1)));
+  const int I = PAIR ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
+  const bool no_block = PAIR && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
   const int64_t head_bytes = int64_t(h) * n_tokens * 128;
   const int64_t rowid = int64_t(h) * nb + I;
   // this query block: first token and number of tokens (a block never crosses the segment boundary)
   const int n_tok = static_cast<int>(n_tokens);
-  const int q_start = I < seg.nbq1 ? I * B : seg.n_first + (I - seg.nbq1) * B;
-  const int q_valid = min(B, (I < seg.nbq1 ? seg.n_first : n_tok) - q_start);
+  const int q_start = I < seg.nbq1 ? I * QB : seg.n_first + (I - seg.nbq1) * QB;
+  const int q_valid = no_block ? 0 : min(QB, (I < seg.nbq1 ? seg.n_first : n_tok) - q_start);
+  const int q_off = PAIR ? 0 : qi * 64;  // this wave's first row in the block
   // raw buffer views of this head's K and V (byte-addressed, bounds-checked by the hardware)
   const unsigned head_size = static_cast<unsigned>(n_tokens * 128);
   const i32x4 krsrc = make_rsrc(k + head_bytes, head_size);
@@ -370,7 +456,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   bf16x8 qf[2][4];
 #pragma unroll
   for (int b2 = 0; b2 < 2; ++b2) {
-    const int64_t row = int64_t(q_start) + qi * 64 + b2 * 32 + n;  // rows past q_valid are computed, not stored
+    const int64_t row = int64_t(q_start) + q_off + b2 * 32 + n;  // rows past q_valid are computed, not stored
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       u32x4 x = {0u, 0u, 0u, 0u};
@@ -431,8 +517,91 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 
   const bool dense = kv_idx == nullptr;
   constexpr int PER = HALF ? 2 : 1;  // list entries per tile
-  const int count_row = dense ? nbk : min(max(kv_cnt[rowid], 0), nbk);  // listed key blocks of the row
-  int count = count_row;                        // of them, those of the tiles this workgroup takes,
+  const int count_row = no_block ? 0 : dense ? nbk : min(max(kv_cnt[rowid], 0), nbk);  // listed key blocks of the row
+  // PAIR: blocks in both lists, then those of the first alone, at list[0 ..); those of the second alone at
+  // list[nbk ..)
+  unsigned short* const list = reinterpret_cast<unsigned short*>(smem + 4 * TILE_BYTES);
+  int n_both = 0, n_alone[2] = {0, 0};
+  if constexpr (PAIR) {
+    unsigned* const bits = reinterpret_cast<unsigned*>(smem);             // two bit sets of kPairMaxBlocks
+    unsigned long long* const part = reinterpret_cast<unsigned long long*>(smem + 1024);  // per wave
+    constexpr int WORDS = kPairMaxBlocks / 32;
+    // counts and the first 256 entries of both lists in one round of loads: entries past a count are
+    // whatever the buffer holds (idx_stride >= nbk) and are not used
+    const int64_t id0 = int64_t(h) * nb + 2 * u_in_head;
+    const bool two = 2 * u_in_head + 1 < nb;
+    const int32_t* const idx0 = kv_idx + id0 * idx_stride;
+    const int32_t* const idx1 = two ? idx0 + idx_stride : idx0;
+    const int c0 = kv_cnt[id0], c1 = kv_cnt[two ? id0 + 1 : id0];
+    int j0 = idx0[min(tid, nbk - 1)], j1 = idx1[min(tid, nbk - 1)];
+    const int n0 = min(max(c0, 0), nbk), n1 = two ? min(max(c1, 0), nbk) : 0;
+    auto enter = [&](int r, int J) {
+      const int j = min(max(J, 0), nbk - 1);
+      atomicOr(&bits[r * WORDS + (j >> 5)], 1u << (j & 31));
+    };
+    if (10 * (n0 + n1) < 6 * nbk) {
+      // Short lists: of unrelated ones few blocks are in both, and sorting costs more than that saves.  5,504
+      // rows of 344 tiles, a tenth kept: sorted 271 us, unsorted 249; a quarter 587, 567; half 1065 sorted.
+      auto put = [&](int e, int a0, int a1) {
+        if (e < n0) list[e] = static_cast<unsigned short>(min(max(a0, 0), nbk - 1));
+        if (e < n1) list[nbk + e] = static_cast<unsigned short>(min(max(a1, 0), nbk - 1));
+      };
+      put(tid, j0, j1);
+      for (int e = tid + 2 * B; e < max(n0, n1); e += 2 * B) put(e, idx0[e], idx1[e]);
+      n_alone[0] = n0;
+      n_alone[1] = n1;
+      __syncthreads();
+    } else {
+      bits[tid] = 0u;  // 256 threads, 2 x 128 words
+      __syncthreads();
+      if (tid < n0) enter(0, j0);
+      if (tid < n1) enter(1, j1);
+      for (int e = tid + 2 * B; e < max(n0, n1); e += 2 * B) {
+        j0 = idx0[e];
+        j1 = idx1[e];
+        if (e < n0) enter(0, j0);
+        if (e < n1) enter(1, j1);
+      }
+      __syncthreads();
+      const unsigned b0 = tid < WORDS ? bits[tid] : 0u, b1 = tid < WORDS ? bits[WORDS + tid] : 0u;
+      unsigned set[3] = {b0 & b1, b0 & ~b1, b1 & ~b0};
+      // the three counts (each at most 4096) in two words, summed over the lanes up to this one
+      const unsigned mine_lo = __popc(set[0]) | (__popc(set[1]) << 16), mine_hi = __popc(set[2]);
+      unsigned lo = mine_lo, hi = mine_hi;
+      auto add_from = [&](auto ctrl, auto rows) {  // adds the value of the lane that the DPP control names, 0 if there is none
+        constexpr int C = decltype(ctrl)::value, R = decltype(rows)::value;
+        lo += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), C, R, 0xf, false));
+        hi += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(hi), C, R, 0xf, false));
+      };
+      add_from(Int<0x111>{}, Int<0xf>{});  // 1, 2, 4, 8 lanes before, within a row of 16
+      add_from(Int<0x112>{}, Int<0xf>{});
+      add_from(Int<0x114>{}, Int<0xf>{});
+      add_from(Int<0x118>{}, Int<0xf>{});
+      add_from(Int<0x142>{}, Int<0xa>{});  // last lane of rows 0 and 2 into rows 1 and 3
+      add_from(Int<0x143>{}, Int<0xc>{});  // lane 31 into rows 2 and 3
+      if (lane == 63) part[wave] = (static_cast<unsigned long long>(hi) << 32) | lo;
+      __syncthreads();
+      const unsigned long long in0 = part[0], all = in0 + part[1];  // words 0..127: the first two waves
+      lo -= mine_lo;
+      hi -= mine_hi;
+      if (wave == 1) {
+        lo += static_cast<unsigned>(in0);
+        hi += static_cast<unsigned>(in0 >> 32);
+      }
+      n_both = __builtin_amdgcn_readfirstlane(static_cast<int>(all & 0xffff));
+      n_alone[0] = __builtin_amdgcn_readfirstlane(static_cast<int>((all >> 16) & 0xffff));
+      n_alone[1] = __builtin_amdgcn_readfirstlane(static_cast<int>(all >> 32));
+      const int before[3] = {static_cast<int>(lo & 0xffff), static_cast<int>(lo >> 16), static_cast<int>(hi)};
+      const int at[3] = {0, n_both, nbk};
+#pragma unroll
+      for (int x = 0; x < 3; ++x) {
+        int pos = at[x] + before[x];
+        for (unsigned b = set[x]; b != 0u; b &= b - 1u) list[pos++] = static_cast<unsigned short>(tid * 32 + __ffs(b) - 1);
+      }
+      __syncthreads();  // the lists are complete; the tiles may overwrite the bit sets
+    }
+  }
+  int count = PAIR ? n_both : count_row;                        // of them, those of the tiles this workgroup takes,
   int ntiles = HALF ? (count + 1) >> 1 : count;  // the number of these tiles
   int first = 0;                                // and the first one
   auto take_tiles = [&](int t0, int t1) {
@@ -455,7 +624,10 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   typedef const int32_t __attribute__((address_space(4))) * const_idx_ptr;
   const const_idx_ptr cidx = dense ? (const_idx_ptr) nullptr : (const_idx_ptr)(kv_idx + rowid * idx_stride);
   auto raw_at = [&](int it) -> Tile {
-    if constexpr (STREAM) {
+    if constexpr (PAIR) {
+      const int e = min(it, ntiles - 1) * 2;
+      return Tile{list[e], list[min(e + 1, count - 1)], 0u, 0u};
+    } else if constexpr (STREAM) {
       if (dense) return Tile{min(first + it, nbk - 1), -1, 0u, 0u};
       const int e = first * PER + min(it, ntiles - 1) * PER;
       Tile t{cidx[e], -1, 0u, 0u};
@@ -473,7 +645,10 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // the loads then zero-fills it.
   auto fix = [&](const Tile& r, int it) -> Tile {  // r = raw_at(it)
     Tile t{r.a, -1, 0u, head_size};
-    if (!dense) {
+    if constexpr (PAIR) {
+      t.a = __builtin_amdgcn_readfirstlane(r.a);
+      if (min(it, ntiles - 1) * 2 + 1 < count) t.b = __builtin_amdgcn_readfirstlane(r.b);
+    } else if (!dense) {
       t.a = min(max(r.a, 0), nbk - 1);
       if constexpr (HALF) {
         if (min(it, ntiles - 1) * 2 + 1 < count) t.b = min(max(r.b, 0), nbk - 1);
@@ -503,14 +678,14 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const int cnt = J < 0 ? 0 : key_count(J);
     return HALF ? kh * KW + cnt : min(cnt, (kh + 1) * KW);
   };
-  // scores of the wave's 32-key sub-tile u: keys at or past `limit` (tile row numbers) get weight 0
-  // (register i of the lane is tile row kh*KW + 32u + 8(i/4) + 4g + i%4).  Runs for the few ragged
+  // scores of a 32-key sub-tile: keys at or past `limit` (tile row numbers) get weight 0
+  // (register i of the lane is tile row row0 + 8(i/4) + 4g + i%4).  Runs for the few ragged
   // tiles only; the lane number is taken afresh through an opaque instruction, so that nothing of
   // this is computed ahead and kept in registers across the tile loops.
-  auto mask_keys = [&](f32x16& sc, int u, int limit) {
+  auto mask_keys = [&](f32x16& sc, int row0, int limit) {  // row0: tile row of the sub-tile's first key
     int l;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    const int t = limit - kh * KW - u * 32 - ((l >> 5) << 2);  // row 8(i/4) + i%4 is masked iff it is >= t
+    const int t = limit - row0 - ((l >> 5) << 2);  // row 8(i/4) + i%4 is masked iff it is >= t
 #pragma unroll
     for (int i = 0; i < 16; ++i) sc[i] = (8 * (i >> 2) + (i & 3) >= t) ? -INFINITY : sc[i];
   };
@@ -562,17 +737,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   };
 
   // K operands (A of S^T = K Q^T) of the wave's 32-key sub-tile u; boff = byte offset of the buffer
-  auto read_k = [&](bf16x8 (&ka)[4], unsigned boff, int u) {
+  auto read_k_at = [&](const unsigned (&at)[4], bf16x8 (&ka)[4], unsigned boff, int u) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) ka[c] = *LDS_PTR(bf16x8, smem + boff + kaddr[(u & 1) ? (c ^ 2) : c] + u * 4096);
+    for (int c = 0; c < 4; ++c) ka[c] = *LDS_PTR(bf16x8, smem + boff + at[(u & 1) ? (c ^ 2) : c] + u * 4096);
   };
+  auto read_k = [&](bf16x8 (&ka)[4], unsigned boff, int u) { read_k_at(kaddr, ka, boff, u); };
   // V^T operands (A of O^T += V^T P^T) of sub-tile u: [dim block][16-key chunk]
-  auto read_v = [&](bf16x8 (&va)[2][2], unsigned boff, int u) {
+  auto read_v_at = [&](const unsigned (&at)[2], bf16x8 (&va)[2][2], unsigned boff, int u) {
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
       for (int cp = 0; cp < 2; ++cp) {
-        const unsigned char* p = smem + boff + vaddr[db] + (32 * u + 16 * cp) * 128;
+        const unsigned char* p = smem + boff + at[db] + (32 * u + 16 * cp) * 128;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
         const s16x4 hi =
             __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 8 * 128));
@@ -581,6 +757,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         va[db][cp] = __builtin_bit_cast(bf16x8, av);
       }
   };
+  auto read_v = [&](bf16x8 (&va)[2][2], unsigned boff, int u) { read_v_at(vaddr, va, boff, u); };
 
   // weights of key pair j (registers 2j, 2j+1) of a score block: exp2, add to the row sum, round to
   // bf16, store as word j of the two B operands.  The row sum takes the fp32 weights with two plain
@@ -602,14 +779,17 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // In both forms the scores of tile rows that are not keys of the listed block are masked.
   // after_reads() runs once every LDS read of the tile has been consumed.
   // ka, va, sc, w: working registers (the pipelined loop lends its own, which are free between runs).
-  auto compute_tile = [&](auto safec, unsigned boff, int limit, auto&& after_reads, bf16x8 (&ka)[4],
-                          bf16x8 (&va)[2][2], f32x16 (&sc)[2], u32x4 (&w)[2][2]) {
+  // row0, nh: the wave's first tile row and number of 32-key sub-tiles; kat, vat: its operand addresses there.
+  auto compute_rows = [&](auto safec, auto nhc, int row0, const unsigned (&kat)[4], const unsigned (&vat)[2], unsigned boff,
+                          int limit, auto&& after_reads, bf16x8 (&ka)[4], bf16x8 (&va)[2][2], f32x16 (&sc)[2],
+                          u32x4 (&w)[2][2]) {
     constexpr bool SAFE = decltype(safec)::value;
-    const bool ragged = limit < (kh + 1) * KW;
+    constexpr int nh = decltype(nhc)::value;
+    const bool ragged = limit < row0 + 32 * nh;
 #pragma unroll
-    for (int u = 0; u < NH; ++u) {
-      read_k(ka, boff, u);
-      read_v(va, boff, u);
+    for (int u = 0; u < nh; ++u) {
+      read_k_at(kat, ka, boff, u);
+      read_v_at(vat, va, boff, u);
       // the scores of both query halves first (eight MFMAs in a row), so that the weights of the
       // first half are computed while the matrix pipe still works on the second, and the O update
       // of the first half runs under the weights of the second
@@ -623,8 +803,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         for (int c = 0; c < 4; ++c) sc[b2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], qf[b2][c], sc[b2], 0, 0, 0);
       }
       if (ragged) {
-        mask_keys(sc[0], u, limit);
-        mask_keys(sc[1], u, limit);
+        mask_keys(sc[0], row0 + 32 * u, limit);
+        mask_keys(sc[1], row0 + 32 * u, limit);
       }
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
@@ -657,8 +837,12 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
             o[db][b2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[db][cp], __builtin_bit_cast(bf16x8, w[b2][cp]),
                                                                 o[db][b2], 0, 0, 0);
       }
-      if (u == NH - 1) after_reads();
+      if (u == nh - 1) after_reads();
     }
+  };
+  auto compute_tile = [&](auto safec, unsigned boff, int limit, auto&& after_reads, bf16x8 (&ka)[4],
+                          bf16x8 (&va)[2][2], f32x16 (&sc)[2], u32x4 (&w)[2][2]) {
+    compute_rows(safec, Int<NH>{}, kh * KW, kaddr, vaddr, boff, limit, after_reads, ka, va, sc, w);
   };
 
   // Plain tile loop: compute_tile per tile, one barrier per tile, the next tile's loads in flight
@@ -682,6 +866,53 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       // tile has been consumed, and used at the top of the next tile.
       compute_tile(safec, buf * TILE_BYTES, wave_limit(J_cur), [&]() { J_pre = raw_at(it + 2); }, ka, va, sc, w);
       J_cur = J_next;
+    }
+  };
+
+  // PAIR: the key blocks that one list alone names.  Tile rows 0..63 hold one of the first block's, rows
+  // 64..127 one of the second's; wave (qi, kh) takes keys 32 kh .. 32 kh + 31 of its own.
+  auto alone_loop = [&](auto safec) {
+    const int steps = max(n_alone[0], n_alone[1]);
+    if (steps <= 0) return;
+    const int row0 = qi * 64 + kh * 32;
+    unsigned kat[4], vat[2];
+    {
+      int l;  // taken afresh, so that the addresses are not kept in registers across the other loop
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+      const int r = row0 + (l & 31);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) kat[c] = r * 128 + (((2 * c + (l >> 5)) ^ swz_k(r)) << 4);
+      const int i16 = l & 15, m = i16 >> 2, j = i16 & 3, G = l >> 4;
+      const int keyl = row0 + 4 * (l >> 5) + m;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        vat[db] = V_BASE + keyl * 128 + (((db * 4 + 2 * (G & 1) + (j >> 1)) ^ swz_v(keyl)) << 4) + (j & 1) * 8;
+    }
+    auto raw = [&](int it) { return Tile{list[n_both + min(it, n_alone[0])], list[nbk + min(it, max(n_alone[1] - 1, 0))], 0u, 0u}; };
+    auto made = [&](const Tile& r, int it) {
+      Tile t{-1, -1, head_size, head_size};
+      if (it < n_alone[0]) t.a = __builtin_amdgcn_readfirstlane(r.a);
+      if (it < n_alone[1]) t.b = __builtin_amdgcn_readfirstlane(r.b);
+      if (t.a >= 0) t.oa = static_cast<unsigned>(key_start(t.a)) * 128u;
+      if (t.b >= 0) t.ob = static_cast<unsigned>(key_start(t.b)) * 128u;
+      return t;
+    };
+    Tile cur = made(raw(0), 0);
+    issue(scalar(cur), Int<0>{});
+    Tile pre = raw(1);
+    bf16x8 ka[4], va[2][2];
+    f32x16 sc[2];
+    u32x4 w[2][2];
+    for (int it = 0; it < steps; ++it) {
+      const Tile nxt = made(pre, it + 1);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of tile `it` has landed
+      __syncthreads();                     // ... and so has everyone else's; the other buffer is free
+      if (it + 1 < steps) issue_rt(scalar(nxt), (it & 1) ^ 1);
+      pre = raw(it + 2);
+      const int J = qi ? cur.b : cur.a;
+      const int limit = qi * 64 + (J < 0 ? 0 : key_count(J));
+      if (limit > row0) compute_rows(safec, Int<1>{}, row0, kat, vat, (it & 1) * TILE_BYTES, limit, []() {}, ka, va, sc, w);
+      cur = nxt;
     }
   };
 
@@ -906,6 +1137,11 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     l_run[0] = l_run[1] = 0.f;
     if constexpr (!SAFE && B == 128) fast_loop();
     else plain_loop(safec);
+    if constexpr (PAIR) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // no load may still be on its way into the buffers ...
+      __syncthreads();                     // ... nor anyone read them
+      alone_loop(safec);
+    }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // no direct-to-LDS load may still be in flight
     __syncthreads();                     // ... in any wave: LDS can be reused
 
@@ -1041,7 +1277,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
         const float inv = lt[b2] > 0.f ? 1.f / lt[b2] : 0.f;
-        const int lrow = qi * 64 + b2 * 32 + n;
+        const int lrow = q_off + b2 * 32 + n;
         const int64_t row = int64_t(q_start) + lrow;
         if (lrow < q_valid) {
 #pragma unroll
@@ -1100,8 +1336,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   //    first come, first served, through one atomic counter, and leave at once when none is left.
   //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
   //    through with its static share early thus takes more of the remaining rows than a slow one.
-  const int64_t total = int64_t(heads) * nb;
-  const int64_t w = int64_t(blockIdx.y) * nb + blockIdx.x;
+  const int64_t total = int64_t(heads) * units;
+  const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
   int64_t pos;
   if (w < n_static) {
     const int r = static_cast<int>(w & 511);
@@ -1124,18 +1360,24 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 // Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
 // partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
 // idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
-//  - Blocks of 64 (two waves per workgroup, four workgroups to fill a CU): 108 rows of 108 tiles 82 / 35 us
-//    (31 / 28), 344 of 344 328 / 175 (103 / 57), 688 of 344 337 / 304 (112 / 91), 520 of 65 69 / 60 (30 / 31);
-//    688 of 43 51 / 54 (25 / 32), 864 of 108 126 / 128 (47 / 51).
+//  - Blocks of 64 (two waves per workgroup, four workgroups to fill a CU): 172 rows of 172 tiles 126 / 56 us
+//    (46 / 31), 344 of 344 328 / 175 (103 / 57); 344 rows of 86 tiles 85 / 54 (26 / 31), 688 of 172 172 / 157
+//    (49 / 55), 688 of 43 51 / 54 (25 / 32).
 //  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
 //    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
 //    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
 //    82 / 81 (36 / 39).
 static bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
   if (rows >= kStreamMaxRows) return false;
-  if (block == 64) return rows <= 700 && tiles >= 64;
+  if (block == 64) return rows <= 400 && tiles >= 128;
   const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
   return (idle && rows * tiles >= 50 * 512) || (!dense && rows * tiles >= 200 * 512);
+}
+
+// Whether query blocks of 64 are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off
+// with a workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
+static bool pairs_rows(int block, int heads, int nb, int nbk) {
+  return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
 }
 
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
@@ -1146,14 +1388,16 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const Segments seg = {static_cast<int>(n_first), static_cast<int>(ceil_div(n_first, block)),
                         static_cast<int>(ceil_div(n_first, block_k))};
   const int32_t* order = nullptr;
-  const int64_t rows = int64_t(heads) * nb;
+  const bool pair = pairs_rows(block, heads, nb, nbk);
+  const int nu = pair ? (nb + 1) >> 1 : nb;  // units of work per head: rows, or pairs of rows
+  const int64_t rows = int64_t(heads) * nu;
   int64_t n_static = rows;  // without a workspace every row is taken by workgroup number
   int extra = 0;                          // workgroups beyond one per row
   int* next_row = nullptr;
   // ordering and balancing matter only when the grid does not fit the chip at once
   // (and only while the extra workgroups fit the grid's second dimension)
   const bool big = workspace != nullptr && rows >= 1024 && rows < (int64_t(1) << 30) &&
-                   heads + ceil_div(rows / 16 + 1024, nb) <= 65535;
+                   heads + ceil_div(rows / 16 + 1024, nu) <= 65535;
   if (big) {
     // The last eighth of the rows is handed out at run time; half as many workgroups again as that
     // are launched for it, so that an XCD can take up to 1.5 times its even share of those rows.
@@ -1170,17 +1414,21 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     // workspace: [heads * nb] launch order, then the [classes][heads] table, the number of the merged
     // class and the counter of the rows handed out at run time (cleared by order_merge_kernel)
     int32_t* ord = static_cast<int32_t*>(workspace);
-    int32_t* table = ord + int64_t(heads) * nb;
+    int32_t* table = ord + rows;
     next_row = table + int64_t(kOrderClasses) * heads + 1;
-    hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nbk, heads, table);
-    hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads);
-    hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, stream, table, int64_t(kOrderClasses) * heads);
-    hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nbk, heads, table, ord);
+    if (rows <= kOrderOneMax) {
+      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, ord, next_row);
+    } else {
+      hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table);
+      hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads);
+      hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, stream, table, int64_t(kOrderClasses) * heads);
+      hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table, ord);
+    }
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (launch order)")) return rc;
     order = ord;
   }
   const float scale_log2 = softmax_scale * kLog2e;
-  dim3 grid(nb, heads + static_cast<int>(ceil_div(extra, nb)));
+  dim3 grid(nu, heads + static_cast<int>(ceil_div(extra, nu)));
   const unsigned char* qp = static_cast<const unsigned char*>(q);
   const unsigned char* kp = static_cast<const unsigned char*>(k);
   const unsigned char* vp = static_cast<const unsigned char*>(v);
@@ -1190,8 +1438,8 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t lds64 = 4 * 64 * 128, lds128 = 4 * 128 * 128;
   if (getenv("BSGA_DEBUG") != nullptr) {
     int n64 = -1, n128 = -1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false>, 128, lds64);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false>, 256, lds128);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false>, 128, lds64);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false>, 256, lds128);
     fprintf(stderr, "[bsga] attention occupancy (workgroups per CU): block 64 -> %d, block 128 -> %d\n", n64, n128);
   }
   auto launch = [&](auto kernel, dim3 g, int threads, size_t lds, StreamTable* tab) {
@@ -1200,22 +1448,23 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   };
   const size_t order_bytes = attn_order_bytes(heads, n_tokens);
   if (!big && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&
-      shares_rows(rows, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
+      shares_rows(int64_t(heads) * nb, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
       attn_workspace_granted() >= order_bytes + kStreamBytes + 256) {
     const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
     StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
     const int places = block == 64 ? 1024 : 512;
-    hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, static_cast<int>(rows), nbk,
+    hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
                        block_k == block ? 1 : 2, places, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
-    if (block == 64) launch(attn_bf16_kernel<64, 64, true>, dim3(places), 128, lds64, tab);
-    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true>, dim3(places), 256, lds128, tab);
-    else launch(attn_bf16_kernel<128, 64, true>, dim3(places), 256, lds128, tab);
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false>, dim3(places), 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false>, dim3(places), 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true, false>, dim3(places), 256, lds128, tab);
     return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
-  if (block == 64) launch(attn_bf16_kernel<64, 64, false>, grid, 128, lds64, nullptr);
-  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false>, grid, 256, lds128, nullptr);
-  else launch(attn_bf16_kernel<128, 64, false>, grid, 256, lds128, nullptr);
+  if (pair) launch(attn_bf16_kernel<128, 64, false, true>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false>, grid, 128, lds64, nullptr);
+  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false>, grid, 256, lds128, nullptr);
+  else launch(attn_bf16_kernel<128, 64, false, false>, grid, 256, lds128, nullptr);
   return check_hip(hipGetLastError(), "bsga bf16 attention launch");
 }
 

@@ -1,0 +1,129 @@
+"""Query blocks of 64 taken two to a workgroup: the key blocks both lists name, those of the first alone and
+those of the second alone go different ways through the kernel.  Every combination of them being empty, odd
+and even, an odd number of blocks in a head, a ragged last block in each of the three, split sequences,
+lists in any order, and rows that need the second, online-softmax pass."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import bsga_oracle as O
+from tests.helpers import attn_errors, bf16_bars_ok, to_device
+from workload import bf16_bits_to_f32, round_to_bf16_bits
+
+pytestmark = pytest.mark.gpu
+NB = 20  # key blocks of the hand-made masks
+ROWS = 1024  # launches of fewer rows are not paired
+
+
+@pytest.fixture(scope="module")
+def B():
+    import paper_2509_07120_amd as pkg
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return pkg
+
+
+def _qkv(H, N, seed, shift=0.0):
+    rng = np.random.default_rng(seed)
+    q, k, v = (rng.standard_normal((H, N, 64)).astype(np.float32) for _ in range(3))
+    q += abs(shift) / 8.0
+    k += shift / 8.0
+    return [bf16_bits_to_f32(round_to_bf16_bits(x)) for x in (q, k, v)]
+
+
+def _run(B, q, k, v, mask, n_first, shuffle=0):
+    idx, cnt = O.mask_to_index_lists(mask)
+    idx = np.where(idx < 0, 0, idx)
+    if shuffle:
+        rng = np.random.default_rng(shuffle)
+        for h in range(idx.shape[0]):
+            for r in range(idx.shape[1]):
+                idx[h, r, :cnt[h, r]] = rng.permutation(idx[h, r, :cnt[h, r]])
+    out, lse = B.bsga_sparse_attn_split(*(to_device(x, "bf16") for x in (q, k, v)), 64, n_first, torch.from_numpy(idx).cuda(),
+                                        torch.from_numpy(cnt).cuda(), return_lse=True)
+    torch.cuda.synchronize()
+    return out, lse
+
+
+def _check(out, lse, q, k, v, mask, n_first, heads=None):
+    empty = ~mask.any(-1)
+    ranges = O.block_ranges(q.shape[1], 64, n_first)
+    want, want_lse = O.sparse_attention(q, k, v, np.where(empty[..., None], True, mask), 64, n_first=n_first, return_lse=True, heads=heads)
+    for h, I in np.argwhere(empty):
+        lo, hi = ranges[I]
+        assert (out[h, lo:hi].float() == 0).all() and torch.isneginf(lse[h, lo:hi]).all()
+        want[h, lo:hi] = np.nan
+        want_lse[h, lo:hi] = np.nan
+    assert bf16_bars_ok(out, want)[0], bf16_bars_ok(out, want)
+    seen = ~np.isnan(want_lse)
+    assert np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 2e-2
+
+
+@pytest.mark.parametrize("tail", [64, 37, 1])            # length of the last block
+@pytest.mark.parametrize("last", ["none", "both", "first", "second"])  # which list names it
+@pytest.mark.parametrize("extra", [0, 8])                # 8 more common blocks: lists long enough to be sorted out
+def test_every_mix_of_common_and_own_blocks(B, tail, last, extra):
+    """One head per (common, first alone, second alone) with counts 0, 1, 2, 3; blocks 0 and 1 are the pair."""
+    mixes = [(c, a, b) for c in range(4) for a in range(4) for b in range(4)]
+    N = (NB - 1) * 64 + tail
+    H = max(len(mixes), -(-ROWS // NB))
+    rng = np.random.default_rng(tail)
+    mask = rng.random((H, NB, NB)) < 0.5
+    mask[:len(mixes), :2] = False
+    for h, (c, a, b) in enumerate(mixes):
+        js = rng.permutation(NB - 1)
+        c += extra
+        mask[h, 0, js[:c + a]] = True
+        mask[h, 1, js[:c]] = True
+        mask[h, 1, js[c + a:c + a + b]] = True
+        mask[h, 0, NB - 1] = last in ("both", "first")
+        mask[h, 1, NB - 1] = last in ("both", "second")
+    q, k, v = _qkv(H, N, tail)
+    out, lse = _run(B, q, k, v, mask, N)
+    _check(out, lse, q, k, v, mask, N)
+
+
+@pytest.mark.parametrize("N,n_first", [(65, 65), (128, 128), (129, 129), (1000, 1000), (1000, 300), (1000, 64), (777, 700), (4200, 4100)])
+@pytest.mark.parametrize("density", [0.1, 0.9])
+def test_shapes_and_list_orders(B, N, n_first, density):
+    nb = len(O.block_ranges(N, 64, n_first))
+    H = -(-ROWS // nb)
+    mask = np.random.default_rng(N).random((H, nb, nb)) < density
+    mask[0, :, 0] = True               # at least the first of the heads compared keeps something
+    q, k, v = _qkv(H, N, N)
+    out, lse = _run(B, q, k, v, mask, n_first)
+    _check(out, lse, q, k, v, mask, n_first, heads=sorted({0, H // 2, H - 1}))
+    again, _ = _run(B, q, k, v, mask, n_first, shuffle=1)
+    if density > 0.5:
+        assert torch.equal(out, again)  # the kernel sorts long lists itself
+    _check(again, lse, q, k, v, mask, n_first, heads=sorted({0, H // 2, H - 1}))
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_rows_out_of_range(B, sign):
+    """Logits near +-91 nats; bars as for the other kernels' fallback."""
+    H, N = 94, 700
+    q, k, v = _qkv(H, N, 11, 27.0 * sign)
+    nb = O.num_blocks(N, 64)
+    mask = np.random.default_rng(3).random((H, nb, nb)) < 0.5
+    mask[:, :, 0] = True
+    out, lse = _run(B, q, k, v, mask, N)
+    want, want_lse = O.sparse_attention(q, k, v, mask, 64, return_lse=True)
+    assert abs(np.median(want_lse)) > 70.0
+    mx, mean = attn_errors(out, want)
+    assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
+    assert np.abs(lse.cpu().numpy() - want_lse).max() <= 0.25
+
+
+def test_longest_list_that_fits(B):
+    """4096 key blocks: the lists fill the LDS beside the tiles; one block more takes the other kernel."""
+    for nb, seed in ((4096, 0), (4096, 1), (4097, 1)):
+        N = nb * 64
+        q, k, v = _qkv(1, N, nb)
+        rng = np.random.default_rng(1)
+        mask = rng.random((1, nb, nb)) < 0.002
+        mask[0, :2] = rng.random((2, nb)) < (0.7 if seed else 0.2)
+        mask[0, :, 0] = True
+        out, lse = _run(B, q, k, v, mask, N)
+        blocks = [0, 1, nb - 2, nb - 1]
+        want = O.sparse_attention(q, k, v, mask, 64, q_blocks=blocks)
+        assert bf16_bars_ok(out, want)[0], bf16_bars_ok(out, want)
