@@ -115,7 +115,13 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without a Stream object around it (0.2 us instead of 1.9), where torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t: torch.Tensor) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
     return torch.cuda.current_stream(t.device).cuda_stream
 
 
@@ -344,10 +350,45 @@ def bsga_dense_attn(q, k, v, softmax_scale: Optional[float] = None, return_lse: 
 def sparse_global_attention(q, k, v, block: int, tau: float, rho: float = 1.0,
                             score_scale: Optional[float] = None, softmax_scale: Optional[float] = None,
                             workspace: Optional[torch.Tensor] = None):
-    """The whole layer: pool -> select -> block-sparse attention.  Returns (O, kv_idx, kv_cnt, mask_bits)."""
-    q_pool, k_pool = bsga_pool_qk(q, k, block)
-    mask_bits, kv_idx, kv_cnt = bsga_select_blocks(q_pool, k_pool, tau, rho, score_scale)
-    out = bsga_sparse_attn(q, k, v, block, kv_idx, kv_cnt, softmax_scale, workspace=workspace)
+    """The whole layer: pool -> select -> block-sparse attention.  Returns (O, kv_idx, kv_cnt, mask_bits).
+
+    A layer of one frame is bound by the host (40 us a pass when each stage was called by its own function),
+    so the inputs are checked once and everything that does not outlive the call is one allocation: the pooled
+    vectors, then the selection's logits, whose place the attention's workspace takes (the stages are ordered
+    by the stream)."""
+    _require(q, "q"); _require(k, "k", q.dtype); _require(v, "v", q.dtype)
+    if q.shape != k.shape or q.dim() != 3:
+        raise ValueError("q and k must both be [heads, n_tokens, head_dim]")
+    H, N, d = q.shape
+    dev, code, stream = q.device, _dtype_code(q), _stream(q)
+    if block not in (64, 128) or d != 64:  # let the library say what is wrong
+        bsga_pool_qk(q, k, block)
+    nb = num_blocks(N, block)
+    pool_bytes = H * nb * d * 8
+    select_bytes = lib.bsga_select_workspace_bytes(H, nb, nb)
+    own = lib.bsga_attn_workspace_bytes(code, H, N, d) if workspace is None else 0
+    scratch = torch.empty(2 * pool_bytes + max(select_bytes, own), dtype=torch.uint8, device=dev)
+    q_pool = scratch.data_ptr()
+    k_pool = q_pool + pool_bytes
+    rest = k_pool + pool_bytes
+    qp, kp = q.data_ptr(), k.data_ptr()
+    _check(lib.bsga_pool_qk(qp, kp, code, H, N, d, block, q_pool, k_pool, stream))
+    mask_bits = torch.empty((H, nb, (nb + 31) // 32), dtype=torch.int32, device=dev)
+    kv_idx = torch.empty((H, nb, nb), dtype=torch.int32, device=dev)
+    kv_cnt = torch.empty((H, nb), dtype=torch.int32, device=dev)
+    scale = 1.0 / math.sqrt(d)
+    idx, cnt = kv_idx.data_ptr(), kv_cnt.data_ptr()
+    _check(lib.bsga_select_blocks(q_pool, k_pool, H, nb, nb, d, scale if score_scale is None else float(score_scale),
+                                  float(tau), float(rho),
+                                  None, None, mask_bits.data_ptr(), idx, cnt, nb, rest, select_bytes, stream))
+    out = torch.empty_like(q)
+    if workspace is None:
+        ws, ws_bytes = (rest, own) if own > 0 else (None, 0)
+    else:
+        ws, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    _check(lib.bsga_sparse_attn(qp, kp, v.data_ptr(), code, H, N, d, block,
+                                scale if softmax_scale is None else float(softmax_scale), idx, cnt, nb, out.data_ptr(), None, ws,
+                                ws_bytes, stream))
     return out, kv_idx, kv_cnt, mask_bits
 
 
