@@ -401,8 +401,11 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // half the keys of its own.  The two lists are sorted into these three in LDS (bit sets, then a scan), so they
 // may come in any order; kPairMaxBlocks key blocks fit beside the tiles with two workgroups to a CU.
 // 2,752 rows of 172 blocks, nine tenths kept: 515 -> 442 us; 5,504 of 344 1,900 -> 1,550.
+//
+// SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
+// waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
 constexpr int kPairMaxBlocks = 4096;
-template <int B, int KB, bool STREAM, bool PAIR>
+template <int B, int KB, bool STREAM, bool PAIR, bool SOLO>
 __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
@@ -411,6 +414,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
   static_assert(!PAIR || (B == 128 && KB == 64 && !STREAM), "pairs of blocks of 64");
+  static_assert(PAIR || !SOLO, "one block instead of a pair");
   constexpr int QB = PAIR ? 64 : B;       // query block size
   constexpr bool HALF = KB != B;          // two listed key blocks per tile
   constexpr int WQ = B / 64;              // waves along queries (64 rows each)
@@ -428,15 +432,15 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int g = lane >> 5;
   const int qi = wave % WQ;
   const int kh = wave / WQ;
-  const int units = PAIR ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
+  const int units = PAIR && !SOLO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
   // this is number `me`.
   auto run = [&](int64_t row, int tile0, int tile1, int w0, int w1, int me) {
   const int h = static_cast<int>(min(max(row / units, int64_t(0)), int64_t(heads - 1)));
   const int u_in_head = static_cast<int>(min(max(row - int64_t(h) * units, int64_t(0)), int64_t(units - 1)));
-  const int I = PAIR ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
-  const bool no_block = PAIR && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
+  const int I = PAIR && !SOLO ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
+  const bool no_block = PAIR && !SOLO && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
   const int64_t head_bytes = int64_t(h) * n_tokens * 128;
   const int64_t rowid = int64_t(h) * nb + I;
   // this query block: first token and number of tokens (a block never crosses the segment boundary)
@@ -522,7 +526,17 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // list[nbk ..)
   unsigned short* const list = reinterpret_cast<unsigned short*>(smem + 4 * TILE_BYTES);
   int n_both = 0, n_alone[2] = {0, 0};
-  if constexpr (PAIR) {
+  if constexpr (SOLO) {
+    const int32_t* const idx0 = kv_idx + rowid * idx_stride;
+    int j = idx0[min(tid, nbk - 1)];  // in one round of loads with the count, see below
+    for (int e = tid; e < count_row; e += 2 * B) {
+      if (e != tid) j = idx0[e];
+      list[(e & 1) * nbk + (e >> 1)] = static_cast<unsigned short>(min(max(j, 0), nbk - 1));
+    }
+    n_alone[0] = (count_row + 1) >> 1;
+    n_alone[1] = count_row >> 1;
+    __syncthreads();
+  } else if constexpr (PAIR) {
     unsigned* const bits = reinterpret_cast<unsigned*>(smem);             // two bit sets of kPairMaxBlocks
     unsigned long long* const part = reinterpret_cast<unsigned long long*>(smem + 1024);  // per wave
     constexpr int WORDS = kPairMaxBlocks / 32;
@@ -1188,6 +1202,42 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
             o[db][b2][i] = o[db][b2][i] * a0 + park[((db * 2 + b2) * 16 + i) * 64 + lane] * a1;
       }
     }
+    if constexpr (SOLO) {  // the states of the two halves of the list, like those of the two halves of a tile
+      float* const mid = reinterpret_cast<float*>(smem) + 16;
+      __syncthreads();
+      if (kh == 0 && qi == 1) {
+#pragma unroll
+        for (int b2 = 0; b2 < 2; ++b2) {
+#pragma unroll
+          for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mid[((db * 2 + b2) * 16 + i) * 64 + lane] = o[db][b2][i];
+          mid[(64 + b2) * 64 + lane] = mt[b2];
+          mid[(66 + b2) * 64 + lane] = lt[b2];
+        }
+      }
+      __syncthreads();
+      if (kh == 0 && qi == 0) {
+#pragma unroll
+        for (int b2 = 0; b2 < 2; ++b2) {
+          float a0 = 1.f, a1 = 1.f;
+          if constexpr (SAFE) {
+            const float m0 = mt[b2], m1 = mid[(64 + b2) * 64 + lane];
+            mt[b2] = fmaxf(m0, m1);
+            const float mu = (mt[b2] == -INFINITY) ? 0.f : mt[b2];
+            a0 = exp2f(m0 - mu);
+            a1 = exp2f(m1 - mu);
+          }
+          lt[b2] = lt[b2] * a0 + mid[(66 + b2) * 64 + lane] * a1;
+#pragma unroll
+          for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              o[db][b2][i] = o[db][b2][i] * a0 + mid[((db * 2 + b2) * 16 + i) * 64 + lane] * a1;
+        }
+      }
+    }
+    const bool writes = kh == 0 && !(SOLO && qi != 0);  // this wave holds the finished rows
     if constexpr (STREAM && !SAFE) {
       if (w1 > w0) {  // uniform: a row of several workgroups
         float* const partials = reinterpret_cast<float*>(tab + 1);
@@ -1256,7 +1306,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       }
     }
     if constexpr (!SAFE) {
-      if (kh == 0) {
+      if (writes) {
 #pragma unroll
         for (int b2 = 0; b2 < 2; ++b2) {
           bad = bad || !(lt[b2] >= 0x1p-80f && lt[b2] <= 0x1p100f);
@@ -1273,7 +1323,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       __syncthreads();
       if (any_bad) return true;
     }
-    if (kh == 0) {
+    if (writes) {
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
         const float inv = lt[b2] > 0.f ? 1.f / lt[b2] : 0.f;
@@ -1360,22 +1410,27 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 // Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
 // partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
 // idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
-//  - Blocks of 64 (two waves per workgroup, four workgroups to fill a CU): 172 rows of 172 tiles 126 / 56 us
-//    (46 / 31), 344 of 344 328 / 175 (103 / 57); 344 rows of 86 tiles 85 / 54 (26 / 31), 688 of 172 172 / 157
-//    (49 / 55), 688 of 43 51 / 54 (25 / 32).
+//  - Blocks of 64 otherwise run four waves to a row (SOLO): 344 rows of 344 tiles 230 / 160 us (63 / 56), but
+//    129 of 129 57 / 41 (21 / 30).
 //  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
 //    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
 //    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
 //    82 / 81 (36 / 39).
 static bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
   if (rows >= kStreamMaxRows) return false;
-  if (block == 64) return rows <= 400 && tiles >= 128;
+  if (block == 64) return rows <= 400 && tiles >= 256;
   const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
   return (idle && rows * tiles >= 50 * 512) || (!dense && rows * tiles >= 200 * 512);
 }
 
-// Whether query blocks of 64 are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off
-// with a workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
+// Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine
+// tenths kept (a quarter): 352 rows of 22 tiles 26 / 21 us (12 / 12), 172 of 43 33 / 23 (13 / 11), 22 of 22 19 / 15
+// (11 / 9); 516 of 43 44 / 48 (17 / 21).
+static bool solo_rows(int block, int64_t rows, int nbk) {
+  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
+}
+// Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
+// workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
 static bool pairs_rows(int block, int heads, int nb, int nbk) {
   return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
 }
@@ -1438,8 +1493,8 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t lds64 = 4 * 64 * 128, lds128 = 4 * 128 * 128;
   if (getenv("BSGA_DEBUG") != nullptr) {
     int n64 = -1, n128 = -1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false>, 128, lds64);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false>, 256, lds128);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false, false>, 128, lds64);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false, false>, 256, lds128);
     fprintf(stderr, "[bsga] attention occupancy (workgroups per CU): block 64 -> %d, block 128 -> %d\n", n64, n128);
   }
   auto launch = [&](auto kernel, dim3 g, int threads, size_t lds, StreamTable* tab) {
@@ -1456,15 +1511,17 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
                        block_k == block ? 1 : 2, places, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
-    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false>, dim3(places), 128, lds64, tab);
-    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false>, dim3(places), 256, lds128, tab);
-    else launch(attn_bf16_kernel<128, 64, true, false>, dim3(places), 256, lds128, tab);
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false>, dim3(places), 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false>, dim3(places), 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true, false, false>, dim3(places), 256, lds128, tab);
     return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
-  if (pair) launch(attn_bf16_kernel<128, 64, false, true>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
-  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false>, grid, 128, lds64, nullptr);
-  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false>, grid, 256, lds128, nullptr);
-  else launch(attn_bf16_kernel<128, 64, false, false>, grid, 256, lds128, nullptr);
+  if (pair) launch(attn_bf16_kernel<128, 64, false, true, false>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (solo_rows(block, rows, nbk))
+    launch(attn_bf16_kernel<128, 64, false, true, true>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false, false>, grid, 128, lds64, nullptr);
+  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false>, grid, 256, lds128, nullptr);
+  else launch(attn_bf16_kernel<128, 64, false, false, false>, grid, 256, lds128, nullptr);
   return check_hip(hipGetLastError(), "bsga bf16 attention launch");
 }
 

@@ -1,4 +1,4 @@
-"""Query blocks of 64 taken two to a workgroup: the key blocks both lists name, those of the first alone and
+"""Query blocks of 64 taken two to a workgroup (1024 rows and more): the key blocks both lists name, those of the first alone and
 those of the second alone go different ways through the kernel.  Every combination of them being empty, odd
 and even, an odd number of blocks in a head, a ragged last block in each of the three, split sequences,
 lists in any order, and rows that need the second, online-softmax pass."""
@@ -98,10 +98,28 @@ def test_shapes_and_list_orders(B, N, n_first, density):
     _check(again, lse, q, k, v, mask, n_first, heads=sorted({0, H // 2, H - 1}))
 
 
+@pytest.mark.parametrize("N,n_first", [(1, 1), (64, 64), (65, 65), (190, 190), (1000, 300), (1700, 1700)])
+def test_four_waves_to_a_block(B, N, n_first):
+    """Up to 512 rows: one list, dealt to the two halves of a workgroup; counts 0, 1, 2, 3, ... and all."""
+    nb = len(O.block_ranges(N, 64, n_first))
+    H = max(1, min(8, 512 // nb))
+    rng = np.random.default_rng(N)
+    mask = np.zeros((H, nb, nb), bool)
+    for h in range(H):
+        for I in range(nb):
+            mask[h, I, rng.permutation(nb)[:(h + I) % (nb + 1)]] = True
+    mask[0, 0] = True
+    q, k, v = _qkv(H, N, N)
+    out, lse = _run(B, q, k, v, mask, n_first)
+    _check(out, lse, q, k, v, mask, n_first)
+    again, lse = _run(B, q, k, v, mask, n_first, shuffle=1)
+    _check(again, lse, q, k, v, mask, n_first)
+
+
 @pytest.mark.parametrize("sign", [1.0, -1.0])
-def test_rows_out_of_range(B, sign):
+@pytest.mark.parametrize("H,N", [(94, 700), (3, 700)])  # two blocks to a workgroup; one
+def test_rows_out_of_range(B, sign, H, N):
     """Logits near +-91 nats; bars as for the other kernels' fallback."""
-    H, N = 94, 700
     q, k, v = _qkv(H, N, 11, 27.0 * sign)
     nb = O.num_blocks(N, 64)
     mask = np.random.default_rng(3).random((H, nb, nb)) < 0.5
