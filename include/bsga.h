@@ -127,6 +127,19 @@ int bsga_gather_tokens(const void* src, int dtype, int heads, int64_t n_src, int
                        const int32_t* index, int64_t n_dst, void* dst, void* stream);
 
 /*
+ * Heads of a projection's output made contiguous, and back, with an optional reordering of the tokens in
+ * the same pass (the token orders of Sec. 4.2):
+ *   bsga_split_heads:  dst[p, h, i, :] = src[index[i], p, h, :]    src [n_tokens, parts, heads, 64]
+ *   bsga_merge_heads:  dst[i, h, :] = src[h, index[i], :]          src [heads, n_tokens, 64]
+ * dst [parts, heads, n_tokens, 64] and [n_tokens, heads, 64], same dtype, must not overlap src; index
+ * [n_tokens] int32 device array or NULL (tokens stay in order), values outside the tensor are clamped into it.
+ */
+int bsga_split_heads(const void* src, int dtype, int64_t n_tokens, int parts, int heads, int head_dim,
+                     const int32_t* index, void* dst, void* stream);
+int bsga_merge_heads(const void* src, int dtype, int heads, int64_t n_tokens, int head_dim,
+                     const int32_t* index, void* dst, void* stream);
+
+/*
  * Bytes of device workspace for a bf16 attention call of this shape (0 for fp32 and for invalid arguments).
  * Q, K and V are read in place; the workspace holds the launch order of the (head, query block) rows,
  * heaviest first, and the counter through which the last rows of a large launch are handed out at run

@@ -35,6 +35,8 @@ EXPORTED_SYMBOLS = (
     "bsga_select_workspace_bytes",
     "bsga_select_blocks",
     "bsga_gather_tokens",
+    "bsga_split_heads",
+    "bsga_merge_heads",
     "bsga_attn_workspace_bytes",
     "bsga_sparse_attn",
     "bsga_sparse_attn_noalloc",
@@ -78,6 +80,10 @@ def _load() -> ctypes.CDLL:
     lib.bsga_select_workspace_bytes.argtypes = [c_int, c_int, c_int]
     lib.bsga_gather_tokens.restype = c_int
     lib.bsga_gather_tokens.argtypes = [c_void_p, c_int, c_int, c_int64, c_int, c_void_p, c_int64, c_void_p, c_void_p]
+    lib.bsga_split_heads.restype = c_int
+    lib.bsga_split_heads.argtypes = [c_void_p, c_int, c_int64, c_int, c_int, c_int, c_void_p, c_void_p, c_void_p]
+    lib.bsga_merge_heads.restype = c_int
+    lib.bsga_merge_heads.argtypes = [c_void_p, c_int, c_int, c_int64, c_int, c_void_p, c_void_p, c_void_p]
     lib.bsga_attn_workspace_bytes.restype = c_size_t
     lib.bsga_attn_workspace_bytes.argtypes = [c_int, c_int, c_int64, c_int]
     lib.bsga_sparse_attn.restype = c_int
@@ -400,6 +406,34 @@ def bsga_gather_tokens(x: torch.Tensor, index: torch.Tensor, out: Optional[torch
     if out is None:
         out = torch.empty((H, n_out, d), dtype=x.dtype, device=x.device)
     _check(lib.bsga_gather_tokens(_ptr(x), _dtype_code(x), H, N, d, _ptr(index), n_out, _ptr(out), _stream(x)))
+    return out
+
+
+def bsga_split_heads(x: torch.Tensor, parts: int, heads: int, index: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """x [N, parts * heads * 64] -> [parts, heads, N, 64], token i taken from row index[i] if an index is given."""
+    _require(x, "x")
+    N = x.shape[0]
+    if x.dim() != 2 or x.shape[1] != parts * heads * 64:
+        raise ValueError("x must be [n_tokens, parts * heads * 64]")
+    if index is not None:
+        _require(index, "index", torch.int32)
+        if index.numel() != N:
+            raise ValueError("index must have one entry per token")
+    out = torch.empty((parts, heads, N, 64), dtype=x.dtype, device=x.device)
+    _check(lib.bsga_split_heads(_ptr(x), _dtype_code(x), N, parts, heads, 64, _ptr(index), _ptr(out), _stream(x)))
+    return out
+
+
+def bsga_merge_heads(x: torch.Tensor, index: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """x [heads, N, 64] -> [N, heads * 64], row i taken from token index[i] if an index is given."""
+    _require(x, "x")
+    H, N, d = x.shape
+    if index is not None:
+        _require(index, "index", torch.int32)
+        if index.numel() != N:
+            raise ValueError("index must have one entry per token")
+    out = torch.empty((N, H * d), dtype=x.dtype, device=x.device)
+    _check(lib.bsga_merge_heads(_ptr(x), _dtype_code(x), H, N, d, _ptr(index), _ptr(out), _stream(x)))
     return out
 
 

@@ -5,7 +5,7 @@ projections plus an MLP with d_ff = 4 d).
 
 Integration shape only: random weights, timing and parity of the data path.  The projections, the
 layer norms and the MLP are plain torch ops (library GEMMs); pooling, selection, block-sparse attention
-and the token gathers are the bsga kernels.
+and the reorderings of tokens and heads are the bsga kernels.
 """
 from __future__ import annotations
 
@@ -54,12 +54,10 @@ class GlobalAttentionBlock(torch.nn.Module):
 
     @torch.no_grad()
     def attention(self, x: torch.Tensor) -> torch.Tensor:
-        N, D = x.shape
-        H = self.heads
-        h = self.ln1(x)
-        if self.plan is not None:  # working order: patch tokens first, special tokens last
-            h = h.index_select(0, self.plan.perm.long())
-        qkv = F.linear(h, self.w_qkv, self.b_qkv).view(N, 3, H, 64).permute(1, 2, 0, 3).contiguous()  # [3, H, N, 64]
+        N, H = x.shape[0], self.heads
+        # working order: patch tokens first, special tokens last
+        perm, inverse = (None, None) if self.plan is None else (self.plan.perm, self.plan.inverse)
+        qkv = B.bsga_split_heads(F.linear(self.ln1(x), self.w_qkv, self.b_qkv), 3, H, perm)  # [3, H, N, 64]
         q, k, v = qkv[0], qkv[1], qkv[2]
         if self.tau >= 1.0 and self.rho >= 1.0:
             o = B.bsga_dense_attn(q, k, v)
@@ -73,10 +71,7 @@ class GlobalAttentionBlock(torch.nn.Module):
                                                      want_bits=False)
             o = B.bsga_sparse_attn_split(q, k, v, self.block, n_first, kv_idx, kv_cnt)
         self.last = {"q": q, "k": k, "v": v, "o": o}
-        y = F.linear(o.permute(1, 0, 2).reshape(N, D), self.w_out, self.b_out)
-        if self.plan is not None:
-            y = y.index_select(0, self.plan.inverse.long())
-        return y
+        return F.linear(B.bsga_merge_heads(o, inverse), self.w_out, self.b_out)
 
     @torch.no_grad()
     def forward(self, x: torch.Tensor) -> torch.Tensor:
