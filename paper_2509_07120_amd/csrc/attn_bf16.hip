@@ -10,8 +10,9 @@
 // two MFMAs (register-file traffic, not LDS bandwidth, is what this saves: LDS read data and MFMA
 // operands share the VGPR ports).  The two key halves keep independent softmax states that are
 // merged once at the end.  Two workgroups share a CU (two waves per SIMD).
-// Which workgroup computes which row: see the top of the kernel (launch order, 64 consecutive rows
-// per XCD, the last eighth of a large launch handed out at run time).
+// Which workgroup computes which row: see the end of the kernel (launch order, 64 consecutive rows
+// per XCD, the last eighth of a large launch handed out at run time).  Launches of few long rows and
+// blocks of 64 rows divide the work otherwise: STREAM, PAIR and SOLO below.
 //
 // Data movement.  K and V tiles go HBM/L2 -> LDS with direct-to-LDS loads (16 bytes per lane, no
 // staging registers), double buffered, with one workgroup barrier per tile.  Tiles stay row-major
@@ -145,17 +146,20 @@ __global__ __launch_bounds__(256) void order_hist_kernel(const int32_t* __restri
   if (t < kOrderClasses) table[int64_t(t) * heads + h] = bins[t];
 }
 
-// The first class whose lower bound (31 - c) / 31 is below 1.4 x the mean kept fraction; total(c) = units of class c.
+// The first class c whose lower bound (31 - c) / 31 is below 1.4 x the mean kept fraction, taking a unit at the
+// middle of its class, (31 - c + 1/2) / 31; total(c) = units of class c.  In whole numbers.
 template <typename Total>
 __device__ __forceinline__ int bulk_class(Total&& total) {
-  double rows = 0.0, mass = 0.0;  // mass: kept fraction at the middle of each class
+  long long units = 0, mass = 0;  // mass: in units of 1/62
+#pragma unroll
   for (int c = 0; c < kOrderClasses; ++c) {
-    rows += static_cast<double>(total(c));
-    mass += static_cast<double>(total(c)) * (kOrderClasses - 1 - c + 0.5) / (kOrderClasses - 1);
+    const long long n = total(c);
+    units += n;
+    mass += n * (2 * (kOrderClasses - 1 - c) + 1);
   }
-  const double mean = rows > 0.0 ? mass / rows : 1.0;
+  if (units == 0) mass = units = 1;  // nothing to order
   int c = 0;
-  while (c < kOrderClasses - 1 && static_cast<double>(kOrderClasses - 1 - c) / (kOrderClasses - 1) >= 1.4 * mean) ++c;
+  while (c < kOrderClasses - 1 && 10 * units * (kOrderClasses - 1 - c) >= 7 * mass) ++c;
   return c;
 }
 
@@ -247,8 +251,9 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
   }
 }
 
-// The whole launch order in one workgroup, for up to kOrderOneMax units: about 7 us, where the four kernels above
-// take 5 us each whatever the size (a fifth of an 8-frame layer at high sparsity).  The units of a thread are consecutive, so the bulk class keeps its order.
+// The whole launch order in one workgroup, for up to kOrderOneMax units: 10 us at 1408 rows, where the
+// four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
+// of a thread are consecutive, so the bulk class keeps its order.
 constexpr int kOrderOneMax = 8192;
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
                                                          int heads, int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int units = PAIR && !SOLO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
-  // this is number `me`.
+  // this is number `me`.  (Everything up to the dispatch at the end; not indented.)
   auto run = [&](int64_t row, int tile0, int tile1, int w0, int w1, int me) {
   const int h = static_cast<int>(min(max(row / units, int64_t(0)), int64_t(heads - 1)));
   const int u_in_head = static_cast<int>(min(max(row - int64_t(h) * units, int64_t(0)), int64_t(units - 1)));

@@ -26,7 +26,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROFILES = os.path.join(ROOT, "profiles")
 ATTN_SOURCE = os.path.join(ROOT, "paper_2509_07120_amd", "csrc", "attn_bf16.hip")
-KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "order_hist", "order_merge", "order_scan",
+KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "order_one", "order_hist", "order_merge", "order_scan",
            "order_place", "gather_kernel", "probe_kernel")
 
 
