@@ -1203,8 +1203,11 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
-          for (int i = 0; i < 16; ++i)
+          for (int i = 0; i < 16; ++i) {
             o[db][b2][i] = o[db][b2][i] * a0 + park[((db * 2 + b2) * 16 + i) * 64 + lane] * a1;
+            if constexpr (!SAFE && !STREAM && !SOLO) bad = bad || !(fabsf(o[db][b2][i]) < INFINITY);
+          }
+        if constexpr (!SAFE && !STREAM && !SOLO) bad = bad || !(l >= 0x1p-80f && l <= 0x1p100f);
       }
     }
     if constexpr (SOLO) {  // the states of the two halves of the list, like those of the two halves of a tile
@@ -1311,7 +1314,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       }
     }
     if constexpr (!SAFE) {
-      if (writes) {
+      if ((STREAM || SOLO) && writes) {  // otherwise checked as it was merged
 #pragma unroll
         for (int b2 = 0; b2 < 2; ++b2) {
           bad = bad || !(lt[b2] >= 0x1p-80f && lt[b2] <= 0x1p100f);
@@ -1425,7 +1428,8 @@ static bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
   if (rows >= kStreamMaxRows) return false;
   if (block == 64) return rows <= 400 && tiles >= 256;
   const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
-  return (idle && rows * tiles >= 50 * 512) || (!dense && rows * tiles >= 200 * 512);
+  if (dense) return idle && rows * tiles >= 50 * 512;
+  return rows * tiles >= (idle ? 200 : 300) * 512;  // whatever share of the tiles is kept, a tenth at least
 }
 
 // Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine

@@ -35,8 +35,8 @@ def _lists(mask):
 
 CASES = [  # heads, tokens, n_first, block, key block, density
     (1, 16330, 16330, 64, 64, 1.0), (1, 16400, 16400, 64, 64, 0.01), (1, 17000, 16900, 64, 64, 0.3), (1, 25000, 25000, 64, 64, 0.1),
-    (1, 21500, 21500, 128, 128, 0.9), (1, 21500, 700, 128, 64, 0.5), (2, 20000, 20000, 128, 128, 0.2),
-    (15, 8600, 8600, 128, 128, 0.1), (4, 32600, 32500, 128, 64, 0.05),
+    (1, 43968, 43968, 128, 128, 0.9), (1, 43000, 700, 128, 64, 0.5), (2, 33000, 33000, 128, 128, 0.2),
+    (5, 25000, 25000, 128, 128, 0.1), (4, 32600, 32500, 128, 64, 0.05),
 ]
 
 
@@ -82,7 +82,8 @@ def test_dense_equals_every_block_listed(B, H, N):
     tq, tk, tv = (to_device(x, "bf16") for x in (q, k, v))
     nb = O.num_blocks(N, 128)
     dense = B.bsga_dense_attn(tq, tk, tv)
-    assert torch.equal(dense, B.bsga_sparse_attn(tq, tk, tv, 128, *_lists(np.ones((H, nb, nb), bool))))
+    a, c = dense.float(), B.bsga_sparse_attn(tq, tk, tv, 128, *_lists(np.ones((H, nb, nb), bool))).float()
+    assert ((a - c).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), c.abs()) + 1e-6).all()  # not shared: another order of sums
     want = O.sparse_attention(q, k, v, np.ones((H, nb, nb), bool), 128, q_blocks=[0, nb - 1])
     assert bf16_bars_ok(dense, want)[0]
 
@@ -92,7 +93,7 @@ def test_dense_equals_every_block_listed(B, H, N):
 def test_rows_out_of_range_are_repeated_whole(B, sign, b, bk):
     """Logits near +-91 nats overflow or vanish in the pass without a reference maximum; only the workgroup that
     sums the parts can tell, and it repeats the whole row.  Bars as for the launch of one workgroup per row."""
-    H, N = (1, 16400) if b == 64 else (1, 20500)
+    H, N = (1, 16400) if b == 64 else (1, 41000)
     q, k, v = _qkv(H, N, 11, 27.0 * sign)
     nbq, nbk = O.num_blocks(N, b), O.num_blocks(N, bk)
     mask = np.random.default_rng(3).random((H, nbq, nbk)) < 0.6
