@@ -971,6 +971,10 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     // half) sum the sixteen weights a lane holds: they replace sixteen fp32 adds per unit (64 cycles
     // of vector issue in a loop whose vector and matrix pipes are both saturated) by 32 cycles of
     // matrix pipe, and the sums are over the bf16 weights, exactly the values that multiply V.
+    // Not for pairs of blocks of 64 (SUM32): their other tiles, and launches of few rows, sum fp32 weights, and a
+    // row's lse must not depend on which way its blocks went.  The sixteen adds cost nothing measurable
+    // here: 2,752 rows of 172 blocks, nine tenths kept, 430 us with the MFMAs, 427 with the adds.
+    constexpr bool SUM32 = PAIR;
     f32x4 lacc = {0.f, 0.f, 0.f, 0.f};
     bf16x8 row_sel[2];
 #pragma unroll
@@ -1013,6 +1017,10 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     /* pair S_ (two fp32 adds).                                                                  */          \
     {                                                                                                          \
       const unsigned pk = pack_bf16(ex[(S_) & 1][0], ex[(S_) & 1][1]);                                         \
+      if constexpr (SUM32) { /* pinned: summed up later, all of a unit's weights would stay alive */           \
+        l_run[BQ] += ex[(S_) & 1][0] + ex[(S_) & 1][1];                                                        \
+        asm volatile("" : "+v"(l_run[BQ]));                                                                    \
+      }                                                                                                        \
       if constexpr ((S_) < 7) {                                                                                \
         ex[((S_) + 1) & 1][0] = __builtin_amdgcn_exp2f(sc[BQ][2 * (S_) + 2]);                                  \
         ex[((S_) + 1) & 1][1] = __builtin_amdgcn_exp2f(sc[BQ][2 * (S_) + 3]);                                  \
@@ -1022,8 +1030,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       }                                                                                                        \
       __builtin_amdgcn_sched_barrier(0);                                                                       \
       /* row sums: the previous unit's second group of weights in slot 1, this unit's first in slot 5 */    \
-      if constexpr ((S_) == 1) add_weights(Int<BP>{}, pw[BP][1]);                                              \
-      if constexpr ((S_) == 5) add_weights(Int<BQ>{}, pw[BQ][0]);                                              \
+      if constexpr (!SUM32 && (S_) == 1) add_weights(Int<BP>{}, pw[BP][1]);                                    \
+      if constexpr (!SUM32 && (S_) == 5) add_weights(Int<BQ>{}, pw[BQ][0]);                                    \
       pw[BQ][(S_) >> 2][(S_) & 3] = pk;                                                                        \
     }                                                                                                          \
     mid(Int<(S_)>{});                                                                                          \
@@ -1119,9 +1127,11 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         for (int cp = 0; cp < 2; ++cp)
           o[db][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1][db][cp], __builtin_bit_cast(bf16x8, pw[1][cp]),
                                                              o[db][1], 0, 0, 0);
-      add_weights(Int<1>{}, pw[1][1]);
-      l_run[0] += lacc[0];
-      l_run[1] += lacc[1];
+      if constexpr (!SUM32) {
+        add_weights(Int<1>{}, pw[1][1]);
+        l_run[0] += lacc[0];
+        l_run[1] += lacc[1];
+      }
     }
     // ---- from the first ragged tile on: plain tiles (the same buffers and the same one barrier per
     // tile; the loads stay two tiles ahead) ------------------------------------------------------------
