@@ -127,10 +127,13 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           vr[i] = *reinterpret_cast<const f32x2*>((base + (i >> 3) * 16 * kD) + at + (8 * ((i >> 2) & 1) + (i & 3)) * kD);
-      } else {  // keys past `valid` repeat the last one; their weight is 0
+      } else {  // keys past `valid` are zeros (the last one is read in their place, and may be infinite); their weight is 0
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          vr[i] = *reinterpret_cast<const f32x2*>(base + static_cast<unsigned>(min(8 * (i >> 2) + 4 * g + (i & 3), valid - 1) * kD + 2 * n));
+        for (int i = 0; i < 16; ++i) {
+          const int key = 8 * (i >> 2) + 4 * g + (i & 3);
+          vr[i] = *reinterpret_cast<const f32x2*>(base + static_cast<unsigned>(min(key, valid - 1) * kD + 2 * n));
+          if (key >= valid) vr[i] = f32x2{0.f, 0.f};
+        }
       }
     }
     f32x16 s[NQ];
@@ -164,7 +167,9 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
         m[b] = m_new;
       }
     }
-    float part[NQ][2] = {};
+    float part[NQ][2] = {}, ref[NQ];  // a wave that has seen nothing but weights of zero (scores of -inf) has no maximum
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) ref[b] = m[b] == -INFINITY ? 0.f : m[b];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       if (i == 8) {  // the first half of V is used up: its registers take the next piece's keys
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
       }
 #pragma unroll
       for (int b = 0; b < NQ; ++b) {
-        const float p = __builtin_amdgcn_exp2f(s[b][i] - m[b]);
+        const float p = __builtin_amdgcn_exp2f(s[b][i] - ref[b]);
         part[b][i & 1] += p;
         o[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][0], p, o[b][0], 0, 0, 0);
         o[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][1], p, o[b][1], 0, 0, 0);
@@ -221,7 +226,8 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
     }
     sum += __shfl_xor(sum, 32);
     if (32 * b + n < rows) {
-      const float inv = sum > 0.f ? 1.f / sum : 0.f;
+      // listed keys, but none with a weight: the softmax is 0 / 0
+      const float inv = sum > 0.f ? 1.f / sum : count > 0 ? NAN : 0.f;
       float* dst = out + head_off + (row0 + 32 * b + n) * kD + 16 * wave + 8 * g;
       *reinterpret_cast<f32x4*>(dst) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
       *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};

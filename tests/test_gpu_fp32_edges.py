@@ -66,3 +66,46 @@ def test_empty_row_and_large_logits(B):
     keep[0, 64:128] = False
     # logits of 300 nats carry an fp32 rounding error of about 300 * 2^-24 * a few, and so do the weights
     assert np.abs(got - want)[keep].max() <= 5e-4
+
+
+@pytest.mark.parametrize("b", [64, 128])
+@pytest.mark.parametrize("H", [2, 200])  # 32 and 64 rows to a workgroup
+@pytest.mark.parametrize("N", [33, 70, 129])
+def test_infinite_value_in_the_last_key(B, b, H, N):
+    """The operands of keys past a ragged block's end are weighted by zero and must themselves be finite: an infinite
+    value of the last key is a weighted term like any other, and its column is infinite, not NaN."""
+    rng = np.random.default_rng(N)
+    q, k, v = (rng.standard_normal((H, N, 64)).astype(np.float32) for _ in range(3))
+    want = O.dense_attention(q[:2], k[:2], v[:2])
+    v[:, -1, 5] = np.inf
+    nb = O.num_blocks(N, b)
+    idx, cnt = O.mask_to_index_lists(np.ones((H, nb, nb), bool))
+    out = B.bsga_sparse_attn(*(to_device(x, "fp32") for x in (q, k, v)), b, torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda())
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.isposinf(got[..., 5]).all()
+    rest = np.arange(64) != 5
+    assert np.isfinite(got[..., rest]).all() and np.abs(got[:2][..., rest] - want[..., rest]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("H", [2, 200])
+def test_whole_pieces_of_zero_weight(B, H):
+    """Finite operands whose score overflows to -inf have weight zero, also where all 32 keys of a piece do."""
+    rng = np.random.default_rng(8)
+    N = 128
+    q, k, v = (rng.standard_normal((H, N, 64)).astype(np.float32) for _ in range(3))
+    q[..., 0] = 1e20
+    k[..., 0] = 0.0
+    seen = np.ones(N, bool)
+    seen[32:70] = seen[96:] = False
+    k[:, ~seen, 0] = -1e20
+    idx, cnt = O.mask_to_index_lists(np.ones((H, 2, 2), bool))
+    out, lse = B.bsga_sparse_attn(*(to_device(x, "fp32") for x in (q, k, v)), 64, torch.from_numpy(idx).cuda(),
+                                  torch.from_numpy(cnt).cuda(), return_lse=True)
+    torch.cuda.synchronize()
+    s = np.einsum("hid,hjd->hij", q[:2].astype(np.float64), k[:2][:, seen].astype(np.float64)) / 8.0
+    p = np.exp(s - s.max(-1, keepdims=True))
+    want = np.einsum("hij,hjd->hid", p, v[:2][:, seen].astype(np.float64)) / p.sum(-1, keepdims=True)
+    assert np.isfinite(out.cpu().numpy()).all() and np.abs(out[:2].cpu().numpy() - want).max() <= 1e-5
+    want_lse = s.max(-1) + np.log(p.sum(-1))
+    assert np.abs(lse[:2].cpu().numpy() - want_lse).max() <= 1e-5
