@@ -94,6 +94,14 @@ __device__ __forceinline__ uint64_t uniform_key(double v) {
 __device__ __forceinline__ double key_value(uint64_t key) { return __longlong_as_double(static_cast<long long>(key)); }
 __device__ __forceinline__ int votes(bool b) { return static_cast<int>(__popcll(__ballot(b))); }
 
+// What lanes of a wave wrote to LDS before this is what its other lanes read after it.  LDS operations of one
+// wave run in order; this keeps the compiler from answering a lane's load with the lane's own earlier store.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // exp(x) for x <= 0 (NaN stays NaN): x = n ln2 + r with |r| <= ln2 / 2, ln2 split in two so that n * hi is
 // exact, then the Taylor series to r^13 / 13! (the next term is below 2^-57 of the result) and a
 // scaling by 2^n.  Largest error against 80-bit exp over 4 million arguments in [-700, 0]: 0.87 units in the
@@ -164,6 +172,7 @@ __device__ __forceinline__ uint64_t find_threshold(const double (&p)[E], uint64_
     const double lo_v = key_value(lo), hi_v = key_value(hi);
     int n = 0;
     lot[lane] = -1.0;
+    wave_lds_fence();
 #pragma unroll
     for (int r = 0; r < E; ++r) {
       const bool in = p[r] >= lo_v && p[r] < hi_v;
@@ -172,6 +181,7 @@ __device__ __forceinline__ uint64_t find_threshold(const double (&p)[E], uint64_
       n += static_cast<int>(__popcll(b));
       if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
+    wave_lds_fence();
     const double x = lot[lane];
     const int cnt_base = cnt_hi;
     const double mass_base = mass_hi;
