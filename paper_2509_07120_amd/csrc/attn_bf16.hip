@@ -1456,7 +1456,7 @@ static bool pairs_rows(int block, int heads, int nb, int nbk) {
 
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
-                     int idx_stride, void* out, float* lse, void* workspace, hipStream_t stream) {
+                     int idx_stride, void* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const int nb = static_cast<int>(split_blocks(n_tokens, n_first, block));     // query blocks
   const int nbk = static_cast<int>(split_blocks(n_tokens, n_first, block_k));  // key blocks the lists refer to
   const Segments seg = {static_cast<int>(n_first), static_cast<int>(ceil_div(n_first, block)),
@@ -1523,7 +1523,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t order_bytes = attn_order_bytes(heads, n_tokens);
   if (!big && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&
       shares_rows(int64_t(heads) * nb, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
-      attn_workspace_granted() >= order_bytes + kStreamBytes + 256) {
+      workspace_bytes >= order_bytes + kStreamBytes + 256) {
     const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
     StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
     const int places = block == 64 ? 1024 : 512;

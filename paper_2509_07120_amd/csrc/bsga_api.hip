@@ -59,9 +59,6 @@ static size_t attn_workspace(int dtype, int heads, int64_t n_tokens) {
   return dtype == BSGA_BF16 ? attn_order_bytes(heads, n_tokens) : 0;
 }
 
-static thread_local size_t g_attn_granted = 0;
-size_t attn_workspace_granted() { return g_attn_granted; }
-
 static int attn_common(const char* fn, const void* q, const void* k, const void* v, int dtype, int heads,
                        int64_t n_tokens, int64_t n_first, int head_dim, int block, int block_k, float softmax_scale,
                        const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, void* out, float* lse,
@@ -98,11 +95,11 @@ static int attn_common(const char* fn, const void* q, const void* k, const void*
   }
   // the dense kernel uses a workspace, if it gets one, for one counter (balancing rows across the XCDs)
   if (!kv_idx && workspace && (workspace_bytes < 16 || !aligned16(workspace))) workspace = nullptr;
-  g_attn_granted = workspace ? workspace_bytes : 0;
+  if (!workspace) workspace_bytes = 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == BSGA_BF16)
     return launch_attn_bf16(q, k, v, heads, n_tokens, n_first, block, block_k, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse,
-                            workspace, s);
+                            workspace, workspace_bytes, s);
   return launch_attn_fp32(static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v),
                           heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride,
                           static_cast<float*>(out), lse, s);

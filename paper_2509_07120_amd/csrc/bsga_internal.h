@@ -38,10 +38,6 @@ constexpr size_t kStreamBytes = 2 * 512 * (2 * 66 * 64 * sizeof(float)) + (size_
 inline bool attn_stream_shape(int heads, int64_t n_tokens) {
   return n_tokens > 4032 && static_cast<int64_t>(heads) * ceil_div(n_tokens, 128) < 1024;
 }
-// Bytes of the workspace of the attention call that this thread is making (a call may come with less than
-// bsga_attn_workspace_bytes, down to the launch order alone).
-size_t attn_workspace_granted();
-
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);
@@ -55,9 +51,10 @@ size_t select_workspace_bytes(int heads, int nb_q, int nb_k);
 int launch_gather(const void* src, int dtype, int heads, int64_t n_src, const int32_t* index,
                   int64_t n_dst, void* dst, hipStream_t stream);
 
+// workspace_bytes: of the call's workspace, 0 without one; the launch order alone or more (see attn_order_bytes).
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
-                     int idx_stride, void* out, float* lse, void* workspace, hipStream_t stream);
+                     int idx_stride, void* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,

@@ -14,6 +14,7 @@
 
 static int g_calls = 0;
 static int g_fail = 0;
+static size_t g_workspace_bytes = 0;  // of the last attention launch
 #define CHECK(cond)                                                        \
   do {                                                                     \
     if (!(cond)) {                                                         \
@@ -57,9 +58,11 @@ static void check_attn(int heads, int64_t n_tokens, int64_t n_first, int block, 
 }
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first, int block,
                      int block_k, float scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, void* out,
-                     float*, void* workspace, hipStream_t) {
+                     float*, void* workspace, size_t workspace_bytes, hipStream_t) {
   ++g_calls;
+  g_workspace_bytes = workspace_bytes;
   CHECK(q && k && v && out && scale > 0.f);
+  CHECK((workspace == nullptr) == (workspace_bytes == 0));
   check_attn(heads, n_tokens, n_first, block, block_k, kv_idx, kv_cnt, idx_stride);
   if (workspace) {  // the launch order needs one word per query block plus the class table: touch it all
     const size_t words = size_t(heads) * split_blocks(n_tokens, n_first, block) + 32u * heads + 1;
@@ -171,6 +174,17 @@ int main() {
   CHECK(bsga_sparse_attn_qk(A, A, A, 0, 4, 1000, 64, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_UNSUPPORTED);
   CHECK(bsga_sparse_attn_qk(A, A, A, 1, 4, 1000, 64, 128, 64, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_UNSUPPORTED);
   CHECK(bsga_sparse_attn_split(A, A, A, 0, 4, 1000, 1001, 64, 128, 128, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_INVALID_ARG);
+
+  // ---- the size of a call's workspace reaches its own launch, and no later one's
+  {
+    const size_t order = bsga::attn_order_bytes(4, 1000);
+    CHECK(bsga_sparse_attn(A, A, A, 0, 4, 1000, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 8, A, nullptr, A, sizeof(buf), nullptr) == BSGA_OK);
+    CHECK(g_workspace_bytes == sizeof(buf));
+    CHECK(bsga_sparse_attn(A, A, A, 0, 4, 1000, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 8, A, nullptr, A, order, nullptr) == BSGA_OK);
+    CHECK(g_workspace_bytes == order);
+    CHECK(bsga_sparse_attn(A, A, A, 0, 4, 1000, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 8, A, nullptr, nullptr, sizeof(buf), nullptr) == BSGA_OK);
+    CHECK(g_workspace_bytes == 0);
+  }
 
   // ---- the entry point on built-in scratch: size limit is checked before any device call; on a
   // machine without a GPU a fitting shape ends in a HIP error, never in a launch
