@@ -338,7 +338,6 @@ struct Tile {
 // workspace and counts itself in; the one that completes the count reads them all, in piece order, so the
 // result does not depend on who came last.  Nobody waits for anybody.
 // Workspace of a launch: the table below, then two partial results per workgroup.
-constexpr int kStreamMaxRows = 1024;     // rows of such a launch are fewer
 constexpr int kStreamMaxPlaces = 1024;   // workgroups: 2 x 256 (blocks of 128 rows), 4 x 256 (blocks of 64)
 constexpr int kMinQuota = 4;
 struct StreamTable {
@@ -1424,23 +1423,6 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 }
 
 }  // namespace
-
-// Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
-// partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
-// idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
-//  - Blocks of 64 otherwise run four waves to a row (SOLO): 344 rows of 344 tiles 230 / 160 us (63 / 56), but
-//    129 of 129 57 / 41 (21 / 30).
-//  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
-//    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
-//    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
-//    82 / 81 (36 / 39).
-static bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
-  if (rows >= kStreamMaxRows) return false;
-  if (block == 64) return rows <= 400 && tiles >= 256;
-  const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
-  if (dense) return idle && rows * tiles >= 50 * 512;
-  return rows * tiles >= (idle ? 200 : 300) * 512;  // whatever share of the tiles is kept, a tenth at least
-}
 
 // Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine
 // tenths kept (a quarter): 352 rows of 22 tiles 26 / 21 us (12 / 12), 172 of 43 33 / 23 (13 / 11), 22 of 22 19 / 15

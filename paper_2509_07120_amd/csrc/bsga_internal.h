@@ -31,13 +31,40 @@ inline size_t attn_order_bytes(int heads, int64_t n_tokens) {
   return (static_cast<size_t>(heads) * static_cast<size_t>(ceil_div(n_tokens, 64) + 1) + 32u * static_cast<size_t>(heads) + 4u) *
          sizeof(int32_t);
 }
-// Calls of few rows share rows between workgroups and then need room for partial results, whatever the
-// number of rows: two of 33 KB for each of 512 workgroups, and a table.  Up to 4032 tokens (63 blocks of 64) a
-// row is too short to be worth sharing.
-constexpr size_t kStreamBytes = 2 * 512 * (2 * 66 * 64 * sizeof(float)) + (size_t(1) << 14);
-inline bool attn_stream_shape(int heads, int64_t n_tokens) {
-  return n_tokens > 4032 && static_cast<int64_t>(heads) * ceil_div(n_tokens, 128) < 1024;
+constexpr int kStreamMaxRows = 1024;  // rows of a launch that shares them between workgroups are fewer
+// Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
+// partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
+// idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
+//  - Blocks of 64 otherwise run four waves to a row (SOLO): 344 rows of 344 tiles 230 / 160 us (63 / 56), but
+//    129 of 129 57 / 41 (21 / 30).
+//  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
+//    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
+//    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
+//    82 / 81 (36 / 39).
+inline bool shares_rows(int64_t rows, int block, int64_t tiles, bool dense) {
+  if (rows >= kStreamMaxRows) return false;
+  if (block == 64) return rows <= 400 && tiles >= 256;
+  const bool idle = 10 * rows < 8 * 256 * ceil_div(rows, 256);
+  if (dense) return idle && rows * tiles >= 50 * 512;
+  return rows * tiles >= (idle ? 200 : 300) * 512;  // whatever share of the tiles is kept, a tenth at least
 }
+// Such a launch needs room for partial results, whatever the number of rows: two of 33 KB for each of 512
+// workgroups, and a table.
+constexpr size_t kStreamBytes = 2 * 512 * (2 * 66 * 64 * sizeof(float)) + (size_t(1) << 14);
+// Whether a call of this shape can come to share its rows, whatever its blocks, its lists and its split (which
+// may add a block): only then does the workspace query count the room.  Up to 4032 tokens (63 blocks of 64) a row is
+// too short to be worth sharing.
+inline bool attn_stream_shape(int heads, int64_t n_tokens) {
+  if (n_tokens <= 4032) return false;
+  const int64_t h = heads, n64 = ceil_div(n_tokens, 64), n128 = ceil_div(n_tokens, 128);
+  for (int more_q = 0; more_q < 2; ++more_q)
+    for (int more_k = 0; more_k < 2; ++more_k) {
+      if (shares_rows(h * (n64 + more_q), 64, n64 + more_k, false)) return true;
+      if (shares_rows(h * (n128 + more_q), 128, n128 + more_k, false)) return true;
+    }
+  return shares_rows(h * n128, 128, n128, true);
+}
+
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);

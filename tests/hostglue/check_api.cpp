@@ -175,6 +175,27 @@ int main() {
   CHECK(bsga_sparse_attn_qk(A, A, A, 1, 4, 1000, 64, 128, 64, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_UNSUPPORTED);
   CHECK(bsga_sparse_attn_split(A, A, A, 0, 4, 1000, 1001, 64, 128, 128, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_INVALID_ARG);
 
+  // ---- the room for partial results is asked for where some call of the shape can use it, and nowhere else
+  for (int heads : {1, 2, 3, 5, 8, 12, 16, 25, 40, 200})
+    for (int64_t n = 1; n < 140000; n += n < 5000 ? 97 : 1013) {
+      bool used = false;
+      for (int64_t n_first : {n, n - 1, n / 2, int64_t(63), int64_t(1)}) {
+        if (n_first < 0 || n_first > n) continue;
+        for (int block : {64, 128})
+          for (int block_k : {64, 128}) {
+            if (block_k > block) continue;
+            const int64_t tiles = bsga::ceil_div(bsga::split_blocks(n, n_first, block_k), block / block_k);
+            used = used || bsga::shares_rows(heads * bsga::split_blocks(n, n_first, block), block, tiles, false);
+          }
+      }
+      used = n > 4032 && (used || bsga::shares_rows(heads * bsga::ceil_div(n, 128), 128, bsga::ceil_div(n, 128), true));
+      const size_t order = bsga::attn_order_bytes(heads, n);
+      CHECK(bsga_attn_workspace_bytes(0, heads, n, 64) == order + (used ? bsga::kStreamBytes + 256 : 0));
+    }
+  // a layer of four frames of 1374 tokens, one head of 5000: nothing to share
+  CHECK(bsga_attn_workspace_bytes(0, 16, 4 * 1374, 64) < (1 << 20) && bsga_attn_workspace_bytes(0, 1, 5000, 64) < (1 << 20));
+  CHECK(bsga_attn_workspace_bytes(0, 2, 32 * 1374, 64) > (32 << 20) && bsga_attn_workspace_bytes(0, 1, 16400, 64) > (32 << 20));
+
   // ---- the size of a call's workspace reaches its own launch, and no later one's
   {
     const size_t order = bsga::attn_order_bytes(4, 1000);
