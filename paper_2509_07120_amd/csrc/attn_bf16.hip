@@ -404,11 +404,16 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // tile holds one key block of the first list alone and one of the second alone, and each wave takes
 // half the keys of its own.  The two lists are sorted into these three in LDS (bit sets, then a scan), so they
 // may come in any order; kPairMaxBlocks key blocks fit beside the tiles with two workgroups to a CU.
-// 2,752 rows of 172 blocks, nine tenths kept: 515 -> 442 us; 5,504 of 344 1,900 -> 1,550.
+// 2,752 rows of 172 blocks, nine tenths kept: 515 -> 434 us; 5,504 of 344 1,910 -> 1,590.
+// While the rest of the longer list runs, the waves of the other block idle.  A pair whose lists differ in length by
+// more than what they share (and a dozen steps, about what another row's start and merge cost) is therefore taken
+// row by row, four waves to each as in SOLO, and so is the odd block at the end of a head.  Lists of nine tenths
+// and a twentieth in turn, 5,504 rows of 344: 1,080 us with two waves to a row, 1,500 in pairs only, 1,115 so.
 //
 // SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
 // waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
 constexpr int kPairMaxBlocks = 4096;
+enum { kDone = -1, kByOne = -2 };  // what a workgroup of a pair has left to do
 template <int B, int KB, bool STREAM, bool PAIR, bool SOLO>
 __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
@@ -436,15 +441,21 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int g = lane >> 5;
   const int qi = wave % WQ;
   const int kh = wave / WQ;
-  const int units = PAIR && !SOLO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
-  // this is number `me`.  (Everything up to the dispatch at the end; not indented.)
-  auto run = [&](int64_t row, int tile0, int tile1, int w0, int w1, int me) {
+  // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, in a SOLO launch or as
+  // one of a pair that is taken row by row; listed >= 0: its list is in LDS already, with that many blocks.
+  // Returns kDone, or, with nothing done, kByOne if the row
+  // or rows are to be run by ONE, or the length of the list that it has sorted into LDS for one row.
+  // (Everything up to the dispatch at the end; not indented.)
+  auto run = [&](auto onec, int64_t row, int tile0, int tile1, int w0, int w1, int me, int listed) -> int {
+  constexpr bool ONE = decltype(onec)::value;
+  constexpr bool TWO = PAIR && !ONE;              // two blocks with a list each
+  const int units = TWO ? (nb + 1) >> 1 : nb;     // rows, or pairs of rows, per head
   const int h = static_cast<int>(min(max(row / units, int64_t(0)), int64_t(heads - 1)));
   const int u_in_head = static_cast<int>(min(max(row - int64_t(h) * units, int64_t(0)), int64_t(units - 1)));
-  const int I = PAIR && !SOLO ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
-  const bool no_block = PAIR && !SOLO && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
+  const int I = TWO ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
+  const bool no_block = TWO && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
   const int64_t head_bytes = int64_t(h) * n_tokens * 128;
   const int64_t rowid = int64_t(h) * nb + I;
   // this query block: first token and number of tokens (a block never crosses the segment boundary)
@@ -530,15 +541,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // list[nbk ..)
   unsigned short* const list = reinterpret_cast<unsigned short*>(smem + 4 * TILE_BYTES);
   int n_both = 0, n_alone[2] = {0, 0};
-  if constexpr (SOLO) {
-    const int32_t* const idx0 = kv_idx + rowid * idx_stride;
-    int j = idx0[min(tid, nbk - 1)];  // in one round of loads with the count, see below
-    for (int e = tid; e < count_row; e += 2 * B) {
-      if (e != tid) j = idx0[e];
-      list[(e & 1) * nbk + (e >> 1)] = static_cast<unsigned short>(min(max(j, 0), nbk - 1));
+  if constexpr (ONE) {
+    const int n_list = listed >= 0 ? listed : count_row;
+    if (listed < 0) {
+      const int32_t* const idx0 = kv_idx + rowid * idx_stride;
+      int j = idx0[min(tid, nbk - 1)];  // in one round of loads with the count, see below
+      for (int e = tid; e < count_row; e += 2 * B) {
+        if (e != tid) j = idx0[e];
+        list[(e & 1) * nbk + (e >> 1)] = static_cast<unsigned short>(min(max(j, 0), nbk - 1));
+      }
     }
-    n_alone[0] = (count_row + 1) >> 1;
-    n_alone[1] = count_row >> 1;
+    n_alone[0] = (n_list + 1) >> 1;
+    n_alone[1] = n_list >> 1;
     __syncthreads();
   } else if constexpr (PAIR) {
     unsigned* const bits = reinterpret_cast<unsigned*>(smem);             // two bit sets of kPairMaxBlocks
@@ -557,7 +571,11 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       const int j = min(max(J, 0), nbk - 1);
       atomicOr(&bits[r * WORDS + (j >> 5)], 1u << (j & 31));
     };
+    auto uneven = [&](int both, int alone0, int alone1) {
+      return __builtin_amdgcn_readfirstlane(abs(alone0 - alone1) > both + 12) != 0;
+    };
     if (10 * (n0 + n1) < 6 * nbk) {
+      if (!two || uneven(0, n0, n1)) return kByOne;
       // Short lists: of unrelated ones few blocks are in both, and sorting costs more than that saves.  5,504
       // rows of 344 tiles, a tenth kept: sorted 271 us, unsorted 249; a quarter 587, 567; half 1065 sorted.
       auto put = [&](int e, int a0, int a1) {
@@ -609,14 +627,17 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       n_both = __builtin_amdgcn_readfirstlane(static_cast<int>(all & 0xffff));
       n_alone[0] = __builtin_amdgcn_readfirstlane(static_cast<int>((all >> 16) & 0xffff));
       n_alone[1] = __builtin_amdgcn_readfirstlane(static_cast<int>(all >> 32));
+      if (two && uneven(n_both, n_alone[0], n_alone[1])) return kByOne;
       const int before[3] = {static_cast<int>(lo & 0xffff), static_cast<int>(lo >> 16), static_cast<int>(hi)};
       const int at[3] = {0, n_both, nbk};
 #pragma unroll
       for (int x = 0; x < 3; ++x) {
         int pos = at[x] + before[x];
-        for (unsigned b = set[x]; b != 0u; b &= b - 1u) list[pos++] = static_cast<unsigned short>(tid * 32 + __ffs(b) - 1);
+        for (unsigned b = set[x]; b != 0u; b &= b - 1u, ++pos)
+          list[two ? pos : (pos & 1) * nbk + (pos >> 1)] = static_cast<unsigned short>(tid * 32 + __ffs(b) - 1);
       }
       __syncthreads();  // the lists are complete; the tiles may overwrite the bit sets
+      if (!two) return n_alone[0];
     }
   }
   int count = PAIR ? n_both : count_row;                        // of them, those of the tiles this workgroup takes,
@@ -971,8 +992,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     // of vector issue in a loop whose vector and matrix pipes are both saturated) by 32 cycles of
     // matrix pipe, and the sums are over the bf16 weights, exactly the values that multiply V.
     // Not for pairs of blocks of 64 (SUM32): their other tiles, and launches of few rows, sum fp32 weights, and a
-    // row's lse must not depend on which way its blocks went.  The sixteen adds cost nothing measurable
-    // here: 2,752 rows of 172 blocks, nine tenths kept, 430 us with the MFMAs, 427 with the adds.
+    // row's lse must not depend on which way its blocks went.  The sixteen adds cost a hundredth:
+    // 2,752 rows of 172 blocks, nine tenths kept, 428 us with the MFMAs, 433 with the adds.
     constexpr bool SUM32 = PAIR;
     f32x4 lacc = {0.f, 0.f, 0.f, 0.f};
     bf16x8 row_sel[2];
@@ -1214,12 +1235,12 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             o[db][b2][i] = o[db][b2][i] * a0 + park[((db * 2 + b2) * 16 + i) * 64 + lane] * a1;
-            if constexpr (!SAFE && !STREAM && !SOLO) bad = bad || !(fabsf(o[db][b2][i]) < INFINITY);
+            if constexpr (!SAFE && !STREAM && !ONE) bad = bad || !(fabsf(o[db][b2][i]) < INFINITY);
           }
-        if constexpr (!SAFE && !STREAM && !SOLO) bad = bad || !(l >= 0x1p-80f && l <= 0x1p100f);
+        if constexpr (!SAFE && !STREAM && !ONE) bad = bad || !(l >= 0x1p-80f && l <= 0x1p100f);
       }
     }
-    if constexpr (SOLO) {  // the states of the two halves of the list, like those of the two halves of a tile
+    if constexpr (ONE) {  // the states of the two halves of the list, like those of the two halves of a tile
       float* const mid = reinterpret_cast<float*>(smem) + 16;
       __syncthreads();
       if (kh == 0 && qi == 1) {
@@ -1254,7 +1275,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         }
       }
     }
-    const bool writes = kh == 0 && !(SOLO && qi != 0);  // this wave holds the finished rows
+    const bool writes = kh == 0 && !(ONE && qi != 0);  // this wave holds the finished rows
     if constexpr (STREAM && !SAFE) {
       if (w1 > w0) {  // uniform: a row of several workgroups
         float* const partials = reinterpret_cast<float*>(tab + 1);
@@ -1323,7 +1344,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       }
     }
     if constexpr (!SAFE) {
-      if ((STREAM || SOLO) && writes) {  // otherwise checked as it was merged
+      if ((STREAM || ONE) && writes) {  // otherwise checked as it was merged
 #pragma unroll
         for (int b2 = 0; b2 < 2; ++b2) {
           bad = bad || !(lt[b2] >= 0x1p-80f && lt[b2] <= 0x1p100f);
@@ -1368,6 +1389,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     if constexpr (STREAM) take_tiles(0, 1 << 30);  // the whole row, whoever had its parts
     pass(std::true_type{});
   }
+  return kDone;
   };  // run
 
   if constexpr (STREAM) {
@@ -1385,7 +1407,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       const int tiles = __builtin_amdgcn_readfirstlane(max(1, HALF ? (cnt + 1) >> 1 : cnt));
       const int take = min(quota - done, tiles - tile);
       const int begin = me * quota + done - tile;  // the row's first tile, counted over all rows
-      run(row, tile, tile + take, begin / quota, (begin + tiles - 1) / quota, me);
+      run(std::false_type{}, row, tile, tile + take, begin / quota, (begin + tiles - 1) / quota, me, -1);
       done += take;
       tile = 0;
       ++row;
@@ -1403,6 +1425,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   //    first come, first served, through one atomic counter, and leave at once when none is left.
   //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
   //    through with its static share early thus takes more of the remaining rows than a slow one.
+  const int units = PAIR && !SOLO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
   const int64_t total = int64_t(heads) * units;
   const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
   int64_t pos;
@@ -1419,7 +1442,19 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     pos = n_static + t;
   }
   const int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
-  run(row, 0, 0, 0, 0, 0);
+  if constexpr (PAIR && !SOLO) {
+    const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
+    const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
+    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, -1);
+    if (listed == kDone) return;
+#pragma unroll 1
+    for (int i = I; i < min(I + 2, nb); ++i) {
+      __syncthreads();  // whatever the end of the row before still reads
+      run(std::true_type{}, h * nb + i, 0, 0, 0, 0, 0, listed);
+    }
+  } else {
+    run(std::bool_constant<SOLO>{}, row, 0, 0, 0, 0, 0, -1);
+  }
 }
 
 }  // namespace

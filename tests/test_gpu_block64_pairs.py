@@ -145,3 +145,44 @@ def test_longest_list_that_fits(B):
         blocks = [0, 1, nb - 2, nb - 1]
         want = O.sparse_attention(q, k, v, mask, 64, q_blocks=blocks)
         assert bf16_bars_ok(out, want)[0], bf16_bars_ok(out, want)
+
+
+@pytest.mark.parametrize("density", [0.2, 0.9])
+@pytest.mark.parametrize("N,n_first", [(1500, 1500), (1590, 700), (4200, 4100)])
+def test_uneven_neighbours(B, N, n_first, density):
+    """Lists of very different length side by side: rows of a pair are then taken one by one.  Every second row keeps
+    `density`, its neighbour one block, none, or a sixth; in the last head the long rows come second."""
+    ranges = O.block_ranges(N, 64, n_first)
+    nb = len(ranges)
+    H = -(-ROWS // nb)
+    rng = np.random.default_rng(N)
+    mask = rng.random((H, nb, nb)) < density
+    for h in range(H):
+        short = np.arange(0 if h == H - 1 else 1, nb, 2)
+        mask[h, short] = rng.random((short.size, nb)) < (0.0, 0.0, 0.17)[h % 3]
+        if h % 3 == 1:
+            mask[h, short, rng.integers(0, nb, short.size)] = True
+    q, k, v = _qkv(H, N, N)
+    out, lse = _run(B, q, k, v, mask, n_first)
+    heads = sorted({0, 1, 2, H - 1})
+    if N > 4000:
+        heads = [0, H - 1]
+    _check(out, lse, q, k, v, mask, n_first, heads=heads)
+    again, again_lse = _run(B, q, k, v, mask, n_first, shuffle=1)
+    _check(again, again_lse, q, k, v, mask, n_first, heads=heads)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_uneven_rows_out_of_range(B, sign):
+    """As test_rows_out_of_range with every second list short."""
+    H, N = 47, 1400
+    q, k, v = _qkv(H, N, 12, 27.0 * sign)
+    nb = O.num_blocks(N, 64)
+    mask = np.ones((H, nb, nb), bool)
+    mask[:, 1::2, 2:] = False
+    out, lse = _run(B, q, k, v, mask, N)
+    want, want_lse = O.sparse_attention(q, k, v, mask, 64, return_lse=True, heads=[0, 20, 46])
+    mx, mean = attn_errors(out, want)
+    assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
+    seen = ~np.isnan(want_lse)
+    assert np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 0.25
