@@ -419,7 +419,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
     const int32_t* __restrict__ kv_cnt, const int32_t* __restrict__ order, int idx_stride, int64_t n_tokens, int nb,
-    int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int* __restrict__ next_row,
+    int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int64_t n_pairs, int* __restrict__ next_row,
     StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
   static_assert(!PAIR || (B == 128 && KB == 64 && !STREAM), "pairs of blocks of 64");
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
   // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, in a SOLO launch or as
   // one of a pair that is taken row by row; listed >= 0: its list is in LDS already, with that many blocks.
-  // Returns kDone, or, with nothing done, kByOne if the row
+  // A pair: listed >= 0 means block `listed` of the two alone.  Returns kDone, or, with nothing done, kByOne if the row
   // or rows are to be run by ONE, or the length of the list that it has sorted into LDS for one row.
   // (Everything up to the dispatch at the end; not indented.)
   auto run = [&](auto onec, int64_t row, int tile0, int tile1, int w0, int w1, int me, int listed) -> int {
@@ -560,8 +560,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     constexpr int WORDS = kPairMaxBlocks / 32;
     // counts and the first 256 entries of both lists in one round of loads: entries past a count are
     // whatever the buffer holds (idx_stride >= nbk) and are not used
-    const int64_t id0 = int64_t(h) * nb + 2 * u_in_head;
-    const bool two = 2 * u_in_head + 1 < nb;
+    const int64_t id0 = int64_t(h) * nb + 2 * u_in_head + max(listed, 0);
+    const bool two = listed < 0 && 2 * u_in_head + 1 < nb;
     const int32_t* const idx0 = kv_idx + id0 * idx_stride;
     const int32_t* const idx1 = two ? idx0 + idx_stride : idx0;
     const int c0 = kv_cnt[id0], c1 = kv_cnt[two ? id0 + 1 : id0];
@@ -1433,6 +1433,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const int r = static_cast<int>(w & 511);
     pos = (w - r) + 512 <= n_static ? (w - r) + (r & 7) * 64 + (r >> 3) : w;
   } else {
+    if (next_row == nullptr) return;  // the grid is rounded up to whole heads
     int* slot = reinterpret_cast<int*>(smem);
     if (tid == 0) *slot = atomicAdd(next_row, 1);
     __syncthreads();
@@ -1441,14 +1442,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     if (t >= total - n_static) return;  // the whole workgroup leaves, before any other barrier
     pos = n_static + t;
   }
-  const int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
+  int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
   if constexpr (PAIR && !SOLO) {
+    const bool single = order == nullptr && pos >= n_pairs;  // positions from n_pairs on are rows, two of each unit
+    if (single) row = n_pairs + ((pos - n_pairs) >> 1);
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
     const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
-    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, -1);
+    const int first = single ? I + static_cast<int>((pos - n_pairs) & 1) : I, last = min(single ? first + 1 : I + 2, nb);
+    if (first >= nb) return;
+    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, single ? first - I : -1);
     if (listed == kDone) return;
 #pragma unroll 1
-    for (int i = I; i < min(I + 2, nb); ++i) {
+    for (int i = first; i < last; ++i) {
       __syncthreads();  // whatever the end of the row before still reads
       run(std::true_type{}, h * nb + i, 0, 0, 0, 0, 0, listed);
     }
@@ -1483,6 +1488,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const int nu = pair ? (nb + 1) >> 1 : nb;  // units of work per head: rows, or pairs of rows
   const int64_t rows = int64_t(heads) * nu;
   int64_t n_static = rows;  // without a workspace every row is taken by workgroup number
+  int64_t n_pairs = rows;   // units that go in pairs; those after them (none if there is a launch order) go row by row
   int extra = 0;                          // workgroups beyond one per row
   int* next_row = nullptr;
   // ordering and balancing matter only when the grid does not fit the chip at once
@@ -1495,6 +1501,18 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     const int64_t dynamic = rows / 8;
     n_static = (rows - dynamic) / 512 * 512;
     extra = static_cast<int>((rows - n_static) / 2 + 512);
+  }
+  if (pair && rows < 1024 && heads + ceil_div(128, nu) <= 65535) {
+    // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
+    // 1,064 rows of 532 blocks, nine tenths, a quarter kept, a band: 655 -> 610, 252 -> 204, 216 -> 179 us.  Where more
+    // are left the last 64 do, which evens out the end: 1,600 rows of 100 blocks 176 -> 164, 69 -> 61, 62 -> 60 us.  With
+    // 400 and more there is no room for them: 1,840 rows of 115 205 -> 207 us, 2,032 of 127 242 -> 261.  Only here, where
+    // the launch has no order: which rows go which way must not depend on one.
+    const int64_t rest = rows - 512;
+    const int64_t singly = rest <= 128 ? rest : rest < 400 ? 64 : 0;
+    n_pairs = rows - singly;
+    extra = static_cast<int>(singly);
+    n_static = rows + singly;
   }
   if (big && kv_idx == nullptr) {
     // dense: the workspace holds the counter only
@@ -1535,7 +1553,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   }
   auto launch = [&](auto kernel, dim3 g, int threads, size_t lds, StreamTable* tab) {
     hipLaunchKernelGGL(kernel, g, dim3(threads), lds, stream, qp, kp, vp, op, lse, kv_idx, kv_cnt, order, idx_stride,
-                       n_tokens, nb, nbk, scale_log2, seg, heads, n_static, next_row, tab);
+                       n_tokens, nb, nbk, scale_log2, seg, heads, n_static, n_pairs, next_row, tab);
   };
   const size_t order_bytes = attn_order_bytes(heads, n_tokens);
   if (!big && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&

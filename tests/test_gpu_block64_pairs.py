@@ -186,3 +186,20 @@ def test_uneven_rows_out_of_range(B, sign):
     assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
     seen = ~np.isnan(want_lse)
     assert np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 0.25
+
+
+@pytest.mark.parametrize("H,N", [(16, 4096), (16, 4225), (64, 1060), (12, 6500), (9, 9200), (16, 7300)])
+def test_pairs_that_go_row_by_row(B, H, N):
+    """512 to 1023 pairs: none, few, many left after the first 512, the last of them taken row by row; odd numbers of
+    blocks in a head."""
+    nb = O.num_blocks(N, 64)
+    assert 512 <= H * ((nb + 1) // 2) < 1024
+    mask = np.random.default_rng(N).random((H, nb, nb)) < 0.4
+    mask[:, :, 0] = True
+    mask[H - 1, nb - 1] = False
+    q, k, v = _qkv(H, N, N)
+    out, lse = _run(B, q, k, v, mask, N)
+    again, _ = _run(B, q, k, v, mask, N)
+    assert torch.equal(out, again)
+    _check(out, lse, q, k, v, mask, N, heads=[0, H - 1])
+    assert torch.isfinite(out.float()).all()
