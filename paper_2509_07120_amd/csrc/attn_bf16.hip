@@ -337,11 +337,16 @@ struct Tile {
 // everywhere, so partial sums just add up): every one leaves its unnormalised output and row sums in the
 // workspace and counts itself in; the one that completes the count reads them all, in piece order, so the
 // result does not depend on who came last.  Nobody waits for anybody.
+// Sharing costs parts and their sum, so the plan leaves the rows whole (quota 0) where lists of nearly equal length
+// would lose by it, see worth_sharing(): there is then a workgroup to each.  (One workgroup for several whole rows stays the
+// oldest of its CU and holds up the other: 980 equal rows 616 -> 714 us.)
 // Workspace of a launch: the table below, then two partial results per workgroup.
 constexpr int kStreamMaxPlaces = 1024;   // workgroups: 2 x 256 (blocks of 128 rows), 4 x 256 (blocks of 64)
+template <int B>
+constexpr int kStreamPlaces = B == 64 ? kStreamMaxPlaces : kStreamMaxPlaces / 2;
 constexpr int kMinQuota = 4;
 struct StreamTable {
-  int quota, used, pad[14];
+  int quota, used, pad[14];          // tiles to a piece (0: rows stay whole), number of pieces
   int start_row[kStreamMaxPlaces];   // workgroup w starts at tile start_tile[w] of row start_row[w]
   int start_tile[kStreamMaxPlaces];
   int arrived[kStreamMaxRows];       // pieces of the row that are done
@@ -358,11 +363,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(float* p) {
   return __builtin_amdgcn_make_buffer_rsrc(p, 0, kStreamPartialWords * sizeof(float), 0x00020000);
 }
 
+// Whether rows of blocks of 128 gain by being shared.  In tiles per CU: what whole rows lose is the idle part of the last
+// round of 256 rows, three tenths of which shows in the time, and the end of the longest rows; what sharing costs
+// is a 25th and seven tiles.  us, whole rows without a plan / always shared / by this rule: 688 rows of 344 tiles, a tenth,
+// a quarter, a half kept in lists of one length 99 / 112 / 102, 232 / 243 / 236, 450 / 460 / 450; lengths uniform
+// 603 / 460 / 459; 344 rows, nine tenths, a tenth kept 489 / 416 / 414, 60 / 67 / 64; 980 rows of 196, a tenth 80 / 97 / 84.
+__device__ __forceinline__ bool worth_sharing(int rows, int total, int longest) {
+  const float mean = static_cast<float>(total) / rows, per_cu = total * (1.f / 256.f);
+  const float idle = static_cast<float>((256 - (rows & 255)) & 255) * (1.f / 256.f);
+  return 0.3f * idle * mean + 0.75f * (longest - mean) > 0.04f * per_cu + 7.f;
+}
+
 // One workgroup, one thread per row: prefix sums of the rows' tiles, then each row writes the pieces that
 // start in it.  An empty row counts one tile, so that somebody writes its zeros.
 __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32_t* __restrict__ kv_cnt, int rows, int nbk,
-                                                                     int per_tile, int places, StreamTable* __restrict__ tab) {
-  __shared__ int wave_sum[kStreamMaxRows / 64];
+                                                                     int per_tile, int places, bool always, StreamTable* __restrict__ tab) {
+  __shared__ int wave_sum[kStreamMaxRows / 64], wave_top[kStreamMaxRows / 64];
   const int t = threadIdx.x;
   const int lane = t & 63;
   int tiles = 0;
@@ -376,12 +392,22 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
     const int x = __shfl_up(end, o);
     if (lane >= o) end += x;
   }
-  if (lane == 63) wave_sum[t >> 6] = end;
+  int top = tiles;
+  for (int o = 1; o < 64; o <<= 1) top = max(top, __shfl_xor(top, o));
+  if (lane == 63) {
+    wave_sum[t >> 6] = end;
+    wave_top[t >> 6] = top;
+  }
   __syncthreads();
   int total = 0;
   for (int w = 0; w < kStreamMaxRows / 64; ++w) {
     end += w < (t >> 6) ? wave_sum[w] : 0;
     total += wave_sum[w];
+    top = max(top, wave_top[w]);
+  }
+  if (!always && !worth_sharing(rows, total, top)) {  // the same in every thread
+    if (t == 0) tab->quota = tab->used = 0;
+    return;
   }
   const int quota = max(kMinQuota, (total + places - 1) / places);
   const int begin = end - tiles;
@@ -1393,21 +1419,33 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   };  // run
 
   if constexpr (STREAM) {
-    // consecutive pieces to one XCD (workgroup w runs on XCD w % 8), as for whole rows
-    const int w = static_cast<int>(blockIdx.x), places = static_cast<int>(gridDim.x);
-    const int me = (w & 7) * (places >> 3) + (w >> 3);
-    if (me >= tab->used) return;  // the whole workgroup, before any barrier
-    const int quota = tab->quota;
+    // consecutive pieces to one XCD (workgroup w runs on XCD w % 8), as for whole rows below
+    constexpr int places = kStreamPlaces<B>;
+    const int w = static_cast<int>(blockIdx.x);
     const int rows = heads * nb;
+    const int me = (w & 7) * (places >> 3) + ((w & (places - 1)) >> 3);
+    const int quota = __builtin_amdgcn_readfirstlane(tab->quota), used = __builtin_amdgcn_readfirstlane(tab->used);
     int row = __builtin_amdgcn_readfirstlane(tab->start_row[me]);
     int tile = __builtin_amdgcn_readfirstlane(tab->start_tile[me]);
-    int done = 0;
-    while (done < quota && row < rows) {
-      const int cnt = kv_cnt != nullptr ? min(max(kv_cnt[row], 0), nbk) : nbk;
-      const int tiles = __builtin_amdgcn_readfirstlane(max(1, HALF ? (cnt + 1) >> 1 : cnt));
-      const int take = min(quota - done, tiles - tile);
-      const int begin = me * quota + done - tile;  // the row's first tile, counted over all rows
-      run(std::false_type{}, row, tile, tile + take, begin / quota, (begin + tiles - 1) / quota, me, -1);
+    int done = 0, most = quota;
+    if (quota == 0) {
+      row = (w | 511) < rows ? (w & ~511) + (w & 7) * 64 + ((w & 511) >> 3) : w;
+      tile = 0;
+      most = 1;
+    } else if (w >= places || me >= used) {
+      return;  // the whole workgroup, before any barrier
+    }
+    while (done < most && row < rows) {
+      int take = 1 << 30, w0 = 0, w1 = 0;
+      if (quota != 0) {
+        const int cnt = kv_cnt != nullptr ? min(max(kv_cnt[row], 0), nbk) : nbk;
+        const int tiles = __builtin_amdgcn_readfirstlane(max(1, HALF ? (cnt + 1) >> 1 : cnt));
+        take = min(quota - done, tiles - tile);
+        const int begin = me * quota + done - tile;  // the row's first tile, counted over all rows
+        w0 = begin / quota;
+        w1 = (begin + tiles - 1) / quota;
+      }
+      run(std::false_type{}, row, tile, tile + take, w0, w1, me, -1);
       done += take;
       tile = 0;
       ++row;
@@ -1561,13 +1599,14 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
       workspace_bytes >= order_bytes + kStreamBytes + 256) {
     const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
     StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
-    const int places = block == 64 ? 1024 : 512;
+    const int places = block == 64 ? kStreamPlaces<64> : kStreamPlaces<128>;
+    const dim3 g(max(places, heads * nb));
     hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
-                       block_k == block ? 1 : 2, places, tab);
+                       block_k == block ? 1 : 2, places, block == 64 || kv_idx == nullptr, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
-    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false>, dim3(places), 128, lds64, tab);
-    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false>, dim3(places), 256, lds128, tab);
-    else launch(attn_bf16_kernel<128, 64, true, false, false>, dim3(places), 256, lds128, tab);
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false>, g, 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false>, g, 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true, false, false>, g, 256, lds128, tab);
     return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
   if (pair) launch(attn_bf16_kernel<128, 64, false, true, false>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);

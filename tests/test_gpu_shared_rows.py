@@ -131,3 +131,33 @@ def test_replays_from_a_graph(B):
         torch.cuda.synchronize()
         assert torch.equal(out, want[which])
         B.bsga_dense_attn(q, k, v)
+
+
+def _plan(ws, H, N):
+    """The plan of the last launch: tiles to a piece (0: whole rows), number of pieces, parts counted in per row."""
+    order = (H * (-(-N // 64) + 33) + 4) * 4
+    at = (ws.data_ptr() + order + 255) // 256 * 256 - ws.data_ptr()
+    words = ws[at:at + (16 + 3 * 1024) * 4].view(torch.int32).cpu().numpy()
+    return words[0], words[1], words[16 + 2048:]
+
+
+@pytest.mark.parametrize("H,N,bk,kept", [(1, 43900, 128, 20), (2, 43968, 128, 34), (5, 25000, 128, 90), (2, 43968, 64, 61)])
+def test_lists_of_one_length_stay_whole(B, H, N, bk, kept):
+    """Short lists of one length gain nothing by being shared: the plan leaves them whole, fewer and more than the
+    512 workgroups of the first round, and every row is what the launch without a plan makes of it."""
+    b = 128
+    nb, nbk = O.num_blocks(N, b), O.num_blocks(N, bk)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    idx = torch.rand((H, nb, nbk), generator=g, device="cuda").argsort(-1)[..., :kept].sort(-1).values
+    idx = torch.nn.functional.pad(idx, (0, nbk - kept)).int().contiguous()
+    cnt = torch.full((H, nb), kept, dtype=torch.int32, device="cuda")
+    cnt[0, 1], cnt[H - 1, nb - 1] = 0, kept - 1
+    q, k, v = (torch.randn((H, N, 64), generator=g, device="cuda").bfloat16() for _ in range(3))
+    ws = torch.full((B.bsga_attn_workspace_bytes(q.dtype, H, N),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    _, lse = B.bsga_sparse_attn(q, k, v, b, idx, cnt, return_lse=True, out=out, workspace=ws, block_k=bk)
+    plain, plse = B.bsga_sparse_attn(q, k, v, b, idx, cnt, return_lse=True, ordered=False, block_k=bk)
+    torch.cuda.synchronize()
+    assert _plan(ws, H, N)[0] == 0
+    assert torch.equal(out, plain) and torch.equal(lse, plse)
+    assert (out[0, b:2 * b].float() == 0).all()
