@@ -141,6 +141,31 @@ def _plan(ws, H, N):
     return words[0], words[1], words[16 + 2048:]
 
 
+@pytest.mark.parametrize("H,N,n_first,b,bk,density", CASES + [(1, 16400, 16400, 64, 64, 0.6), (1, 41000, 41000, 128, 128, 0.6), (1, 41000, 41000, 128, 64, 0.6)])
+def test_rows_of_these_cases_are_shared(B, H, N, n_first, b, bk, density):
+    """The launches of this file do take the way that it is about."""
+    nbq, nbk = len(O.block_ranges(N, b, n_first)), len(O.block_ranges(N, bk, n_first))
+    mask = np.random.default_rng(N + b).random((H, nbq, nbk)) < density
+    mask[:, :, 0] = True
+    mask[0, nbq // 2] = True
+    ws = torch.full((B.bsga_attn_workspace_bytes(torch.bfloat16, H, N),), 255, dtype=torch.uint8, device="cuda")
+    q, k, v = (torch.randn((H, N, 64), device="cuda").bfloat16() for _ in range(3))
+    B.bsga_sparse_attn_split(q, k, v, b, n_first, *_lists(mask), block_k=bk, workspace=ws)
+    torch.cuda.synchronize()
+    quota, used, arrived = _plan(ws, H, N)
+    assert quota >= 4 and used > 0 and (arrived[:H * nbq] > 1).any()
+
+
+@pytest.mark.parametrize("H,N", [(1, 20600), (2, 21999)])
+def test_dense_rows_are_shared(B, H, N):
+    ws = torch.full((B.bsga_attn_workspace_bytes(torch.bfloat16, H, N),), 255, dtype=torch.uint8, device="cuda")
+    q, k, v = (torch.randn((H, N, 64), device="cuda").bfloat16() for _ in range(3))
+    B.bsga_dense_attn(q, k, v, workspace=ws)
+    torch.cuda.synchronize()
+    quota, used, arrived = _plan(ws, H, N)
+    assert quota >= 4 and used > 0 and (arrived[:H * O.num_blocks(N, 128)] > 1).any()
+
+
 @pytest.mark.parametrize("H,N,bk,kept", [(1, 43900, 128, 20), (2, 43968, 128, 34), (5, 25000, 128, 90), (2, 43968, 64, 61)])
 def test_lists_of_one_length_stay_whole(B, H, N, bk, kept):
     """Short lists of one length gain nothing by being shared: the plan leaves them whole, fewer and more than the
