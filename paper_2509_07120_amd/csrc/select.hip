@@ -386,41 +386,42 @@ __device__ __forceinline__ f64x4 products(const double (&a)[16], const double (&
   return acc;
 }
 
-// Logits of 48 query rows against 128 key blocks per wave, four waves of a workgroup below each other.
+// Logits of 48 (16) query rows against 128 key blocks per wave, four waves of a workgroup below each other.
 // Column 2i of a pair of column tiles comes from the first, column 2i + 1 from the second, so a lane holds
 // two neighbours and 16 lanes store 256 consecutive bytes (8-byte aligned: nb_k may be odd).  The stores bypass
 // the L2, which holds the key rows all workgroups share: at 2440 x 2440 blocks and 16 heads (762 MB
 // written, 12.2 GFLOP) 250 us, 349 us with plain stores; a plain fill of the same buffer takes 157 us and the
 // products alone 230 us.  32 rows per wave: 312 us, 64 rows: 313 us.  The version before this one (vector
 // fp64, four rows per workgroup, every key row read by each) took 810 us.
-constexpr int kLogitRowTiles = 3, kLogitCols = 128, kLogitRows = 4 * 16 * kLogitRowTiles;
+constexpr int kLogitCols = 128;
+template <int ROW_TILES>  // 16 query rows each
 __global__ __launch_bounds__(kThreads) void logits_kernel(const double* __restrict__ q_pool, const double* __restrict__ k_pool,
                                                           int nb_q, int nb_k, double score_scale, double* __restrict__ logits) {
   typedef double f64x2_at8 __attribute__((ext_vector_type(2), aligned(8)));
   const int h = blockIdx.z;
   const int lane = threadIdx.x & 63;
   const int i16 = lane & 15;
-  const int I0 = blockIdx.y * kLogitRows + (threadIdx.x >> 6) * 16 * kLogitRowTiles;
+  const int I0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 16 * ROW_TILES;
   const int J0 = blockIdx.x * kLogitCols;
   if (I0 >= nb_q) return;  // whole wave; the kernel has no barriers
   const double* qh = q_pool + int64_t(h) * nb_q * kD;
   const double* kh = k_pool + int64_t(h) * nb_k * kD;
-  double a[kLogitRowTiles][16], b[2][16];
+  double a[ROW_TILES][16], b[2][16];
 #pragma unroll
-  for (int rt = 0; rt < kLogitRowTiles; ++rt) load_rows(a[rt], qh, I0 + rt * 16 + i16, nb_q);
+  for (int rt = 0; rt < ROW_TILES; ++rt) load_rows(a[rt], qh, I0 + rt * 16 + i16, nb_q);
   load_rows(b[0], kh, J0 + 2 * i16, nb_k);
 #pragma unroll
   for (int cp = 0; cp < kLogitCols / 32; ++cp) {
     const int J = J0 + cp * 32 + 2 * i16;
-    f64x4 even[kLogitRowTiles], odd[kLogitRowTiles];
+    f64x4 even[ROW_TILES], odd[ROW_TILES];
     load_rows(b[1], kh, J + 1, nb_k);
 #pragma unroll
-    for (int rt = 0; rt < kLogitRowTiles; ++rt) even[rt] = products(a[rt], b[0]);
+    for (int rt = 0; rt < ROW_TILES; ++rt) even[rt] = products(a[rt], b[0]);
     if (cp + 1 < kLogitCols / 32) load_rows(b[0], kh, J + 32, nb_k);
 #pragma unroll
-    for (int rt = 0; rt < kLogitRowTiles; ++rt) odd[rt] = products(a[rt], b[1]);
+    for (int rt = 0; rt < ROW_TILES; ++rt) odd[rt] = products(a[rt], b[1]);
 #pragma unroll
-    for (int rt = 0; rt < kLogitRowTiles; ++rt)
+    for (int rt = 0; rt < ROW_TILES; ++rt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int I = I0 + rt * 16 + (lane >> 4) + 4 * r;
@@ -497,8 +498,16 @@ int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_
     return check_hip(hipGetLastError(), "bsga_select_blocks launch");
   }
   double* logits = static_cast<double*>(workspace);
-  const dim3 lgrid(static_cast<unsigned>(ceil_div(nb_k, kLogitCols)), static_cast<unsigned>(ceil_div(nb_q, kLogitRows)), heads);
-  hipLaunchKernelGGL(logits_kernel, lgrid, dim3(kThreads), 0, stream, q_pool, k_pool, nb_q, nb_k, score_scale, logits);
+  auto scores = [&](auto kernel, int row_tiles) {
+    const dim3 g(static_cast<unsigned>(ceil_div(nb_k, kLogitCols)), static_cast<unsigned>(ceil_div(nb_q, 4 * 16 * row_tiles)), heads);
+    hipLaunchKernelGGL(kernel, g, dim3(kThreads), 0, stream, q_pool, k_pool, nb_q, nb_k, score_scale, logits);
+  };
+  // Three row tiles to a wave use a loaded key row most; one spreads a few heads over more of the card.  The whole selection,
+  // three / one: 60 workgroups of the first kind (4 heads of 513 x 513 blocks) 32 / 24 us, 54 (1 x 1074) 35 / 28, 96 (4 x
+  // 700) 34 / 35, 120 (8 x 513) 37 / 38, 192 (8 x 700) 44 / 52, 240 (16 x 513) 49 / 58; 20 rows of 1074, 16 heads 29 / 21.
+  const bool few = nb_q <= 64 || ceil_div(nb_k, kLogitCols) * ceil_div(nb_q, 4 * 16 * 3) * heads < 90;
+  if (few) scores(logits_kernel<1>, 1);
+  else scores(logits_kernel<3>, 3);
   if (int rc = check_hip(hipGetLastError(), "bsga_select_blocks (logits) launch")) return rc;
   const int64_t rows = int64_t(heads) * nb_q;
   const dim3 grid(static_cast<unsigned>(ceil_div(rows, kWaves)));

@@ -93,3 +93,13 @@ def test_rows_that_keep_everything(B, nbk):
     assert c[2] == nbk and c[3] == nbk               # the mass never gets to tau
     assert c[0] == int(np.ceil(0.9 * nbk - 1e-9))    # equal scores: the shortest prefix
     assert c[1] < nbk
+
+
+@pytest.mark.parametrize("H,nbq,nbk", [(1, 1, 513), (3, 64, 600), (1, 65, 640), (2, 193, 641), (5, 513, 513), (6, 500, 700), (7, 513, 513)])
+def test_score_tiles(B, H, nbq, nbk):
+    """Rows and columns around the tiles of the score kernel's two widths (16 and 48 query rows to a wave), and launches on
+    either side of the line between them."""
+    rng = np.random.default_rng(nbq)
+    qp = rng.standard_normal((H, nbq, 64)) * 0.3
+    kp = rng.standard_normal((H, nbk, 64))
+    _check(B, qp, kp, 0.9, 0.8, 0.125)
