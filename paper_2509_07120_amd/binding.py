@@ -409,16 +409,23 @@ def bsga_gather_tokens(x: torch.Tensor, index: torch.Tensor, out: Optional[torch
     return out
 
 
+def _require_order(index: Optional[torch.Tensor], x: torch.Tensor, n_tokens: int) -> None:
+    if index is None:
+        return
+    _require(index, "index", torch.int32)
+    if index.device != x.device:
+        raise ValueError("index must be on the same device as x")
+    if index.numel() != n_tokens:
+        raise ValueError("index must have one entry per token")
+
+
 def bsga_split_heads(x: torch.Tensor, parts: int, heads: int, index: Optional[torch.Tensor] = None) -> torch.Tensor:
     """x [N, parts * heads * 64] -> [parts, heads, N, 64], token i taken from row index[i] if an index is given."""
     _require(x, "x")
     N = x.shape[0]
     if x.dim() != 2 or x.shape[1] != parts * heads * 64:
         raise ValueError("x must be [n_tokens, parts * heads * 64]")
-    if index is not None:
-        _require(index, "index", torch.int32)
-        if index.numel() != N:
-            raise ValueError("index must have one entry per token")
+    _require_order(index, x, N)
     out = torch.empty((parts, heads, N, 64), dtype=x.dtype, device=x.device)
     _check(lib.bsga_split_heads(_ptr(x), _dtype_code(x), N, parts, heads, 64, _ptr(index), _ptr(out), _stream(x)))
     return out
@@ -428,10 +435,7 @@ def bsga_merge_heads(x: torch.Tensor, index: Optional[torch.Tensor] = None) -> t
     """x [heads, N, 64] -> [N, heads * 64], row i taken from token index[i] if an index is given."""
     _require(x, "x")
     H, N, d = x.shape
-    if index is not None:
-        _require(index, "index", torch.int32)
-        if index.numel() != N:
-            raise ValueError("index must have one entry per token")
+    _require_order(index, x, N)
     out = torch.empty((N, H * d), dtype=x.dtype, device=x.device)
     _check(lib.bsga_merge_heads(_ptr(x), _dtype_code(x), H, N, d, _ptr(index), _ptr(out), _stream(x)))
     return out
