@@ -361,7 +361,8 @@ def sparse_global_attention(q, k, v, block: int, tau: float, rho: float = 1.0,
     A layer of one frame is bound by the host (40 us a pass when each stage was called by its own function),
     so the inputs are checked once and everything that does not outlive the call is one allocation: the pooled
     vectors, then the selection's logits, whose place the attention's workspace takes (the stages are ordered
-    by the stream)."""
+    by the stream).  The logits of a long sequence are allocated apart and freed before the output is, so that the
+    peak is the larger of the two (762 and 640 MB at 300 frames)."""
     _require(q, "q"); _require(k, "k", q.dtype); _require(v, "v", q.dtype)
     if q.shape != k.shape or q.dim() != 3:
         raise ValueError("q and k must both be [heads, n_tokens, head_dim]")
@@ -373,10 +374,12 @@ def sparse_global_attention(q, k, v, block: int, tau: float, rho: float = 1.0,
     pool_bytes = H * nb * d * 8
     select_bytes = lib.bsga_select_workspace_bytes(H, nb, nb)
     own = lib.bsga_attn_workspace_bytes(code, H, N, d) if workspace is None else 0
-    scratch = torch.empty(2 * pool_bytes + max(select_bytes, own), dtype=torch.uint8, device=dev)
+    together = max(select_bytes, own) <= 1 << 20
+    scratch = torch.empty(2 * pool_bytes + (max(select_bytes, own) if together else 0), dtype=torch.uint8, device=dev)
     q_pool = scratch.data_ptr()
     k_pool = q_pool + pool_bytes
-    rest = k_pool + pool_bytes
+    logits = None if together else torch.empty(select_bytes, dtype=torch.uint8, device=dev)
+    rest = k_pool + pool_bytes if together else logits.data_ptr()
     qp, kp = q.data_ptr(), k.data_ptr()
     _check(lib.bsga_pool_qk(qp, kp, code, H, N, d, block, q_pool, k_pool, stream))
     mask_bits = torch.empty((H, nb, (nb + 31) // 32), dtype=torch.int32, device=dev)
@@ -387,7 +390,10 @@ def sparse_global_attention(q, k, v, block: int, tau: float, rho: float = 1.0,
     _check(lib.bsga_select_blocks(q_pool, k_pool, H, nb, nb, d, scale if score_scale is None else float(score_scale),
                                   float(tau), float(rho),
                                   None, None, mask_bits.data_ptr(), idx, cnt, nb, rest, select_bytes, stream))
+    del logits
     out = torch.empty_like(q)
+    if workspace is None and not together and own > 0:
+        workspace = torch.empty(own, dtype=torch.uint8, device=dev)
     if workspace is None:
         ws, ws_bytes = (rest, own) if own > 0 else (None, 0)
     else:
