@@ -438,7 +438,6 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 //
 // SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
 // waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
-constexpr int kPairMaxBlocks = 4096;
 enum { kDone = -1, kByOne = -2 };  // what a workgroup of a pair has left to do
 template <int B, int KB, bool STREAM, bool PAIR, bool SOLO>
 __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
@@ -1501,18 +1500,6 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 }
 
 }  // namespace
-
-// Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine
-// tenths kept (a quarter): 352 rows of 22 tiles 26 / 21 us (12 / 12), 172 of 43 33 / 23 (13 / 11), 22 of 22 19 / 15
-// (11 / 9); 516 of 43 44 / 48 (17 / 21).
-static bool solo_rows(int block, int64_t rows, int nbk) {
-  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
-}
-// Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
-// workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
-static bool pairs_rows(int block, int heads, int nb, int nbk) {
-  return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
-}
 
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,

@@ -65,6 +65,19 @@ inline bool attn_stream_shape(int heads, int64_t n_tokens) {
   return shares_rows(h * n128, 128, n128, true);
 }
 
+constexpr int kPairMaxBlocks = 4096;  // key blocks of which two lists fit the LDS beside the tiles
+// Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine
+// tenths kept (a quarter): 352 rows of 22 tiles 26 / 21 us (12 / 12), 172 of 43 33 / 23 (13 / 11), 22 of 22 19 / 15
+// (11 / 9); 516 of 43 44 / 48 (17 / 21).
+inline bool solo_rows(int block, int64_t rows, int nbk) {
+  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
+}
+// Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
+// workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
+inline bool pairs_rows(int block, int heads, int nb, int nbk) {
+  return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
+}
+
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);

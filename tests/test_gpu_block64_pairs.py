@@ -203,3 +203,61 @@ def test_pairs_that_go_row_by_row(B, H, N):
     assert torch.equal(out, again)
     _check(out, lse, q, k, v, mask, N, heads=[0, H - 1])
     assert torch.isfinite(out.float()).all()
+
+
+@pytest.mark.parametrize("density", [0.1, 0.9])
+@pytest.mark.parametrize("H,N,n_first", [(513, 64, 64), (300, 65, 40), (60, 700, 700), (47, 700, 333), (10, 5100, 5037), (33, 1000, 64)])
+def test_two_waves_to_a_block(B, H, N, n_first, density):
+    """513 to 1023 rows: a workgroup of two waves to a block of 64 and its list as it is; empty rows, ragged and split
+    sequences, any order of the list."""
+    nb = len(O.block_ranges(N, 64, n_first))
+    assert 512 < H * nb < 1024
+    rng = np.random.default_rng(N + H)
+    mask = rng.random((H, nb, nb)) < density
+    mask[0, :, 0] = True
+    mask[H - 1, nb - 1] = False
+    q, k, v = _qkv(H, N, N)
+    heads = sorted({0, H // 2, H - 1})
+    out, lse = _run(B, q, k, v, mask, n_first)
+    _check(out, lse, q, k, v, mask, n_first, heads=heads)
+    again, again_lse = _run(B, q, k, v, mask, n_first, shuffle=1)
+    _check(again, again_lse, q, k, v, mask, n_first, heads=heads)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_two_waves_out_of_range(B, sign):
+    """As test_rows_out_of_range for the launches between."""
+    H, N = 60, 700
+    q, k, v = _qkv(H, N, 13, 27.0 * sign)
+    nb = O.num_blocks(N, 64)
+    mask = np.random.default_rng(3).random((H, nb, nb)) < 0.5
+    mask[:, :, 0] = True
+    out, lse = _run(B, q, k, v, mask, N)
+    want, want_lse = O.sparse_attention(q, k, v, mask, 64, return_lse=True, heads=[0, 30, 59])
+    mx, mean = attn_errors(out, want)
+    assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
+    seen = ~np.isnan(want_lse)
+    assert abs(np.median(want_lse[seen])) > 70.0 and np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 0.25
+
+
+@pytest.mark.parametrize("n_first", [4097 * 64 - 20, 700])
+def test_more_key_blocks_than_pairs_take(B, n_first):
+    """4097 key blocks and more: two waves to a block again, with lse, empty rows, a ragged and a split sequence."""
+    N = 4097 * 64 - 20
+    nb = len(O.block_ranges(N, 64, n_first))
+    assert nb > 4096
+    q, k, v = _qkv(1, N, 5)
+    rng = np.random.default_rng(2)
+    mask = rng.random((1, nb, nb)) < 0.002
+    mask[0, [0, 10]] = rng.random((2, nb)) < 0.3
+    mask[0, :, 0] = mask[0, :, nb - 1] = True
+    mask[0, 7] = False
+    out, lse = _run(B, q, k, v, mask, n_first)
+    blocks = [0, 1, 10, nb - 2, nb - 1]
+    want, want_lse = O.sparse_attention(q, k, v, np.where(mask.any(-1, keepdims=True), mask, True), 64, q_blocks=blocks,
+                                        n_first=n_first, return_lse=True)
+    assert bf16_bars_ok(out, want)[0], bf16_bars_ok(out, want)
+    seen = ~np.isnan(want_lse)
+    assert np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 2e-2
+    lo, hi = O.block_ranges(N, 64, n_first)[7]
+    assert (out[0, lo:hi].float() == 0).all() and torch.isneginf(lse[0, lo:hi]).all()
