@@ -105,8 +105,8 @@ size_t bsga_select_workspace_bytes(int heads, int nb_q, int nb_k);
  *   workspace, workspace_bytes: device scratch of at least bsga_select_workspace_bytes(...) bytes,
  *             16-byte aligned; holds the block logits between the two kernels of this call and is
  *             overwritten; calls sharing one workspace must be stream-ordered.
- * Limits: 1 <= nb_k <= 8192 (rows are held in registers; above 4096 key blocks the kernel spills and
- * is several times slower per row), 1 <= nb_q <= 2^18, heads <= 65535.  score_scale must be finite;
+ * Limits: 1 <= nb_k <= 8192 (rows are held in registers; above 4096 key blocks a row takes most of a SIMD's and
+ * about twice as long per key block), 1 <= nb_q <= 2^18, heads <= 65535.  score_scale must be finite;
  * 0 <= tau; 0 <= rho <= 1.
  */
 int bsga_select_blocks(const double* q_pool, const double* k_pool, int heads, int nb_q, int nb_k,
@@ -144,10 +144,9 @@ int bsga_merge_heads(const void* src, int dtype, int heads, int64_t n_tokens, in
  * Q, K and V are read in place; the workspace holds the launch order of the (head, query block) rows,
  * heaviest first, and the counter through which the last rows of a large launch are handed out at run
  * time: 4 bytes per row, sized for block 64 and a split sequence, plus 128 bytes per head and 16 bytes.  That
- * much a workspace must have.  For sequences above 4032 tokens with heads * ceil(n_tokens/128) < 1024 the
- * answer also counts 35 MB of partial results, with which a call of few long rows shares rows between
- * workgroups; a call given less than that computes every row in one workgroup (same results up to the
- * order of fp32 sums).  bsga_dense_attn needs none and accepts NULL.
+ * much a workspace must have.  For shapes of few long rows the answer also counts 35 MB of partial results, with
+ * which a call shares rows between workgroups if that is faster; a call given less than that computes every
+ * row in one workgroup (same results up to the order of fp32 sums).  bsga_dense_attn needs none and accepts NULL.
  */
 size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int head_dim);
 
@@ -163,12 +162,16 @@ size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int hea
  *   workspace, workspace_bytes: device scratch of bsga_attn_workspace_bytes(...) bytes (see there for
  *            the least); overwritten; calls sharing one workspace must be stream-ordered.  May be
  *            NULL: the query blocks are then launched in index order instead of heaviest first,
- *            and every row is tied to the workgroup of its number (same results; a longer tail when
- *            row lengths differ a lot, and a few per cent slower on large shapes because the XCDs of
- *            a part do not run equally fast and cannot then share the last rows unevenly).
+ *            and every row is tied to the workgroup of its number (the same results, up to the order of
+ *            fp32 sums where a workspace would have let rows be shared; a longer tail when row lengths
+ *            differ a lot, and a few per cent slower on large shapes because the XCDs of a part do not
+ *            run equally fast and cannot then share the last rows unevenly).
  * bf16: products on bf16 MFMA with fp32 accumulation, fp32 softmax weights.  softmax_scale > 0.
  * The index lists are trusted to be in range (they come from bsga_select_blocks); block
  * indices are clamped to [0, nb) before use so a corrupt list cannot read out of bounds.
+ * A call gives the same bits every time.  Blocks of 64 may be computed two at a time: a row's sums are then
+ * taken in an order that its neighbour's list has a part in, and if one of the two needs the second pass with
+ * a running maximum (logits beyond the range of the first), both take it.
  * Any order of a row's entries gives the same result up to rounding; the ascending order that
  * bsga_select_blocks writes is the fast one (a ragged block, which is always the last block of the
  * sequence or of its first part, should come last or nearly last in its row: the tiles after it
@@ -183,7 +186,7 @@ int bsga_sparse_attn(const void* q, const void* k, const void* v, int dtype, int
 /*
  * bsga_sparse_attn for callers that cannot allocate or hand over device memory beyond the tensors
  * themselves: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same arguments and results as bsga_sparse_attn without the workspace: the launch order of the rows
+ * Same arguments and results as bsga_sparse_attn without the workspace (rows are never shared): the launch order of the rows
  * lives in a buffer built into the library (bsga_noalloc_scratch_bytes() bytes of device memory per
  * GPU, held from the first call on that GPU until the process ends).  The call allocates and frees
  * nothing and clears nothing with a memset.  Shapes whose launch order does not fit, i.e.

@@ -33,9 +33,9 @@
 // gives the same O / l, the choice only matters for range, and the range is checked afterwards
 // (see pass()).  Only if that check fails is the workgroup repeated with a running reference
 // maximum (SAFE pass).  V is multiplied by the bf16 roundings of the weights.  The pipelined loop
-// sums those same bf16 weights (on the matrix pipe, see fast_loop), so numerator and denominator
-// agree exactly; the plain tile code sums the fp32 weights, which differ from the bf16 ones by at
-// most one rounding (2^-9 relative), the size of rounding the output itself.
+// of blocks of 128 rows sums those same bf16 weights (on the matrix pipe, see fast_loop), so numerator and
+// denominator agree exactly; the plain tile code, and everything on blocks of 64 rows, sums the fp32 weights, which
+// differ from the bf16 ones by at most one rounding (2^-9 relative), the size of rounding the output itself.
 //
 // Tile rows that are not keys of the listed block (past the end of a ragged block, or the absent
 // second half of a tile of half-size key blocks) get weight exactly 0: their scores are set to -inf
@@ -910,7 +910,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   };
 
   // Plain tile loop: compute_tile per tile, one barrier per tile, the next tile's loads in flight
-  // meanwhile.  Used for the SAFE pass and for block 64.
+  // meanwhile.  Used for the SAFE pass and by workgroups of one block of 64 rows and two waves.
   auto plain_loop = [&](auto safec) {
     if (ntiles <= 0) return;
     Tile J_cur = block_at(0);
@@ -1058,8 +1058,8 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
           0, 0);                                                                                               \
     }                                                                                                          \
     /* weights, staggered by one slot so that no instruction waits for the one just before it:   */          \
-    /* pack pair S_ (exponentiated in the previous slot), exponentiate the next pair, then sum   */          \
-    /* pair S_ (two fp32 adds).                                                                  */          \
+    /* pack pair S_ (exponentiated in the previous slot), with SUM32 sum it (two fp32 adds), then */          \
+    /* exponentiate the next pair.                                                               */          \
     {                                                                                                          \
       const unsigned pk = pack_bf16(ex[(S_) & 1][0], ex[(S_) & 1][1]);                                         \
       if constexpr (SUM32) { /* pinned: summed up later, all of a unit's weights would stay alive */           \
@@ -1546,7 +1546,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   }
   if (big && kv_idx != nullptr) {
     // workspace: [heads * nb] launch order, then the [classes][heads] table, the number of the merged
-    // class and the counter of the rows handed out at run time (cleared by order_merge_kernel)
+    // class and the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel)
     int32_t* ord = static_cast<int32_t*>(workspace);
     int32_t* table = ord + rows;
     next_row = table + int64_t(kOrderClasses) * heads + 1;

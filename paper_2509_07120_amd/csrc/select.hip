@@ -26,7 +26,7 @@
 //   reduction over six LDS permutes); four waves per SIMD up to 40 slots.
 //
 // Two ways to launch.  Up to 512 key blocks one kernel does both: a workgroup of 16 waves computes the
-//   scores of 16 rows into LDS (64 KB at 512 key blocks, so two workgroups share a CU) and each wave then
+//   scores of 16 rows into LDS (72 KB at 512 key blocks with the candidates, so two workgroups share a CU) and each wave then
 //   selects one of the rows.  Longer rows go through the workspace, [heads, nb_q, nb_k] float64, because
 //   16 of them do not fit the LDS.
 #include <type_traits>
@@ -103,7 +103,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // exp(x) for x <= 0 (NaN stays NaN): x = n ln2 + r with |r| <= ln2 / 2, ln2 split in two so that n * hi is
-// exact, then the Taylor series to r^13 / 13! (the next term is below 2^-57 of the result) and a
+// exact (Cody and Waite's reduction, with fdlibm's two halves), then the Taylor series to r^13 / 13! (the next term is below 2^-57 of the result) and a
 // scaling by 2^n.  Largest error against 80-bit exp over 4 million arguments in [-700, 0]: 0.87 units in the
 // last place.
 __device__ __forceinline__ double exp_nonpos(double x) {
@@ -265,7 +265,8 @@ __device__ __forceinline__ void select_row(Ptr lrow, int64_t row, int I, const S
   }
   z = wave_sum(z);
   // p = e / z, rounded as the division rounds it: with the rounded reciprocal of z one correction of
-  // the quotient by its exact remainder suffices (Markstein)
+  // the quotient by its exact remainder suffices (Markstein).  Below e = 1e-296 the remainder can be inexact
+  // and p a unit of its last place off; it stays monotone in e, so the ranking is the same.
   const double rz = 1.0 / z;
   auto over_z = [&](double e) {
     const double q0 = e * rz;

@@ -95,6 +95,22 @@ def test_rows_that_keep_everything(B, nbk):
     assert c[1] < nbk
 
 
+@pytest.mark.parametrize("nbk", [200, 500, 700, 2400, 5000])
+@pytest.mark.parametrize("low", [-690.0, -725.0, -743.0])
+def test_ranking_of_probabilities_near_zero(B, nbk, low):
+    """One block takes the mass and a top-k floor ranks the others, whose probabilities lie around the smallest
+    normal and among the subnormal values: the ranking there is that of e / z as it is rounded to float64."""
+    rng = np.random.default_rng(nbk)
+    logits = rng.uniform(low, low + 25.0, (1, 6, nbk))
+    logits[..., nbk // 3:nbk // 3 + 5] = rng.uniform(-2.0, 0.0, (1, 6, 5))
+    qp = np.zeros((1, 6, 64))
+    qp[0, :, :6] = np.eye(6)
+    kp = np.zeros((1, nbk, 64))
+    kp[0, :, :6] = logits[0].T          # products with 1 and 0: the scores are these values themselves
+    for rho in (0.25, 0.5, 0.8):
+        _check(B, qp, kp, 0.0, rho, 1.0)
+
+
 @pytest.mark.parametrize("H,nbq,nbk", [(1, 1, 513), (3, 64, 600), (1, 65, 640), (2, 193, 641), (5, 513, 513), (6, 500, 700), (7, 513, 513)])
 def test_score_tiles(B, H, nbq, nbk):
     """Rows and columns around the tiles of the score kernel's two widths (16 and 48 query rows to a wave), and launches on
