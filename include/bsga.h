@@ -163,15 +163,15 @@ size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int hea
  *            the least); overwritten; calls sharing one workspace must be stream-ordered.  May be
  *            NULL: the query blocks are then launched in index order instead of heaviest first,
  *            and every row is tied to the workgroup of its number (the same results, up to the order of
- *            fp32 sums where a workspace would have let rows be shared; a longer tail when row lengths
+ *            sums where a workspace would have let rows be shared or paired; a longer tail when row lengths
  *            differ a lot, and a few per cent slower on large shapes because the XCDs of a part do not
  *            run equally fast and cannot then share the last rows unevenly).
  * bf16: products on bf16 MFMA with fp32 accumulation, fp32 softmax weights.  softmax_scale > 0.
  * The index lists are trusted to be in range (they come from bsga_select_blocks); block
  * indices are clamped to [0, nb) before use so a corrupt list cannot read out of bounds.
- * A call gives the same bits every time.  Blocks of 64 may be computed two at a time: a row's sums are then
- * taken in an order that its neighbour's list has a part in, and if one of the two needs the second pass with
- * a running maximum (logits beyond the range of the first), both take it.
+ * A call gives the same bits every time.  Blocks may be computed two at a time (those of 128 in large calls with a
+ * workspace): a row's sums are then taken in an order that its neighbour's list has a part in, and if one of the two
+ * needs the second pass with a running maximum (logits beyond the range of the first), both take it.
  * Any order of a row's entries gives the same result up to rounding; the ascending order that
  * bsga_select_blocks writes is the fast one (a ragged block, which is always the last block of the
  * sequence or of its first part, should come last or nearly last in its row: the tiles after it

@@ -11,8 +11,8 @@
 // operands share the VGPR ports).  The two key halves keep independent softmax states that are
 // merged once at the end.  Two workgroups share a CU (two waves per SIMD).
 // Which workgroup computes which row: see the end of the kernel (launch order, 64 consecutive rows
-// per XCD, the last eighth of a large launch handed out at run time).  Launches of few long rows and
-// blocks of 64 rows divide the work otherwise: STREAM, PAIR and SOLO below.
+// per XCD, the last eighth of a large launch handed out at run time).  Launches of few long rows,
+// blocks of 64 rows and large launches of blocks of 128 divide the work otherwise: STREAM, PAIR and SOLO, DUO below.
 //
 // Data movement.  K and V tiles go HBM/L2 -> LDS with direct-to-LDS loads (16 bytes per lane, no
 // staging registers), double buffered, with one workgroup barrier per tile.  Tiles stay row-major
@@ -81,6 +81,14 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(two, bf16x2));
 }
 
+// the lane's number, through an instruction that the compiler does not see through: nothing that is computed from it can be
+// made ahead of it and kept in registers
+__device__ __forceinline__ int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32); }
 
 // 16 bytes per lane from a raw buffer straight into LDS (buffer_load_dwordx4 ... lds): lane i's
@@ -133,10 +141,49 @@ __device__ __forceinline__ int unit_count(const int32_t* __restrict__ kv_cnt, in
   return pair ? max(c[2 * I], c[min(2 * I + 1, nb - 1)]) : c[I];
 }
 
-// Below: nu = units (rows, or pairs of rows) per head.
+// Whether a large sparse launch of blocks of 128 takes them two to a workgroup (DUO) or one by one: known on the card only,
+// because it depends on the lists.  Both kernels are launched and one of them finds nothing to do (two microseconds).
+// Pairs are worth it where a row has tiles enough to make up for the start of a pair, which nothing runs beside, and the
+// lists of neighbours are of one length, or else they are taken one after the other.  16 heads, one by one / in pairs (ms),
+// 344 blocks, nine tenths kept in lists of one length 5.69 / 5.58, half 3.20 / 3.21, a quarter 1.64 / 1.68, lengths uniform
+// 3.49 / 3.73; 1,074 blocks 55.3 / 53.1, 30.8 / 30.2, 15.6 / 15.5, 33.3 / 35.2.
+__global__ __launch_bounds__(1024) void choose_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nbk, int heads, int per_tile,
+                                                      int32_t* __restrict__ choice) {
+  __shared__ long long sum[2];
+  const int t = threadIdx.x;
+  if (t < 2) sum[t] = 0;
+  __syncthreads();
+  long long all = 0, apart = 0;
+  const int nu = (nb + 1) >> 1;
+  for (int64_t u = t; u < int64_t(heads) * nu; u += 1024) {
+    const int64_t h = u / nu;
+    const int i = 2 * static_cast<int>(u - h * nu);
+    const int a = min(max(kv_cnt[h * nb + i], 0), nbk), b = i + 1 < nb ? min(max(kv_cnt[h * nb + i + 1], 0), nbk) : a;
+    all += a + b;
+    apart += abs(a - b);
+  }
+  for (int o = 1; o < 64; o <<= 1) {
+    all += __shfl_xor(all, o);
+    apart += __shfl_xor(apart, o);
+  }
+  if ((t & 63) == 0) {
+    atomicAdd(reinterpret_cast<unsigned long long*>(&sum[0]), static_cast<unsigned long long>(all));
+    atomicAdd(reinterpret_cast<unsigned long long*>(&sum[1]), static_cast<unsigned long long>(apart));
+  }
+  __syncthreads();
+  if (t == 0) *choice = sum[0] >= 200ll * per_tile * heads * nb && 8 * sum[1] <= sum[0];
+}
+
+// Below: nu = units (rows, or pairs of rows) per head; `choice` (or null): where choose_kernel has left which of the two.
+__device__ __forceinline__ void read_choice(const int32_t* choice, int nb, int& nu, bool& pair) {
+  if (choice == nullptr) return;
+  pair = *choice != 0;
+  nu = pair ? (nb + 1) >> 1 : nb;
+}
 __global__ __launch_bounds__(256) void order_hist_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, int32_t* __restrict__ table) {
+                                                         int heads, const int32_t* choice, int32_t* __restrict__ table) {
   __shared__ int bins[kOrderClasses];
+  read_choice(choice, nb, nu, pair);
   const int h = blockIdx.x;
   const int t = threadIdx.x;
   if (t < kOrderClasses) bins[t] = 0;
@@ -220,8 +267,9 @@ __global__ __launch_bounds__(1024) void order_scan_kernel(int32_t* __restrict__ 
 }
 
 __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu,
-                                                          bool pair, int nbk, int heads, const int32_t* __restrict__ table,
-                                                          int32_t* __restrict__ order) {
+                                                          bool pair, int nbk, int heads, const int32_t* choice,
+                                                          const int32_t* __restrict__ table, int32_t* __restrict__ order) {
+  read_choice(choice, nb, nu, pair);
   __shared__ int next[kOrderClasses];
   __shared__ int wave_bulk[4];
   const int h = blockIdx.x;
@@ -256,7 +304,9 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
 // of a thread are consecutive, so the bulk class keeps its order.
 constexpr int kOrderOneMax = 8192;
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
+                                                         int heads, const int32_t* choice, int32_t* __restrict__ order,
+                                                         int32_t* __restrict__ next_row) {
+  read_choice(choice, nb, nu, pair);
   constexpr int MAX = kOrderOneMax / 1024;
   __shared__ int total[kOrderClasses], next[kOrderClasses];
   __shared__ int c_bulk_s, wave_bulk[16];
@@ -438,34 +488,49 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 //
 // SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
 // waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
+//
+// DUO: eight waves, one workgroup to a CU, take two neighbouring blocks of 128 rows (four waves to each, as above).  Large
+// launches are bound by energy (the part lowers its clock), and moving the tiles costs a twentieth of it.  Tiles that both
+// rows need are loaded once for all eight waves, which halves the L2 -> LDS traffic: dense, 16 heads x 137,400 tokens 60.8 ->
+// 58.0 ms, 43,968 6.31 -> 6.10.  The lists are sorted into common and own blocks as for PAIR (below a kept fraction of 0.3
+// they stay as they are); own tiles follow, each group of four waves on its own, but with barriers for all eight.  That is no
+// slower than two separate workgroups (dense without any sharing 60.8 -> 59.5: the groups stay in step, so what one loads the other
+// finds in the L1); four buffers and a barrier for two tiles are (58.0 -> 58.8).
+// A pair whose lists differ in length is taken row by row (`deal`), a row's tiles dealt to the two groups in turn.
+// Nothing runs beside the start and the end of a pair, 13 us: Q is loaded while the lists are sorted, the first own tiles
+// under the common ones, and every wave finishes 32 rows.
 enum { kDone = -1, kByOne = -2 };  // what a workgroup of a pair has left to do
-template <int B, int KB, bool STREAM, bool PAIR, bool SOLO>
-__global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
+template <int B, int KB, bool STREAM, bool PAIR, bool SOLO, bool DUO>
+__global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
     const int32_t* __restrict__ kv_cnt, const int32_t* __restrict__ order, int idx_stride, int64_t n_tokens, int nb,
     int nbk, float scale_log2, Segments seg, int heads, int64_t n_static, int64_t n_pairs, int* __restrict__ next_row,
-    StreamTable* __restrict__ tab) {
+    const int32_t* choice, StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
   static_assert(!PAIR || (B == 128 && KB == 64 && !STREAM), "pairs of blocks of 64");
   static_assert(PAIR || !SOLO, "one block instead of a pair");
+  static_assert(!DUO || (B == 128 && !STREAM && !PAIR), "pairs of blocks of 128");
+  constexpr int NT = DUO ? 512 : 2 * B;   // threads
   constexpr int QB = PAIR ? 64 : B;       // query block size
   constexpr bool HALF = KB != B;          // two listed key blocks per tile
   constexpr int WQ = B / 64;              // waves along queries (64 rows each)
   constexpr int KW = B / 2;               // keys per wave per tile
   constexpr int NH = KW / 32;             // 32-key sub-tiles per wave per tile
-  constexpr int NW = B / 32;              // waves per workgroup
+  constexpr int NW = B / 32;              // waves that share a tile (DUO: of one of the two blocks)
   constexpr int TILE_BYTES = B * 128;     // one K or V tile
-  constexpr int V_BASE = 2 * TILE_BYTES;  // LDS layout: K buffers 0, 1, then V buffers 0, 1
+  // LDS layout: K buffers 0, 1, then V buffers 0, 1.  DUO: four buffer pairs, each K then V, see take_part.
+  constexpr int V_BASE = DUO ? TILE_BYTES : 2 * TILE_BYTES;
+  constexpr int BUF_BYTES = DUO ? 2 * TILE_BYTES : TILE_BYTES;  // from one buffer of a tensor to the other
   extern __shared__ __align__(16) unsigned char smem[];
+  if (choice != nullptr && (*choice != 0) != DUO) return;  // see choose_kernel
 
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const int n = lane & 31;
-  const int g = lane >> 5;
-  const int qi = wave % WQ;
-  const int kh = wave / WQ;
+  const int tid0 = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+  const int gw = DUO ? wave & 3 : wave;  // number of the wave among those of its block ...
+  const int gb = DUO ? wave >> 2 : 0;    // ... and which of the two blocks that is
+  const int qi = gw % WQ;
+  const int kh = gw / WQ;
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
   // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, in a SOLO launch or as
@@ -473,13 +538,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // A pair: listed >= 0 means block `listed` of the two alone.  Returns kDone, or, with nothing done, kByOne if the row
   // or rows are to be run by ONE, or the length of the list that it has sorted into LDS for one row.
   // (Everything up to the dispatch at the end; not indented.)
-  auto run = [&](auto onec, int64_t row, int tile0, int tile1, int w0, int w1, int me, int listed) -> int {
+  // DUO: `deal` means block `row` alone, its tiles dealt to the two groups of waves in turn.
+  auto run = [&](auto onec, int64_t row, int tile0, int tile1, int w0, int w1, int me, int listed, bool deal) -> int {
+  const int lane = DUO ? fresh_lane() : tid0 & 63;  // fresh: what follows from the lane is not kept from call to call
+  const int tid = DUO ? wave * 64 + lane : tid0;
+  const int n = lane & 31;
+  const int g = lane >> 5;
   constexpr bool ONE = decltype(onec)::value;
   constexpr bool TWO = PAIR && !ONE;              // two blocks with a list each
-  const int units = TWO ? (nb + 1) >> 1 : nb;     // rows, or pairs of rows, per head
+  const int units = TWO || (DUO && !deal) ? (nb + 1) >> 1 : nb;  // rows, or pairs of rows, per head
   const int h = static_cast<int>(min(max(row / units, int64_t(0)), int64_t(heads - 1)));
   const int u_in_head = static_cast<int>(min(max(row - int64_t(h) * units, int64_t(0)), int64_t(units - 1)));
-  const int I = TWO ? min(2 * u_in_head + qi, nb - 1) : u_in_head;  // this wave's query block
+  const int I = TWO ? min(2 * u_in_head + qi, nb - 1) : DUO && !deal ? min(2 * u_in_head + gb, nb - 1) : u_in_head;  // this wave's query block
   const bool no_block = TWO && 2 * u_in_head + qi >= nb;            // the last pair of a head may be one block
   const int64_t head_bytes = int64_t(h) * n_tokens * 128;
   const int64_t rowid = int64_t(h) * nb + I;
@@ -496,25 +566,17 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) unsigned char*)smem));
 
   // ---- Q fragments (B operand of S^T = K Q^T), pre-scaled: [query half][16-dim chunk]; lane (n, g)
-  // holds dims 16c + 8g .. +7 of query row 32 b + n of the wave's 64
-  bf16x8 qf[2][4];
+  // holds dims 16c + 8g .. +7 of query row 32 b + n of the wave's 64 (rows past q_valid are computed, not stored).
+  // A row with lists to sort asks for them first, so that both are on their way together.
+  u32x4 q_raw[2][4];
+  auto load_q = [&]() {
 #pragma unroll
-  for (int b2 = 0; b2 < 2; ++b2) {
-    const int64_t row = int64_t(q_start) + q_off + b2 * 32 + n;  // rows past q_valid are computed, not stored
+    for (int b2 = 0; b2 < 2; ++b2) {
+      const int64_t row = min(int64_t(q_start) + q_off + b2 * 32 + n, n_tokens - 1);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      u32x4 x = {0u, 0u, 0u, 0u};
-      if (row < n_tokens) x = *reinterpret_cast<const u32x4*>(q + head_bytes + row * 128 + (2 * c + g) * 16);
-      u32x4 y;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float lo = __uint_as_float(x[e] << 16) * scale_log2;
-        const float hi = __uint_as_float(x[e] & 0xffff0000u) * scale_log2;
-        y[e] = pack_bf16(lo, hi);
-      }
-      qf[b2][c] = __builtin_bit_cast(bf16x8, y);
+      for (int c = 0; c < 4; ++c) q_raw[b2][c] = *reinterpret_cast<const u32x4*>(q + head_bytes + row * 128 + (2 * c + g) * 16);
     }
-  }
+  };
 
   // ---- per-lane constants -------------------------------------------------------------------------
   // direct-to-LDS loads: wave-load j covers LDS bytes [1024 j, 1024 j + 1024) of a tile; this wave
@@ -524,7 +586,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // swz_v(r_0): the K offsets repeat with period KN in i up to a multiple of 1024 NW (which goes
   // into the wave-uniform offset), the V offsets differ by that multiple only.
   constexpr int KN = (B == 128) ? 2 : 4;
-  const int dma_r0 = wave * 8 + (lane >> 3);
+  const int dma_r0 = gw * 8 + (lane >> 3);
   const int dma_pc = lane & 7;
   unsigned koff[KN];
 #pragma unroll
@@ -564,14 +626,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   const int count_row = no_block ? 0 : dense ? nbk : min(max(kv_cnt[rowid], 0), nbk);  // listed key blocks of the row
   // PAIR: blocks in both lists, then those of the first alone, at list[0 ..); those of the second alone at
   // list[nbk ..)
-  unsigned short* const list = reinterpret_cast<unsigned short*>(smem + 4 * TILE_BYTES);
+  unsigned short* const list = reinterpret_cast<unsigned short*>(smem + (DUO ? 2 : 1) * 4 * TILE_BYTES);
   int n_both = 0, n_alone[2] = {0, 0};
+  constexpr bool LATE_Q = PAIR || DUO;
+  if constexpr (!LATE_Q) load_q();
   if constexpr (ONE) {
     const int n_list = listed >= 0 ? listed : count_row;
+    if (listed >= 0) load_q();
     if (listed < 0) {
       const int32_t* const idx0 = kv_idx + rowid * idx_stride;
       int j = idx0[min(tid, nbk - 1)];  // in one round of loads with the count, see below
-      for (int e = tid; e < count_row; e += 2 * B) {
+      load_q();
+      for (int e = tid; e < count_row; e += NT) {
         if (e != tid) j = idx0[e];
         list[(e & 1) * nbk + (e >> 1)] = static_cast<unsigned short>(min(max(j, 0), nbk - 1));
       }
@@ -579,25 +645,38 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     n_alone[0] = (n_list + 1) >> 1;
     n_alone[1] = n_list >> 1;
     __syncthreads();
-  } else if constexpr (PAIR) {
-    unsigned* const bits = reinterpret_cast<unsigned*>(smem);             // two bit sets of kPairMaxBlocks
-    unsigned long long* const part = reinterpret_cast<unsigned long long*>(smem + 1024);  // per wave
-    constexpr int WORDS = kPairMaxBlocks / 32;
+  } else if (DUO && dense) {
+    load_q();
+    n_both = nbk;  // also for the last pair of a head if it is one block: dense rows come out the same whatever their place
+  } else if (DUO && deal) {
+    const int32_t* const idx0 = kv_idx + rowid * idx_stride;
+    int j = idx0[min(tid, nbk - 1)];
+    load_q();
+    for (int e = tid; e < count_row; e += NT) {
+      if (e != tid) j = idx0[e];
+      list[(e & 1) * nbk + (e >> 1)] = static_cast<unsigned short>(min(max(j, 0), nbk - 1));
+    }
+    n_alone[0] = (count_row + 1) >> 1;
+    n_alone[1] = count_row >> 1;
+    __syncthreads();
+  } else if constexpr (PAIR || DUO) {
+    unsigned char* const named = smem;  // per key block: in which of the two lists it is, kPairMaxBlocks each
+    unsigned* const part = reinterpret_cast<unsigned*>(smem + 2 * kPairMaxBlocks);  // per 64 key blocks: two words of counts
     // counts and the first 256 entries of both lists in one round of loads: entries past a count are
     // whatever the buffer holds (idx_stride >= nbk) and are not used
     const int64_t id0 = int64_t(h) * nb + 2 * u_in_head + max(listed, 0);
     const bool two = listed < 0 && 2 * u_in_head + 1 < nb;
     const int32_t* const idx0 = kv_idx + id0 * idx_stride;
     const int32_t* const idx1 = two ? idx0 + idx_stride : idx0;
+    if (DUO && !two) return kByOne;
     const int c0 = kv_cnt[id0], c1 = kv_cnt[two ? id0 + 1 : id0];
     int j0 = idx0[min(tid, nbk - 1)], j1 = idx1[min(tid, nbk - 1)];
+    load_q();
     const int n0 = min(max(c0, 0), nbk), n1 = two ? min(max(c1, 0), nbk) : 0;
-    auto enter = [&](int r, int J) {
-      const int j = min(max(J, 0), nbk - 1);
-      atomicOr(&bits[r * WORDS + (j >> 5)], 1u << (j & 31));
-    };
+    auto enter = [&](int r, int J) { named[r * kPairMaxBlocks + min(max(J, 0), nbk - 1)] = 1; };
     auto uneven = [&](int both, int alone0, int alone1) {
-      return __builtin_amdgcn_readfirstlane(abs(alone0 - alone1) > both + 12) != 0;
+      // DUO: what idles is half the difference, what another row costs 13 us (8 tiles) and the common tiles unshared (3 %)
+      return __builtin_amdgcn_readfirstlane(abs(alone0 - alone1) > (DUO ? 16 + (both >> 4) : both + 12)) != 0;
     };
     if (10 * (n0 + n1) < 6 * nbk) {
       if (!two || uneven(0, n0, n1)) return kByOne;
@@ -608,27 +687,45 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         if (e < n1) list[nbk + e] = static_cast<unsigned short>(min(max(a1, 0), nbk - 1));
       };
       put(tid, j0, j1);
-      for (int e = tid + 2 * B; e < max(n0, n1); e += 2 * B) put(e, idx0[e], idx1[e]);
+      for (int e = tid + NT; e < max(n0, n1); e += NT) put(e, idx0[e], idx1[e]);
       n_alone[0] = n0;
       n_alone[1] = n1;
       __syncthreads();
     } else {
-      bits[tid] = 0u;  // 256 threads, 2 x 128 words
+      // A wave takes 64 key blocks at a time: two votes tell which list names them, and their counts, summed up over the
+      // pieces before, where they go.  (One thread per 32 blocks, bit sets filled with atomics: 2 us more per pair.)
+      const int pieces = (nbk + 63) >> 6;
+      for (int i = tid; i < pieces * 4; i += NT) {
+        reinterpret_cast<u32x4*>(named)[i] = u32x4{0u, 0u, 0u, 0u};
+        reinterpret_cast<u32x4*>(named + kPairMaxBlocks)[i] = u32x4{0u, 0u, 0u, 0u};
+      }
       __syncthreads();
       if (tid < n0) enter(0, j0);
       if (tid < n1) enter(1, j1);
-      for (int e = tid + 2 * B; e < max(n0, n1); e += 2 * B) {
+      for (int e = tid + NT; e < max(n0, n1); e += NT) {
         j0 = idx0[e];
         j1 = idx1[e];
         if (e < n0) enter(0, j0);
         if (e < n1) enter(1, j1);
       }
       __syncthreads();
-      const unsigned b0 = tid < WORDS ? bits[tid] : 0u, b1 = tid < WORDS ? bits[WORDS + tid] : 0u;
-      unsigned set[3] = {b0 & b1, b0 & ~b1, b1 & ~b0};
-      // the three counts (each at most 4096) in two words, summed over the lanes up to this one
-      const unsigned mine_lo = __popc(set[0]) | (__popc(set[1]) << 16), mine_hi = __popc(set[2]);
-      unsigned lo = mine_lo, hi = mine_hi;
+      auto votes = [&](int piece, unsigned long long (&set)[3]) {
+        const unsigned long long b0 = __ballot(named[piece * 64 + lane] != 0), b1 = __ballot(named[kPairMaxBlocks + piece * 64 + lane] != 0);
+        set[0] = b0 & b1;
+        set[1] = b0 & ~b1;
+        set[2] = b1 & ~b0;
+      };
+      unsigned long long set[3];
+      for (int p = wave; p < pieces; p += NT / 64) {
+        votes(p, set);
+        if (lane == 0) {
+          part[2 * p] = __popcll(set[0]) | (__popcll(set[1]) << 16);
+          part[2 * p + 1] = __popcll(set[2]);
+        }
+      }
+      __syncthreads();
+      // the three counts (each at most 4096) in two words, summed over the pieces up to this lane's
+      unsigned lo = lane < pieces ? part[2 * lane] : 0u, hi = lane < pieces ? part[2 * lane + 1] : 0u;
       auto add_from = [&](auto ctrl, auto rows) {  // adds the value of the lane that the DPP control names, 0 if there is none
         constexpr int C = decltype(ctrl)::value, R = decltype(rows)::value;
         lo += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), C, R, 0xf, false));
@@ -640,32 +737,41 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       add_from(Int<0x118>{}, Int<0xf>{});
       add_from(Int<0x142>{}, Int<0xa>{});  // last lane of rows 0 and 2 into rows 1 and 3
       add_from(Int<0x143>{}, Int<0xc>{});  // lane 31 into rows 2 and 3
-      if (lane == 63) part[wave] = (static_cast<unsigned long long>(hi) << 32) | lo;
-      __syncthreads();
-      const unsigned long long in0 = part[0], all = in0 + part[1];  // words 0..127: the first two waves
-      lo -= mine_lo;
-      hi -= mine_hi;
-      if (wave == 1) {
-        lo += static_cast<unsigned>(in0);
-        hi += static_cast<unsigned>(in0 >> 32);
-      }
-      n_both = __builtin_amdgcn_readfirstlane(static_cast<int>(all & 0xffff));
-      n_alone[0] = __builtin_amdgcn_readfirstlane(static_cast<int>((all >> 16) & 0xffff));
-      n_alone[1] = __builtin_amdgcn_readfirstlane(static_cast<int>(all >> 32));
+      const unsigned all = __builtin_amdgcn_readlane(lo, 63);
+      n_both = static_cast<int>(all & 0xffff);
+      n_alone[0] = static_cast<int>(all >> 16);
+      n_alone[1] = static_cast<int>(__builtin_amdgcn_readlane(hi, 63));
       if (two && uneven(n_both, n_alone[0], n_alone[1])) return kByOne;
-      const int before[3] = {static_cast<int>(lo & 0xffff), static_cast<int>(lo >> 16), static_cast<int>(hi)};
       const int at[3] = {0, n_both, nbk};
+      for (int p = wave; p < pieces; p += NT / 64) {
+        votes(p, set);
+        const unsigned before_lo = p > 0 ? __builtin_amdgcn_readlane(lo, p - 1) : 0u, before_hi = p > 0 ? __builtin_amdgcn_readlane(hi, p - 1) : 0u;
+        const int before[3] = {static_cast<int>(before_lo & 0xffff), static_cast<int>(before_lo >> 16), static_cast<int>(before_hi)};
 #pragma unroll
-      for (int x = 0; x < 3; ++x) {
-        int pos = at[x] + before[x];
-        for (unsigned b = set[x]; b != 0u; b &= b - 1u, ++pos)
-          list[two ? pos : (pos & 1) * nbk + (pos >> 1)] = static_cast<unsigned short>(tid * 32 + __ffs(b) - 1);
+        for (int x = 0; x < 3; ++x) {
+          const int pos = __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(set[x] >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(set[x]), at[x] + before[x]));
+          if ((set[x] >> lane) & 1) list[two ? pos : (pos & 1) * nbk + (pos >> 1)] = static_cast<unsigned short>(p * 64 + lane);
+        }
       }
-      __syncthreads();  // the lists are complete; the tiles may overwrite the bit sets
+      __syncthreads();  // the lists are complete; the tiles may overwrite the rest
       if (!two) return n_alone[0];
     }
   }
-  int count = PAIR ? n_both : count_row;                        // of them, those of the tiles this workgroup takes,
+  bf16x8 qf[2][4];
+#pragma unroll
+  for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      u32x4 y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lo = __uint_as_float(q_raw[b2][c][e] << 16) * scale_log2;
+        const float hi = __uint_as_float(q_raw[b2][c][e] & 0xffff0000u) * scale_log2;
+        y[e] = pack_bf16(lo, hi);
+      }
+      qf[b2][c] = __builtin_bit_cast(bf16x8, y);
+    }
+  int count = PAIR || DUO ? n_both : count_row;  // of them, those of the tiles this workgroup takes,
   int ntiles = HALF ? (count + 1) >> 1 : count;  // the number of these tiles
   int first = 0;                                // and the first one
   auto take_tiles = [&](int t0, int t1) {
@@ -674,6 +780,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     count = min(count_row - t0 * PER, ntiles * PER);
   };
   if constexpr (STREAM) take_tiles(tile0, tile1);
+  int lbase = 0;  // DUO: where in `list` these are
+  // DUO: on to the blocks in both lists, or to those of this wave's block alone.  Buffer pairs in the LDS, 32 KB each:
+  //   first block's own tile 0 | shared tile 0, first block's own tile 1 | shared tile 1, second block's own tile 1 | its own tile 0
+  // so the first of the own tiles can be loaded before the shared ones are through.  Of two neighbouring pairs, `flip` says
+  // whether even tiles go to the upper.
+  int flip = 0;
+  auto take_part = [&](bool both) {
+    count = both ? n_both : gb ? n_alone[1] : n_alone[0];
+    ntiles = HALF ? (count + 1) >> 1 : count;
+    lbase = both ? 0 : gb ? nbk : n_both;
+    flip = both ? 0 : gb;
+  };
   // key block J: first token and number of tokens.  Blocks of the first segment (J < nbk1) tile
   // tokens [0, n_first), the others tokens [n_first, n_tokens); the last block of each may be ragged.
   auto key_start = [&](int J) { return J < seg.nbk1 ? J * KB : seg.n_first + (J - seg.nbk1) * KB; };
@@ -691,6 +809,12 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     if constexpr (PAIR) {
       const int e = min(it, ntiles - 1) * 2;
       return Tile{list[e], list[min(e + 1, count - 1)], 0u, 0u};
+    } else if constexpr (DUO) {
+      if (dense) return Tile{min(it, nbk - 1), -1, 0u, 0u};
+      const int e = min(it, ntiles - 1) * PER;
+      Tile t{list[lbase + e], -1, 0u, 0u};
+      if constexpr (HALF) t.b = list[lbase + min(e + 1, count - 1)];
+      return t;
     } else if constexpr (STREAM) {
       if (dense) return Tile{min(first + it, nbk - 1), -1, 0u, 0u};
       const int e = first * PER + min(it, ntiles - 1) * PER;
@@ -709,9 +833,9 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // the loads then zero-fills it.
   auto fix = [&](const Tile& r, int it) -> Tile {  // r = raw_at(it)
     Tile t{r.a, -1, 0u, head_size};
-    if constexpr (PAIR) {
+    if constexpr (PAIR || DUO) {  // dense too: uniform already
       t.a = __builtin_amdgcn_readfirstlane(r.a);
-      if (min(it, ntiles - 1) * 2 + 1 < count) t.b = __builtin_amdgcn_readfirstlane(r.b);
+      if (HALF && min(it, ntiles - 1) * 2 + 1 < count) t.b = __builtin_amdgcn_readfirstlane(r.b);
     } else if (!dense) {
       t.a = min(max(r.a, 0), nbk - 1);
       if constexpr (HALF) {
@@ -747,8 +871,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // tiles only; the lane number is taken afresh through an opaque instruction, so that nothing of
   // this is computed ahead and kept in registers across the tile loops.
   auto mask_keys = [&](f32x16& sc, int row0, int limit) {  // row0: tile row of the sub-tile's first key
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    const int l = fresh_lane();
     const int t = limit - row0 - ((l >> 5) << 2);  // row 8(i/4) + i%4 is masked iff it is >= t
 #pragma unroll
     for (int i = 0; i < 16; ++i) sc[i] = (8 * (i >> 2) + (i & 3) >= t) ? -INFINITY : sc[i];
@@ -769,12 +892,23 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // are finite; rows past a ragged block inside the sequence hold the following tokens).
   // With half-tile key blocks, loads i = 0, 1 fill tile rows 0..63 from block a and i = 2, 3 rows
   // 64..127 from block b (an absent b: zero-filled, see fix()).
-  const unsigned dma_base = smem_addr + wave * 1024;  // this wave's 1 KB slice of every 4 KB (8 KB) group
-  auto issue_part = [&](const Tile& J, auto bufc, auto i2c) {
+  // `both` (DUO): the eight waves load the tile together, four parts each: wave-load j = wave + 8 i, of which rows r_0 + 64 i.
+  const unsigned dma_base = smem_addr + gw * 1024 + (DUO ? gb * 2 * BUF_BYTES : 0);  // this wave's 1 KB slice of every 4 KB (2 KB) group
+  auto issue_part = [&](auto bothc, const Tile& J, auto bufc, auto i2c) {
     constexpr int buf = decltype(bufc)::value, i2 = decltype(i2c)::value;
+    if constexpr (decltype(bothc)::value) {
+      constexpr int i = i2 >> 1;
+      if constexpr (i < 2) {
+        constexpr unsigned dst = 2 * NW * i * 1024 + ((i2 & 1) ? V_BASE : 0) + buf * BUF_BYTES;
+        const unsigned at = smem_addr + BUF_BYTES + wave * 1024, soff = HALF && i ? J.ob : J.oa + (HALF ? 0 : i * 2 * NW * 1024);
+        if ((i2 & 1) != 0) dma16<dst>(vrsrc, voff + gb * 4096, soff, at);
+        else dma16<dst>(krsrc, gb ? koff[1 % KN] : koff[0], soff, at);
+      }
+      return;
+    } else {
     constexpr int i = i2 >> 1;
     constexpr bool is_v = (i2 & 1) != 0;
-    constexpr unsigned dst = NW * i * 1024 + (is_v ? V_BASE : 0) + buf * TILE_BYTES;
+    constexpr unsigned dst = NW * i * 1024 + (is_v ? V_BASE : 0) + buf * BUF_BYTES;
     if constexpr (HALF) {
       const unsigned soff = (i >> 1) ? J.ob : J.oa;
       if (is_v) {
@@ -790,14 +924,15 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         dma16<dst>(krsrc, koff[i % KN], soff + (i / KN) * KN * NW * 1024, dma_base);
       }
     }
+    }
   };
-  auto issue = [&](const Tile& J, auto bufc) {
-    issue_part(J, bufc, Int<0>{}); issue_part(J, bufc, Int<1>{}); issue_part(J, bufc, Int<2>{}); issue_part(J, bufc, Int<3>{});
-    issue_part(J, bufc, Int<4>{}); issue_part(J, bufc, Int<5>{}); issue_part(J, bufc, Int<6>{}); issue_part(J, bufc, Int<7>{});
+  auto issue = [&](auto both, const Tile& J, auto bufc) {
+    issue_part(both, J, bufc, Int<0>{}); issue_part(both, J, bufc, Int<1>{}); issue_part(both, J, bufc, Int<2>{}); issue_part(both, J, bufc, Int<3>{});
+    issue_part(both, J, bufc, Int<4>{}); issue_part(both, J, bufc, Int<5>{}); issue_part(both, J, bufc, Int<6>{}); issue_part(both, J, bufc, Int<7>{});
   };
-  auto issue_rt = [&](const Tile& J, int buf) {  // buffer known at run time only
-    if (buf) issue(J, Int<1>{});
-    else issue(J, Int<0>{});
+  auto issue_rt = [&](auto both, const Tile& J, int buf) {  // buffer known at run time only
+    if (buf) issue(both, J, Int<1>{});
+    else issue(both, J, Int<0>{});
   };
 
   // K operands (A of S^T = K Q^T) of the wave's 32-key sub-tile u; boff = byte offset of the buffer
@@ -911,24 +1046,29 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 
   // Plain tile loop: compute_tile per tile, one barrier per tile, the next tile's loads in flight
   // meanwhile.  Used for the SAFE pass and by workgroups of one block of 64 rows and two waves.
-  auto plain_loop = [&](auto safec) {
-    if (ntiles <= 0) return;
-    Tile J_cur = block_at(0);
-    issue(J_cur, Int<0>{});
+  // DUO: `steps` tiles take the workgroup's barriers, ntiles of them (or none) are this wave's.
+  auto plain_loop = [&](auto safec, auto both, int steps) {
+    if (steps <= 0) return;
+    Tile J_cur{0, -1, 0u, 0u};
+    if (!DUO || ntiles > 0) {
+      J_cur = block_at(0);
+      if (!DUO || decltype(both)::value) issue(both, scalar(J_cur), Int<0>{});
+    }
     Tile J_pre = raw_at(1);  // list entries are fetched a tile before they are used
     bf16x8 ka[4], va[2][2];
     f32x16 sc[2];
     u32x4 w[2][2];
-    for (int it = 0; it < ntiles; ++it) {
-      const int buf = it & 1;
+    for (int it = 0; it < steps; ++it) {
+      const int buf = (it + flip) & 1;
       const Tile J_next = (it + 1 < ntiles) ? fix(J_pre, it + 1) : Tile{0, -1, 0u, 0u};
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of tile `it` has landed
       __syncthreads();                     // ... and so has everyone else's; buffer buf^1 is free
-      if (it + 1 < ntiles) issue_rt(scalar(J_next), buf ^ 1);
+      if (DUO && it >= ntiles) continue;
+      if (it + 1 < ntiles) issue_rt(both, scalar(J_next), buf ^ 1);
       // The list entries of the tile after next.  Scalar loads return out of order with LDS reads, so
       // a wait for LDS data would also wait for them: they are issued where every LDS read of the
       // tile has been consumed, and used at the top of the next tile.
-      compute_tile(safec, buf * TILE_BYTES, wave_limit(J_cur), [&]() { J_pre = raw_at(it + 2); }, ka, va, sc, w);
+      compute_tile(safec, buf * BUF_BYTES, wave_limit(J_cur), [&]() { J_pre = raw_at(it + 2); }, ka, va, sc, w);
       J_cur = J_next;
     }
   };
@@ -941,8 +1081,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     const int row0 = qi * 64 + kh * 32;
     unsigned kat[4], vat[2];
     {
-      int l;  // taken afresh, so that the addresses are not kept in registers across the other loop
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+      const int l = fresh_lane();  // so that the addresses are not kept in registers across the other loop
       const int r = row0 + (l & 31);
 #pragma unroll
       for (int c = 0; c < 4; ++c) kat[c] = r * 128 + (((2 * c + (l >> 5)) ^ swz_k(r)) << 4);
@@ -962,7 +1101,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       return t;
     };
     Tile cur = made(raw(0), 0);
-    issue(scalar(cur), Int<0>{});
+    issue(std::false_type{}, scalar(cur), Int<0>{});
     Tile pre = raw(1);
     bf16x8 ka[4], va[2][2];
     f32x16 sc[2];
@@ -971,7 +1110,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
       const Tile nxt = made(pre, it + 1);
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of tile `it` has landed
       __syncthreads();                     // ... and so has everyone else's; the other buffer is free
-      if (it + 1 < steps) issue_rt(scalar(nxt), (it & 1) ^ 1);
+      if (it + 1 < steps) issue_rt(std::false_type{}, scalar(nxt), (it & 1) ^ 1);
       pre = raw(it + 2);
       const int J = qi ? cur.b : cur.a;
       const int limit = qi * 64 + (J < 0 ? 0 : key_count(J));
@@ -999,8 +1138,9 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   // lists that is the row's last tile, or, for a split sequence with the short first segment's
   // blocks listed last but a few, the last few tiles.  Either way a tile costs every wave exactly
   // one barrier, and the loads stay two tiles ahead.
-  auto fast_loop = [&]() {
-    if (ntiles <= 0) return;
+  auto fast_loop = [&](auto both, int steps) {  // as plain_loop
+    constexpr bool BOTH = decltype(both)::value;
+    if (steps <= 0) return;
     f32x16 sc[2];        // scores: [query half]
     u32x4 pw[2][2];      // weights as packed bf16 pairs: [query half][16-key chunk]
     bf16x8 ka[4];        // K operands of the sub-tile whose scores are computed next
@@ -1086,14 +1226,14 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
 #undef BSGA_SLOT
     };
 
-    // a whole (full) tile in buffer pair `buf` (byte offset boff; the other pair is at boff ^ TILE_BYTES).
+    // a whole (full) tile in buffer pair `buf` (byte offset boff; the other pair is at boff ^ BUF_BYTES).
     // On entry: sc[0] = QK(0) of this tile, ka = K operands of sub-tile 0, pw[1] / va[1] = weights /
     // V operands of the previous tile's unit 3 (zeros at the start of a run).  What it prepares for
     // the following tile (K operands and first scores from the other buffer) goes unused when the run
     // ends here.
     auto tile = [&](const Tile& J_next2, auto bufc) {
       constexpr int buf = decltype(bufc)::value;
-      constexpr unsigned boff = buf * TILE_BYTES;
+      constexpr unsigned boff = buf * BUF_BYTES;
       unit(Int<0>{}, [&](auto slot) {  // QK(1); K(u1); PV(previous 3); V(u0)
         constexpr int S = decltype(slot)::value;
         if constexpr (S == 0) read_v(va[0], boff, 0);
@@ -1109,22 +1249,26 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
           __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the next tile has landed
           __syncthreads();                     // every read of this tile is complete in every wave
         }
-        if constexpr (S == 3) read_k(ka, boff ^ TILE_BYTES, 0);
-        if constexpr (S >= 4) issue_part(J_next2, bufc, Int<S - 4>{});
+        if constexpr (S == 3) read_k(ka, boff ^ BUF_BYTES, 0);
+        if constexpr (S >= 4) issue_part(both, J_next2, bufc, Int<S - 4>{});
       });
       unit(Int<3>{}, [&](auto slot) {  // QK(next tile's unit 0); PV(2) + loads 4..7
         constexpr int S = decltype(slot)::value;
-        if constexpr (S >= 4) issue_part(J_next2, bufc, slot);
+        if constexpr (S >= 4 && !BOTH) issue_part(both, J_next2, bufc, slot);
       });
     };
 
     // ---- tiles 0 and 1 on their way ----------------------------------------------------------------
-    Tile J_cur = block_at(0);
-    issue(J_cur, Int<0>{});
+    Tile J_cur{0, -1, 0u, 0u};
+    if (!DUO || ntiles > 0) {
+      J_cur = block_at(0);
+      if (!DUO || BOTH) issue(both, scalar(J_cur), Int<0>{});  // own tiles of DUO: under way already
+    }
     Tile J_nxt = J_cur;
     if (ntiles > 1) {
       J_nxt = block_at(1);
-      issue(J_nxt, Int<1>{});
+      if constexpr (DUO && !BOTH) issue_rt(both, scalar(J_nxt), flip ^ 1);
+      else issue(both, scalar(J_nxt), Int<1>{});
     }
     Tile J_pre = raw_at(2);  // fetched one tile before it becomes "the tile after next"
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -1133,9 +1277,10 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     // of tile T+1 into the other buffer have been issued; J_cur / J_nxt are tiles T / T+1 and J_pre
     // holds the raw list entries of tile T+2.
     int T = 0;
-    if (!tile_ragged(J_cur)) {
+    if ((!DUO || ntiles > 0) && !tile_ragged(J_cur)) {
       // ---- the run of full tiles: K operands of sub-tile 0, QK(0), nothing pending for the O update --
-      read_k(ka, 0u, 0);
+      if (DUO && flip) read_k(ka, BUF_BYTES, 0);
+      else read_k(ka, 0u, 0);
 #pragma unroll
       for (int cp = 0; cp < 2; ++cp) {
         pw[1][cp] = u32x4{0u, 0u, 0u, 0u};
@@ -1163,8 +1308,11 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         ++T;
         return T < ntiles && !tile_ragged(J_cur);
       };
-      while (step(Int<0>{}) && step(Int<1>{})) {
-      }
+      // The place of the loop in the code matters: of the 16 in 64 bytes, those at 28 and 60 take 3 % longer, those at 0, 16 and 32 1 %
+      // (dense, 43,968 tokens: 6.29, 6.19, and 6.10 ms here); the loops of the other kernels do not care.
+      if constexpr (DUO && BOTH) asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0");
+      for (bool odd = DUO && !BOTH && flip != 0; odd || step(Int<0>{}); odd = false)
+        if (!step(Int<1>{})) break;
       // ---- the O update and the last row-sum step of the run's last unit ------------------------------
 #pragma unroll
       for (int db = 0; db < 2; ++db)
@@ -1181,15 +1329,106 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     // ---- from the first ragged tile on: plain tiles (the same buffers and the same one barrier per
     // tile; the loads stay two tiles ahead) ------------------------------------------------------------
     for (; T < ntiles; ++T) {
-      compute_tile(std::false_type{}, (T & 1) * TILE_BYTES, wave_limit(J_cur), []() {}, ka, va[0], sc, pw);
+      compute_tile(std::false_type{}, ((T + flip) & 1) * BUF_BYTES, wave_limit(J_cur), []() {}, ka, va[0], sc, pw);
       const Tile J2 = scalar((T + 2 < ntiles) ? fix(J_pre, T + 2) : J_cur);
       J_pre = raw_at(T + 3);
       __builtin_amdgcn_s_waitcnt(0x0F70);  // this wave's share of tile T+1 has landed
       __syncthreads();                     // ... everyone's has, and nobody still reads tile T
-      issue_rt(J2, T & 1);
+      issue_rt(both, J2, (T + flip) & 1);
       J_cur = J_nxt;
       J_nxt = J2;
     }
+    if constexpr (DUO && !BOTH) {
+      for (; T < steps; ++T) __syncthreads();  // the other block's tiles
+    }
+  };
+
+  // DUO: the end of a pass, as below.  Of the two waves that hold the key halves of 64 query rows each finishes 32, and
+  // leaves the other its share of the other 32; then (deal) the second four waves theirs to the first four.
+  auto end_duo = [&](auto safec) -> bool {
+    constexpr bool SAFE = decltype(safec)::value;
+    constexpr int WORDS = 34 * 64;  // 32 accumulators, reference maximum and row sum of 64 lanes
+    const int lane = fresh_lane(), n = lane & 31, g = lane >> 5;
+    float* const parked = reinterpret_cast<float*>(smem) + 16;
+    volatile int* flag = reinterpret_cast<volatile int*>(smem);
+    auto leave = [&](float* at, const f32x16& x0, const f32x16& x1, float m, float l) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        at[i * 64 + lane] = x0[i];
+        at[(16 + i) * 64 + lane] = x1[i];
+      }
+      at[32 * 64 + lane] = m;
+      at[33 * 64 + lane] = l;
+    };
+    f32x16 x[2];
+    float m, l;
+    if (kh == 0) {
+      leave(parked + wave * WORDS, o[0][1], o[1][1], m_ref[1], l_run[1]);
+      x[0] = o[0][0];
+      x[1] = o[1][0];
+      m = m_ref[0];
+      l = l_run[0];
+    } else {
+      leave(parked + wave * WORDS, o[0][0], o[1][0], m_ref[0], l_run[0]);
+      x[0] = o[0][1];
+      x[1] = o[1][1];
+      m = m_ref[1];
+      l = l_run[1];
+    }
+    if (wave == 0 && lane == 0) *flag = 0;
+    auto take = [&](const float* at) {
+      float a0 = 1.f, a1 = 1.f;
+      if constexpr (SAFE) {
+        const float m1 = at[32 * 64 + lane], top = fmaxf(m, m1);
+        const float mu = (top == -INFINITY) ? 0.f : top;
+        a0 = exp2f(m - mu);  // exp2f(-inf) = 0 for a half that saw nothing
+        a1 = exp2f(m1 - mu);
+        m = top;
+      }
+      l = l * a0 + at[33 * 64 + lane] * a1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        x[0][i] = x[0][i] * a0 + at[i * 64 + lane] * a1;
+        x[1][i] = x[1][i] * a0 + at[(16 + i) * 64 + lane] * a1;
+      }
+    };
+    __syncthreads();
+    take(parked + (wave ^ 2) * WORDS);
+    l += xor32(l);
+    if (deal) {
+      if (gb == 1) leave(parked + (8 + gw) * WORDS, x[0], x[1], m, l);
+      __syncthreads();
+      if (gb == 0) take(parked + (8 + gw) * WORDS);
+    }
+    const bool writes = !(deal && gb == 1);
+    if constexpr (!SAFE) {
+      bool bad = false;
+      if (writes && count_row > 0) {  // an empty row is zeros by definition, not a range problem
+        bad = !(l >= 0x1p-80f && l <= 0x1p100f);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) bad = bad || !(fabsf(x[0][i]) < INFINITY) || !(fabsf(x[1][i]) < INFINITY);
+      }
+      if (bad) *flag = 1;
+      __syncthreads();
+      const bool any_bad = *flag != 0;
+      __syncthreads();
+      if (any_bad) return true;
+    }
+    const int lrow = q_off + kh * 32 + n;
+    if (writes && lrow < q_valid) {
+      const int64_t row = int64_t(q_start) + lrow;
+      const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const int i = 4 * r4;
+          const u32x2 w = {pack_bf16(x[db][i] * inv, x[db][i + 1] * inv), pack_bf16(x[db][i + 2] * inv, x[db][i + 3] * inv)};
+          *reinterpret_cast<u32x2*>(out + (int64_t(h) * n_tokens + row) * kD + db * 32 + 8 * r4 + 4 * g) = w;
+        }
+      if (lse != nullptr && g == 0) lse[int64_t(h) * n_tokens + row] = l > 0.f ? ((SAFE ? m : 0.f) + log2f(l)) * kLn2 : -INFINITY;
+    }
+    return false;
   };
 
   // A whole pass over the row's key tiles, then the merge of the two key halves (wave (qi, 1) parks
@@ -1209,8 +1448,35 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         for (int i = 0; i < 16; ++i) o[db][b2][i] = 0.f;
     m_ref[0] = m_ref[1] = -INFINITY;
     l_run[0] = l_run[1] = 0.f;
-    if constexpr (!SAFE && B == 128) fast_loop();
-    else plain_loop(safec);
+    if constexpr (DUO) {
+      auto shift = [&](unsigned by) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) kaddr[c] += by;
+        vaddr[0] += by;
+        vaddr[1] += by;
+      };
+      const int most = max(n_alone[0], n_alone[1]);
+      take_part(false);
+      if (ntiles > 0) issue_rt(std::false_type{}, scalar(block_at(0)), flip);
+      if (n_both > 0) {
+        take_part(true);
+        shift(BUF_BYTES);
+        if constexpr (SAFE) plain_loop(safec, std::true_type{}, ntiles);
+        else fast_loop(std::true_type{}, ntiles);
+        shift(0u - BUF_BYTES);
+        take_part(false);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // no load may still be on its way into the buffers ...
+        __syncthreads();                     // ... nor anyone read them
+      }
+      if (most > 0) {
+        shift(gb * 2 * BUF_BYTES);
+        const int steps = HALF ? (most + 1) >> 1 : most;
+        if constexpr (SAFE) plain_loop(safec, std::false_type{}, steps);
+        else fast_loop(std::false_type{}, steps);
+        shift(0u - gb * 2 * BUF_BYTES);
+      }
+    } else if constexpr (!SAFE && B == 128) fast_loop(std::false_type{}, ntiles);
+    else plain_loop(safec, std::false_type{}, ntiles);
     if constexpr (PAIR) {
       __builtin_amdgcn_s_waitcnt(0x0F70);  // no load may still be on its way into the buffers ...
       __syncthreads();                     // ... nor anyone read them
@@ -1219,6 +1485,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     __builtin_amdgcn_s_waitcnt(0x0F70);  // no direct-to-LDS load may still be in flight
     __syncthreads();                     // ... in any wave: LDS can be reused
 
+    if constexpr (DUO) return end_duo(safec);
     float* park = reinterpret_cast<float*>(smem) + 16 + qi * 68 * 64;
     if (kh == 1) {
 #pragma unroll
@@ -1444,7 +1711,7 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
         w0 = begin / quota;
         w1 = (begin + tiles - 1) / quota;
       }
-      run(std::false_type{}, row, tile, tile + take, w0, w1, me, -1);
+      run(std::false_type{}, row, tile, tile + take, w0, w1, me, -1, false);
       done += take;
       tile = 0;
       ++row;
@@ -1462,17 +1729,18 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
   //    first come, first served, through one atomic counter, and leave at once when none is left.
   //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
   //    through with its static share early thus takes more of the remaining rows than a slow one.
-  const int units = PAIR && !SOLO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
+  const int units = (PAIR && !SOLO) || DUO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
   const int64_t total = int64_t(heads) * units;
   const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
   int64_t pos;
   if (w < n_static) {
-    const int r = static_cast<int>(w & 511);
-    pos = (w - r) + 512 <= n_static ? (w - r) + (r & 7) * 64 + (r >> 3) : w;
+    constexpr int PLACES = DUO ? 256 : 512;  // workgroups that the chip holds
+    const int r = static_cast<int>(w & (PLACES - 1));
+    pos = (w - r) + PLACES <= n_static ? (w - r) + (r & 7) * (PLACES / 8) + (r >> 3) : w;
   } else {
     if (next_row == nullptr) return;  // the grid is rounded up to whole heads
     int* slot = reinterpret_cast<int*>(smem);
-    if (tid == 0) *slot = atomicAdd(next_row, 1);
+    if (tid0 == 0) *slot = atomicAdd(next_row, 1);
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane(*slot);
     __syncthreads();  // the slot lies where the first K tile goes
@@ -1480,22 +1748,32 @@ __global__ __launch_bounds__(2 * B, 2) void attn_bf16_kernel(
     pos = n_static + t;
   }
   int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
-  if constexpr (PAIR && !SOLO) {
+  if constexpr ((PAIR && !SOLO) || DUO) {
     const bool single = order == nullptr && pos >= n_pairs;  // positions from n_pairs on are rows, two of each unit
     if (single) row = n_pairs + ((pos - n_pairs) >> 1);
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
     const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
     const int first = single ? I + static_cast<int>((pos - n_pairs) & 1) : I, last = min(single ? first + 1 : I + 2, nb);
     if (first >= nb) return;
-    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, single ? first - I : -1);
+    if constexpr (DUO) {
+      for (int next = single ? first : -1;;) {  // -1: the pair
+        const bool deal = next >= 0;
+        const int left = run(std::false_type{}, deal ? h * nb + next : row, 0, 0, 0, 0, 0, -1, deal);
+        if (!deal && left == kDone) return;
+        next = deal ? next + 1 : first;
+        if (next >= last) return;
+        __syncthreads();  // whatever the end of the row before still reads
+      }
+    }
+    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, single ? first - I : -1, false);
     if (listed == kDone) return;
 #pragma unroll 1
     for (int i = first; i < last; ++i) {
       __syncthreads();  // whatever the end of the row before still reads
-      run(std::true_type{}, h * nb + i, 0, 0, 0, 0, 0, listed);
+      run(std::true_type{}, h * nb + i, 0, 0, 0, 0, 0, listed, false);
     }
   } else {
-    run(std::bool_constant<SOLO>{}, row, 0, 0, 0, 0, 0, -1);
+    run(std::bool_constant<SOLO>{}, row, 0, 0, 0, 0, 0, -1, false);
   }
 }
 
@@ -1509,60 +1787,85 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const Segments seg = {static_cast<int>(n_first), static_cast<int>(ceil_div(n_first, block)),
                         static_cast<int>(ceil_div(n_first, block_k))};
   const int32_t* order = nullptr;
-  const bool pair = pairs_rows(block, heads, nb, nbk);
-  const int nu = pair ? (nb + 1) >> 1 : nb;  // units of work per head: rows, or pairs of rows
-  const int64_t rows = int64_t(heads) * nu;
-  int64_t n_static = rows;  // without a workspace every row is taken by workgroup number
-  int64_t n_pairs = rows;   // units that go in pairs; those after them (none if there is a launch order) go row by row
-  int extra = 0;                          // workgroups beyond one per row
+  const int32_t* choice = nullptr;
+  const size_t order_bytes = attn_order_bytes(heads, n_tokens);
+  const bool duo = block == 128 && kv_idx == nullptr && dense_pairs(heads, nb);  // every row is the same: no need to choose
+  // few long rows, shared between workgroups (a launch of 1024 rows or more is never one of these)
+  const bool share = !(duo && int64_t(heads) * nb > 512) && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&
+                     shares_rows(int64_t(heads) * nb, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
+                     workspace_bytes >= order_bytes + kStreamBytes + 256;
+  const bool choose = block == 128 && kv_idx != nullptr && workspace != nullptr && chooses_pairs(heads, nb, nbk);
+  const bool pair = pairs_rows(block, heads, nb, nbk) || (duo && !share);
+
+  // How the units (rows, or pairs of rows) of a kernel go to its workgroups; see the end of the kernel.
+  struct Spread {
+    dim3 grid;
+    int64_t n_static;  // units taken by workgroup number
+    int64_t n_pairs;   // units that go in pairs; those after them go row by row (none if there is a launch order)
+    bool big;          // the other units are handed out at run time
+  };
+  auto spread = [&](bool two, bool eight_waves) {
+    const int nu = two ? (nb + 1) >> 1 : nb;
+    const int64_t rows = int64_t(heads) * nu;
+    int64_t n_static = rows, n_pairs = rows;  // without a workspace every row is taken by workgroup number
+    int64_t extra = 0;                        // workgroups beyond one per row
+    // ordering and balancing matter only when the grid does not fit the chip at once
+    // (and only while the extra workgroups fit the grid's second dimension)
+    const bool big = workspace != nullptr && rows >= 1024 && rows < (int64_t(1) << 30) &&
+                     heads + ceil_div(rows / 16 + 1024, nu) <= 65535;
+    if (big) {
+      // The last eighth of the rows is handed out at run time; half as many workgroups again as that
+      // are launched for it, so that an XCD can take up to 1.5 times its even share of those rows.
+      const int64_t dynamic = rows / 8;
+      n_static = (rows - dynamic) / 512 * 512;
+      extra = (rows - n_static) / 2 + 512;
+    }
+    if (two && !eight_waves && rows < 1024 && heads + ceil_div(128, nu) <= 65535) {
+      // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
+      // 1,064 rows of 532 blocks, nine tenths, a quarter kept, a band: 655 -> 610, 252 -> 204, 216 -> 179 us.  Where more
+      // are left the last 64 do, which evens out the end: 1,600 rows of 100 blocks 176 -> 164, 69 -> 61, 62 -> 60 us.  With
+      // 400 and more there is no room for them: 1,840 rows of 115 205 -> 207 us, 2,032 of 127 242 -> 261.  Only here, where
+      // the launch has no order: which rows go which way must not depend on one.
+      const int64_t rest = rows - 512;
+      const int64_t singly = rest <= 128 ? rest : rest < 400 ? 64 : 0;
+      n_pairs = rows - singly;
+      extra = singly;
+      n_static = rows + singly;
+    }
+    return Spread{dim3(nu, heads + static_cast<int>(ceil_div(extra, nu))), n_static, n_pairs, big};
+  };
+  const Spread plan = spread(pair, block == 128);
   int* next_row = nullptr;
-  // ordering and balancing matter only when the grid does not fit the chip at once
-  // (and only while the extra workgroups fit the grid's second dimension)
-  const bool big = workspace != nullptr && rows >= 1024 && rows < (int64_t(1) << 30) &&
-                   heads + ceil_div(rows / 16 + 1024, nu) <= 65535;
-  if (big) {
-    // The last eighth of the rows is handed out at run time; half as many workgroups again as that
-    // are launched for it, so that an XCD can take up to 1.5 times its even share of those rows.
-    const int64_t dynamic = rows / 8;
-    n_static = (rows - dynamic) / 512 * 512;
-    extra = static_cast<int>((rows - n_static) / 2 + 512);
-  }
-  if (pair && rows < 1024 && heads + ceil_div(128, nu) <= 65535) {
-    // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
-    // 1,064 rows of 532 blocks, nine tenths, a quarter kept, a band: 655 -> 610, 252 -> 204, 216 -> 179 us.  Where more
-    // are left the last 64 do, which evens out the end: 1,600 rows of 100 blocks 176 -> 164, 69 -> 61, 62 -> 60 us.  With
-    // 400 and more there is no room for them: 1,840 rows of 115 205 -> 207 us, 2,032 of 127 242 -> 261.  Only here, where
-    // the launch has no order: which rows go which way must not depend on one.
-    const int64_t rest = rows - 512;
-    const int64_t singly = rest <= 128 ? rest : rest < 400 ? 64 : 0;
-    n_pairs = rows - singly;
-    extra = static_cast<int>(singly);
-    n_static = rows + singly;
-  }
-  if (big && kv_idx == nullptr) {
+  if (plan.big && kv_idx == nullptr) {
     // dense: the workspace holds the counter only
     next_row = static_cast<int*>(workspace);
     hipLaunchKernelGGL(zero_word_kernel, dim3(1), dim3(64), 0, stream, next_row);
   }
-  if (big && kv_idx != nullptr) {
-    // workspace: [heads * nb] launch order, then the [classes][heads] table, the number of the merged
-    // class and the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel)
+  if (plan.big && kv_idx != nullptr) {
+    // workspace: launch order of the rows or pairs, then the [classes][heads] table, the number of the merged
+    // class, the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel) and the choice
+    const int nu = static_cast<int>(plan.grid.x);
+    const int64_t rows = int64_t(heads) * nu;
     int32_t* ord = static_cast<int32_t*>(workspace);
     int32_t* table = ord + rows;
     next_row = table + int64_t(kOrderClasses) * heads + 1;
+    if (choose) {
+      int32_t* c = table + int64_t(kOrderClasses) * heads + 2;
+      hipLaunchKernelGGL(choose_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nbk, heads, block_k == block ? 1 : 2, c);
+      choice = c;
+    }
     if (rows <= kOrderOneMax) {
-      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, ord, next_row);
+      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, ord, next_row);
     } else {
-      hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table);
+      hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, table);
       hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads);
       hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, stream, table, int64_t(kOrderClasses) * heads);
-      hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table, ord);
+      hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, table, ord);
     }
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (launch order)")) return rc;
     order = ord;
   }
   const float scale_log2 = softmax_scale * kLog2e;
-  dim3 grid(nu, heads + static_cast<int>(ceil_div(extra, nu)));
   const unsigned char* qp = static_cast<const unsigned char*>(q);
   const unsigned char* kp = static_cast<const unsigned char*>(k);
   const unsigned char* vp = static_cast<const unsigned char*>(v);
@@ -1572,36 +1875,41 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t lds64 = 4 * 64 * 128, lds128 = 4 * 128 * 128;
   if (getenv("BSGA_DEBUG") != nullptr) {
     int n64 = -1, n128 = -1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false, false>, 128, lds64);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false, false>, 256, lds128);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false, false, false>, 128, lds64);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false, false, false>, 256, lds128);
     fprintf(stderr, "[bsga] attention occupancy (workgroups per CU): block 64 -> %d, block 128 -> %d\n", n64, n128);
   }
-  auto launch = [&](auto kernel, dim3 g, int threads, size_t lds, StreamTable* tab) {
-    hipLaunchKernelGGL(kernel, g, dim3(threads), lds, stream, qp, kp, vp, op, lse, kv_idx, kv_cnt, order, idx_stride,
-                       n_tokens, nb, nbk, scale_log2, seg, heads, n_static, n_pairs, next_row, tab);
+  auto launch = [&](auto kernel, const Spread& to, int threads, size_t lds, StreamTable* tab) {
+    hipLaunchKernelGGL(kernel, to.grid, dim3(threads), lds, stream, qp, kp, vp, op, lse, kv_idx, kv_cnt, order, idx_stride,
+                       n_tokens, nb, nbk, scale_log2, seg, heads, to.n_static, to.n_pairs, next_row, choice, tab);
   };
-  const size_t order_bytes = attn_order_bytes(heads, n_tokens);
-  if (!big && workspace != nullptr && attn_stream_shape(heads, n_tokens) &&
-      shares_rows(int64_t(heads) * nb, block, ceil_div(nbk, block / block_k), kv_idx == nullptr) &&
-      workspace_bytes >= order_bytes + kStreamBytes + 256) {
+  if (share) {
     const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
     StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
     const int places = block == 64 ? kStreamPlaces<64> : kStreamPlaces<128>;
-    const dim3 g(max(places, heads * nb));
+    const Spread all = {dim3(max(places, heads * nb)), 0, 0, false};
     hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
                        block_k == block ? 1 : 2, places, block == 64 || kv_idx == nullptr, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
-    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false>, g, 128, lds64, tab);
-    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false>, g, 256, lds128, tab);
-    else launch(attn_bf16_kernel<128, 64, true, false, false>, g, 256, lds128, tab);
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false, false>, all, 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false, false>, all, 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true, false, false, false>, all, 256, lds128, tab);
     return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
-  if (pair) launch(attn_bf16_kernel<128, 64, false, true, false>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
-  else if (solo_rows(block, rows, nbk))
-    launch(attn_bf16_kernel<128, 64, false, true, true>, grid, 256, lds128 + 4 * size_t(nbk), nullptr);
-  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false, false>, grid, 128, lds64, nullptr);
-  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false>, grid, 256, lds128, nullptr);
-  else launch(attn_bf16_kernel<128, 64, false, false, false>, grid, 256, lds128, nullptr);
+  if (duo || choice != nullptr) {
+    const Spread pairs = spread(true, true);
+    const size_t lds = 2 * lds128 + (kv_idx != nullptr ? 4 * size_t(nbk) : 0);
+    if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false, true>, pairs, 512, lds, nullptr);
+    else launch(attn_bf16_kernel<128, 64, false, false, false, true>, pairs, 512, lds, nullptr);
+    if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention launch")) return rc;
+    if (duo) return BSGA_OK;
+  }
+  if (pair) launch(attn_bf16_kernel<128, 64, false, true, false, false>, plan, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (solo_rows(block, int64_t(heads) * nb, nbk))
+    launch(attn_bf16_kernel<128, 64, false, true, true, false>, plan, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false, false, false>, plan, 128, lds64, nullptr);
+  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false, false>, plan, 256, lds128, nullptr);
+  else launch(attn_bf16_kernel<128, 64, false, false, false, false>, plan, 256, lds128, nullptr);
   return check_hip(hipGetLastError(), "bsga bf16 attention launch");
 }
 

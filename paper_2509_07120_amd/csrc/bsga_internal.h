@@ -78,6 +78,20 @@ inline bool pairs_rows(int block, int heads, int nb, int nbk) {
   return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
 }
 
+// Whether a dense launch takes blocks of 128 two to a workgroup of eight waves (see DUO): where the busiest CU then has no more rows
+// to work on than with a row to each workgroup, or has twenty and more.  Row by row / in pairs, 16 heads (rows per CU): 2,748
+// tokens (1.4) 41.6 / 40.4 us, 6,870 (3.4) 186 / 176, 10,992 (5.4) 435 / 412, 43,968 (21.5)
+// 6,310 / 6,100, 137,400 (67) 60.8 / 58.0 ms; but 4,122 (2.1) 89 / 108, 8,244 (4.1) 270 / 305, 16,488 (8.1) 946 / 979,
+// 21,984 (10.8) 1,621 / 1,629.
+inline bool dense_pairs(int heads, int nb) {
+  const int64_t rows = int64_t(heads) * nb, pairs = int64_t(heads) * ((nb + 1) / 2);
+  return rows >= 20 * 256 || 2 * ceil_div(pairs, 256) <= ceil_div(rows, 256);
+}
+// Whether a sparse launch of blocks of 128 is large enough for choose_kernel to look at its lists, and these fit the LDS.
+inline bool chooses_pairs(int heads, int nb, int nbk) {
+  return int64_t(heads) * nb >= 4096 && nb >= 256 && nbk <= kPairMaxBlocks;
+}
+
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);
