@@ -1,45 +1,389 @@
-// fp32 attention over kept key blocks (Sec. 4.1, Eq. (2); Eq. (1) when no index list is given), both
-// products on v_mfma_f32_32x32x2 (fp32 operands, fp32 accumulation), online softmax in fp32.
+// fp32 attention over kept key blocks (Sec. 4.1, Eq. (2); Eq. (1) when no index list is given), online softmax in fp32.
+// Two kernels: attn_fp32_split_kernel for launches of more than 128 units of 64 query rows, attn_fp32_kernel for the rest.
 //
-// Work split.  A workgroup of four waves owns 64 (or, where that leaves CUs idle, 32) query rows of one block;
-// its waves take the 32-key pieces of the row's key blocks in turn, each with a softmax state of its own,
-// and the four states are merged through LDS at the end.  Consecutive units run on one XCD (workgroup w runs
-// on XCD w % 8), so that an L2 holds the keys of two heads and not of all of them.
+// attn_fp32_split_kernel: both products on the bf16 matrix instructions, every fp32 operand split in three.
+//   x = x1 + x2 + x3, eight bits each, what is left over is below 2^-25 |x|.  Of the nine products of two such sums
+//   the six of the order of 2^-18 and above are taken (11, 12, 21, 22, 13, 31), the small ones first, accumulated in fp32.
+//   A bf16 product is exact in fp32 and 16 of them are summed per instruction, so a sum has fewer roundings than
+//   on v_mfma_f32_32x32x2; the output products of a tile are summed apart and added to the output with one more.  Error of the output
+//   against float64 (2-norms): 2,748 tokens of a scene 2.0e-7, on the fp32 instructions 4.7e-7; 5,496 2.5e-7 and 6.5e-7; logits
+//   a hundred times as large 3.1e-6 and 4.4e-6; the row sums' logarithm as before.
+//   Six instructions of 32 cycles stand for eight of 64, and the vector work grows by the splits: 1,900 cycles of vector
+//   issue beside 1,540 of matrix products per tile and wave, which two workgroups to a CU overlap in part (45 % of the matrix pipe).
+//   A workgroup of four waves owns 64 query rows of one block; wave (qi, kh) takes 32 of them and 32 keys of every
+//   tile of 64, and the two key halves have softmax states of their own, merged at the end.  The four waves split a tile
+//   together and leave the parts in the LDS (48 KB).  Rows are 128 bytes, chunks of 16 bytes permuted as in the bf16 kernel, whose operand
+//   layouts these are: S^T = K Q^T leaves the weights where they are the B operand of O^T = V^T P^T, and V^T comes by
+//   transposing LDS reads.
+//   Values the split cannot hold (infinities, NaN, what rounds to infinity in bf16) make a row sum or an output something else
+//   than a finite number.  The workgroup then starts over with fp32 instructions (pass<true>: no LDS, no prefetch; slow).
+//   16 heads, dense, 32 rows or 64 on the fp32 instructions / so: 700 tokens 33 / 28 us, 1,374 109 / 70, 2,748 288 / 219, 5,496
+//   1,074 / 795 (156 TFLOP/s; a library fp32 GEMM reaches 154).
+//   Measured and not taken: the next tile's split and the weights interleaved with the products in one wave (820 us: what
+//   one wave can issue in a row then bounds it); three workgroups to a CU (168 registers spill: 868).
 //
-// Bound by the matrix pipe: a piece of 32 keys is 128 MFMAs of 64 cycles per wave against 32 exponentials and
-// 24 loads.  K and V therefore come straight from global memory into operand registers, without LDS or
-// barriers: V of a piece is loaded under its score products, K of the next one under its output products.
-// Each loaded operand feeds two MFMAs with 64 rows; with 32 rows the loads cost a third of the time.
+// attn_fp32_kernel: both products on v_mfma_f32_32x32x2.  A workgroup of four waves owns 32 query rows; its waves take the
+//   32-key pieces of the row's key blocks in turn, each with a softmax state of its own, merged through LDS at the end.  Twice
+//   as many workgroups, and four times the waves to a key: a head of 1,374 tokens 33 us, split 51; two of 2,748 65 and 96.
+//   A piece of 32 keys is 64 MFMAs of 64 cycles per wave.  K and V come straight from global memory into operand registers, without LDS or
+//   barriers: V of a piece is loaded under its score products, K of the next one under its output products.
 //   S^T = K Q^T: lane (n = lane%32, g = lane/32) holds dims 8c + 4g .. +3, c = 0..7, of key n as A operand and
 //   of query n as B operand (the contraction takes the dims in that order); accumulator register i of the lane
 //   is key 8(i/4) + 4g + i%4 of query n.
 //   O^T += V^T P^T: step i multiplies keys 8(i/4) + 4g + i%4, so the weights are used where they are; the lane
 //   supplies dims 2n and 2n + 1 of that key, one for each of the two accumulators.
-// 16 heads x 2,748 tokens, dense (30.9 GFLOP): 0.32 ms, 96 TFLOP/s, 5,496 tokens 108, of 154 that a library
-// fp32 GEMM reaches here; one thread per row with scalar FMAs took 1.95 ms (16 TFLOP/s).
+//
+// In both, consecutive units run on one XCD (workgroup w runs on XCD w % 8), so that an L2 holds the keys of two heads and
+// not of all of them.
 #include "bsga_internal.h"
+
+#include <type_traits>
 
 namespace bsga {
 namespace {
 
 constexpr int kD = 64;
-constexpr int kPiece = 32;  // keys a wave takes at a time
+constexpr int kTile = 64;                       // keys
+constexpr int kPiece = 32;                      // keys a wave takes at a time on the fp32 instructions
+constexpr int kPlane = kTile * kD * 2;          // one of the three parts of a K or V tile, bytes
+constexpr int kRowWords = 18 * 64;              // what a wave leaves for its neighbour: 16 accumulators, maximum, sum of 64 lanes
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-template <int B, int NQ>
+// chunk swizzles: 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
+__device__ __forceinline__ int swz_k(int row) { return (row ^ (row >> 3)) & 7; }
+__device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
+
+// the three parts of a and b, packed in pairs.  The first is rounded to nearest, so that the rest has either sign; the others
+// are cut off, which is a byte permutation instead of a conversion of twice the time.
+__device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3) {
+  p1 = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+  a -= __uint_as_float(p1 << 16);
+  b -= __uint_as_float(p1 & 0xffff0000u);
+  p2 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+  a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
+  b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
+  p3 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+
+// c + x y of two split operands, the small products first
+__device__ __forceinline__ f32x16 products(const bf16x8 (&x)[3], const bf16x8 (&y)[3], f32x16 c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], y[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[2], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], c, 0, 0, 0);
+}
+
+template <int B>
+__global__ __launch_bounds__(256, 2) void attn_fp32_split_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                           const float* __restrict__ v, int64_t n_tokens, int64_t n_first,
+                                                           int nb1, int nb, float scale_log2,
+                                                           const int32_t* __restrict__ kv_idx,
+                                                           const int32_t* __restrict__ kv_cnt, int idx_stride,
+                                                           float* __restrict__ out, float* __restrict__ lse) {
+  constexpr int UNITS = B / 64;     // workgroups per query block
+  constexpr int PIECES = B / kTile;  // tiles per key block
+  __shared__ __align__(16) unsigned char smem[6 * kPlane];  // K parts 1, 2, 3, V parts 1, 2, 3
+  __shared__ int bad_s;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qi = wave & 1;
+  const int kh = wave >> 1;
+  const int n = lane & 31;
+  const int g = lane >> 5;
+  // unit of this workgroup: XCD x takes the x-th eighth of all units
+  const int64_t total = int64_t(gridDim.x) * gridDim.y;
+  const int64_t w = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t xcd = w & 7, per = total >> 3, rest = total & 7;
+  const int64_t unit = xcd * per + min(xcd, rest) + (w >> 3);
+  const int h = static_cast<int>(unit / gridDim.x);
+  const int u = static_cast<int>(unit - int64_t(h) * gridDim.x);
+  const int I = u / UNITS;
+  const int64_t head_off = int64_t(h) * n_tokens * kD;
+  // blocks 0 .. nb1-1 tile tokens [0, n_first), the others tokens [n_first, n_tokens)
+  auto block_start = [&](int J) { return J < nb1 ? int64_t(J) * B : n_first + int64_t(J - nb1) * B; };
+  auto block_count = [&](int J) {
+    return static_cast<int>(min<int64_t>(B, (J < nb1 ? n_first : n_tokens) - block_start(J)));
+  };
+  const int rows = block_count(I) - (u % UNITS) * 64;  // query rows from this unit's first on
+  if (rows <= 0) return;                               // the whole workgroup, before any barrier
+  const int64_t row0 = block_start(I) + (u % UNITS) * 64;
+  if (tid == 0) bad_s = 0;
+  const float* const q_row = q + head_off + (row0 + min(32 * qi + n, rows - 1)) * kD;  // rows past the end are not stored
+
+  const bool dense = kv_idx == nullptr;
+  const int64_t row = int64_t(h) * nb + I;
+  const int count = dense ? nb : min(max(kv_cnt[row], 0), nb);
+  const int pieces = count * PIECES;
+  // the first tile from `piece` on that holds a key at all: a short block may end before its later tiles
+  auto next_piece = [&](int piece, int64_t& key0, int& valid) {
+    for (; piece < pieces; ++piece) {
+      const int it = piece / PIECES;
+      const int J = dense ? it : min(max(kv_idx[row * idx_stride + it], 0), nb - 1);
+      key0 = block_start(J) + (piece % PIECES) * kTile;
+      valid = block_count(J) - (piece % PIECES) * kTile;
+      if (valid > 0) break;
+    }
+    return piece;
+  };
+
+  f32x16 o[2];  // O^T: [dim block], this lane's query
+  float m, l;
+  // scores of 32 keys, of which those from `valid` on do not count -> weights; maximum and sum follow.  Returns what the
+  // output so far is to be multiplied by.
+  auto weigh = [&](f32x16& s, int valid) -> float {
+    if (valid < 32) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + 4 * g + (i & 3) >= valid) ? -INFINITY : s[i];
+    }
+    float top = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) top = fmaxf(top, s[i]);
+    top = fmaxf(top, __shfl_xor(top, 32));
+    float a = 1.f;
+    if (__any(top > m)) {
+      const float m_new = fmaxf(m, top);
+      a = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);  // 0 on the first tile
+      m = m_new;
+    }
+    const float ref = m == -INFINITY ? 0.f : m;  // a wave that has seen nothing but weights of zero (scores of -inf) has no maximum
+    float part[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(s[i] - ref);
+      part[i & 1] += s[i];
+    }
+    l = fmaf(l, a, part[0] + part[1]);
+    return a;
+  };
+
+  // ---- the products in split operands ---------------------------------------------------------------
+  auto tiles_split = [&]() {
+    bf16x8 qf[4][3];  // [16-dim chunk][part]: dims 16c + 8g .. +7 of query n
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g), x1 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g + 4);
+      u32x4 y[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = (e < 2 ? x0[2 * e] : x1[2 * e - 4]) * scale_log2, b = (e < 2 ? x0[2 * e + 1] : x1[2 * e - 3]) * scale_log2;
+        unsigned p1, p2, p3;
+        split_pair(a, b, p1, p2, p3);
+        y[0][e] = p1;
+        y[1][e] = p2;
+        y[2][e] = p3;
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x) qf[c][x] = __builtin_bit_cast(bf16x8, y[x]);
+    }
+    // this thread's share of a tile: chunk (eight dims) tid % 8 of tile rows tid / 8 and 32 + tid / 8, of K and of V
+    const int lr = tid >> 3, lc = tid & 7;
+    f32x4 raw[2][2][2];  // [K, V][row][half of the chunk]
+    auto load = [&](int64_t key0, int valid) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = lr + 32 * i;
+        // keys past `valid` repeat the last one; they are masked
+        const int64_t at = head_off + (key0 + min(r, valid - 1)) * kD + 8 * lc;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          raw[0][i][x] = *reinterpret_cast<const f32x4*>(k + at + 4 * x);
+          raw[1][i][x] = *reinterpret_cast<const f32x4*>(v + at + 4 * x);
+        }
+      }
+    };
+    auto store = [&](int valid) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int r = lr + 32 * i;
+          u32x4 y[3];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float a = raw[t][i][e >> 1][2 * (e & 1)], b = raw[t][i][e >> 1][2 * (e & 1) + 1];
+            if (t == 1 && r >= valid) a = b = 0.f;  // the weight of these keys is 0, and the last one may be infinite
+            unsigned p1, p2, p3;
+            split_pair(a, b, p1, p2, p3);
+            y[0][e] = p1;
+            y[1][e] = p2;
+            y[2][e] = p3;
+          }
+          unsigned char* at = smem + t * 3 * kPlane + r * 128 + ((lc ^ (t ? swz_v(r) : swz_k(r))) << 4);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[x];
+        }
+    };
+    unsigned kaddr[4], vaddr[2];  // operand addresses in a part, see attn_bf16.hip
+    {
+      const int r = kh * 32 + n;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) kaddr[c] = r * 128 + (((2 * c + g) ^ swz_k(r)) << 4);
+      const int i16 = lane & 15, mm = i16 >> 2, j = i16 & 3, G = lane >> 4;
+      const int key = kh * 32 + 4 * g + mm;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        vaddr[db] = 3 * kPlane + key * 128 + (((db * 4 + 2 * (G & 1) + (j >> 1)) ^ swz_v(key)) << 4) + (j & 1) * 8;
+    }
+    int64_t key0 = 0;
+    int valid = 0;
+    int piece = next_piece(0, key0, valid);
+    if (piece < pieces) load(key0, valid);
+    while (piece < pieces) {
+      const int here = valid;
+      store(here);
+      __syncthreads();
+      piece = next_piece(piece + 1, key0, valid);
+      if (piece < pieces) load(key0, valid);
+      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        bf16x8 kf[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) kf[x] = *reinterpret_cast<const bf16x8*>(smem + x * kPlane + kaddr[c]);
+        s = products(kf, qf[c], s);
+      }
+      const float a = weigh(s, here - 32 * kh);
+      bf16x8 pf[2][3];
+#pragma unroll
+      for (int cp = 0; cp < 2; ++cp) {
+        u32x4 y[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          unsigned p1, p2, p3;
+          split_pair(s[8 * cp + 2 * e], s[8 * cp + 2 * e + 1], p1, p2, p3);
+          y[0][e] = p1;
+          y[1][e] = p2;
+          y[2][e] = p3;
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) pf[cp][x] = __builtin_bit_cast(bf16x8, y[x]);
+      }
+      // summed up apart and added with one fp32 rounding: the matrix instructions round a sum that has grown large worse
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        f32x16 t = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int cp = 0; cp < 2; ++cp) {
+          bf16x8 vf[3];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            const unsigned char* p = smem + x * kPlane + vaddr[db] + 16 * cp * 128;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 8 * 128));
+            const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
+            vf[x] = __builtin_bit_cast(bf16x8, u32x4{lo2[0], lo2[1], hi2[0], hi2[1]});
+          }
+          t = products(vf, pf[cp], t);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[i]);
+      }
+      __syncthreads();
+    }
+  };
+
+  // ---- the same in fp32 instructions: step d multiplies dims 2d and 2d + 1, step i keys 8(i/4) + 4g + i%4 ----
+  auto tiles_fp32 = [&]() {
+    int64_t key0 = 0;
+    int valid = 0;
+    for (int piece = next_piece(0, key0, valid); piece < pieces; piece = next_piece(piece + 1, key0, valid)) {
+      const int mine = valid - 32 * kh;  // keys of this wave
+      if (mine <= 0) continue;
+      const float* k_row = k + head_off + (key0 + 32 * kh + min(n, mine - 1)) * kD;
+      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int d = 0; d < 32; ++d) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k_row[2 * d + g], q_row[2 * d + g] * scale_log2, s, 0, 0, 0);
+      const float a = weigh(s, mine);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        o[0][i] *= a;
+        o[1][i] *= a;
+      }
+      const float* v_row = v + head_off + (key0 + 32 * kh) * kD + n;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int key = 8 * (i >> 2) + 4 * g + (i & 3);
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          float x = v_row[min(key, mine - 1) * kD + 32 * db];
+          if (key >= mine) x = 0.f;
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, s[i], o[db], 0, 0, 0);
+        }
+      }
+    }
+  };
+
+  // A whole pass over the row's tiles; then wave (qi, kh) finishes dims 32 kh .. 32 kh + 31 of its 32 rows, with what wave
+  // (qi, 1 - kh) leaves.  Returns true, to every thread, if the split operands did not do.
+  auto pass = [&](auto exactc) -> bool {
+    constexpr bool EXACT = decltype(exactc)::value;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[0][i] = o[1][i] = 0.f;
+    m = -INFINITY;
+    l = 0.f;
+    if constexpr (EXACT) tiles_fp32();
+    else tiles_split();
+    float* const park = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) park[wave * kRowWords + i * 64 + lane] = kh ? o[0][i] : o[1][i];
+    park[wave * kRowWords + 16 * 64 + lane] = m;
+    park[wave * kRowWords + 17 * 64 + lane] = l;
+    __syncthreads();
+    const float* other = park + (wave ^ 2) * kRowWords;
+    const float m1 = other[16 * 64 + lane], top = fmaxf(m, m1);
+    const float mu = top == -INFINITY ? 0.f : top;
+    const float a0 = __builtin_amdgcn_exp2f(m - mu), a1 = __builtin_amdgcn_exp2f(m1 - mu);  // 0 for a wave that saw no key
+    float sum = l * a0 + other[17 * 64 + lane] * a1;
+    sum += __shfl_xor(sum, 32);
+    f32x16 x;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = (kh ? o[1][i] : o[0][i]) * a0 + other[i * 64 + lane] * a1;
+    if constexpr (!EXACT) {
+      bool bad = count > 0 && !(sum > 0.f && sum < INFINITY);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) bad = bad || !(fabsf(x[i]) < INFINITY);
+      if (bad) bad_s = 1;
+      __syncthreads();
+      if (bad_s != 0) return true;
+    }
+    const int r = 32 * qi + n;
+    if (r < rows) {
+      // listed keys, but none with a weight: the softmax is 0 / 0
+      const float inv = sum > 0.f ? 1.f / sum : count > 0 ? NAN : 0.f;
+      float* dst = out + head_off + (row0 + r) * kD + 32 * kh + 4 * g;
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        *reinterpret_cast<f32x4*>(dst + 8 * r4) = f32x4{x[4 * r4] * inv, x[4 * r4 + 1] * inv, x[4 * r4 + 2] * inv, x[4 * r4 + 3] * inv};
+      if (lse != nullptr && kh == 0 && g == 0)
+        lse[int64_t(h) * n_tokens + row0 + r] = sum > 0.f ? (top + log2f(sum)) * 0.6931471805599453f : -INFINITY;
+    }
+    return false;
+  };
+  if (pass(std::false_type{})) pass(std::true_type{});
+}
+
+template <int B>
 __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                                                            const float* __restrict__ v, int64_t n_tokens, int64_t n_first,
                                                            int nb1, int nb, float scale_log2,
                                                            const int32_t* __restrict__ kv_idx,
                                                            const int32_t* __restrict__ kv_cnt, int idx_stride,
                                                            float* __restrict__ out, float* __restrict__ lse) {
-  constexpr int ROWS = 32 * NQ;       // query rows of a workgroup
+  constexpr int ROWS = 32;            // query rows of a workgroup
   constexpr int UNITS = B / ROWS;     // workgroups per query block
   constexpr int PIECES = B / kPiece;  // pieces per key block
-  __shared__ float park[4][34 * NQ][64];  // per wave and lane: 32 NQ output accumulators, NQ reference maxima, NQ row sums
+  __shared__ float park[4][34][64];  // per wave and lane: 32 output accumulators, reference maximum, row sum
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31;
@@ -62,26 +406,20 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
   if (rows <= 0) return;                                  // the whole workgroup, before any barrier
   const int64_t row0 = block_start(I) + (u % UNITS) * ROWS;
 
-  float qr[NQ][32];
+  float qr[32];
+  const float* src = q + head_off + (row0 + min(n, rows - 1)) * kD + 4 * g;  // rows past the end are not stored
 #pragma unroll
-  for (int b = 0; b < NQ; ++b) {
-    const float* src = q + head_off + (row0 + min(32 * b + n, rows - 1)) * kD + 4 * g;  // rows past the end are not stored
+  for (int c = 0; c < 8; ++c) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(src + 8 * c);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(src + 8 * c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) qr[b][4 * c + e] = x[e] * scale_log2;
-    }
+    for (int e = 0; e < 4; ++e) qr[4 * c + e] = x[e] * scale_log2;
   }
-  f32x16 o[NQ][2];
-  float m[NQ], l[NQ];
+  f32x16 o[2];
+  float m, l;
 #pragma unroll
-  for (int b = 0; b < NQ; ++b) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[b][0][i] = o[b][1][i] = 0.f;
-    m[b] = -INFINITY;
-    l[b] = 0.f;
-  }
+  for (int i = 0; i < 16; ++i) o[0][i] = o[1][i] = 0.f;
+  m = -INFINITY;
+  l = 0.f;
 
   const bool dense = kv_idx == nullptr;
   const int64_t row = int64_t(h) * nb + I;
@@ -136,40 +474,33 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
         }
       }
     }
-    f32x16 s[NQ];
+    f32x16 s;
+    s = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < NQ; ++b) s[b] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int d = 0; d < 32; ++d)
-#pragma unroll
-      for (int b = 0; b < NQ; ++b) s[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[d], qr[b][d], s[b], 0, 0, 0);
+    for (int d = 0; d < 32; ++d) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[d], qr[d], s, 0, 0, 0);
     if (valid < kPiece) {
 #pragma unroll
-      for (int b = 0; b < NQ; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[b][i] = (8 * (i >> 2) + 4 * g + (i & 3) >= valid) ? -INFINITY : s[b][i];
+      for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + 4 * g + (i & 3) >= valid) ? -INFINITY : s[i];
     }
+    {
+      float top = s[0];
 #pragma unroll
-    for (int b = 0; b < NQ; ++b) {
-      float top = s[b][0];
-#pragma unroll
-      for (int i = 1; i < 16; ++i) top = fmaxf(top, s[b][i]);
+      for (int i = 1; i < 16; ++i) top = fmaxf(top, s[i]);
       top = fmaxf(top, __shfl_xor(top, 32));
-      if (__any(top > m[b])) {
-        const float m_new = fmaxf(m[b], top);
-        const float a = m[b] == m_new ? 1.f : __builtin_amdgcn_exp2f(m[b] - m_new);  // 0 on the first piece
-        l[b] *= a;
+      if (__any(top > m)) {
+        const float m_new = fmaxf(m, top);
+        const float a = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);  // 0 on the first piece
+        l *= a;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          o[b][0][i] *= a;
-          o[b][1][i] *= a;
+          o[0][i] *= a;
+          o[1][i] *= a;
         }
-        m[b] = m_new;
+        m = m_new;
       }
     }
-    float part[NQ][2] = {}, ref[NQ];  // a wave that has seen nothing but weights of zero (scores of -inf) has no maximum
-#pragma unroll
-    for (int b = 0; b < NQ; ++b) ref[b] = m[b] == -INFINITY ? 0.f : m[b];
+    float part[2] = {}, ref;  // a wave that has seen nothing but weights of zero (scores of -inf) has no maximum
+    ref = m == -INFINITY ? 0.f : m;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       if (i == 8) {  // the first half of V is used up: its registers take the next piece's keys
@@ -181,61 +512,52 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int b = 0; b < NQ; ++b) {
-        const float p = __builtin_amdgcn_exp2f(s[b][i] - ref[b]);
-        part[b][i & 1] += p;
-        o[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][0], p, o[b][0], 0, 0, 0);
-        o[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][1], p, o[b][1], 0, 0, 0);
-      }
+      const float p = __builtin_amdgcn_exp2f(s[i] - ref);
+      part[i & 1] += p;
+      o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][0], p, o[0], 0, 0, 0);
+      o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][1], p, o[1], 0, 0, 0);
     }
-#pragma unroll
-    for (int b = 0; b < NQ; ++b) l[b] += part[b][0] + part[b][1];
+    l += part[0] + part[1];
   }
 
   // ---- merge: wave w finishes accumulator registers 4w .. 4w+3, i.e. dims 16w + 8g .. +7 ------------
 #pragma unroll
-  for (int b = 0; b < NQ; ++b) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      park[wave][32 * b + 2 * i][lane] = o[b][0][i];
-      park[wave][32 * b + 2 * i + 1][lane] = o[b][1][i];
-    }
-    park[wave][32 * NQ + b][lane] = m[b];
-    park[wave][33 * NQ + b][lane] = l[b];
+  for (int i = 0; i < 16; ++i) {
+    park[wave][2 * i][lane] = o[0][i];
+    park[wave][2 * i + 1][lane] = o[1][i];
   }
+  park[wave][32][lane] = m;
+  park[wave][33][lane] = l;
   __syncthreads();
+  float mw[4], top = -INFINITY;
 #pragma unroll
-  for (int b = 0; b < NQ; ++b) {
-    float mw[4], top = -INFINITY;
+  for (int x = 0; x < 4; ++x) {
+    mw[x] = park[x][32][lane];
+    top = fmaxf(top, mw[x]);
+  }
+  const float mu = top == -INFINITY ? 0.f : top;
+  float sum = 0.f, acc[8];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      mw[x] = park[x][32 * NQ + b][lane];
-      top = fmaxf(top, mw[x]);
-    }
-    const float mu = top == -INFINITY ? 0.f : top;
-    float sum = 0.f, acc[8];
+  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+  for (int x = 0; x < 4; ++x) {
+    const float a = __builtin_amdgcn_exp2f(mw[x] - mu);  // 0 for a wave that saw no key
+    sum += park[x][33][lane] * a;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const float a = __builtin_amdgcn_exp2f(mw[x] - mu);  // 0 for a wave that saw no key
-      sum += park[x][33 * NQ + b][lane] * a;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] += park[x][32 * b + 8 * wave + j][lane] * a;
-    }
-    sum += __shfl_xor(sum, 32);
-    if (32 * b + n < rows) {
-      // listed keys, but none with a weight: the softmax is 0 / 0
-      const float inv = sum > 0.f ? 1.f / sum : count > 0 ? NAN : 0.f;
-      float* dst = out + head_off + (row0 + 32 * b + n) * kD + 16 * wave + 8 * g;
-      *reinterpret_cast<f32x4*>(dst) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-      *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
-      if (lse != nullptr && wave == 0 && g == 0)
-        lse[int64_t(h) * n_tokens + row0 + 32 * b + n] = sum > 0.f ? (top + log2f(sum)) * 0.6931471805599453f : -INFINITY;
-    }
+    for (int j = 0; j < 8; ++j) acc[j] += park[x][8 * wave + j][lane] * a;
+  }
+  sum += __shfl_xor(sum, 32);
+  if (n < rows) {
+    // listed keys, but none with a weight: the softmax is 0 / 0
+    const float inv = sum > 0.f ? 1.f / sum : count > 0 ? NAN : 0.f;
+    float* dst = out + head_off + (row0 + n) * kD + 16 * wave + 8 * g;
+    *reinterpret_cast<f32x4*>(dst) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+    *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
+    if (lse != nullptr && wave == 0 && g == 0)
+      lse[int64_t(h) * n_tokens + row0 + n] = sum > 0.f ? (top + log2f(sum)) * 0.6931471805599453f : -INFINITY;
   }
 }
+
 
 }  // namespace
 
@@ -249,18 +571,15 @@ int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, 
     hipLaunchKernelGGL(kernel, dim3(nb * (block / rows), heads), dim3(256), 0, stream, q, k, v, n_tokens, n_first, nb1, nb,
                        scale_log2, kv_idx, kv_cnt, idx_stride, out, lse);
   };
-  // 64 rows per workgroup load half as much per product (0.88 of the time per row when both fill the card), 32
-  // rows spread a short layer better: compare the longest CU, 256 CUs, in units of 32 rows.  Dense, 16 heads,
-  // 32 / 64 rows: 340 tokens 12.3 / 19.7 us, 700 40 / 34, 1040 76 / 90, 1374 120 / 119, 2000 193 / 172,
-  // 2748 366 / 322, 5496 1214 / 1147; two heads, 2748 tokens 62 / 103, 4122 179 / 157.
-  const int64_t units = int64_t(heads) * nb * (block / 64);
-  const bool wide = 0.88 * static_cast<double>(2 * ceil_div(units, 256)) <= static_cast<double>(ceil_div(2 * units, 256));
+  // A unit of 64 rows to a workgroup where that keeps half of the CUs busy.  Dense, 32 rows on the fp32 instructions / 64 split: 86
+  // units 65 / 96 us, 96 12 / 17, 172 201 / 188, 176 33 / 28, 272 69 / 54.
+  const bool split = int64_t(heads) * nb * (block / 64) > 128;
   if (block == 64) {
-    if (wide) launch(attn_fp32_kernel<64, 2>, 64);
-    else launch(attn_fp32_kernel<64, 1>, 32);
+    if (split) launch(attn_fp32_split_kernel<64>, 64);
+    else launch(attn_fp32_kernel<64>, 32);
   } else {
-    if (wide) launch(attn_fp32_kernel<128, 2>, 64);
-    else launch(attn_fp32_kernel<128, 1>, 32);
+    if (split) launch(attn_fp32_split_kernel<128>, 64);
+    else launch(attn_fp32_kernel<128>, 32);
   }
   return check_hip(hipGetLastError(), "bsga fp32 attention launch");
 }
