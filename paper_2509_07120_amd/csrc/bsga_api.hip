@@ -148,6 +148,7 @@ static int pool_common(const char* fn, const void* q, const void* k, int dtype, 
   if ((q && !aligned16(q)) || (k && !aligned16(k)) || (q_pool && !aligned16(q_pool)) || (k_pool && !aligned16(k_pool)))
     return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (q && k && launch_pool_both) return launch_pool_both(q, k, dtype, heads, n_tokens, n_first, block, q_pool, k_pool, s);
   if (q)
     if (int rc = launch_pool(q, dtype, heads, n_tokens, n_first, block, q_pool, s)) return rc;
   if (k)

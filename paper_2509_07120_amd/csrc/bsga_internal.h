@@ -95,6 +95,10 @@ inline bool chooses_pairs(int heads, int nb, int nbk) {
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);
+// Two tensors in one launch.  Weak: a program that puts launchers of its own under the API layer need not have it, and
+// then sees two calls of the one above.
+int launch_pool_both(const void* q, const void* k, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* q_pool,
+                     double* k_pool, hipStream_t stream) __attribute__((weak));
 
 int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_q, int nb_k,
                   double score_scale, double tau, double one_minus_rho, const uint8_t* force_q,
