@@ -140,7 +140,8 @@ int bsga_merge_heads(const void* src, int dtype, int heads, int64_t n_tokens, in
                      const int32_t* index, void* dst, void* stream);
 
 /*
- * Bytes of device workspace for a bf16 attention call of this shape (0 for fp32 and for invalid arguments).
+ * Bytes of device workspace for a bf16 attention call of this shape (0 for fp32, see bsga_attn_fp32_parts_bytes, and for
+ * invalid arguments).
  * Q, K and V are read in place; the workspace holds the launch order of the (head, query block) rows,
  * heaviest first, and the counter through which the last rows of a large launch are handed out at run
  * time: 4 bytes per row, sized for block 64 and a split sequence, plus 128 bytes per head and 16 bytes.  That
@@ -149,6 +150,15 @@ int bsga_merge_heads(const void* src, int dtype, int heads, int64_t n_tokens, in
  * row in one workgroup (same results up to the order of fp32 sums).  bsga_dense_attn needs none and accepts NULL.
  */
 size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int head_dim);
+
+/*
+ * Bytes of device workspace with which an fp32 attention call of this shape is faster (0 where it is not and for invalid
+ * arguments): K and V, each split in three bf16 parts, 768 bytes per token and head.  kept: the share of the key blocks that rows
+ * are expected to keep, 1 for bsga_dense_attn.  An fp32 call given 768 bytes per token and head uses them whatever its lists hold, as
+ * soon as it has more than 128 rows of 64; given less, none, or a workspace that is not 16-byte aligned it does without and gives the
+ * same bits.
+ */
+size_t bsga_attn_fp32_parts_bytes(int heads, int64_t n_tokens, int head_dim, double kept);
 
 /*
  * Block-sparse attention  (Sec. 4.1, Eq. (2), with masked entries excluded from the softmax).

@@ -37,7 +37,7 @@ EXPORTED_SYMBOLS = (
     "bsga_gather_tokens",
     "bsga_split_heads",
     "bsga_merge_heads",
-    "bsga_attn_workspace_bytes",
+    "bsga_attn_workspace_bytes", "bsga_attn_fp32_parts_bytes",
     "bsga_sparse_attn",
     "bsga_sparse_attn_noalloc",
     "bsga_noalloc_scratch_bytes",
@@ -86,6 +86,8 @@ def _load() -> ctypes.CDLL:
     lib.bsga_merge_heads.argtypes = [c_void_p, c_int, c_int, c_int64, c_int, c_void_p, c_void_p, c_void_p]
     lib.bsga_attn_workspace_bytes.restype = c_size_t
     lib.bsga_attn_workspace_bytes.argtypes = [c_int, c_int, c_int64, c_int]
+    lib.bsga_attn_fp32_parts_bytes.restype = c_size_t
+    lib.bsga_attn_fp32_parts_bytes.argtypes = [c_int, c_int64, c_int, c_double]
     lib.bsga_sparse_attn.restype = c_int
     lib.bsga_sparse_attn.argtypes = [c_void_p, c_void_p, c_void_p, c_int, c_int, c_int64, c_int, c_int, c_float,
                                      c_void_p, c_void_p, c_int, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
@@ -259,9 +261,20 @@ def bsga_attn_workspace_bytes(dtype: torch.dtype, heads: int, n_tokens: int, hea
     return int(lib.bsga_attn_workspace_bytes(code, heads, n_tokens, head_dim))
 
 
-def _workspace(q: torch.Tensor, workspace: Optional[torch.Tensor]) -> Tuple[Optional[torch.Tensor], int]:
+def bsga_attn_fp32_parts_bytes(heads: int, n_tokens: int, head_dim: int = 64, kept: float = 1.0) -> int:
+    return int(lib.bsga_attn_fp32_parts_bytes(heads, n_tokens, head_dim, float(kept)))
+
+
+def _attn_bytes(code: int, heads: int, n_tokens: int, head_dim: int, kept: float) -> int:
+    """Workspace that an attention call makes use of; `kept`: the share of the key blocks it is expected to keep."""
+    if code == BSGA_FP32:
+        return lib.bsga_attn_fp32_parts_bytes(heads, n_tokens, head_dim, kept)
+    return lib.bsga_attn_workspace_bytes(code, heads, n_tokens, head_dim)
+
+
+def _workspace(q: torch.Tensor, workspace: Optional[torch.Tensor], kept: float = 0.1) -> Tuple[Optional[torch.Tensor], int]:
     H, N, d = q.shape
-    need = bsga_attn_workspace_bytes(q.dtype, H, N, d)
+    need = _attn_bytes(_dtype_code(q), H, N, d, kept) if workspace is None else 0
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
@@ -347,7 +360,7 @@ def bsga_dense_attn(q, k, v, softmax_scale: Optional[float] = None, return_lse: 
     if out is None:
         out = torch.empty_like(q)
     lse = torch.empty((H, N), dtype=torch.float32, device=q.device) if return_lse else None
-    workspace, ws_bytes = _workspace(q, workspace) if balanced else (None, 0)
+    workspace, ws_bytes = _workspace(q, workspace, kept=1.0) if balanced else (None, 0)
     _check(lib.bsga_dense_attn(_ptr(q), _ptr(k), _ptr(v), _dtype_code(q), H, N, d, float(softmax_scale),
                                _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, _stream(q)))
     return (out, lse) if return_lse else out
@@ -373,7 +386,8 @@ def sparse_global_attention(q, k, v, block: int, tau: float, rho: float = 1.0,
     nb = num_blocks(N, block)
     pool_bytes = H * nb * d * 8
     select_bytes = lib.bsga_select_workspace_bytes(H, nb, nb)
-    own = lib.bsga_attn_workspace_bytes(code, H, N, d) if workspace is None else 0
+    # rows keep about tau of their blocks where the map is flat, and the top-k floor at least
+    own = _attn_bytes(code, H, N, d, max(min(float(tau), 1.0), 1.0 - float(rho))) if workspace is None else 0
     together = max(select_bytes, own) <= 1 << 20
     scratch = torch.empty(2 * pool_bytes + (max(select_bytes, own) if together else 0), dtype=torch.uint8, device=dev)
     q_pool = scratch.data_ptr()

@@ -8,19 +8,25 @@
 //   on v_mfma_f32_32x32x2; the output products of a tile are summed apart and added to the output with one more.  Error of the output
 //   against float64 (2-norms): 2,748 tokens of a scene 2.0e-7, on the fp32 instructions 4.7e-7; 5,496 2.5e-7 and 6.5e-7; logits
 //   a hundred times as large 3.1e-6 and 4.4e-6; the row sums' logarithm as before.
-//   Six instructions of 32 cycles stand for eight of 64, and the vector work grows by the splits: 1,900 cycles of vector
-//   issue beside 1,540 of matrix products per tile and wave, which two workgroups to a CU overlap in part (45 % of the matrix pipe).
+//   Six instructions of 32 cycles stand for eight of 64: 1,540 cycles of matrix products per tile and wave.  What bounds the kernel is
+//   the chain of steps that a tile is for a wave (about 5,000 cycles alone), so what counts is how many workgroups a CU holds.
 //   A workgroup of four waves owns 64 query rows of one block; wave (qi, kh) takes 32 of them and 32 keys of every
-//   tile of 64, and the two key halves have softmax states of their own, merged at the end.  The four waves split a tile
-//   together and leave the parts in the LDS (48 KB).  Rows are 128 bytes, chunks of 16 bytes permuted as in the bf16 kernel, whose operand
+//   tile of 64, and the two key halves have softmax states of their own, merged at the end.
+//   PRE: split_kv_kernel has left the parts of K and V in the call's workspace, and tiles go from there straight to the LDS (48 KB),
+//   K under the output products of the tile before, V under the scores of its own.  No tile passes through registers, which leaves
+//   room for three workgroups to a CU: 5,496 tokens 794 -> 664 us, 2,748 221 -> 178 (both with the split), 50 % of the
+//   matrix pipe before.  With two workgroups and the parts through registers 774 and 219.
+//   Otherwise the four waves load a tile, split it together and leave the parts in the LDS, two workgroups to a CU.  Two accumulators in
+//   turn keep the matrix pipe from waiting for itself: 827 -> 802 us (with three workgroups there is no room for that in the output
+//   products, and no need).  Rows are 128 bytes, chunks of 16 bytes permuted as in the bf16 kernel, whose operand
 //   layouts these are: S^T = K Q^T leaves the weights where they are the B operand of O^T = V^T P^T, and V^T comes by
 //   transposing LDS reads.
 //   Values the split cannot hold (infinities, NaN, what rounds to infinity in bf16) make a row sum or an output something else
 //   than a finite number.  The workgroup then starts over with fp32 instructions (pass<true>: no LDS, no prefetch; slow).
 //   16 heads, dense, 32 rows or 64 on the fp32 instructions / so: 700 tokens 33 / 28 us, 1,374 109 / 70, 2,748 288 / 219, 5,496
-//   1,074 / 795 (156 TFLOP/s; a library fp32 GEMM reaches 154).
+//   1,074 / 664 (186 TFLOP/s; a library fp32 GEMM reaches 154).
 //   Measured and not taken: the next tile's split and the weights interleaved with the products in one wave (820 us: what
-//   one wave can issue in a row then bounds it); three workgroups to a CU (168 registers spill: 868).
+//   one wave can issue in a row then bounds it); three workgroups to a CU that split for themselves (168 registers spill: 868).
 //
 // attn_fp32_kernel: both products on v_mfma_f32_32x32x2.  A workgroup of four waves owns 32 query rows; its waves take the
 //   32-key pieces of the row's key blocks in turn, each with a softmax state of its own, merged through LDS at the end.  Twice
@@ -55,6 +61,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // chunk swizzles: 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
@@ -73,19 +80,76 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsig
   p3 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
 }
 
-// c + x y of two split operands, the small products first
-__device__ __forceinline__ f32x16 products(const bf16x8 (&x)[3], const bf16x8 (&y)[3], f32x16 c) {
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], y[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[2], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], y[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[1], c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], c, 0, 0, 0);
+// the three parts of eight values
+__device__ __forceinline__ void split_chunk(f32x4 x0, f32x4 x1, u32x4 (&y)[3]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    unsigned p1, p2, p3;
+    split_pair(e < 2 ? x0[2 * e] : x1[2 * e - 4], e < 2 ? x0[2 * e + 1] : x1[2 * e - 3], p1, p2, p3);
+    y[0][e] = p1;
+    y[1][e] = p2;
+    y[2][e] = p3;
+  }
 }
 
-template <int B>
-__global__ __launch_bounds__(256, 2) void attn_fp32_split_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                           const float* __restrict__ v, int64_t n_tokens, int64_t n_first,
+// 16 bytes per lane from a raw buffer straight into the LDS, and the descriptor of such a buffer; see attn_bf16.hip
+template <unsigned LDS_IMM>
+__device__ __forceinline__ void dma16(i32x4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
+  asm volatile(
+      "s_add_u32 m0, %0, %4\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds"
+      :
+      : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(LDS_IMM)
+      : "memory", "m0", "scc");
+}
+__device__ __forceinline__ i32x4 make_rsrc(const void* base, unsigned bytes) {
+  const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+  return i32x4{__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a))),
+               __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a >> 32) & 0xffffu)),
+               __builtin_amdgcn_readfirstlane(static_cast<int>(bytes)), 0x00020000};
+}
+
+// c + x y of two split operands, the small products first
+__device__ __forceinline__ f32x16 products(const bf16x8 (&x)[3], const bf16x8 (&y)[3], f32x16 c) {
+  constexpr int X[6] = {2, 0, 1, 1, 0, 0}, Y[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[X[i]], y[Y[i]], c, 0, 0, 0);
+  return c;
+}
+
+// the same; two such sums in turn, since an instruction that waits for the one before
+// it leaves the matrix pipe idle
+__device__ __forceinline__ void products(const bf16x8 (&x0)[3], const bf16x8 (&y0)[3], f32x16& c0, const bf16x8 (&x1)[3],
+                                         const bf16x8 (&y1)[3], f32x16& c1) {
+  constexpr int X[6] = {2, 0, 1, 1, 0, 0}, Y[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0[X[i]], y0[Y[i]], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[X[i]], y1[Y[i]], c1, 0, 0, 0);
+  }
+}
+
+// K and V split beforehand: token t of head h has kPartRow bytes at (h n_tokens + t) kPartRow, the three parts of its key, then
+// those of its value.  A thread splits eight dims of one of the two.
+constexpr int kPartRow = 6 * kD * 2;
+__global__ __launch_bounds__(256) void split_kv_kernel(const float* __restrict__ k, const float* __restrict__ v, int64_t chunks,
+                                                       unsigned char* __restrict__ parts) {
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (t >= chunks) return;
+  const float* const src = (blockIdx.y ? v : k) + t * 8;
+  const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
+  u32x4 y[3];
+  split_chunk(x0, x1, y);
+  unsigned char* const dst = parts + (t >> 3) * kPartRow + blockIdx.y * 3 * 128 + (t & 7) * 16;
+#pragma unroll
+  for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(dst + x * 128) = y[x];
+}
+
+template <int B, bool PRE>
+__global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                           const float* __restrict__ v, const unsigned char* __restrict__ parts,
+                                                           int64_t n_tokens, int64_t n_first,
                                                            int nb1, int nb, float scale_log2,
                                                            const int32_t* __restrict__ kv_idx,
                                                            const int32_t* __restrict__ kv_cnt, int idx_stride,
@@ -174,56 +238,10 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_split_kernel(const float* __
     for (int c = 0; c < 4; ++c) {
       const f32x4 x0 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g), x1 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g + 4);
       u32x4 y[3];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float a = (e < 2 ? x0[2 * e] : x1[2 * e - 4]) * scale_log2, b = (e < 2 ? x0[2 * e + 1] : x1[2 * e - 3]) * scale_log2;
-        unsigned p1, p2, p3;
-        split_pair(a, b, p1, p2, p3);
-        y[0][e] = p1;
-        y[1][e] = p2;
-        y[2][e] = p3;
-      }
+      split_chunk(x0 * scale_log2, x1 * scale_log2, y);
 #pragma unroll
       for (int x = 0; x < 3; ++x) qf[c][x] = __builtin_bit_cast(bf16x8, y[x]);
     }
-    // this thread's share of a tile: chunk (eight dims) tid % 8 of tile rows tid / 8 and 32 + tid / 8, of K and of V
-    const int lr = tid >> 3, lc = tid & 7;
-    f32x4 raw[2][2][2];  // [K, V][row][half of the chunk]
-    auto load = [&](int64_t key0, int valid) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = lr + 32 * i;
-        // keys past `valid` repeat the last one; they are masked
-        const int64_t at = head_off + (key0 + min(r, valid - 1)) * kD + 8 * lc;
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-          raw[0][i][x] = *reinterpret_cast<const f32x4*>(k + at + 4 * x);
-          raw[1][i][x] = *reinterpret_cast<const f32x4*>(v + at + 4 * x);
-        }
-      }
-    };
-    auto store = [&](int valid) {
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int r = lr + 32 * i;
-          u32x4 y[3];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float a = raw[t][i][e >> 1][2 * (e & 1)], b = raw[t][i][e >> 1][2 * (e & 1) + 1];
-            if (t == 1 && r >= valid) a = b = 0.f;  // the weight of these keys is 0, and the last one may be infinite
-            unsigned p1, p2, p3;
-            split_pair(a, b, p1, p2, p3);
-            y[0][e] = p1;
-            y[1][e] = p2;
-            y[2][e] = p3;
-          }
-          unsigned char* at = smem + t * 3 * kPlane + r * 128 + ((lc ^ (t ? swz_v(r) : swz_k(r))) << 4);
-#pragma unroll
-          for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[x];
-        }
-    };
     unsigned kaddr[4], vaddr[2];  // operand addresses in a part, see attn_bf16.hip
     {
       const int r = kh * 32 + n;
@@ -235,61 +253,165 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_split_kernel(const float* __
       for (int db = 0; db < 2; ++db)
         vaddr[db] = 3 * kPlane + key * 128 + (((db * 4 + 2 * (G & 1) + (j >> 1)) ^ swz_v(key)) << 4) + (j & 1) * 8;
     }
-    int64_t key0 = 0;
-    int valid = 0;
-    int piece = next_piece(0, key0, valid);
-    if (piece < pieces) load(key0, valid);
-    while (piece < pieces) {
-      const int here = valid;
-      store(here);
-      __syncthreads();
-      piece = next_piece(piece + 1, key0, valid);
-      if (piece < pieces) load(key0, valid);
-      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        bf16x8 kf[3];
+    bf16x8 pf[2][3];
+    // scores and weights of the K tile in the LDS; returns what weigh() does
+    auto scores = [&](int valid) -> float {
+      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s2 = s;  // dims 0 .. 31 and 32 .. 63
+      auto read_k = [&](int c, bf16x8 (&kf)[3]) {
 #pragma unroll
         for (int x = 0; x < 3; ++x) kf[x] = *reinterpret_cast<const bf16x8*>(smem + x * kPlane + kaddr[c]);
-        s = products(kf, qf[c], s);
+      };
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bf16x8 kf[2][3];
+        read_k(c, kf[0]);
+        read_k(c + 2, kf[1]);
+        products(kf[0], qf[c], s, kf[1], qf[c + 2], s2);
       }
-      const float a = weigh(s, here - 32 * kh);
-      bf16x8 pf[2][3];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] += s2[i];
+      const float a = weigh(s, valid - 32 * kh);
 #pragma unroll
       for (int cp = 0; cp < 2; ++cp) {
         u32x4 y[3];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          unsigned p1, p2, p3;
-          split_pair(s[8 * cp + 2 * e], s[8 * cp + 2 * e + 1], p1, p2, p3);
-          y[0][e] = p1;
-          y[1][e] = p2;
-          y[2][e] = p3;
-        }
+        split_chunk(f32x4{s[8 * cp], s[8 * cp + 1], s[8 * cp + 2], s[8 * cp + 3]}, f32x4{s[8 * cp + 4], s[8 * cp + 5], s[8 * cp + 6], s[8 * cp + 7]}, y);
 #pragma unroll
         for (int x = 0; x < 3; ++x) pf[cp][x] = __builtin_bit_cast(bf16x8, y[x]);
       }
-      // summed up apart and added with one fp32 rounding: the matrix instructions round a sum that has grown large worse
+      return a;
+    };
+    // output products of the V tile.  Summed up apart and added with one fp32 rounding: the matrix instructions round a sum that has
+    // grown large worse.
+    auto outputs = [&](float a) {
+      auto read_v = [&](int db, int cp, bf16x8 (&vf)[3]) {
 #pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        f32x16 t = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < 3; ++x) {
+          const unsigned char* p = smem + x * kPlane + vaddr[db] + 16 * cp * 128;
+          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 8 * 128));
+          const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
+          vf[x] = __builtin_bit_cast(bf16x8, u32x4{lo2[0], lo2[1], hi2[0], hi2[1]});
+        }
+      };
+      const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if constexpr (PRE) {  // one after the other: the registers are three workgroups'
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          f32x16 t = zero;
+#pragma unroll
+          for (int cp = 0; cp < 2; ++cp) {
+            bf16x8 vf[3];
+            read_v(db, cp, vf);
+            t = products(vf, pf[cp], t);
+          }
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[i]);
+        }
+      } else {
+        f32x16 t[2] = {zero, zero};
 #pragma unroll
         for (int cp = 0; cp < 2; ++cp) {
-          bf16x8 vf[3];
-#pragma unroll
-          for (int x = 0; x < 3; ++x) {
-            const unsigned char* p = smem + x * kPlane + vaddr[db] + 16 * cp * 128;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 8 * 128));
-            const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
-            vf[x] = __builtin_bit_cast(bf16x8, u32x4{lo2[0], lo2[1], hi2[0], hi2[1]});
-          }
-          t = products(vf, pf[cp], t);
+          bf16x8 vf[2][3];
+          read_v(0, cp, vf[0]);
+          read_v(1, cp, vf[1]);
+          products(vf[0], pf[cp], t[0], vf[1], pf[cp], t[1]);
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[i]);
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[db][i]);
+      }
+    };
+    int64_t key0 = 0;
+    int valid = 0;
+    int piece = next_piece(0, key0, valid);
+    if constexpr (PRE) {
+      // Direct to the LDS: load i of a wave covers rows 8 j .. 8 j + 7, j = wave + 4 (i / 3), of part i % 3; lane -> row 8 j + lane / 8
+      // and, at chunk position lane % 8, the chunk that belongs there.  Rows past the end of the head come as zeros, those past the end of
+      // a key block are the tokens that follow: their weight is 0 (and where they are not finite, see `bad` below).
+      const i32x4 rsrc = make_rsrc(parts + int64_t(h) * n_tokens * kPartRow, static_cast<unsigned>(n_tokens * kPartRow));
+      const unsigned lds = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) unsigned char*)smem)) + wave * 1024;
+      unsigned off[2][2];  // [K, V][row]
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = (wave + 4 * i) * 8 + (lane >> 3), c = lane & 7;
+        off[0][i] = r * kPartRow + ((c ^ swz_k(r)) << 4);
+        off[1][i] = r * kPartRow + 3 * 128 + ((c ^ swz_v(r)) << 4);
+      }
+      auto fetch = [&](auto tc, int64_t key0) {
+        constexpr int T = decltype(tc)::value;
+        const unsigned at = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(key0) * kPartRow);
+        const unsigned base = __builtin_amdgcn_readfirstlane(lds);
+        dma16<(3 * T + 0) * kPlane>(rsrc, off[T][0], at, base);
+        dma16<(3 * T + 1) * kPlane>(rsrc, off[T][0], at + 128, base);
+        dma16<(3 * T + 2) * kPlane>(rsrc, off[T][0], at + 256, base);
+        dma16<(3 * T + 0) * kPlane + 4096>(rsrc, off[T][1], at, base);
+        dma16<(3 * T + 1) * kPlane + 4096>(rsrc, off[T][1], at + 128, base);
+        dma16<(3 * T + 2) * kPlane + 4096>(rsrc, off[T][1], at + 256, base);
+      };
+      // K of the next tile is loaded under the output products, V under the scores of its own; each has one place in the LDS, which
+      // is free from the barrier on that ends the products with it.
+      auto arrived = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0): this wave's share has landed, and it has read what it had to
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      };
+      if (piece < pieces) fetch(std::integral_constant<int, 0>{}, key0);
+      while (piece < pieces) {
+        asm volatile("" ::: "memory");
+        arrived();
+        fetch(std::integral_constant<int, 1>{}, key0);
+        const int here = valid;
+        piece = next_piece(piece + 1, key0, valid);
+        const float a = scores(here);
+        asm volatile("" ::: "memory");
+        arrived();
+        if (piece < pieces) fetch(std::integral_constant<int, 0>{}, key0);
+        outputs(a);
       }
       __syncthreads();
+    } else {
+      // this thread's share of a tile: chunk (eight dims) tid % 8 of tile rows tid / 8 and 32 + tid / 8, of K and of V
+      const int lr = tid >> 3, lc = tid & 7;
+      f32x4 raw[2][2][2];  // [K, V][row][half of the chunk]
+      auto load = [&](int64_t key0, int valid) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int r = lr + 32 * i;
+          // keys past `valid` repeat the last one; they are masked
+          const int64_t at = head_off + (key0 + min(r, valid - 1)) * kD + 8 * lc;
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            raw[0][i][x] = *reinterpret_cast<const f32x4*>(k + at + 4 * x);
+            raw[1][i][x] = *reinterpret_cast<const f32x4*>(v + at + 4 * x);
+          }
+        }
+      };
+      auto store = [&](int valid) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int r = lr + 32 * i;
+            if (t == 1 && r >= valid) raw[t][i][0] = raw[t][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};  // their weight is 0, and the last one may be infinite
+            u32x4 y[3];
+            split_chunk(raw[t][i][0], raw[t][i][1], y);
+            unsigned char* at = smem + t * 3 * kPlane + r * 128 + ((lc ^ (t ? swz_v(r) : swz_k(r))) << 4);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[x];
+          }
+      };
+      if (piece < pieces) load(key0, valid);
+      while (piece < pieces) {
+        const int here = valid;
+        store(here);
+        __syncthreads();
+        piece = next_piece(piece + 1, key0, valid);
+        if (piece < pieces) load(key0, valid);
+        const float a = scores(here);
+        outputs(a);
+        __syncthreads();
+      }
     }
   };
 
@@ -564,22 +686,44 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, float* out,
                      float* lse, hipStream_t stream) {
+  return launch_attn_fp32_parts(q, k, v, heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse, nullptr, 0,
+                                stream);
+}
+
+int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
+                           int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, float* out,
+                           float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const int nb = static_cast<int>(split_blocks(n_tokens, n_first, block));
   const int nb1 = static_cast<int>(ceil_div(n_first, block));
   const float scale_log2 = softmax_scale * 1.4426950408889634f;
-  auto launch = [&](auto kernel, int rows) {
-    hipLaunchKernelGGL(kernel, dim3(nb * (block / rows), heads), dim3(256), 0, stream, q, k, v, n_tokens, n_first, nb1, nb,
-                       scale_log2, kv_idx, kv_cnt, idx_stride, out, lse);
+  const dim3 grid(nb * (block / 64), heads), grid32(nb * (block / 32), heads);
+  unsigned char* parts = nullptr;
+  auto launch_split = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, q, k, v, parts, n_tokens, n_first, nb1, nb, scale_log2, kv_idx, kv_cnt,
+                       idx_stride, out, lse);
+  };
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid32, dim3(256), 0, stream, q, k, v, n_tokens, n_first, nb1, nb, scale_log2, kv_idx, kv_cnt, idx_stride,
+                       out, lse);
   };
   // A unit of 64 rows to a workgroup where that keeps half of the CUs busy.  Dense, 32 rows on the fp32 instructions / 64 split: 86
   // units 65 / 96 us, 96 12 / 17, 172 201 / 188, 176 33 / 28, 272 69 / 54.
-  const bool split = int64_t(heads) * nb * (block / 64) > 128;
-  if (block == 64) {
-    if (split) launch(attn_fp32_split_kernel<64>, 64);
-    else launch(attn_fp32_kernel<64>, 32);
+  if (int64_t(heads) * nb * (block / 64) <= kFp32FewUnits) {
+    if (block == 64) launch(attn_fp32_kernel<64>);
+    else launch(attn_fp32_kernel<128>);
+    return check_hip(hipGetLastError(), "bsga fp32 attention launch");
+  }
+  const size_t need = static_cast<size_t>(heads) * static_cast<size_t>(n_tokens) * kPartRow;
+  if (need <= kPartsMaxBytes && workspace != nullptr && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
+    parts = static_cast<unsigned char*>(workspace);
+    const int64_t chunks = int64_t(heads) * n_tokens * (kD / 8);
+    hipLaunchKernelGGL(split_kv_kernel, dim3(static_cast<unsigned>(ceil_div(chunks, 256)), 2), dim3(256), 0, stream, k, v, chunks, parts);
+    if (int rc = check_hip(hipGetLastError(), "bsga fp32 attention (operand split)")) return rc;
+    if (block == 64) launch_split(attn_fp32_split_kernel<64, true>);
+    else launch_split(attn_fp32_split_kernel<128, true>);
   } else {
-    if (split) launch(attn_fp32_split_kernel<128>, 64);
-    else launch(attn_fp32_kernel<128>, 32);
+    if (block == 64) launch_split(attn_fp32_split_kernel<64, false>);
+    else launch_split(attn_fp32_split_kernel<128, false>);
   }
   return check_hip(hipGetLastError(), "bsga fp32 attention launch");
 }

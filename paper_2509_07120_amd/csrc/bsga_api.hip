@@ -100,6 +100,10 @@ static int attn_common(const char* fn, const void* q, const void* k, const void*
   if (dtype == BSGA_BF16)
     return launch_attn_bf16(q, k, v, heads, n_tokens, n_first, block, block_k, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse,
                             workspace, workspace_bytes, s);
+  if (workspace && launch_attn_fp32_parts)
+    return launch_attn_fp32_parts(static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v),
+                                  heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride,
+                                  static_cast<float*>(out), lse, workspace, workspace_bytes, s);
   return launch_attn_fp32(static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v),
                           heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride,
                           static_cast<float*>(out), lse, s);
@@ -224,6 +228,11 @@ size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int hea
   const size_t order = attn_workspace(dtype, heads, n_tokens);
   // 256 more to align the partial results
   return order > 0 && attn_stream_shape(heads, n_tokens) ? order + kStreamBytes + 256 : order;
+}
+
+size_t bsga_attn_fp32_parts_bytes(int heads, int64_t n_tokens, int head_dim, double kept) {
+  if (heads < 1 || heads > 65535 || n_tokens < 1 || n_tokens > (int64_t(1) << 24) || head_dim != 64) return 0;
+  return attn_fp32_parts_bytes(heads, n_tokens, kept);
 }
 
 int bsga_sparse_attn(const void* q, const void* k, const void* v, int dtype, int heads, int64_t n_tokens,

@@ -92,6 +92,21 @@ inline bool chooses_pairs(int heads, int nb, int nbk) {
   return int64_t(heads) * nb >= 4096 && nb >= 256 && nbk <= kPairMaxBlocks;
 }
 
+constexpr int64_t kFp32FewUnits = 128;  // units of 64 rows, of which an fp32 launch goes to attn_fp32_kernel
+// Bytes that K and V of an fp32 call take when they are split in three bf16 parts before the attention and not by every workgroup
+// for itself; 0 where that gives nothing.  The pass over K and V costs about 10 us, the attention's steps get a sixth shorter.  Split by the
+// workgroups / before, us: 688 rows of 64 that keep 4 tiles each 28 / 35, 9 tiles 48 / 50, 15 85 / 77, 39 203 / 167; 1,376 rows,
+// 9 tiles 91 / 92, 17 178 / 162, 77 746 / 626.  Up to 512 rows the chip holds them all at once, and a step is only
+// shorter, not cheaper: 344 rows, 15 tiles 49 / 54, 21 67 / 68, 30 93 / 90, 77 228 / 203.  The call uses the room whenever it has
+// it; `kept` is what the caller expects the lists to hold of all key blocks.
+constexpr size_t kPartsMaxBytes = size_t(256) << 20;  // 21,845 tokens of 16 heads; fp32 is for shorter sequences
+inline size_t attn_fp32_parts_bytes(int heads, int64_t n_tokens, double kept) {
+  const int64_t tiles = ceil_div(n_tokens, 64), rows = heads * tiles;
+  const size_t bytes = static_cast<size_t>(heads) * static_cast<size_t>(n_tokens) * (6 * 64 * 2);
+  if (rows <= kFp32FewUnits || bytes > kPartsMaxBytes) return 0;
+  return kept * static_cast<double>(tiles) >= (rows > 512 ? 12.0 : 25.0) ? bytes : 0;
+}
+
 // Kernel launchers.  Arguments are already validated.
 int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
                 hipStream_t stream);
@@ -117,6 +132,13 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
                      int idx_stride, float* out, float* lse, hipStream_t stream);
+
+// The same with room for K and V split beforehand (ignored if it is too small or misaligned).  Weak, as launch_pool_both: without it
+// fp32 calls take the one above.
+int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
+                           int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
+                           int idx_stride, float* out, float* lse, void* workspace, size_t workspace_bytes,
+                           hipStream_t stream) __attribute__((weak));
 
 int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t sink_bytes, double* flops,
                       hipStream_t stream);
