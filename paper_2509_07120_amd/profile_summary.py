@@ -26,7 +26,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROFILES = os.path.join(ROOT, "profiles")
 ATTN_SOURCE = os.path.join(ROOT, "paper_2509_07120_amd", "csrc", "attn_bf16.hip")
-KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "order_one", "order_hist", "order_merge", "order_scan",
+KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "choose_kernel", "order_one", "order_hist", "order_merge", "order_scan",
            "order_place", "gather_kernel", "probe_kernel")
 
 
@@ -59,6 +59,14 @@ def dispatches(folder: str):
     return [out[k] for k in sorted(out)]
 
 
+LEFT_AT_ONCE_MS = 0.1  # a large sparse call enqueues two attention kernels, of which one finds that it is not meant and leaves
+
+
+def attention(rows):
+    """Dispatches of the attention kernel that did the work."""
+    return [x for x in rows if "attn_bf16" in x["name"] and x["ms"] > LEFT_AT_ONCE_MS]
+
+
 # --------------------------------------------------------------------------------------------- stats
 def cmd_stats(folder: str, bench_json: str) -> None:
     bench = json.loads(open(bench_json).read().strip().splitlines()[-1])
@@ -70,7 +78,7 @@ def cmd_stats(folder: str, bench_json: str) -> None:
                          float(r["Percentage"])))
     trace = [(r["Kernel_Name"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6)
              for r in csv.DictReader(open(one(folder, "kernel_trace.csv")))]
-    attn = [ms for n, ms in trace if "attn_bf16" in n]
+    attn = [x["ms"] for x in attention([{"name": n, "ms": ms} for n, ms in trace])]
     steps, warmup = bench["steps"], bench["warmup"]
     sparse_timed = attn[warmup:warmup + steps]
     rest = attn[warmup + steps:]
@@ -98,8 +106,9 @@ two.  The per-dispatch trace (`stats_kernel_trace.csv`) separates them.
         for n, c, a, mn, mx, p in rows:
             f.write(f"| {n} | {c} | {a:.4f} | {mn:.4f} | {mx:.4f} | {p:.3f} |\n")
         f.write(f"""
-`pool_kernel` runs twice per step (Q and K); the four `order_*` kernels build the launch order of the sparse
-attention kernel and run once per sparse launch.
+`pool_kernel` pools Q and K in one launch; `choose_kernel` decides whether rows are taken in pairs and the four `order_*`
+kernels build the launch order; a sparse call enqueues the attention kernel in both forms, and the one that was not
+chosen leaves at once (the minimum in its row above).
 
 ## attn_bf16_kernel per dispatch (stats_kernel_trace.csv), ms
 
@@ -126,8 +135,7 @@ def cmd_traffic(d_fetch: str, d_write: str, d_tcc: str) -> None:
     copy_f = [x["FETCH_SIZE"] for x in F if "copyBuffer" in x["name"] and x["grid"] == 131072][0]
     copy_w = [x["WRITE_SIZE"] for x in W if "copyBuffer" in x["name"] and x["grid"] == 131072][0]
     sf, sw = 1048576.0 / copy_f, 1048576.0 / copy_w
-    aF = [x for x in F if "attn_bf16" in x["name"]]
-    aW = [x for x in W if "attn_bf16" in x["name"]]
+    aF, aW = attention(F), attention(W)
     n_sparse = 3  # bench.py --steps 2 --warmup 1: three sparse launches, then the dense ones
     sparse_f = sum(x["FETCH_SIZE"] for x in aF[1:n_sparse]) / (n_sparse - 1)
     sparse_w = sum(x["WRITE_SIZE"] for x in aW[1:n_sparse]) / (n_sparse - 1)
@@ -166,7 +174,7 @@ Counter values per dispatch (KiB, unscaled):
 
 | kernel | FETCH_SIZE | WRITE_SIZE |
 |---|---|---|
-| pool_kernel (one tensor) | {mean_of(F, 'pool_kernel', 'FETCH_SIZE'):.1f} | {mean_of(W, 'pool_kernel', 'WRITE_SIZE'):.1f} |
+| pool_kernel (Q and K) | {mean_of(F, 'pool_kernel', 'FETCH_SIZE'):.1f} | {mean_of(W, 'pool_kernel', 'WRITE_SIZE'):.1f} |
 | logits_kernel | {mean_of(F, 'logits_kernel', 'FETCH_SIZE'):.1f} | {mean_of(W, 'logits_kernel', 'WRITE_SIZE'):.1f} |
 | select_kernel | {mean_of(F, 'select_kernel', 'FETCH_SIZE'):.1f} | {mean_of(W, 'select_kernel', 'WRITE_SIZE'):.1f} |
 | attn_bf16_kernel, sparse launches (1 warm-up + 2 timed) | {', '.join(f"{x['FETCH_SIZE']:.0f}" for x in aF[:n_sparse])} | {', '.join(f"{x['WRITE_SIZE']:.0f}" for x in aW[:n_sparse])} |
@@ -184,17 +192,17 @@ L2 (TCC) requests of the attention kernel per launch:
 | launch | TCC_REQ | TCC_HIT | TCC_MISS | hit rate | ms |
 |---|---|---|---|---|---|
 """)
-        for i, x in enumerate(y for y in T if "attn_bf16" in y["name"]):
+        for i, x in enumerate(attention(T)):
             kind = "sparse" if i < n_sparse else "dense"
             f.write(f"| {kind} {i} | {x['TCC_REQ_sum']:.4g} | {x['TCC_HIT_sum']:.4g} | {x['TCC_MISS_sum']:.4g} | "
                     f"{x['TCC_HIT_sum'] / x['TCC_REQ_sum']:.3f} | {x['ms']:.2f} |\n")
         f.write("""
 Reading.  The write side equals the output tensor (137,400 x 16 x 64 x 2 B = 274,805 KiB).  The fetch side is what the
 eight L2 caches request from the fabric (Infinity Cache hits included; the counter sits at the L2 boundary): Q, K, V
-are 0.84 GB, and every workgroup streams its ~966 kept K and V tiles (31 MB) through LDS: L2 requests of 128 B, none of
-them absorbed by the CUs' own caches.  The 64 workgroups resident on one XCD walk the same head's keys; they start
+are 0.84 GB, and every workgroup streams the ~966 K and V tiles (31 MB) that each of its two rows keeps through LDS,
+those of both (nine tenths of them) once.  The 32 workgroups resident on one XCD walk the same head's keys; they start
 together and have rows of nearly equal length, so they stay roughly in step and most requests hit in L2.  If they were
-exactly in step each tile would be fetched once per XCD per round (about 9.4 GB per launch).  The 4 MB L2 cannot hold
+exactly in step each tile would be fetched once per XCD per round (about 9.4 GB per launch; the dense launch comes close).  The 4 MB L2 cannot hold
 the 35 MB of one head's K and V, so workgroups that fall more than about 64 tiles behind miss; the misses are served by
 the Infinity Cache (one head fits it), not by HBM.
 """)
@@ -217,7 +225,7 @@ def cmd_pipes(*folders: str) -> None:
     bench command.  Counters of different runs are merged per dispatch position of the attention kernel."""
     merged = None
     for d in folders:
-        attn = [x for x in dispatches(d) if "attn_bf16" in x["name"]]
+        attn = attention(dispatches(d))
         if merged is None:
             merged = [dict(x) for x in attn]
         else:
@@ -279,8 +287,7 @@ SQ_WAVE_CYCLES counts, in units of 4 cycles, the time waves are resident; the "w
 # ---------------------------------------------------------------------------------------------- topk
 def cmd_topk(d_tcc: str, d_pipes: str) -> None:
     """Counters of the short-row regime (top-k only, rho = 0.9) next to the dense launch of the same run."""
-    T = [x for x in dispatches(d_tcc) if "attn_bf16" in x["name"]]
-    P = [x for x in dispatches(d_pipes) if "attn_bf16" in x["name"]]
+    T, P = attention(dispatches(d_tcc)), attention(dispatches(d_pipes))
     n_sparse = 3
     cmd = ("cd /tmp && export TMPDIR=/tmp && rocprofv3 --pmc {c} -d <out>/{d} -o pmc --output-format csv -- python3 "
            "<repo>/bench.py --no-cpu-baseline --no-probe --rows none --tau 0 --rho 0.9 --copy-calibration --steps 2 "
