@@ -78,14 +78,19 @@ inline bool pairs_rows(int block, int heads, int nb, int nbk) {
   return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
 }
 
-// Whether a dense launch takes blocks of 128 two to a workgroup of eight waves (see DUO): where the busiest CU then has no more rows
-// to work on than with a row to each workgroup, or has twenty and more.  Row by row / in pairs, 16 heads (rows per CU): 2,748
-// tokens (1.4) 41.6 / 40.4 us, 6,870 (3.4) 186 / 176, 10,992 (5.4) 435 / 412, 43,968 (21.5)
-// 6,310 / 6,100, 137,400 (67) 60.8 / 58.0 ms; but 4,122 (2.1) 89 / 108, 8,244 (4.1) 270 / 305, 16,488 (8.1) 946 / 979,
-// 21,984 (10.8) 1,621 / 1,629.
+// Whether a dense launch takes blocks of 128 two to a workgroup of eight waves (see DUO).  Row by row / in pairs, us, 16 heads:
+//  - Up to eight rows per CU: where the busiest CU then has no more rows to work on than with a row to each workgroup.  2,748
+//    tokens (1.4 rows) 41.6 / 40.4, 6,870 (3.4) 186 / 176, 10,992 (5.4) 435 / 412, 16,300 (8) 884 / 857; but 4,122 (2.1) 89 / 108,
+//    8,244 (4.1) 270 / 305.
+//  - Up to twelve: rows alone even out by then, so the pairs' last round has to be nearly full.  20,400 (10) 1,375 / 1,329, 24,400 (11.9)
+//    1,961 / 1,895; but 19,000 (9.3) 1,225 / 1,220, 21,984 (10.8) 1,621 / 1,629, 23,300 (11.4) 1,776 / 1,800.
+//  - From there on nothing is to be gained, 27,000 (13.2) 2,444 / 2,449, 32,500 (15.9) 3,461 / 3,444, 35,000 (17.1) 4,041 / 4,063, until twenty:
+//    43,968 (21.5) 6,310 / 6,100, 137,400 (67) 60.8 / 58.0 ms.
 inline bool dense_pairs(int heads, int nb) {
-  const int64_t rows = int64_t(heads) * nb, pairs = int64_t(heads) * ((nb + 1) / 2);
-  return rows >= 20 * 256 || 2 * ceil_div(pairs, 256) <= ceil_div(rows, 256);
+  const int64_t rows = int64_t(heads) * nb, rounds = ceil_div(int64_t(heads) * ((nb + 1) / 2), 256);  // of pairs
+  if (rows >= 20 * 256) return true;
+  if (rows <= 8 * 256) return 2 * rounds <= ceil_div(rows, 256);
+  return rows <= 12 * 256 && 50 * 2 * rounds * 256 <= 51 * rows;
 }
 // Whether a sparse launch of blocks of 128 is large enough for choose_kernel to look at its lists, and these fit the LDS.
 inline bool chooses_pairs(int heads, int nb, int nbk) {
