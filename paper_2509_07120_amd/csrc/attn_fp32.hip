@@ -2,7 +2,7 @@
 // Two kernels: attn_fp32_split_kernel for launches of more than 128 units of 64 query rows, attn_fp32_kernel for the rest.
 //
 // attn_fp32_split_kernel: both products on the bf16 matrix instructions, every fp32 operand split in three.
-//   x = x1 + x2 + x3, eight bits each, what is left over is below 2^-25 |x|.  Of the nine products of two such sums
+//   x = x1 + x2 + x3, eight bits each, and nothing is left over (almost: see split_key_value).  Of the nine products of two such sums
 //   the six of the order of 2^-18 and above are taken (11, 12, 21, 22, 13, 31), the small ones first, accumulated in fp32.
 //   A bf16 product is exact in fp32 and 16 of them are summed per instruction, so a sum has fewer roundings than
 //   on v_mfma_f32_32x32x2; the output products of a tile are summed apart and added to the output with one more.  Error of the output
@@ -21,7 +21,7 @@
 //   products, and no need).  Rows are 128 bytes, chunks of 16 bytes permuted as in the bf16 kernel, whose operand
 //   layouts these are: S^T = K Q^T leaves the weights where they are the B operand of O^T = V^T P^T, and V^T comes by
 //   transposing LDS reads.
-//   Values the split cannot hold (infinities, NaN, what rounds to infinity in bf16) make a row sum or an output something else
+//   Values the split cannot hold (infinities, NaN, very small ones) make a row sum or an output something else
 //   than a finite number.  The workgroup then starts over with fp32 instructions (pass<true>: no LDS, no prefetch; slow).
 //   16 heads, dense, 32 rows or 64 on the fp32 instructions / so: 700 tokens 33 / 28 us, 1,374 109 / 70, 2,748 288 / 219, 5,496
 //   1,074 / 664 (186 TFLOP/s; a library fp32 GEMM reaches 154).
@@ -69,8 +69,8 @@ __device__ __forceinline__ int swz_k(int row) { return (row ^ (row >> 3)) & 7; }
 __device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
 
 // the three parts of a and b, packed in pairs.  The first is rounded to nearest, so that the rest has either sign; the others
-// are cut off, which is a byte permutation instead of a conversion of twice the time.
-__device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3) {
+// are cut off, which is a byte permutation instead of a conversion of twice the time.  `left`: what the third parts are cut from, ORed.
+__device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3, unsigned& left) {
   p1 = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
   a -= __uint_as_float(p1 << 16);
   b -= __uint_as_float(p1 & 0xffff0000u);
@@ -78,18 +78,43 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsig
   a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
   b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
   p3 = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+  left |= __float_as_uint(a) | __float_as_uint(b);
 }
 
-// the three parts of eight values
-__device__ __forceinline__ void split_chunk(f32x4 x0, f32x4 x1, u32x4 (&y)[3]) {
+// the three parts of eight values; returns `left` of all of them
+__device__ __forceinline__ unsigned split_chunk(f32x4 x0, f32x4 x1, u32x4 (&y)[3]) {
+  unsigned left = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     unsigned p1, p2, p3;
-    split_pair(e < 2 ? x0[2 * e] : x1[2 * e - 4], e < 2 ? x0[2 * e + 1] : x1[2 * e - 3], p1, p2, p3);
+    split_pair(e < 2 ? x0[2 * e] : x1[2 * e - 4], e < 2 ? x0[2 * e + 1] : x1[2 * e - 3], p1, p2, p3, left);
     y[0][e] = p1;
     y[1][e] = p2;
     y[2][e] = p3;
   }
+  return left;
+}
+
+// Three times eight bits are a whole fp32 number, down to about 2^-110: bf16 ends 16 bits above fp32 (the matrix
+// instructions keep subnormal numbers of both), and what is cut off there, half of 2^-133, is 7e-5 of 2^-120.
+//  - A value counts to its own size: those that the parts do not hold whole are left to the fp32 instructions.
+//  - Keys and queries count by what they do to a logit, which is nothing (64 products of 2^96 and 2^-134) as long as both are below
+//    2^96: larger ones are left to the fp32 instructions.
+//  - A weight of less than 2^-110 of its row's largest is off by 2^-134 of that one.  Nothing is done about it.
+// The mark is a NaN in the key: it makes the row sums of all who list it NaN.  It also tells of values that are not
+// finite, so that it is known before the products with them; one in the shadow of a ragged block tells by itself.
+constexpr unsigned kCutOff = 0xffffu;     // bits of `left` that the third parts have no room for
+constexpr unsigned kLarge = 0x40000000u;  // set where something is left of 2 and more (the number is 2^16 and more), or of no number
+constexpr float kLargestKey = 0x1p96f;
+__device__ __forceinline__ void split_key_value(f32x4 k0, f32x4 k1, f32x4 v0, f32x4 v1, u32x4 (&ky)[3], u32x4 (&vy)[3]) {
+  const unsigned left_k = split_chunk(k0, k1, ky), left_v = split_chunk(v0, v1, vy);
+  bool mark = (left_v & kCutOff) != 0u;
+  if (((left_k | left_v) & kLarge) != 0u) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      mark = mark || !(fabsf(v0[e]) < INFINITY) || !(fabsf(v1[e]) < INFINITY) || !(fabsf(k0[e]) < kLargestKey) || !(fabsf(k1[e]) < kLargestKey);
+  }
+  if (mark) ky[0][0] |= 0x7fffu;
 }
 
 // 16 bytes per lane from a raw buffer straight into the LDS, and the descriptor of such a buffer; see attn_bf16.hip
@@ -131,19 +156,22 @@ __device__ __forceinline__ void products(const bf16x8 (&x0)[3], const bf16x8 (&y
 }
 
 // K and V split beforehand: token t of head h has kPartRow bytes at (h n_tokens + t) kPartRow, the three parts of its key, then
-// those of its value.  A thread splits eight dims of one of the two.
+// those of its value.  A thread splits eight dims of both.
 constexpr int kPartRow = 6 * kD * 2;
 __global__ __launch_bounds__(256) void split_kv_kernel(const float* __restrict__ k, const float* __restrict__ v, int64_t chunks,
                                                        unsigned char* __restrict__ parts) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (t >= chunks) return;
-  const float* const src = (blockIdx.y ? v : k) + t * 8;
-  const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
-  u32x4 y[3];
-  split_chunk(x0, x1, y);
-  unsigned char* const dst = parts + (t >> 3) * kPartRow + blockIdx.y * 3 * 128 + (t & 7) * 16;
+  const f32x4* const kp = reinterpret_cast<const f32x4*>(k + t * 8);
+  const f32x4* const vp = reinterpret_cast<const f32x4*>(v + t * 8);
+  u32x4 ky[3], vy[3];
+  split_key_value(kp[0], kp[1], vp[0], vp[1], ky, vy);
+  unsigned char* const dst = parts + (t >> 3) * kPartRow + (t & 7) * 16;
 #pragma unroll
-  for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(dst + x * 128) = y[x];
+  for (int x = 0; x < 3; ++x) {
+    *reinterpret_cast<u32x4*>(dst + x * 128) = ky[x];
+    *reinterpret_cast<u32x4*>(dst + (3 + x) * 128) = vy[x];
+  }
 }
 
 template <int B, bool PRE>
@@ -239,6 +267,9 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
       const f32x4 x0 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g), x1 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g + 4);
       u32x4 y[3];
       split_chunk(x0 * scale_log2, x1 * scale_log2, y);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)  // as keys
+        if (!(fabsf((e < 4 ? x0[e] : x1[e - 4]) * scale_log2) < kLargestKey)) y[0][0] |= 0x7fffu;
 #pragma unroll
       for (int x = 0; x < 3; ++x) qf[c][x] = __builtin_bit_cast(bf16x8, y[x]);
     }
@@ -389,17 +420,18 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
       };
       auto store = [&](int valid) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < 2; ++i) {
+          const int r = lr + 32 * i;
+          if (r >= valid) raw[1][i][0] = raw[1][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};  // their weight is 0, and the last one may be infinite
+          u32x4 y[2][3];
+          split_key_value(raw[0][i][0], raw[0][i][1], raw[1][i][0], raw[1][i][1], y[0], y[1]);
 #pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const int r = lr + 32 * i;
-            if (t == 1 && r >= valid) raw[t][i][0] = raw[t][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};  // their weight is 0, and the last one may be infinite
-            u32x4 y[3];
-            split_chunk(raw[t][i][0], raw[t][i][1], y);
+          for (int t = 0; t < 2; ++t) {
             unsigned char* at = smem + t * 3 * kPlane + r * 128 + ((lc ^ (t ? swz_v(r) : swz_k(r))) << 4);
 #pragma unroll
-            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[x];
+            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[t][x];
           }
+        }
       };
       if (piece < pieces) load(key0, valid);
       while (piece < pieces) {
@@ -717,7 +749,7 @@ int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int h
   if (need <= kPartsMaxBytes && workspace != nullptr && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
     parts = static_cast<unsigned char*>(workspace);
     const int64_t chunks = int64_t(heads) * n_tokens * (kD / 8);
-    hipLaunchKernelGGL(split_kv_kernel, dim3(static_cast<unsigned>(ceil_div(chunks, 256)), 2), dim3(256), 0, stream, k, v, chunks, parts);
+    hipLaunchKernelGGL(split_kv_kernel, dim3(static_cast<unsigned>(ceil_div(chunks, 256))), dim3(256), 0, stream, k, v, chunks, parts);
     if (int rc = check_hip(hipGetLastError(), "bsga fp32 attention (operand split)")) return rc;
     if (block == 64) launch_split(attn_fp32_split_kernel<64, true>);
     else launch_split(attn_fp32_split_kernel<128, true>);

@@ -42,6 +42,35 @@ def test_error_against_64_bits(B, qs, ks, vs):
         assert ((out.double() - o).norm() / o.norm()).item() <= 3.5e-7  # on the fp32 instructions: 4.1e-7
 
 
+@pytest.mark.parametrize("room", [False, True])     # K and V split by each workgroup, or once into the workspace
+@pytest.mark.parametrize("qs,ks,vs", [(1, 1, 2.0 ** -99), (1, 1, 2.0 ** -101), (1, 1, 2.0 ** -112), (1, 1, 1e-34), (1, 1, 1e-36), (1, 1, 2e-38),
+                                      (1e36, 1e-37, 1), (1e-37, 1e36, 1)])
+def test_operands_whose_low_parts_end_below_bf16(B, room, qs, ks, vs):
+    """Values of one size, so that each counts, and keys or queries so small that only the size of the others makes them count."""
+    q, k, v = _qkv(7)
+    v = v.sign() * (1.0 + v.abs().clamp(max=1.0)) * vs
+    q, k = q * qs, k * ks
+    out = B.bsga_dense_attn(q, k, v, workspace=torch.empty(H * N * 768 if room else 16, dtype=torch.uint8, device="cuda"))
+    o, _ = _float64(q, k, v)
+    size = float((q.double().norm(dim=-1).max() * k.double().norm(dim=-1).max()) / 8.0)
+    # as above; values of both signs cancel to a fifteenth of their size, so what fp32 sums round counts for more
+    assert ((out.double() - o).norm() / o.norm()).item() <= 2.0 ** -24 * (8.0 + 2.0 * size)
+
+
+def test_one_small_value(B):
+    """A column of small values beside ordinary ones, and one small value in a column of zeros: each to its own size."""
+    q, k, v = _qkv(8)
+    v[:, :, 9] = (1.0 + v[:, :, 9].abs()) * 1e-35
+    v[:, :, 10] = 0.0
+    v[3, 100, 10] = 3e-36
+    out, (o, _) = B.bsga_dense_attn(q, k, v).double(), _float64(q, k, v)
+    size = float((q.double().norm(dim=-1).max() * k.double().norm(dim=-1).max()) / 8.0)
+    bar = 2.0 ** -24 * (8.0 + 2.0 * size)
+    assert ((out - o)[..., 9].norm() / o[..., 9].norm()).item() <= bar
+    assert ((out - o)[3, :, 10].abs() / o[3, :, 10].clamp(min=2.0 ** -126)).max().item() <= 4 * bar   # weights down to 2^-10 of the sum
+    assert (out[torch.arange(H) != 3, :, 10] == 0).all()
+
+
 @pytest.mark.parametrize("block", [64, 128])
 @pytest.mark.parametrize("what", ["q inf", "k inf", "v inf", "v nan", "v rounds to inf", "q rounds to inf", "k -inf"])
 def test_values_that_the_parts_cannot_hold(B, what, block):
