@@ -2,7 +2,7 @@
 // Two kernels: attn_fp32_split_kernel for launches of more than 128 units of 64 query rows, attn_fp32_kernel for the rest.
 //
 // attn_fp32_split_kernel: both products on the bf16 matrix instructions, every fp32 operand split in three.
-//   x = x1 + x2 + x3, eight bits each, and nothing is left over (almost: see split_key_value).  Of the nine products of two such sums
+//   x = x1 + x2 + x3, eight bits each, and nothing is left over (almost: see kCutOff).  Of the nine products of two such sums
 //   the six of the order of 2^-18 and above are taken (11, 12, 21, 22, 13, 31), the small ones first, accumulated in fp32.
 //   A bf16 product is exact in fp32 and 16 of them are summed per instruction, so a sum has fewer roundings than
 //   on v_mfma_f32_32x32x2; the output products of a tile are summed apart and added to the output with one more.  Error of the output
@@ -21,8 +21,10 @@
 //   products, and no need).  Rows are 128 bytes, chunks of 16 bytes permuted as in the bf16 kernel, whose operand
 //   layouts these are: S^T = K Q^T leaves the weights where they are the B operand of O^T = V^T P^T, and V^T comes by
 //   transposing LDS reads.
-//   Values the split cannot hold (infinities, NaN, very small ones) make a row sum or an output something else
-//   than a finite number.  The workgroup then starts over with fp32 instructions (pass<true>: no LDS, no prefetch; slow).
+//   Values the split cannot hold (infinities, NaN, very small ones, see below) make a row sum or an output something else
+//   than a finite number.  The unit then starts over on fp32 instructions (unit_fp32).  16 heads of 2,748 tokens, dense, with the workspace /
+//   without, 181 / 224 us: one NaN in a head 300 / 369, NaN in every tile 338 / 367, an infinity in the last token of each head, which is met
+//   at the end, 478 / 548, all values of 1e-36 344 / 368.  On the fp32 instructions throughout 290.
 //   16 heads, dense, 32 rows or 64 on the fp32 instructions / so: 700 tokens 33 / 28 us, 1,374 109 / 70, 2,748 288 / 219, 5,496
 //   1,074 / 664 (186 TFLOP/s; a library fp32 GEMM reaches 154).
 //   Measured and not taken: the next tile's split and the weights interleaved with the products in one wave (820 us: what
@@ -96,26 +98,15 @@ __device__ __forceinline__ unsigned split_chunk(f32x4 x0, f32x4 x1, u32x4 (&y)[3
 }
 
 // Three times eight bits are a whole fp32 number, down to about 2^-110: bf16 ends 16 bits above fp32 (the matrix
-// instructions keep subnormal numbers of both), and what is cut off there, half of 2^-133, is 7e-5 of 2^-120.
-//  - A value counts to its own size: those that the parts do not hold whole are left to the fp32 instructions.
-//  - Keys and queries count by what they do to a logit, which is nothing (64 products of 2^96 and 2^-134) as long as both are below
-//    2^96: larger ones are left to the fp32 instructions.
-//  - A weight of less than 2^-110 of its row's largest is off by 2^-134 of that one.  Nothing is done about it.
-// The mark is a NaN in the key: it makes the row sums of all who list it NaN.  It also tells of values that are not
-// finite, so that it is known before the products with them; one in the shadow of a ragged block tells by itself.
-constexpr unsigned kCutOff = 0xffffu;     // bits of `left` that the third parts have no room for
-constexpr unsigned kLarge = 0x40000000u;  // set where something is left of 2 and more (the number is 2^16 and more), or of no number
-constexpr float kLargestKey = 0x1p96f;
-__device__ __forceinline__ void split_key_value(f32x4 k0, f32x4 k1, f32x4 v0, f32x4 v1, u32x4 (&ky)[3], u32x4 (&vy)[3]) {
-  const unsigned left_k = split_chunk(k0, k1, ky), left_v = split_chunk(v0, v1, vy);
-  bool mark = (left_v & kCutOff) != 0u;
-  if (((left_k | left_v) & kLarge) != 0u) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      mark = mark || !(fabsf(v0[e]) < INFINITY) || !(fabsf(v1[e]) < INFINITY) || !(fabsf(k0[e]) < kLargestKey) || !(fabsf(k1[e]) < kLargestKey);
-  }
-  if (mark) ky[0][0] |= 0x7fffu;
-}
+// instructions keep subnormal numbers of both), and what is cut off there, up to 2^-133, is 1e-4 of 2^-120.
+//  - A value counts to its own size.  One that the parts do not hold whole is reported by the unit that splits it, or written as a NaN
+//    beforehand, and so come the outputs of all who list its key.
+//  - Keys and queries count by what they do to a logit, which is nothing (64 products of 2^96 and 2^-133) as long as the key is whole
+//    or the query below 2^96, and the other way round.  It is queries that are looked at: those below 2^-110 or from 2^96 on become NaN.
+//  - A weight of less than 2^-110 of its row's largest is off by up to 2^-133 of that one.  Nothing is done about it.
+// The unit then starts over on fp32 instructions, see unit_fp32.
+constexpr unsigned kCutOff = 0xffffu;  // bits of `left` that the third parts have no room for
+__device__ __forceinline__ void mark(u32x4 (&y)[3]) { y[2][0] |= 0x7fffu; }
 
 // 16 bytes per lane from a raw buffer straight into the LDS, and the descriptor of such a buffer; see attn_bf16.hip
 template <unsigned LDS_IMM>
@@ -133,6 +124,13 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, unsigned bytes) {
   return i32x4{__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a))),
                __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a >> 32) & 0xffffu)),
                __builtin_amdgcn_readfirstlane(static_cast<int>(bytes)), 0x00020000};
+}
+
+// the lane's number, through an instruction that the compiler does not see through; see attn_bf16.hip
+__device__ __forceinline__ int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
 }
 
 // c + x y of two split operands, the small products first
@@ -156,84 +154,61 @@ __device__ __forceinline__ void products(const bf16x8 (&x0)[3], const bf16x8 (&y
 }
 
 // K and V split beforehand: token t of head h has kPartRow bytes at (h n_tokens + t) kPartRow, the three parts of its key, then
-// those of its value.  A thread splits eight dims of both.
+// those of its value.  A thread splits eight dims of one of the two.
 constexpr int kPartRow = 6 * kD * 2;
 __global__ __launch_bounds__(256) void split_kv_kernel(const float* __restrict__ k, const float* __restrict__ v, int64_t chunks,
                                                        unsigned char* __restrict__ parts) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (t >= chunks) return;
-  const f32x4* const kp = reinterpret_cast<const f32x4*>(k + t * 8);
-  const f32x4* const vp = reinterpret_cast<const f32x4*>(v + t * 8);
-  u32x4 ky[3], vy[3];
-  split_key_value(kp[0], kp[1], vp[0], vp[1], ky, vy);
-  unsigned char* const dst = parts + (t >> 3) * kPartRow + (t & 7) * 16;
+  const float* const src = (blockIdx.y ? v : k) + t * 8;
+  const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
+  u32x4 y[3];
+  if ((split_chunk(x0, x1, y) & kCutOff) != 0u && blockIdx.y) mark(y);
+  unsigned char* const dst = parts + (t >> 3) * kPartRow + blockIdx.y * 3 * 128 + (t & 7) * 16;
 #pragma unroll
-  for (int x = 0; x < 3; ++x) {
-    *reinterpret_cast<u32x4*>(dst + x * 128) = ky[x];
-    *reinterpret_cast<u32x4*>(dst + (3 + x) * 128) = vy[x];
-  }
+  for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(dst + x * 128) = y[x];
 }
 
-template <int B, bool PRE>
-__global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                           const float* __restrict__ v, const unsigned char* __restrict__ parts,
-                                                           int64_t n_tokens, int64_t n_first,
-                                                           int nb1, int nb, float scale_log2,
-                                                           const int32_t* __restrict__ kv_idx,
-                                                           const int32_t* __restrict__ kv_cnt, int idx_stride,
-                                                           float* __restrict__ out, float* __restrict__ lse) {
-  constexpr int UNITS = B / 64;     // workgroups per query block
-  constexpr int PIECES = B / kTile;  // tiles per key block
-  __shared__ __align__(16) unsigned char smem[6 * kPlane];  // K parts 1, 2, 3, V parts 1, 2, 3
-  __shared__ int bad_s;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qi = wave & 1;
-  const int kh = wave >> 1;
-  const int n = lane & 31;
-  const int g = lane >> 5;
-  // unit of this workgroup: XCD x takes the x-th eighth of all units
-  const int64_t total = int64_t(gridDim.x) * gridDim.y;
-  const int64_t w = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
-  const int64_t xcd = w & 7, per = total >> 3, rest = total & 7;
-  const int64_t unit = xcd * per + min(xcd, rest) + (w >> 3);
-  const int h = static_cast<int>(unit / gridDim.x);
-  const int u = static_cast<int>(unit - int64_t(h) * gridDim.x);
-  const int I = u / UNITS;
-  const int64_t head_off = int64_t(h) * n_tokens * kD;
+// What a workgroup of attn_fp32_split_kernel works on: 64 rows of a query block and the key blocks of its list.
+template <int B>
+struct Unit {
+  int64_t n_tokens, n_first, head_off, row0;
+  const int32_t* list;  // null: all blocks
+  int nb1, nb, h, rows, count;
   // blocks 0 .. nb1-1 tile tokens [0, n_first), the others tokens [n_first, n_tokens)
-  auto block_start = [&](int J) { return J < nb1 ? int64_t(J) * B : n_first + int64_t(J - nb1) * B; };
-  auto block_count = [&](int J) {
+  __device__ __forceinline__ int64_t block_start(int J) const { return J < nb1 ? int64_t(J) * B : n_first + int64_t(J - nb1) * B; }
+  __device__ __forceinline__ int block_count(int J) const {
     return static_cast<int>(min<int64_t>(B, (J < nb1 ? n_first : n_tokens) - block_start(J)));
-  };
-  const int rows = block_count(I) - (u % UNITS) * 64;  // query rows from this unit's first on
-  if (rows <= 0) return;                               // the whole workgroup, before any barrier
-  const int64_t row0 = block_start(I) + (u % UNITS) * 64;
-  if (tid == 0) bad_s = 0;
-  const float* const q_row = q + head_off + (row0 + min(32 * qi + n, rows - 1)) * kD;  // rows past the end are not stored
-
-  const bool dense = kv_idx == nullptr;
-  const int64_t row = int64_t(h) * nb + I;
-  const int count = dense ? nb : min(max(kv_cnt[row], 0), nb);
-  const int pieces = count * PIECES;
+  }
+  static constexpr int PIECES = B / kTile;  // tiles per key block
+  __device__ __forceinline__ int pieces() const { return count * PIECES; }
   // the first tile from `piece` on that holds a key at all: a short block may end before its later tiles
-  auto next_piece = [&](int piece, int64_t& key0, int& valid) {
-    for (; piece < pieces; ++piece) {
+  __device__ __forceinline__ int next_piece(int piece, int64_t& key0, int& valid) const {
+    for (; piece < pieces(); ++piece) {
       const int it = piece / PIECES;
-      const int J = dense ? it : min(max(kv_idx[row * idx_stride + it], 0), nb - 1);
+      // through the scalar cache: a vector load's wait would be for the tiles on their way too
+      const int J = list == nullptr ? it : min(max(((const int32_t __attribute__((address_space(4)))*)list)[it], 0), nb - 1);
       key0 = block_start(J) + (piece % PIECES) * kTile;
       valid = block_count(J) - (piece % PIECES) * kTile;
       if (valid > 0) break;
     }
     return piece;
-  };
+  }
+};
 
-  f32x16 o[2];  // O^T: [dim block], this lane's query
+// State of a wave's softmax over 32 rows: O^T: [dim block], the lane's query
+struct Softmax {
+  f32x16 o[2];
   float m, l;
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[0][i] = o[1][i] = 0.f;
+    m = -INFINITY;
+    l = 0.f;
+  }
   // scores of 32 keys, of which those from `valid` on do not count -> weights; maximum and sum follow.  Returns what the
   // output so far is to be multiplied by.
-  auto weigh = [&](f32x16& s, int valid) -> float {
+  __device__ __forceinline__ float weigh(f32x16& s, int valid, int g) {
     if (valid < 32) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + 4 * g + (i & 3) >= valid) ? -INFINITY : s[i];
@@ -257,19 +232,177 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
     }
     l = fmaf(l, a, part[0] + part[1]);
     return a;
+  }
+  // The end of a pass: wave (qi, kh) finishes dims 32 kh .. 32 kh + 31 of its 32 rows, with what wave (qi, 1 - kh) leaves.  `bad` (or
+  // null): set, and nothing is stored, if a sum or an output is no finite number.  Returns whether it is set, to every thread.
+  template <int B>
+  __device__ __forceinline__ bool finish(const Unit<B>& un, int wave, int lane, float* park, int* bad, float* out, float* lse) const {
+    const int qi = wave & 1, kh = wave >> 1, n = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) park[wave * kRowWords + i * 64 + lane] = kh ? o[0][i] : o[1][i];
+    park[wave * kRowWords + 16 * 64 + lane] = m;
+    park[wave * kRowWords + 17 * 64 + lane] = l;
+    __syncthreads();
+    const float* other = park + (wave ^ 2) * kRowWords;
+    const float m1 = other[16 * 64 + lane], top = fmaxf(m, m1);
+    const float mu = top == -INFINITY ? 0.f : top;
+    const float a0 = __builtin_amdgcn_exp2f(m - mu), a1 = __builtin_amdgcn_exp2f(m1 - mu);  // 0 for a wave that saw no key
+    float sum = l * a0 + other[17 * 64 + lane] * a1;
+    sum += __shfl_xor(sum, 32);
+    f32x16 x;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = (kh ? o[1][i] : o[0][i]) * a0 + other[i * 64 + lane] * a1;
+    if (bad != nullptr) {
+      bool b = un.count > 0 && !(sum > 0.f && sum < INFINITY);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) b = b || !(fabsf(x[i]) < INFINITY);
+      if (b) *bad = 1;
+      __syncthreads();
+      if (*bad != 0) return true;
+    }
+    const int r = 32 * qi + n;
+    if (r < un.rows) {
+      // listed keys, but none with a weight: the softmax is 0 / 0
+      const float inv = sum > 0.f ? 1.f / sum : un.count > 0 ? NAN : 0.f;
+      float* dst = out + un.head_off + (un.row0 + r) * kD + 32 * kh + 4 * g;
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        *reinterpret_cast<f32x4*>(dst + 8 * r4) = f32x4{x[4 * r4] * inv, x[4 * r4 + 1] * inv, x[4 * r4 + 2] * inv, x[4 * r4 + 3] * inv};
+      if (lse != nullptr && kh == 0 && g == 0)
+        lse[int64_t(un.h) * un.n_tokens + un.row0 + r] = sum > 0.f ? (top + log2f(sum)) * 0.6931471805599453f : -INFINITY;
+    }
+    return false;
+  }
+};
+
+// A unit in fp32 instructions, where it has numbers that the parts do not hold.  Tiles go through registers to the LDS, the next one on
+// its way meanwhile; the chunks of Q and K are permuted.  Step d multiplies dims 8(d/4) + 4g + d%4, step i keys 8(i/4) + 4g + i%4 of the wave's.
+template <int B>
+__device__ __forceinline__ void unit_fp32(const Unit<B>& un, int wave, const float* __restrict__ q, const float* __restrict__ k,
+                                          const float* __restrict__ v, float scale_log2, float* smem, float* out, float* lse) {
+  const int lane = fresh_lane();  // so that nothing of this is kept in registers beside the split operands
+  const int tid = wave * 64 + lane, qi = wave & 1, kh = wave >> 1, n = lane & 31, g = lane >> 5;
+  float* const kt = smem;
+  float* const vt = smem + kTile * kD;
+  float* const qt = vt + kTile * kD;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (tid >> 4) + 16 * i, c = tid & 15;
+    *reinterpret_cast<f32x4*>(qt + r * kD + ((c ^ (r & 15)) << 2)) =
+        *reinterpret_cast<const f32x4*>(q + un.head_off + (un.row0 + min(r, un.rows - 1)) * kD + 4 * c) * scale_log2;
+  }
+  f32x4 raw[2][4];  // [K, V]: chunk (four dims) tid % 16 of tile rows tid / 16 + 16 i
+  auto load = [&](int64_t key0, int valid) {  // keys past `valid` repeat the last one; they are masked, and their values are zeros
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (tid >> 4) + 16 * i;
+      const int64_t at = un.head_off + (key0 + min(r, valid - 1)) * kD + 4 * (tid & 15);
+      raw[0][i] = *reinterpret_cast<const f32x4*>(k + at);
+      raw[1][i] = *reinterpret_cast<const f32x4*>(v + at);
+      if (r >= valid) raw[1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   };
+  Softmax st;
+  st.clear();
+  int64_t key0 = 0;
+  int valid = 0;
+  int piece = un.next_piece(0, key0, valid);
+  if (piece < un.pieces()) load(key0, valid);
+  while (piece < un.pieces()) {
+    __syncthreads();  // whatever is still read
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (tid >> 4) + 16 * i, c = tid & 15;
+      *reinterpret_cast<f32x4*>(kt + r * kD + ((c ^ (r & 15)) << 2)) = raw[0][i];
+      *reinterpret_cast<f32x4*>(vt + r * kD + 4 * c) = raw[1][i];
+    }
+    __syncthreads();
+    const int mine = valid - 32 * kh;  // keys of this wave
+    piece = un.next_piece(piece + 1, key0, valid);
+    if (piece < un.pieces()) load(key0, valid);
+    if (mine <= 0) continue;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 s = zero;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int at = ((2 * c + g) ^ (n & 15)) << 2;
+      const f32x4 x = *reinterpret_cast<const f32x4*>(kt + (32 * kh + n) * kD + at), y = *reinterpret_cast<const f32x4*>(qt + (32 * qi + n) * kD + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], s, 0, 0, 0);
+    }
+    const float a = st.weigh(s, mine, g);
+#pragma unroll
+    for (int db = 0; db < 2; ++db) {
+      f32x16 t = zero;  // apart, as the split products are
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        t = __builtin_amdgcn_mfma_f32_32x32x2f32(vt[(32 * kh + 8 * (i >> 2) + 4 * g + (i & 3)) * kD + 32 * db + n], s[i], t, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) st.o[db][i] = fmaf(st.o[db][i], a, t[i]);
+    }
+  }
+  __syncthreads();
+  st.finish(un, wave, lane, smem, nullptr, out, lse);
+}
+
+template <int B, bool PRE>
+__global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                           const float* __restrict__ v, const unsigned char* __restrict__ parts,
+                                                           int64_t n_tokens, int64_t n_first,
+                                                           int nb1, int nb, float scale_log2,
+                                                           const int32_t* __restrict__ kv_idx,
+                                                           const int32_t* __restrict__ kv_cnt, int idx_stride,
+                                                           float* __restrict__ out, float* __restrict__ lse) {
+  constexpr int UNITS = B / 64;  // workgroups per query block
+  __shared__ __align__(16) unsigned char smem[6 * kPlane];  // K parts 1, 2, 3, V parts 1, 2, 3
+  __shared__ int bad_s;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qi = wave & 1;
+  const int kh = wave >> 1;
+  const int n = lane & 31;
+  const int g = lane >> 5;
+  // unit of this workgroup: XCD x takes the x-th eighth of all units
+  const int64_t total = int64_t(gridDim.x) * gridDim.y;
+  const int64_t w = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t xcd = w & 7, per = total >> 3, rest = total & 7;
+  const int64_t unit = xcd * per + min(xcd, rest) + (w >> 3);
+  const int h = static_cast<int>(unit / gridDim.x);
+  const int u = static_cast<int>(unit - int64_t(h) * gridDim.x);
+  const int I = u / UNITS;
+  const int64_t row = int64_t(h) * nb + I;
+  Unit<B> un{n_tokens, n_first, int64_t(h) * n_tokens * kD, 0, kv_idx == nullptr ? nullptr : kv_idx + row * idx_stride, nb1, nb, h, 0, 0};
+  un.rows = un.block_count(I) - (u % UNITS) * 64;  // query rows from this unit's first on
+  if (un.rows <= 0) return;                        // the whole workgroup, before any barrier
+  un.row0 = un.block_start(I) + (u % UNITS) * 64;
+  un.count = kv_idx == nullptr ? nb : min(max(kv_cnt[row], 0), nb);
+  const int pieces = un.pieces();
+  const int64_t head_off = un.head_off;
+  auto next_piece = [&](int piece, int64_t& key0, int& valid) { return un.next_piece(piece, key0, valid); };
+  if (tid == 0) bad_s = 0;
+  const float* const q_row = q + head_off + (un.row0 + min(32 * qi + n, un.rows - 1)) * kD;  // rows past the end are not stored
+  Softmax st;
+  st.clear();
 
   // ---- the products in split operands ---------------------------------------------------------------
-  auto tiles_split = [&]() {
+  // returns true, to every thread, if a row sum or an output is not finite already
+  auto tiles = [&]() -> bool {
     bf16x8 qf[4][3];  // [16-dim chunk][part]: dims 16c + 8g .. +7 of query n
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const f32x4 x0 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g), x1 = *reinterpret_cast<const f32x4*>(q_row + 16 * c + 8 * g + 4);
       u32x4 y[3];
       split_chunk(x0 * scale_log2, x1 * scale_log2, y);
+      float top = 0.f;
+      unsigned low = ~0u;
 #pragma unroll
-      for (int e = 0; e < 8; ++e)  // as keys
-        if (!(fabsf((e < 4 ? x0[e] : x1[e - 4]) * scale_log2) < kLargestKey)) y[0][0] |= 0x7fffu;
+      for (int e = 0; e < 8; ++e) {
+        const float x = (e < 4 ? x0[e] : x1[e - 4]) * scale_log2;
+        top = fmaxf(top, fabsf(x));
+        low = min(low, 2u * __float_as_uint(x) - 1u);  // without its sign; a zero is the largest
+      }
+      if (top >= 0x1p96f || low < 2u * 0x08800000u - 1u) mark(y);  // 2^-110
 #pragma unroll
       for (int x = 0; x < 3; ++x) qf[c][x] = __builtin_bit_cast(bf16x8, y[x]);
     }
@@ -301,7 +434,7 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] += s2[i];
-      const float a = weigh(s, valid - 32 * kh);
+      const float a = st.weigh(s, valid - 32 * kh, g);
 #pragma unroll
       for (int cp = 0; cp < 2; ++cp) {
         u32x4 y[3];
@@ -336,7 +469,7 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
             t = products(vf, pf[cp], t);
           }
 #pragma unroll
-          for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[i]);
+          for (int i = 0; i < 16; ++i) st.o[db][i] = fmaf(st.o[db][i], a, t[i]);
         }
       } else {
         f32x16 t[2] = {zero, zero};
@@ -350,16 +483,27 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], a, t[db][i]);
+          for (int i = 0; i < 16; ++i) st.o[db][i] = fmaf(st.o[db][i], a, t[db][i]);
       }
     };
+    // Whether a row sum or an output is not finite, which it then stays, or a number was not whole: looked at every eight tiles, before a
+    // barrier, and known to all after it.
+    unsigned left = 0;
+    auto look = [&]() {
+      float top = st.l;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)  // three operands to an instruction, and NaN if one is
+        top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top, fabsf(st.o[0][i])), fabsf(st.o[1][i]));
+      if (!(top < INFINITY) || (left & kCutOff) != 0u) bad_s = 1;
+    };
+    auto given_up = [&]() { return __builtin_amdgcn_readfirstlane(*const_cast<volatile int*>(&bad_s)) != 0; };
     int64_t key0 = 0;
-    int valid = 0;
+    int valid = 0, done = 0;
     int piece = next_piece(0, key0, valid);
     if constexpr (PRE) {
       // Direct to the LDS: load i of a wave covers rows 8 j .. 8 j + 7, j = wave + 4 (i / 3), of part i % 3; lane -> row 8 j + lane / 8
       // and, at chunk position lane % 8, the chunk that belongs there.  Rows past the end of the head come as zeros, those past the end of
-      // a key block are the tokens that follow: their weight is 0 (and where they are not finite, see `bad` below).
+      // a key block are the tokens that follow: their weight is 0 (and where they are not finite, see Softmax::finish).
       const i32x4 rsrc = make_rsrc(parts + int64_t(h) * n_tokens * kPartRow, static_cast<unsigned>(n_tokens * kPartRow));
       const unsigned lds = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) unsigned char*)smem)) + wave * 1024;
       unsigned off[2][2];  // [K, V][row]
@@ -389,8 +533,11 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
       };
       if (piece < pieces) fetch(std::integral_constant<int, 0>{}, key0);
       while (piece < pieces) {
+        const bool ask = (++done & 7) == 0;
+        if (ask) look();
         asm volatile("" ::: "memory");
         arrived();
+        if (ask && given_up()) return true;
         fetch(std::integral_constant<int, 1>{}, key0);
         const int here = valid;
         piece = next_piece(piece + 1, key0, valid);
@@ -400,7 +547,8 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
         if (piece < pieces) fetch(std::integral_constant<int, 0>{}, key0);
         outputs(a);
       }
-      __syncthreads();
+      asm volatile("" ::: "memory");
+      arrived();
     } else {
       // this thread's share of a tile: chunk (eight dims) tid % 8 of tile rows tid / 8 and 32 + tid / 8, of K and of V
       const int lr = tid >> 3, lc = tid & 7;
@@ -420,111 +568,41 @@ __global__ __launch_bounds__(256, PRE ? 3 : 2) void attn_fp32_split_kernel(const
       };
       auto store = [&](int valid) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int r = lr + 32 * i;
-          if (r >= valid) raw[1][i][0] = raw[1][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};  // their weight is 0, and the last one may be infinite
-          u32x4 y[2][3];
-          split_key_value(raw[0][i][0], raw[0][i][1], raw[1][i][0], raw[1][i][1], y[0], y[1]);
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
+          for (int i = 0; i < 2; ++i) {
+            const int r = lr + 32 * i;
+            if (t == 1 && r >= valid) raw[t][i][0] = raw[t][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};  // their weight is 0, and the last one may be infinite
+            u32x4 y[3];
+            const unsigned rest = split_chunk(raw[t][i][0], raw[t][i][1], y);
+            if (t == 1) left |= rest;
             unsigned char* at = smem + t * 3 * kPlane + r * 128 + ((lc ^ (t ? swz_v(r) : swz_k(r))) << 4);
 #pragma unroll
-            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[t][x];
+            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x4*>(at + x * kPlane) = y[x];
           }
-        }
       };
       if (piece < pieces) load(key0, valid);
       while (piece < pieces) {
         const int here = valid;
         store(here);
+        const bool ask = (++done & 7) == 0;
+        if (ask) look();
         __syncthreads();
+        if (ask && given_up()) return true;
         piece = next_piece(piece + 1, key0, valid);
         if (piece < pieces) load(key0, valid);
         const float a = scores(here);
         outputs(a);
         __syncthreads();
       }
-    }
-  };
-
-  // ---- the same in fp32 instructions: step d multiplies dims 2d and 2d + 1, step i keys 8(i/4) + 4g + i%4 ----
-  auto tiles_fp32 = [&]() {
-    int64_t key0 = 0;
-    int valid = 0;
-    for (int piece = next_piece(0, key0, valid); piece < pieces; piece = next_piece(piece + 1, key0, valid)) {
-      const int mine = valid - 32 * kh;  // keys of this wave
-      if (mine <= 0) continue;
-      const float* k_row = k + head_off + (key0 + 32 * kh + min(n, mine - 1)) * kD;
-      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int d = 0; d < 32; ++d) s = __builtin_amdgcn_mfma_f32_32x32x2f32(k_row[2 * d + g], q_row[2 * d + g] * scale_log2, s, 0, 0, 0);
-      const float a = weigh(s, mine);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        o[0][i] *= a;
-        o[1][i] *= a;
-      }
-      const float* v_row = v + head_off + (key0 + 32 * kh) * kD + n;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = 8 * (i >> 2) + 4 * g + (i & 3);
-#pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          float x = v_row[min(key, mine - 1) * kD + 32 * db];
-          if (key >= mine) x = 0.f;
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, s[i], o[db], 0, 0, 0);
-        }
-      }
-    }
-  };
-
-  // A whole pass over the row's tiles; then wave (qi, kh) finishes dims 32 kh .. 32 kh + 31 of its 32 rows, with what wave
-  // (qi, 1 - kh) leaves.  Returns true, to every thread, if the split operands did not do.
-  auto pass = [&](auto exactc) -> bool {
-    constexpr bool EXACT = decltype(exactc)::value;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[0][i] = o[1][i] = 0.f;
-    m = -INFINITY;
-    l = 0.f;
-    if constexpr (EXACT) tiles_fp32();
-    else tiles_split();
-    float* const park = reinterpret_cast<float*>(smem);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) park[wave * kRowWords + i * 64 + lane] = kh ? o[0][i] : o[1][i];
-    park[wave * kRowWords + 16 * 64 + lane] = m;
-    park[wave * kRowWords + 17 * 64 + lane] = l;
-    __syncthreads();
-    const float* other = park + (wave ^ 2) * kRowWords;
-    const float m1 = other[16 * 64 + lane], top = fmaxf(m, m1);
-    const float mu = top == -INFINITY ? 0.f : top;
-    const float a0 = __builtin_amdgcn_exp2f(m - mu), a1 = __builtin_amdgcn_exp2f(m1 - mu);  // 0 for a wave that saw no key
-    float sum = l * a0 + other[17 * 64 + lane] * a1;
-    sum += __shfl_xor(sum, 32);
-    f32x16 x;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = (kh ? o[1][i] : o[0][i]) * a0 + other[i * 64 + lane] * a1;
-    if constexpr (!EXACT) {
-      bool bad = count > 0 && !(sum > 0.f && sum < INFINITY);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) bad = bad || !(fabsf(x[i]) < INFINITY);
-      if (bad) bad_s = 1;
-      __syncthreads();
-      if (bad_s != 0) return true;
-    }
-    const int r = 32 * qi + n;
-    if (r < rows) {
-      // listed keys, but none with a weight: the softmax is 0 / 0
-      const float inv = sum > 0.f ? 1.f / sum : count > 0 ? NAN : 0.f;
-      float* dst = out + head_off + (row0 + r) * kD + 32 * kh + 4 * g;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        *reinterpret_cast<f32x4*>(dst + 8 * r4) = f32x4{x[4 * r4] * inv, x[4 * r4 + 1] * inv, x[4 * r4 + 2] * inv, x[4 * r4 + 3] * inv};
-      if (lse != nullptr && kh == 0 && g == 0)
-        lse[int64_t(h) * n_tokens + row0 + r] = sum > 0.f ? (top + log2f(sum)) * 0.6931471805599453f : -INFINITY;
+      if ((left & kCutOff) != 0u) bad_s = 1;  // finish() asks for it after a barrier
     }
     return false;
   };
-  if (pass(std::false_type{})) pass(std::true_type{});
+
+  bool given_up = tiles();
+  if (!given_up) given_up = st.finish(un, wave, lane, reinterpret_cast<float*>(smem), &bad_s, out, lse);
+  if (given_up) unit_fp32(un, wave, q, k, v, scale_log2, reinterpret_cast<float*>(smem), out, lse);
 }
 
 template <int B>
@@ -749,7 +827,7 @@ int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int h
   if (need <= kPartsMaxBytes && workspace != nullptr && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
     parts = static_cast<unsigned char*>(workspace);
     const int64_t chunks = int64_t(heads) * n_tokens * (kD / 8);
-    hipLaunchKernelGGL(split_kv_kernel, dim3(static_cast<unsigned>(ceil_div(chunks, 256))), dim3(256), 0, stream, k, v, chunks, parts);
+    hipLaunchKernelGGL(split_kv_kernel, dim3(static_cast<unsigned>(ceil_div(chunks, 256)), 2), dim3(256), 0, stream, k, v, chunks, parts);
     if (int rc = check_hip(hipGetLastError(), "bsga fp32 attention (operand split)")) return rc;
     if (block == 64) launch_split(attn_fp32_split_kernel<64, true>);
     else launch_split(attn_fp32_split_kernel<128, true>);
