@@ -78,19 +78,25 @@ inline bool pairs_rows(int block, int heads, int nb, int nbk) {
   return block == 64 && int64_t(heads) * nb >= 1024 && nb >= 2 && nbk <= kPairMaxBlocks;
 }
 
-// Whether a dense launch takes blocks of 128 two to a workgroup of eight waves (see DUO).  Row by row / in pairs, us, 16 heads:
-//  - Up to eight rows per CU: where the busiest CU then has no more rows to work on than with a row to each workgroup.  2,748
-//    tokens (1.4 rows) 41.6 / 40.4, 6,870 (3.4) 186 / 176, 10,992 (5.4) 435 / 412, 16,300 (8) 884 / 857; but 4,122 (2.1) 89 / 108,
-//    8,244 (4.1) 270 / 305.
-//  - Up to twelve: rows alone even out by then, so the pairs' last round has to be nearly full.  20,400 (10) 1,375 / 1,329, 24,400 (11.9)
-//    1,961 / 1,895; but 19,000 (9.3) 1,225 / 1,220, 21,984 (10.8) 1,621 / 1,629, 23,300 (11.4) 1,776 / 1,800.
-//  - From there on nothing is to be gained, 27,000 (13.2) 2,444 / 2,449, 32,500 (15.9) 3,461 / 3,444, 35,000 (17.1) 4,041 / 4,063, until twenty:
-//    43,968 (21.5) 6,310 / 6,100, 137,400 (67) 60.8 / 58.0 ms.
+// Whether a dense launch takes blocks of 128 two to a workgroup of eight waves (see DUO).  Nothing runs beside the start and the end
+// of a pair, so its rows have to be long, and the more so the more pairs a CU takes; and a CU with an odd row left idles half.
+// Row by row / in pairs, us:
+//  - Up to eight rows per CU, where the busiest CU has no more rows to work on in pairs.  16 heads: 2,748 tokens (1.4 rows) 41.5 / 39.9, 6,870
+//    (3.4) 185 / 175, 10,992 (5.4) 431 / 419, 16,300 (8) 895 / 877; but 4,122 (2.1) 88 / 109, 8,244 (4.1) 267 / 312.  Heads of 16 blocks 37 /
+//    36.6 (2 rows per CU), 75.3 / 72.7 (4), but of 8 23.5 / 23.9 (2), and of 24 at 6 144 / 146, 32 at 8 243 / 249 (48 at 6 270 / 265,
+//    64 at 8 467 / 460).
+//  - From there on where the last round of pairs is nearly full.  20,400 tokens (10) 1,401 / 1,361, 32,731 (16) 3,475 / 3,417, 36,827 (18)
+//    4,381 / 4,351; but 19,000 (9.3) 1,220 / 1,241, 22,491 (11) 1,669 / 1,718, 27,000 (13.2) 2,401 / 2,440, 35,000 (17.1) 4,010 / 4,045.  51 heads of 100
+//    blocks 1,737 / 1,706, 80 of 96 2,488 / 2,463, 80 of 64 1,199 / 1,211.
+//  - From twenty rows per CU on rows of 256 blocks and more make up for the rest of a round: 41,179 (20.1) 5,444 / 5,345, 49,371 (24.1) 7,802 /
+//    7,722, 137,400 (67) 60.8 / 58.0 ms.  Rows of 112: 46 heads (20.1) 1,956 / 1,966 and, on another card,
+//    2,016 / 2,002.
+// Short rows lose by the start of the pairs (1,024 heads of 2 blocks 47 / 61), heads of one block run every row twice.
 inline bool dense_pairs(int heads, int nb) {
   const int64_t rows = int64_t(heads) * nb, rounds = ceil_div(int64_t(heads) * ((nb + 1) / 2), 256);  // of pairs
-  if (rows >= 20 * 256) return true;
-  if (rows <= 8 * 256) return 2 * rounds <= ceil_div(rows, 256);
-  return rows <= 12 * 256 && 50 * 2 * rounds * 256 <= 51 * rows;
+  if (rows <= 8 * 256) return nb >= (rows <= 4 * 256 ? 16 : 48) && 2 * rounds <= ceil_div(rows, 256);
+  if (rows >= 20 * 256 && nb >= 256) return true;
+  return nb >= 96 && 50 * 2 * rounds * 256 <= 51 * rows;
 }
 // Whether a sparse launch of blocks of 128 is large enough for choose_kernel to look at its lists, and these fit the LDS.
 inline bool chooses_pairs(int heads, int nb, int nbk) {

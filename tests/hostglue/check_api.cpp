@@ -86,6 +86,8 @@ int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t, doub
 }
 }  // namespace bsga
 
+using bsga::dense_pairs;
+
 static bool err_has(const char* what) { return strstr(bsga_last_error(), what) != nullptr; }
 
 int main() {
@@ -94,6 +96,19 @@ int main() {
                   // by the API layer; the stubs only touch the workspace)
   CHECK(bsga_version() == 3);
   CHECK(strlen(bsga_last_error()) == 0);
+
+  // ---- which dense launches take rows in pairs: (heads, blocks per head) at the lines of the rule
+  struct { int heads, nb; bool pairs; } dense[] = {
+      {16, 22, true}, {16, 33, false}, {16, 54, true}, {16, 65, false}, {16, 86, true}, {16, 128, true},  // the busiest CU: no more rows in pairs
+      {32, 16, true}, {64, 15, false}, {64, 16, true}, {32, 48, true}, {64, 24, false}, {64, 32, false}, {128, 16, false},  // long enough for it
+      {16, 129, false}, {20, 128, true}, {16, 176, false}, {16, 191, true}, {16, 211, false}, {16, 256, true},  // the last round is full
+      {51, 100, true}, {80, 95, false}, {80, 96, true}, {46, 112, false}, {20, 255, true}, {20, 256, true}, {16, 322, true}, {90, 65, false},
+      {1, 1, false}, {512, 1, false}, {5120, 1, false}, {65535, 1, false}, {512, 2, false}, {2560, 2, false}, {2000, 3, false}, {640, 8, false}};
+  for (const auto& c : dense)
+    if (dense_pairs(c.heads, c.nb) != c.pairs) {
+      fprintf(stderr, "FAILED dense_pairs(%d, %d)\n", c.heads, c.nb);
+      ++g_fail;
+    }
 
   // ---- pooling
   CHECK(bsga_pool_qk(A, A, 0, 16, 1000, 64, 128, (double*)A, (double*)A, nullptr) == BSGA_OK);

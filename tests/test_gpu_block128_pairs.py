@@ -118,3 +118,13 @@ def test_dense_pairs(B, heads, n):
     assert torch.equal(out, B.bsga_dense_attn(q, k, v))
     hot = [x * 30.0 for x in (q, k)] + [v]         # beyond the range of the first pass
     assert bool(torch.isfinite(B.bsga_dense_attn(*hot)).all())
+
+
+@pytest.mark.parametrize("heads,n", [(5200, 100), (2600, 256), (1800, 300)])
+def test_dense_many_short_heads(B, heads, n):
+    """Rows too short for pairs, and heads of one block, which have none."""
+    spans = _starts(n, n, 128)
+    q, k, v = _qkv(n, n, heads=heads)
+    out, lse = B.bsga_dense_attn(q, k, v, return_lse=True)
+    rows = [(h, i) for h in {0, 1, heads // 2, heads - 1} for i in range(len(spans))]
+    _check(out, lse, q, k, v, None, rows, spans, spans)
