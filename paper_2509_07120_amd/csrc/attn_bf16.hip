@@ -141,56 +141,44 @@ __device__ __forceinline__ int unit_count(const int32_t* __restrict__ kv_cnt, in
   return pair ? max(c[2 * I], c[min(2 * I + 1, nb - 1)]) : c[I];
 }
 
-// Whether a large sparse launch of blocks of 128 takes them two to a workgroup (DUO) or one by one: known on the card only,
-// because it depends on the lists.  Both kernels are launched and one of them finds nothing to do (two microseconds).
-// Pairs are worth it where a row has tiles enough to make up for the start of a pair, which nothing runs beside, and the
-// lists of neighbours are of one length, or else they are taken one after the other.  16 heads, one by one / in pairs (ms),
-// 344 blocks, nine tenths kept in lists of one length 5.69 / 5.58, half 3.20 / 3.21, a quarter 1.64 / 1.68, lengths uniform
-// 3.49 / 3.73; 1,074 blocks 55.3 / 53.1, 30.8 / 30.2, 15.6 / 15.5, 33.3 / 35.2.
-__global__ __launch_bounds__(1024) void choose_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nbk, int heads, int per_tile,
-                                                      int32_t* __restrict__ choice) {
-  __shared__ long long sum[2];
-  const int t = threadIdx.x;
-  if (t < 2) sum[t] = 0;
-  __syncthreads();
-  long long all = 0, apart = 0;
-  const int nu = (nb + 1) >> 1;
-  for (int64_t u = t; u < int64_t(heads) * nu; u += 1024) {
-    const int64_t h = u / nu;
-    const int i = 2 * static_cast<int>(u - h * nu);
-    const int a = min(max(kv_cnt[h * nb + i], 0), nbk), b = i + 1 < nb ? min(max(kv_cnt[h * nb + i + 1], 0), nbk) : a;
-    all += a + b;
-    apart += abs(a - b);
-  }
-  for (int o = 1; o < 64; o <<= 1) {
-    all += __shfl_xor(all, o);
-    apart += __shfl_xor(apart, o);
-  }
-  if ((t & 63) == 0) {
-    atomicAdd(reinterpret_cast<unsigned long long*>(&sum[0]), static_cast<unsigned long long>(all));
-    atomicAdd(reinterpret_cast<unsigned long long*>(&sum[1]), static_cast<unsigned long long>(apart));
-  }
-  __syncthreads();
-  if (t == 0) *choice = sum[0] >= 200ll * per_tile * heads * nb && 8 * sum[1] <= sum[0];
-}
-
-// Below: nu = units (rows, or pairs of rows) per head; `choice` (or null): where choose_kernel has left which of the two.
+// Whether a large sparse launch of blocks of 128 takes them two to a workgroup (DUO) or one by one is known on the card only,
+// because it depends on the lists, see pairs_pay.  The order is then counted both ways, order_merge_kernel goes on with one of them and
+// leaves which in `choice` (else null), and both attention kernels are launched, of which one finds nothing to do.
+// Below: nu = units (rows, or pairs of rows) per head.
 __device__ __forceinline__ void read_choice(const int32_t* choice, int nb, int& nu, bool& pair) {
   if (choice == nullptr) return;
   pair = *choice != 0;
   nu = pair ? (nb + 1) >> 1 : nb;
 }
+// What order_hist_kernel leaves of the pairs: a table as that of the rows, lengths and differences of each head (2^24 at most).
+constexpr int kPairsWords = kOrderClasses + 2;  // per head
 __global__ __launch_bounds__(256) void order_hist_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, const int32_t* choice, int32_t* __restrict__ table) {
-  __shared__ int bins[kOrderClasses];
-  read_choice(choice, nb, nu, pair);
+                                                         int heads, int32_t* __restrict__ table, int32_t* __restrict__ pairs) {
+  __shared__ int bins[kOrderClasses], pair_bins[kPairsWords];
   const int h = blockIdx.x;
   const int t = threadIdx.x;
   if (t < kOrderClasses) bins[t] = 0;
+  if (t < kPairsWords) pair_bins[t] = 0;
   __syncthreads();
-  for (int I = t; I < nu; I += 256) atomicAdd(&bins[order_class(unit_count(kv_cnt, h, nb, I, pair), nbk)], 1);
+  if (pairs == nullptr) {
+    for (int I = t; I < nu; I += 256) atomicAdd(&bins[order_class(unit_count(kv_cnt, h, nb, I, pair), nbk)], 1);
+  } else {
+    const int32_t* const c = kv_cnt + int64_t(h) * nb;
+    int all = 0, apart = 0;
+    for (int i = 2 * t; i < nb; i += 512) {
+      const int a = min(max(c[i], 0), nbk), b = i + 1 < nb ? min(max(c[i + 1], 0), nbk) : a;
+      atomicAdd(&bins[order_class(a, nbk)], 1);
+      if (i + 1 < nb) atomicAdd(&bins[order_class(b, nbk)], 1);
+      atomicAdd(&pair_bins[order_class(max(a, b), nbk)], 1);
+      all += a + b;
+      apart += abs(a - b);
+    }
+    atomicAdd(&pair_bins[kOrderClasses], all);
+    atomicAdd(&pair_bins[kOrderClasses + 1], apart);
+  }
   __syncthreads();
   if (t < kOrderClasses) table[int64_t(t) * heads + h] = bins[t];
+  if (pairs != nullptr && t < kPairsWords) pairs[int64_t(t) * heads + h] = pair_bins[t];
 }
 
 // The first class c whose lower bound (31 - c) / 31 is below 1.4 x the mean kept fraction, taking a unit at the
@@ -212,11 +200,25 @@ __device__ __forceinline__ int bulk_class(Total&& total) {
 
 // One workgroup.  Finds the first class c_bulk whose lower bound (31 - c) / 31 is below 1.4 x the
 // mean kept fraction, folds every lighter class into it (table rows c > c_bulk are added to row
-// c_bulk and zeroed) and leaves c_bulk in table[kOrderClasses * heads].
-__global__ __launch_bounds__(256) void order_merge_kernel(int32_t* __restrict__ table, int heads) {
+// c_bulk and zeroed) and leaves c_bulk in table[kOrderClasses * heads].  pairs (or null): what order_hist_kernel has left of
+// the pairs; whether the launch takes pairs goes to table[kOrderClasses * heads + 2], and if it does the table becomes theirs.
+__global__ __launch_bounds__(256) void order_merge_kernel(int32_t* __restrict__ table, int heads, const int32_t* __restrict__ pairs, int nb,
+                                                          int nbk, int per_tile) {
   __shared__ long long total[kOrderClasses];
   __shared__ int c_bulk;
   const int t = threadIdx.x;
+  if (pairs != nullptr) {
+    if (t < 2) total[t] = 0;
+    __syncthreads();
+    for (int64_t i = t; i < 2 * int64_t(heads); i += 256)
+      atomicAdd(reinterpret_cast<unsigned long long*>(&total[i >= heads]), static_cast<unsigned long long>(pairs[int64_t(kOrderClasses) * heads + i]));
+    __syncthreads();
+    const bool pay = pairs_pay(total[0], total[1], static_cast<long long>(heads) * nb, nbk, per_tile);
+    if (pay)
+      for (int64_t i = t; i < int64_t(kOrderClasses) * heads; i += 256) table[i] = pairs[i];
+    if (t == 0) table[int64_t(kOrderClasses) * heads + 2] = pay;
+    __syncthreads();
+  }
   if (t < kOrderClasses) total[t] = 0;
   __syncthreads();
   for (int64_t i = t; i < int64_t(kOrderClasses) * heads; i += 256)
@@ -303,10 +305,9 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
 // four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
 // of a thread are consecutive, so the bulk class keeps its order.
 constexpr int kOrderOneMax = 8192;
+static_assert(kPairsMinRows >= kOrderOneMax, "order_one_kernel knows nothing of the choice");
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, const int32_t* choice, int32_t* __restrict__ order,
-                                                         int32_t* __restrict__ next_row) {
-  read_choice(choice, nb, nu, pair);
+                                                         int heads, int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
   constexpr int MAX = kOrderOneMax / 1024;
   __shared__ int total[kOrderClasses], next[kOrderClasses];
   __shared__ int c_bulk_s, wave_bulk[16];
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   constexpr int V_BASE = DUO ? TILE_BYTES : 2 * TILE_BYTES;
   constexpr int BUF_BYTES = DUO ? 2 * TILE_BYTES : TILE_BYTES;  // from one buffer of a tensor to the other
   extern __shared__ __align__(16) unsigned char smem[];
-  if (choice != nullptr && (*choice != 0) != DUO) return;  // see choose_kernel
+  if (choice != nullptr && (*choice != 0) != DUO) return;  // see order_merge_kernel
 
   const int tid0 = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
@@ -1843,22 +1844,23 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   }
   if (plan.big && kv_idx != nullptr) {
     // workspace: launch order of the rows or pairs, then the [classes][heads] table, the number of the merged
-    // class, the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel) and the choice
+    // class, the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel) and, where
+    // pairs are thought of, the choice and the pairs' table (there is room: it is sized for blocks of 64, and has nb - 2 words a head left)
     const int nu = static_cast<int>(plan.grid.x);
     const int64_t rows = int64_t(heads) * nu;
     int32_t* ord = static_cast<int32_t*>(workspace);
     int32_t* table = ord + rows;
     next_row = table + int64_t(kOrderClasses) * heads + 1;
-    if (choose) {
-      int32_t* c = table + int64_t(kOrderClasses) * heads + 2;
-      hipLaunchKernelGGL(choose_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nbk, heads, block_k == block ? 1 : 2, c);
-      choice = c;
-    }
-    if (rows <= kOrderOneMax) {
-      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, ord, next_row);
+    if (rows <= kOrderOneMax) {  // too few for pairs, see chooses_pairs
+      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, ord, next_row);
     } else {
-      hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, table);
-      hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads);
+      int32_t* pairs = nullptr;
+      if (choose) {
+        choice = table + int64_t(kOrderClasses) * heads + 2;
+        pairs = table + int64_t(kOrderClasses) * heads + 3;
+      }
+      hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table, pairs);
+      hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads, pairs, nb, nbk, block_k == block ? 1 : 2);
       hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, stream, table, int64_t(kOrderClasses) * heads);
       hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, table, ord);
     }

@@ -98,9 +98,29 @@ inline bool dense_pairs(int heads, int nb) {
   if (rows >= 20 * 256 && nb >= 256) return true;
   return nb >= 96 && 50 * 2 * rounds * 256 <= 51 * rows;
 }
-// Whether a sparse launch of blocks of 128 is large enough for choose_kernel to look at its lists, and these fit the LDS.
+// Whether a sparse launch of blocks of 128 is large enough to look at its lists before it takes rows one by one or in pairs, and these fit
+// the LDS.  The kernel that then is not meant costs 5 us, and the look itself cost 8 where the launch order is made by one kernel (up to
+// 8,192 rows): 4,112 rows of 257 blocks, a twentieth and a tenth kept, 224 -> 228 and 393 -> 401 us, 5,504 of 344 718 -> 728.  Rows of fewer
+// than 300 blocks gain 1 % at most, when they keep nearly all.
+constexpr int kPairsMinRows = 8192;  // more than this
 inline bool chooses_pairs(int heads, int nb, int nbk) {
-  return int64_t(heads) * nb >= 4096 && nb >= 256 && nbk <= kPairMaxBlocks;
+  return int64_t(heads) * nb > kPairsMinRows && nb >= 300 && nbk <= kPairMaxBlocks;
+}
+// What it looks for, in the sum of the lists' lengths and the sum of the differences between the two of a pair (half a difference is time
+// that one of the two waits, and of a pair that differs by much each row is taken apart, see `uneven`).  One by one / in pairs, ms:
+//  - Long rows, which make up for the start of a pair, that nothing runs beside: 16,384 rows of 512 blocks, lists of one length, four tenths
+//    kept 11.28 / 11.42, six tenths 17.0 / 16.7, nine 25.2 / 24.6; 17,184 of 1,074, a quarter kept 15.6 / 15.4, half 30.7 / 30.3.
+//  - 64 rows per CU and more, rows of 500 tiles: 17,184 rows of 1,074 blocks, nine tenths kept in lists of one length 55.2 / 53.3, lengths
+//    within 5 % of eight tenths 52.5 / 50.0, within 12 % 53.7 / 52.7, within 20 % of seven 46.8 / 46.3; uniform, or alternating
+//    7 : 9, no gain.
+//  - Otherwise less evens out.  Shorter rows: 16,384 of 512 blocks within 20 % of seven tenths 20.8 / 20.9, 19,264 of 301 that alternate 8 : 9
+//    17.34 / 17.54; within 5 % of nine 25.5 / 24.2, 17.23 / 16.76.  Fewer: within 20 % of seven tenths 513 blocks 10.35 / 10.47, 700
+//    19.5 / 19.6, within 12 % of eight 11.66 / 11.59, 21.97 / 21.77; of one length, half kept, 512 blocks 6.97 / 7.02, 700, four tenths,
+//    10.17 / 10.28, six tenths 15.27 / 15.12, nine 22.8 / 22.2, within 5 % of nine 12.60 / 12.13, 23.9 / 22.9.
+inline __host__ __device__ bool pairs_pay(long long all, long long apart, long long rows, int nbk, int per_tile) {
+  const bool many = rows >= 64 * 256;
+  if (all < 260 * per_tile * rows || (!many && 10 * all < 6 * nbk * rows)) return false;
+  return (many && all >= 500 * per_tile * rows ? 8 : 32) * apart <= all;
 }
 
 constexpr int64_t kFp32FewUnits = 128;  // units of 64 rows, of which an fp32 launch goes to attn_fp32_kernel

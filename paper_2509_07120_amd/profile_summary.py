@@ -26,7 +26,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROFILES = os.path.join(ROOT, "profiles")
 ATTN_SOURCE = os.path.join(ROOT, "paper_2509_07120_amd", "csrc", "attn_bf16.hip")
-KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "choose_kernel", "order_one", "order_hist", "order_merge", "order_scan",
+KERNELS = ("attn_bf16_kernel", "select_kernel", "logits_kernel", "pool_kernel", "order_one", "order_hist", "order_merge", "order_scan",
            "order_place", "gather_kernel", "probe_kernel")
 
 
@@ -106,8 +106,8 @@ two.  The per-dispatch trace (`stats_kernel_trace.csv`) separates them.
         for n, c, a, mn, mx, p in rows:
             f.write(f"| {n} | {c} | {a:.4f} | {mn:.4f} | {mx:.4f} | {p:.3f} |\n")
         f.write(f"""
-`pool_kernel` pools Q and K in one launch; `choose_kernel` decides whether rows are taken in pairs and the four `order_*`
-kernels build the launch order; a sparse call enqueues the attention kernel in both forms, and the one that was not
+`pool_kernel` pools Q and K in one launch; the four `order_*` kernels decide whether rows are taken in pairs and build
+the launch order; a sparse call enqueues the attention kernel in both forms, and the one that was not
 chosen leaves at once (the minimum in its row above).
 
 ## attn_bf16_kernel per dispatch (stats_kernel_trace.csv), ms

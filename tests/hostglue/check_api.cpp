@@ -86,7 +86,9 @@ int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t, doub
 }
 }  // namespace bsga
 
+using bsga::chooses_pairs;
 using bsga::dense_pairs;
+using bsga::pairs_pay;
 
 static bool err_has(const char* what) { return strstr(bsga_last_error(), what) != nullptr; }
 
@@ -109,6 +111,26 @@ int main() {
       fprintf(stderr, "FAILED dense_pairs(%d, %d)\n", c.heads, c.nb);
       ++g_fail;
     }
+
+  // ---- which sparse launches look at their lists, and what for (lengths in tiles of all blocks, differences of all pairs)
+  CHECK(!chooses_pairs(16, 257, 257) && !chooses_pairs(16, 344, 344) && !chooses_pairs(16, 512, 512) && chooses_pairs(16, 513, 513));
+  CHECK(!chooses_pairs(64, 299, 299) && chooses_pairs(32, 300, 300) && chooses_pairs(3, 4096, 4096) && !chooses_pairs(3, 4097, 4097));
+  auto pays = [](long long rows, int nb, int per_tile, double kept, double apart) {  // apart: difference of a pair over its sum
+    const long long all = static_cast<long long>(kept * per_tile * nb * rows);
+    return pairs_pay(all, static_cast<long long>(apart * all), rows, per_tile * nb, per_tile);
+  };
+  for (int per_tile : {1, 2}) {
+    CHECK(pays(17184, 1074, per_tile, 0.25, 0.0) && pays(17184, 1074, per_tile, 0.7, 0.1) && !pays(17184, 1074, per_tile, 0.8, 0.13));
+    CHECK(!pays(17184, 1074, per_tile, 0.24, 0.0) && !pays(16384, 512, per_tile, 0.5, 0.0) && pays(16384, 512, per_tile, 0.51, 0.0));
+    CHECK(pays(16384, 1024, per_tile, 0.4, 0.0) && !pays(16383, 1024, per_tile, 0.4, 0.0));
+    CHECK(!pays(19264, 301, per_tile, 0.9, 0.05) && pays(19264, 301, per_tile, 0.9, 0.03) && !pays(16384, 512, per_tile, 0.7, 0.07));
+    CHECK(pays(8208, 513, per_tile, 0.61, 0.03) && !pays(8208, 513, per_tile, 0.59, 0.03) && !pays(8208, 513, per_tile, 0.9, 0.04));
+    // the room of the launch order, sized for blocks of 64, holds what is left of the pairs: two tables and five words
+    for (int heads : {1, 16, 28, 400, 65535})
+      for (int64_t nb : {300, 301, 513, 4096})
+        for (int64_t n : {nb * 128, nb * 128 - 127, (nb - 2) * 128 + 2})  // the last: split, with a ragged block in each part
+          CHECK(bsga::attn_order_bytes(heads, n) >= 4 * (heads * (nb + 32 + 34) + 5));
+  }
 
   // ---- pooling
   CHECK(bsga_pool_qk(A, A, 0, 16, 1000, 64, 128, (double*)A, (double*)A, nullptr) == BSGA_OK);
