@@ -676,8 +676,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     const int n0 = min(max(c0, 0), nbk), n1 = two ? min(max(c1, 0), nbk) : 0;
     auto enter = [&](int r, int J) { named[r * kPairMaxBlocks + min(max(J, 0), nbk - 1)] = 1; };
     auto uneven = [&](int both, int alone0, int alone1) {
-      // DUO: what idles is half the difference, what another row costs 13 us (8 tiles) and the common tiles unshared (3 %)
-      return __builtin_amdgcn_readfirstlane(abs(alone0 - alone1) > (DUO ? 16 + (both >> 4) : both + 12)) != 0;
+      return __builtin_amdgcn_readfirstlane(DUO ? pair_differs(both, alone0, alone1, HALF ? 2 : 1) : abs(alone0 - alone1) > both + 12) != 0;
     };
     if (10 * (n0 + n1) < 6 * nbk) {
       if (!two || uneven(0, n0, n1)) return kByOne;

@@ -107,7 +107,7 @@ inline bool chooses_pairs(int heads, int nb, int nbk) {
   return int64_t(heads) * nb > kPairsMinRows && nb >= 300 && nbk <= kPairMaxBlocks;
 }
 // What it looks for, in the sum of the lists' lengths and the sum of the differences between the two of a pair (half a difference is time
-// that one of the two waits, and of a pair that differs by much each row is taken apart, see `uneven`).  One by one / in pairs, ms:
+// that one of the two waits, and of a pair that differs by much each row is taken apart, see pair_differs).  One by one / in pairs, ms:
 //  - Long rows, which make up for the start of a pair, that nothing runs beside: 16,384 rows of 512 blocks, lists of one length, four tenths
 //    kept 11.28 / 11.42, six tenths 17.0 / 16.7, nine 25.2 / 24.6; 17,184 of 1,074, a quarter kept 15.6 / 15.4, half 30.7 / 30.3.
 //  - 64 rows per CU and more, rows of 500 tiles: 17,184 rows of 1,074 blocks, nine tenths kept in lists of one length 55.2 / 53.3, lengths
@@ -121,6 +121,14 @@ inline __host__ __device__ bool pairs_pay(long long all, long long apart, long l
   const bool many = rows >= 64 * 256;
   if (all < 260 * per_tile * rows || (!many && 10 * all < 6 * nbk * rows)) return false;
   return (many && all >= 500 * per_tile * rows ? 8 : 32) * apart <= all;
+}
+
+// Whether a pair's lists, of which `both` entries are common, differ so much in length that its rows are taken one after the other.  What idles
+// is half the difference; another row costs 13 us, which is eight tiles, and the common tiles unshared, 3 % of them.
+// (Sixteen entries for key blocks of 64 too: 17,184 rows, lengths within 5 % of eight tenths, 52.04 ms and not 51.80, 8,208 11.74 and not 11.63.)
+inline __host__ __device__ bool pair_differs(int both, int alone0, int alone1, int per_tile) {
+  const int apart = alone0 < alone1 ? alone1 - alone0 : alone0 - alone1;
+  return apart > 16 * per_tile + (both >> 4);
 }
 
 constexpr int64_t kFp32FewUnits = 128;  // units of 64 rows, of which an fp32 launch goes to attn_fp32_kernel

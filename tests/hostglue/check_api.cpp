@@ -88,6 +88,7 @@ int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t, doub
 
 using bsga::chooses_pairs;
 using bsga::dense_pairs;
+using bsga::pair_differs;
 using bsga::pairs_pay;
 
 static bool err_has(const char* what) { return strstr(bsga_last_error(), what) != nullptr; }
@@ -125,6 +126,8 @@ int main() {
     CHECK(pays(16384, 1024, per_tile, 0.4, 0.0) && !pays(16383, 1024, per_tile, 0.4, 0.0));
     CHECK(!pays(19264, 301, per_tile, 0.9, 0.05) && pays(19264, 301, per_tile, 0.9, 0.03) && !pays(16384, 512, per_tile, 0.7, 0.07));
     CHECK(pays(8208, 513, per_tile, 0.61, 0.03) && !pays(8208, 513, per_tile, 0.59, 0.03) && !pays(8208, 513, per_tile, 0.9, 0.04));
+    CHECK(!pair_differs(0, 16 * per_tile, 0, per_tile) && pair_differs(0, 0, 16 * per_tile + 1, per_tile));  // tiles, not entries
+    CHECK(!pair_differs(320, 40 + 16 * per_tile, 20, per_tile) && pair_differs(320, 20, 41 + 16 * per_tile, per_tile));
     // the room of the launch order, sized for blocks of 64, holds what is left of the pairs: two tables and five words
     for (int heads : {1, 16, 28, 400, 65535})
       for (int64_t nb : {300, 301, 513, 4096})
