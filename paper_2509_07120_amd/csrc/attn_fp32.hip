@@ -155,7 +155,7 @@ __device__ __forceinline__ void products(const bf16x8 (&x0)[3], const bf16x8 (&y
 
 // K and V split beforehand: token t of head h has kPartRow bytes at (h n_tokens + t) kPartRow, the three parts of its key, then
 // those of its value.  A thread splits eight dims of one of the two.
-constexpr int kPartRow = 6 * kD * 2;
+static_assert(kPartRow == 6 * kD * 2, "three parts of a key and of a value");
 __global__ __launch_bounds__(256) void split_kv_kernel(const float* __restrict__ k, const float* __restrict__ v, int64_t chunks,
                                                        unsigned char* __restrict__ parts) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -795,14 +795,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp32_kernel(const float* __restri
 
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, float* out,
-                     float* lse, hipStream_t stream) {
-  return launch_attn_fp32_parts(q, k, v, heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse, nullptr, 0,
-                                stream);
-}
-
-int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
-                           int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, float* out,
-                           float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+                     float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const int nb = static_cast<int>(split_blocks(n_tokens, n_first, block));
   const int nb1 = static_cast<int>(ceil_div(n_first, block));
   const float scale_log2 = softmax_scale * 1.4426950408889634f;

@@ -100,13 +100,9 @@ static int attn_common(const char* fn, const void* q, const void* k, const void*
   if (dtype == BSGA_BF16)
     return launch_attn_bf16(q, k, v, heads, n_tokens, n_first, block, block_k, softmax_scale, kv_idx, kv_cnt, idx_stride, out, lse,
                             workspace, workspace_bytes, s);
-  if (workspace && launch_attn_fp32_parts)
-    return launch_attn_fp32_parts(static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v),
-                                  heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride,
-                                  static_cast<float*>(out), lse, workspace, workspace_bytes, s);
   return launch_attn_fp32(static_cast<const float*>(q), static_cast<const float*>(k), static_cast<const float*>(v),
                           heads, n_tokens, n_first, block, softmax_scale, kv_idx, kv_cnt, idx_stride,
-                          static_cast<float*>(out), lse, s);
+                          static_cast<float*>(out), lse, workspace, workspace_bytes, s);
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
@@ -152,12 +148,8 @@ static int pool_common(const char* fn, const void* q, const void* k, int dtype, 
   if ((q && !aligned16(q)) || (k && !aligned16(k)) || (q_pool && !aligned16(q_pool)) || (k_pool && !aligned16(k_pool)))
     return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (q && k && launch_pool_both) return launch_pool_both(q, k, dtype, heads, n_tokens, n_first, block, q_pool, k_pool, s);
-  if (q)
-    if (int rc = launch_pool(q, dtype, heads, n_tokens, n_first, block, q_pool, s)) return rc;
-  if (k)
-    if (int rc = launch_pool(k, dtype, heads, n_tokens, n_first, block, k_pool, s)) return rc;
-  return BSGA_OK;
+  if (!q) return launch_pool(k, k_pool, nullptr, nullptr, dtype, heads, n_tokens, n_first, block, s);
+  return launch_pool(q, q_pool, k, k_pool, dtype, heads, n_tokens, n_first, block, s);
 }
 
 int bsga_pool_qk(const void* q, const void* k, int dtype, int heads, int64_t n_tokens, int head_dim, int block,

@@ -138,21 +138,19 @@ constexpr int64_t kFp32FewUnits = 128;  // units of 64 rows, of which an fp32 la
 // 9 tiles 91 / 92, 17 178 / 162, 77 746 / 626.  Up to 512 rows the chip holds them all at once, and a step is only
 // shorter, not cheaper: 344 rows, 15 tiles 49 / 54, 21 67 / 68, 30 93 / 90, 77 228 / 203.  The call uses the room whenever it has
 // it; `kept` is what the caller expects the lists to hold of all key blocks.
+constexpr int kPartRow = 6 * 64 * 2;  // three parts of a key, then of a value
 constexpr size_t kPartsMaxBytes = size_t(256) << 20;  // 21,845 tokens of 16 heads; fp32 is for shorter sequences
 inline size_t attn_fp32_parts_bytes(int heads, int64_t n_tokens, double kept) {
   const int64_t tiles = ceil_div(n_tokens, 64), rows = heads * tiles;
-  const size_t bytes = static_cast<size_t>(heads) * static_cast<size_t>(n_tokens) * (6 * 64 * 2);
+  const size_t bytes = static_cast<size_t>(heads) * static_cast<size_t>(n_tokens) * kPartRow;
   if (rows <= kFp32FewUnits || bytes > kPartsMaxBytes) return 0;
   return kept * static_cast<double>(tiles) >= (rows > 512 ? 12.0 : 25.0) ? bytes : 0;
 }
 
 // Kernel launchers.  Arguments are already validated.
-int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
-                hipStream_t stream);
-// Two tensors in one launch.  Weak: a program that puts launchers of its own under the API layer need not have it, and
-// then sees two calls of the one above.
-int launch_pool_both(const void* q, const void* k, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* q_pool,
-                     double* k_pool, hipStream_t stream) __attribute__((weak));
+// One tensor, or (x1 not null) two in one launch.
+int launch_pool(const void* x0, double* pooled0, const void* x1, double* pooled1, int dtype, int heads, int64_t n_tokens, int64_t n_first,
+                int block, hipStream_t stream);
 
 int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_q, int nb_k,
                   double score_scale, double tau, double one_minus_rho, const uint8_t* force_q,
@@ -168,16 +166,10 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
                      int idx_stride, void* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
+// workspace: room for K and V split beforehand, kPartRow bytes per token and head; ignored if it is less or misaligned.
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
-                     int idx_stride, float* out, float* lse, hipStream_t stream);
-
-// The same with room for K and V split beforehand (ignored if it is too small or misaligned).  Weak, as launch_pool_both: without it
-// fp32 calls take the one above.
-int launch_attn_fp32_parts(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
-                           int block, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
-                           int idx_stride, float* out, float* lse, void* workspace, size_t workspace_bytes,
-                           hipStream_t stream) __attribute__((weak));
+                     int idx_stride, float* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t sink_bytes, double* flops,
                       hipStream_t stream);

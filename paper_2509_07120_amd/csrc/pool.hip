@@ -81,9 +81,8 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(const uint4* __restrict_
 
 }  // namespace
 
-namespace {
-int launch(const void* x0, double* pooled0, const void* x1, double* pooled1, int dtype, int heads, int64_t n_tokens, int64_t n_first,
-           int block, hipStream_t stream) {
+int launch_pool(const void* x0, double* pooled0, const void* x1, double* pooled1, int dtype, int heads, int64_t n_tokens, int64_t n_first,
+                int block, hipStream_t stream) {
   const int nb = static_cast<int>(split_blocks(n_tokens, n_first, block));
   const int nb1 = static_cast<int>(ceil_div(n_first, block));
   auto go = [&](auto kernel) {
@@ -98,17 +97,6 @@ int launch(const void* x0, double* pooled0, const void* x1, double* pooled1, int
     else go(pool_kernel<4, 128>);
   }
   return check_hip(hipGetLastError(), "bsga_pool_qk launch");
-}
-}  // namespace
-
-int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
-                hipStream_t stream) {
-  return launch(x, pooled, nullptr, nullptr, dtype, heads, n_tokens, n_first, block, stream);
-}
-
-int launch_pool_both(const void* q, const void* k, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* q_pool,
-                     double* k_pool, hipStream_t stream) {
-  return launch(q, q_pool, k, k_pool, dtype, heads, n_tokens, n_first, block, stream);
 }
 
 }  // namespace bsga

@@ -8,12 +8,14 @@
 #include <string.h>
 
 #include <string>
+#include <vector>
 
 #include "bsga.h"
 #include "bsga_internal.h"
 
 static int g_calls = 0;
 static int g_fail = 0;
+static int g_pooled = 0;              // tensors of the last pooling launch
 static size_t g_workspace_bytes = 0;  // of the last attention launch
 #define CHECK(cond)                                                        \
   do {                                                                     \
@@ -25,10 +27,11 @@ static size_t g_workspace_bytes = 0;  // of the last attention launch
 
 namespace bsga {
 // ---- stubs: the launchers' preconditions, as the API layer must establish them -------------------
-int launch_pool(const void* x, int dtype, int heads, int64_t n_tokens, int64_t n_first, int block, double* pooled,
-                hipStream_t) {
+int launch_pool(const void* x0, double* pooled0, const void* x1, double* pooled1, int dtype, int heads, int64_t n_tokens,
+                int64_t n_first, int block, hipStream_t) {
   ++g_calls;
-  CHECK(x && pooled && heads >= 1 && n_tokens >= 1 && n_first >= 0 && n_first <= n_tokens);
+  g_pooled = x1 ? 2 : 1;
+  CHECK(x0 && pooled0 && !x1 == !pooled1 && heads >= 1 && n_tokens >= 1 && n_first >= 0 && n_first <= n_tokens);
   CHECK((block == 64 || block == 128) && (dtype == BSGA_BF16 || dtype == BSGA_FP32));
   return BSGA_OK;
 }
@@ -64,18 +67,25 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   CHECK(q && k && v && out && scale > 0.f);
   CHECK((workspace == nullptr) == (workspace_bytes == 0));
   check_attn(heads, n_tokens, n_first, block, block_k, kv_idx, kv_cnt, idx_stride);
-  if (workspace) {  // the launch order needs one word per query block plus the class table: touch it all
-    const size_t words = size_t(heads) * split_blocks(n_tokens, n_first, block) + 32u * heads + 1;
+  if (workspace) {  // the launch order needs one word per query block plus the class table, the merged class and a counter: touch
+                    // it all, and what a choice between rows and pairs takes beyond that
+    const int64_t nb = split_blocks(n_tokens, n_first, block);
+    const bool choice = block == 128 && kv_idx && chooses_pairs(heads, static_cast<int>(nb), static_cast<int>(split_blocks(n_tokens, n_first, block_k)));
+    const size_t words = kv_idx ? size_t(heads) * nb + 32u * heads + 2 + (choice ? 34u * heads + 1 : 0) : 1;
     memset(workspace, 0, words * sizeof(int32_t));  // ASan faults here if the API sized the workspace too small
   }
   return BSGA_OK;
 }
 int launch_attn_fp32(const float* q, const float* k, const float* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, float scale, const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, float* out,
-                     float*, hipStream_t) {
+                     float*, void* workspace, size_t workspace_bytes, hipStream_t) {
   ++g_calls;
+  g_workspace_bytes = workspace_bytes;
   CHECK(q && k && v && out && scale > 0.f);
+  CHECK((workspace == nullptr) == (workspace_bytes == 0));
   check_attn(heads, n_tokens, n_first, block, block, kv_idx, kv_cnt, idx_stride);
+  const size_t parts = size_t(heads) * n_tokens * kPartRow;  // used if it is all there
+  if (workspace && workspace_bytes >= parts && parts <= kPartsMaxBytes) memset(workspace, 0, parts);
   return BSGA_OK;
 }
 int launch_probe_mfma(int pattern, int mix, int iters, float* sink, size_t, double* flops, hipStream_t) {
@@ -137,7 +147,9 @@ int main() {
 
   // ---- pooling
   CHECK(bsga_pool_qk(A, A, 0, 16, 1000, 64, 128, (double*)A, (double*)A, nullptr) == BSGA_OK);
-  CHECK(bsga_pool_qk(A, nullptr, 0, 16, 1000, 64, 128, (double*)A, nullptr, nullptr) == BSGA_OK);
+  CHECK(g_calls == 1 && g_pooled == 2);  // one launch
+  CHECK(bsga_pool_qk(A, nullptr, 0, 16, 1000, 64, 128, (double*)A, nullptr, nullptr) == BSGA_OK && g_pooled == 1);
+  CHECK(bsga_pool_qk(nullptr, A, 0, 16, 1000, 64, 128, nullptr, (double*)A, nullptr) == BSGA_OK && g_calls == 3 && g_pooled == 1);
   CHECK(bsga_pool_qk(nullptr, nullptr, 0, 16, 1000, 64, 128, nullptr, nullptr, nullptr) == BSGA_ERR_INVALID_ARG && err_has("nothing"));
   CHECK(bsga_pool_qk(A, A, 9, 16, 1000, 64, 128, (double*)A, (double*)A, nullptr) == BSGA_ERR_INVALID_ARG && err_has("dtype"));
   CHECK(bsga_pool_qk(A, A, 0, 16, 1000, 64, 96, (double*)A, (double*)A, nullptr) == BSGA_ERR_UNSUPPORTED && err_has("block"));
@@ -254,6 +266,31 @@ int main() {
     CHECK(g_workspace_bytes == order);
     CHECK(bsga_sparse_attn(A, A, A, 0, 4, 1000, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 8, A, nullptr, nullptr, sizeof(buf), nullptr) == BSGA_OK);
     CHECK(g_workspace_bytes == 0);
+  }
+
+  // ---- an fp32 call hands its workspace on, of any size and place; a buffer of what the query says holds the parts
+  {
+    std::vector<unsigned char> room(bsga_attn_fp32_parts_bytes(3, 4100, 64, 1.0) + 16);
+    CHECK(room.size() == size_t(3) * 4100 * 768 + 16);
+    unsigned char* const at = reinterpret_cast<unsigned char*>((reinterpret_cast<uintptr_t>(room.data()) + 15) & ~uintptr_t(15));
+    const size_t bytes = room.size() - 16;
+    auto sparse = [&](void* ws, size_t n) {
+      return bsga_sparse_attn(A, A, A, 1, 3, 4100, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 33, A, nullptr, ws, n, nullptr);
+    };
+    CHECK(sparse(at, bytes) == BSGA_OK && g_workspace_bytes == bytes);
+    CHECK(sparse(at, 16) == BSGA_OK && g_workspace_bytes == 16);
+    CHECK(sparse(nullptr, bytes) == BSGA_OK && g_workspace_bytes == 0);
+    CHECK(bsga_dense_attn(A, A, A, 1, 3, 4100, 64, 0.125f, A, nullptr, at, bytes, nullptr) == BSGA_OK && g_workspace_bytes == bytes);
+    CHECK(bsga_dense_attn(A, A, A, 1, 3, 4100, 64, 0.125f, A, nullptr, at, 8, nullptr) == BSGA_OK && g_workspace_bytes == 0);
+  }
+  // ---- a bf16 call that looks at its lists, in a workspace of the size that the query says
+  {
+    const int64_t n = int64_t(301) * 128 - 5, first = int64_t(299) * 128 + 1;
+    std::vector<unsigned char> room(bsga_attn_workspace_bytes(0, 28, n, 64) + 16);
+    void* const at = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(room.data()) + 15) & ~uintptr_t(15));
+    CHECK(chooses_pairs(28, 301, 301));
+    CHECK(bsga_sparse_attn(A, A, A, 0, 28, n, 64, 128, 0.125f, (int32_t*)A, (int32_t*)A, 301, A, nullptr, at, room.size() - 16, nullptr) == BSGA_OK);
+    CHECK(bsga_sparse_attn_split(A, A, A, 0, 28, n, first, 64, 128, 64, 0.125f, (int32_t*)A, (int32_t*)A, 604, A, nullptr, at, room.size() - 16, nullptr) == BSGA_OK);
   }
 
   // ---- the entry point on built-in scratch: size limit is checked before any device call; on a
