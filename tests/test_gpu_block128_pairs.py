@@ -1,5 +1,6 @@
-"""Query blocks of 128 taken two to a workgroup of eight waves: dense launches of even rounds, and large sparse launches
-whose lists are long and of nearly one length (the rest goes row by row).  Every mix of common and own blocks in the first
+"""Query blocks of 128 taken two to a workgroup of eight waves: dense launches of long rows (which ones, hostglue/check_api.cpp
+tells: dense bits are the same both ways), and large sparse launches whose lists are long and of nearly one length (the rest
+goes row by row).  Every mix of common and own blocks in the first
 pairs, an odd number of blocks in a head, ragged last blocks, split sequences, key blocks of 64, uneven pairs and
 empty rows among them, lists in any order, and rows that need the second pass."""
 import pytest
@@ -107,7 +108,7 @@ def test_sparse_pairs(B, n, n_first, bk, shift):
         assert d.max() <= 1e-2 and d.mean() <= 1e-3
 
 
-@pytest.mark.parametrize("heads,n", [(16, 2748), (8, 5496), (3, 11000), (12, 13740 - 77), (16, 43968), (1, 100001)])
+@pytest.mark.parametrize("heads,n", [(16, 2748), (8, 5496), (3, 11000), (12, 13740 - 77), (16, 20400), (16, 43968), (1, 100001)])
 def test_dense_pairs(B, heads, n):
     spans = _starts(n, n, 128)
     nb = len(spans)
@@ -116,8 +117,11 @@ def test_dense_pairs(B, heads, n):
     rows = [(h, i) for h in {0, heads - 1} for i in {0, 1, nb // 2, nb - 2, nb - 1}]
     _check(out, lse, q, k, v, None, rows, spans, spans)
     assert torch.equal(out, B.bsga_dense_attn(q, k, v))
-    hot = [x * 30.0 for x in (q, k)] + [v]         # beyond the range of the first pass
-    assert bool(torch.isfinite(B.bsga_dense_attn(*hot)).all())
+    hot = _qkv(n, n + 1, 27.0, heads=heads)        # logits of 91 nats: beyond the range of the first pass
+    out, lse = B.bsga_dense_attn(*hot, return_lse=True)
+    _check(out, lse, *hot, None, rows, spans, spans, 27.0)
+    assert bool(torch.isfinite(out).all())
+    assert bool(torch.isfinite(B.bsga_dense_attn(q * 30.0, k * 30.0, v)).all())
 
 
 @pytest.mark.parametrize("heads,n", [(5200, 100), (2600, 256), (1800, 300)])

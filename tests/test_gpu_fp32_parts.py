@@ -58,11 +58,13 @@ def test_values_that_are_not_finite(B, what):
         run = lambda ws: B.bsga_sparse_attn_split(q, k, v, 64, n_first, idx, cnt, workspace=ws)
         o = run(torch.empty(16, dtype=torch.uint8, device="cuda"))
         got = run(_workspace(H, N))
-        assert torch.equal(got.isnan(), o.isnan())
-        o, got = o.nan_to_num(), got.nan_to_num()
+        # what is not finite is the same in both, sign and place
+        assert torch.equal(got.isnan(), o.isnan()) and torch.equal(got.isposinf(), o.isposinf()) and torch.equal(got.isneginf(), o.isneginf())
+        assert what == "k inf" or bool((~o.isfinite()).any())
         # rows that do not list the token's block but load the tokens after one that they do run on fp32 instructions: both ways
         # are as near to float64 as fp32 sums are
-        assert (got - o).abs().max() <= 1e-5 * max(1.0, float(o.abs().max()))
+        finite = o.isfinite()
+        assert finite.float().mean() > 0.9 and (got - o)[finite].abs().max() <= 1e-5 * max(1.0, float(o[finite].abs().max()))
 
 
 def test_layer_and_graph(B):
