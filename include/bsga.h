@@ -155,8 +155,10 @@ size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int hea
  * Bytes of device workspace with which an fp32 attention call of this shape is faster (0 where it is not and for invalid
  * arguments): K and V, each split in three bf16 parts, 768 bytes per token and head.  kept: the share of the key blocks that rows
  * are expected to keep, 1 for bsga_dense_attn.  An fp32 call given 768 bytes per token and head uses them whatever its lists hold, as
- * soon as it has more than 128 rows of 64; given less, none, or a workspace that is not 16-byte aligned it does without and gives the
- * same bits.
+ * soon as it has more than 128 rows of 64 (with lists of four blocks of 64 it is then a quarter slower than without); given less, none, or
+ * a workspace that is not 16-byte aligned it does without and gives the same bits, as long as all numbers are finite and none but zeros
+ * are below 2^-110: rows that meet others are computed anew on fp32 instructions, and a call with a workspace also does so for rows
+ * that come near them, in the tokens after a ragged block.
  */
 size_t bsga_attn_fp32_parts_bytes(int heads, int64_t n_tokens, int head_dim, double kept);
 
@@ -177,10 +179,12 @@ size_t bsga_attn_fp32_parts_bytes(int heads, int64_t n_tokens, int head_dim, dou
  *            differ a lot, and a few per cent slower on large shapes because the XCDs of a part do not
  *            run equally fast and cannot then share the last rows unevenly).
  * bf16: products on bf16 MFMA with fp32 accumulation, fp32 softmax weights.  softmax_scale > 0.
+ * fp32: products on fp32 MFMA, or in large calls on bf16 MFMA with every operand in three parts, whose error against 64 bits is smaller
+ * (numbers below 2^-110, infinities and NaN go to the fp32 instructions, at up to three times the time).
  * The index lists are trusted to be in range (they come from bsga_select_blocks); block
  * indices are clamped to [0, nb) before use so a corrupt list cannot read out of bounds.
  * A call gives the same bits every time.  Blocks may be computed two at a time (those of 128 in large calls with a
- * workspace): a row's sums are then taken in an order that its neighbour's list has a part in, and if one of the two
+ * workspace and, which changes no bits, in dense calls): a row's sums are then taken in an order that its neighbour's list has a part in, and if one of the two
  * needs the second pass with a running maximum (logits beyond the range of the first), both take it.
  * Any order of a row's entries gives the same result up to rounding; the ascending order that
  * bsga_select_blocks writes is the fast one (a ragged block, which is always the last block of the
