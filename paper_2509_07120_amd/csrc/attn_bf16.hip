@@ -132,7 +132,7 @@ constexpr int kOrderClasses = 32;
 
 __device__ __forceinline__ int order_class(int cnt, int nb) {  // class 0 holds the longest rows
   const int c = min(max(cnt, 0), nb);
-  return (kOrderClasses - 1) - static_cast<int>((int64_t(c) * (kOrderClasses - 1)) / nb);
+  return (kOrderClasses - 1) - static_cast<int>(static_cast<unsigned>(c) * (kOrderClasses - 1) / static_cast<unsigned>(nb));  // nb <= 2^18
 }
 
 // kept count of unit I of head h: of row I, or (pair) of the longer of rows 2I and 2I + 1
@@ -142,8 +142,9 @@ __device__ __forceinline__ int unit_count(const int32_t* __restrict__ kv_cnt, in
 }
 
 // Whether a large sparse launch of blocks of 128 takes them two to a workgroup (DUO) or one by one is known on the card only,
-// because it depends on the lists, see pairs_pay.  The order is then counted both ways, order_merge_kernel goes on with one of them and
-// leaves which in `choice` (else null), and both attention kernels are launched, of which one finds nothing to do.
+// because it depends on the lists, see pairs_pay.  The kernels below look at them (above kOrderOneMax rows the order is
+// counted both ways and order_merge_kernel goes on with one of them) and leave which in `choice` (else null); both
+// attention kernels are launched, of which one finds nothing to do.
 // Below: nu = units (rows, or pairs of rows) per head.
 __device__ __forceinline__ void read_choice(const int32_t* choice, int nb, int& nu, bool& pair) {
   if (choice == nullptr) return;
@@ -303,18 +304,47 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
 
 // The whole launch order in one workgroup, for up to kOrderOneMax units: 10 us at 1408 rows, where the
 // four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
-// of a thread are consecutive, so the bulk class keeps its order.
+// of a thread are consecutive, so the bulk class keeps its order.  choice: where it leaves whether pairs are taken (or null: as `pair` says).
 constexpr int kOrderOneMax = 8192;
-static_assert(kPairsMinRows >= kOrderOneMax, "order_one_kernel knows nothing of the choice");
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
+                                                         int heads, int per_tile, int32_t* choice, int32_t* __restrict__ order,
+                                                         int32_t* __restrict__ next_row) {
   constexpr int MAX = kOrderOneMax / 1024;
   __shared__ int total[kOrderClasses], next[kOrderClasses];
-  __shared__ int c_bulk_s, wave_bulk[16];
+  __shared__ int c_bulk_s, wave_bulk[16], sum[2];
   const int t = threadIdx.x;
+  if (t < kOrderClasses) total[t] = 0;
+  if (choice != nullptr) {
+    if (t < 2) sum[t] = 0;
+    const int half = (nb + 1) >> 1;
+    int all = 0, apart = 0;  // kOrderOneMax lists of kPairMaxBlocks are 2^25
+#pragma unroll
+    for (int i = 0; i < MAX / 2 + 1; ++i) {  // heads of an odd number of blocks have half a pair more
+      const int u = t + i * 1024;
+      if (u < heads * half) {
+        const int h = u / half, r = 2 * (u - h * half);
+        const int32_t* const c = kv_cnt + int64_t(h) * nb;
+        const int x = min(max(c[r], 0), nbk), y = r + 1 < nb ? min(max(c[r + 1], 0), nbk) : x;
+        all += x + y;
+        apart += abs(x - y);
+      }
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+      all += __shfl_xor(all, o);
+      apart += __shfl_xor(apart, o);
+    }
+    __syncthreads();
+    if ((t & 63) == 0) {
+      atomicAdd(&sum[0], all);
+      atomicAdd(&sum[1], apart);
+    }
+    __syncthreads();
+    pair = pairs_pay(sum[0], sum[1], static_cast<long long>(heads) * nb, nbk, per_tile);
+    if (pair) nu = half;
+    if (t == 0) *choice = pair;
+  }
   const int units = heads * nu;
   const int per = (units + 1023) >> 10;
-  if (t < kOrderClasses) total[t] = 0;
   __syncthreads();
   int cls[MAX];
 #pragma unroll
@@ -328,15 +358,21 @@ __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restri
     }
   }
   __syncthreads();
-  if (t == 0) {
-    const int c_bulk = bulk_class([&](int c) { return total[c]; });
-    int at = 0;
-    for (int c = 0; c <= c_bulk; ++c) {
-      next[c] = at;
-      at += total[c];
+  if (t < 64) {  // bulk_class and the classes' first places, a class to a lane
+    const int n = t < kOrderClasses ? total[t] : 0, weight = 2 * (kOrderClasses - 1 - t) + 1;
+    int all = n, mass = n * weight, upto = n;
+    for (int o = 1; o < 64; o <<= 1) {
+      all += __shfl_xor(all, o);
+      mass += __shfl_xor(mass, o);
+      const int x = __shfl_up(upto, o);
+      if (t >= o) upto += x;
     }
-    c_bulk_s = c_bulk;
-    *next_row = 0;  // the attention kernel's counter of rows handed out at run time
+    if (t < kOrderClasses) next[t] = upto - n;
+    const unsigned long long longer = __ballot(t < kOrderClasses - 1 && 10 * all * (kOrderClasses - 1 - t) >= 7 * mass);
+    if (t == 0) {
+      c_bulk_s = __popcll(longer);
+      *next_row = 0;  // the attention kernel's counter of rows handed out at run time
+    }
   }
   __syncthreads();
   const int c_bulk = c_bulk_s;
@@ -524,7 +560,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   constexpr int V_BASE = DUO ? TILE_BYTES : 2 * TILE_BYTES;
   constexpr int BUF_BYTES = DUO ? 2 * TILE_BYTES : TILE_BYTES;  // from one buffer of a tensor to the other
   extern __shared__ __align__(16) unsigned char smem[];
-  if (choice != nullptr && (*choice != 0) != DUO) return;  // see order_merge_kernel
+  if (choice != nullptr && (*choice != 0) != DUO) return;  // see read_choice
 
   const int tid0 = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
@@ -1850,16 +1886,15 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     int32_t* ord = static_cast<int32_t*>(workspace);
     int32_t* table = ord + rows;
     next_row = table + int64_t(kOrderClasses) * heads + 1;
-    if (rows <= kOrderOneMax) {  // too few for pairs, see chooses_pairs
-      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, ord, next_row);
+    const int per_tile = block_k == block ? 1 : 2;
+    int32_t* const chosen = choose ? table + int64_t(kOrderClasses) * heads + 2 : nullptr;
+    choice = chosen;
+    if (rows <= kOrderOneMax) {
+      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, per_tile, chosen, ord, next_row);
     } else {
-      int32_t* pairs = nullptr;
-      if (choose) {
-        choice = table + int64_t(kOrderClasses) * heads + 2;
-        pairs = table + int64_t(kOrderClasses) * heads + 3;
-      }
+      int32_t* const pairs = choose ? chosen + 1 : nullptr;
       hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table, pairs);
-      hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads, pairs, nb, nbk, block_k == block ? 1 : 2);
+      hipLaunchKernelGGL(order_merge_kernel, dim3(1), dim3(256), 0, stream, table, heads, pairs, nb, nbk, per_tile);
       hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, stream, table, int64_t(kOrderClasses) * heads);
       hipLaunchKernelGGL(order_place_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, choice, table, ord);
     }

@@ -99,12 +99,11 @@ inline bool dense_pairs(int heads, int nb) {
   return nb >= 96 && 50 * 2 * rounds * 256 <= 51 * rows;
 }
 // Whether a sparse launch of blocks of 128 is large enough to look at its lists before it takes rows one by one or in pairs, and these fit
-// the LDS.  The kernel that then is not meant costs 5 us, and the look itself cost 8 where the launch order is made by one kernel (up to
-// 8,192 rows): 4,112 rows of 257 blocks, a twentieth and a tenth kept, 224 -> 228 and 393 -> 401 us, 5,504 of 344 718 -> 728.  Rows of fewer
-// than 300 blocks gain 1 % at most, when they keep nearly all.
-constexpr int kPairsMinRows = 8192;  // more than this
+// the LDS.  The kernel that then is not meant costs 3 to 5 us (5,504 rows of 344 blocks, a twentieth and a tenth kept 397 -> 400 and 703 ->
+// 707 us); what there is to gain (nine tenths kept, lists of one length, 5,764 -> 5,639) is less with fewer rows: 4,816 of 301 4,445 ->
+// 4,385, 4,214 of 301 3,872 -> 3,869, 4,112 of 257 3,208 -> 3,238.
 inline bool chooses_pairs(int heads, int nb, int nbk) {
-  return int64_t(heads) * nb > kPairsMinRows && nb >= 300 && nbk <= kPairMaxBlocks;
+  return int64_t(heads) * nb > 20 * 256 && nb >= 300 && nbk <= kPairMaxBlocks;
 }
 // What it looks for, in the sum of the lists' lengths and the sum of the differences between the two of a pair (half a difference is time
 // that one of the two waits, and of a pair that differs by much each row is taken apart, see pair_differs).  One by one / in pairs, ms:

@@ -124,8 +124,8 @@ int main() {
     }
 
   // ---- which sparse launches look at their lists, and what for (lengths in tiles of all blocks, differences of all pairs)
-  CHECK(!chooses_pairs(16, 257, 257) && !chooses_pairs(16, 344, 344) && !chooses_pairs(16, 512, 512) && chooses_pairs(16, 513, 513));
-  CHECK(!chooses_pairs(64, 299, 299) && chooses_pairs(32, 300, 300) && chooses_pairs(3, 4096, 4096) && !chooses_pairs(3, 4097, 4097));
+  CHECK(!chooses_pairs(16, 257, 257) && !chooses_pairs(17, 301, 301) && chooses_pairs(18, 301, 301) && chooses_pairs(16, 344, 344));
+  CHECK(!chooses_pairs(64, 299, 299) && chooses_pairs(32, 300, 300) && chooses_pairs(2, 4096, 4096) && !chooses_pairs(2, 4097, 4097));
   auto pays = [](long long rows, int nb, int per_tile, double kept, double apart) {  // apart: difference of a pair over its sum
     const long long all = static_cast<long long>(kept * per_tile * nb * rows);
     return pairs_pay(all, static_cast<long long>(apart * all), rows, per_tile * nb, per_tile);

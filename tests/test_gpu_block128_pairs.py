@@ -9,7 +9,7 @@ import torch
 from tests.helpers import bf16_bars_ok
 
 pytestmark = pytest.mark.gpu
-H, NB = 28, 301
+H, NB = 18, 301  # 5,418 rows: the launch order is made by one kernel
 
 
 @pytest.fixture(scope="module")
@@ -122,6 +122,27 @@ def test_dense_pairs(B, heads, n):
     _check(out, lse, *hot, None, rows, spans, spans, 27.0)
     assert bool(torch.isfinite(out).all())
     assert bool(torch.isfinite(B.bsga_dense_attn(q * 30.0, k * 30.0, v)).all())
+
+
+def test_many_sparse_pairs(B):
+    """More rows than one kernel puts in order."""
+    heads, n = 28, NB * 128 - 70
+    spans = _starts(n, n, 128)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    keep = torch.rand((heads, NB, NB), generator=g, device="cuda") < 0.9
+    keep[7, 20] = keep[7, 21] = False
+    keep[7, 20, 5:40] = True
+    keep[9, 100, 30:200] = False                   # a pair that is taken apart
+    q, k, v = _qkv(n, 6, heads=heads)
+    idx, cnt = _lists(keep)
+    out, lse = B.bsga_sparse_attn(q, k, v, 128, idx, cnt, return_lse=True)
+    rows = [(7, 20), (7, 21), (9, 100), (9, 101), (0, 0), (0, NB - 1), (27, NB - 1), (13, 150), (27, 0)]
+    _check(out, lse, q, k, v, keep, rows, spans, spans)
+    one = B.bsga_sparse_attn(q, k, v, 128, idx, cnt, ordered=False)
+    assert not torch.equal(out, one) and (out.float() - one.float()).abs().max() <= 1e-2
+    keep = torch.rand((heads, NB, NB), generator=g, device="cuda") < 0.8   # rows of 240 tiles: one by one, the same bits
+    idx, cnt = _lists(keep)
+    assert torch.equal(B.bsga_sparse_attn(q, k, v, 128, idx, cnt), B.bsga_sparse_attn(q, k, v, 128, idx, cnt, ordered=False))
 
 
 @pytest.mark.parametrize("heads,n", [(5200, 100), (2600, 256), (1800, 300)])
