@@ -526,10 +526,11 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
 // waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
 //
-// DUO: eight waves, one workgroup to a CU, take two neighbouring blocks of 128 rows (four waves to each, as above).  Large
-// launches are bound by energy (the part lowers its clock), and moving the tiles costs a twentieth of it.  Tiles that both
-// rows need are loaded once for all eight waves, which halves the L2 -> LDS traffic: dense, 16 heads x 137,400 tokens 60.8 ->
-// 58.0 ms, 43,968 6.31 -> 6.10.  The lists are sorted into common and own blocks as for PAIR (below a kept fraction of 0.3
+// DUO: eight waves, one workgroup to a CU, take two neighbouring blocks of 128 rows (four waves to each, as above).  The part lowers its
+// clock under large launches, and with no tiles moved at all the kernel is 10 % faster, half of that by a higher clock (loads left out
+// after the first two tiles, 62.5 -> 56.2 ms, 1.60 -> 1.69 GHz).  Tiles that both rows need are loaded once for all eight
+// waves, which halves the L2 -> LDS traffic: dense, 16 heads x 137,400 tokens 60.8 -> 58.0 ms, 43,968 6.35 -> 6.12 (by 0.4 to 4 % over
+// cards).  The lists are sorted into common and own blocks as for PAIR (below a kept fraction of 0.3
 // they stay as they are); own tiles follow, each group of four waves on its own, but with barriers for all eight.  That is no
 // slower than two separate workgroups (dense without any sharing 60.8 -> 59.5: the groups stay in step, so what one loads the other
 // finds in the L1); four buffers and a barrier for two tiles are (58.0 -> 58.8).
@@ -1344,9 +1345,10 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
         ++T;
         return T < ntiles && !tile_ragged(J_cur);
       };
-      // The place of the loop in the code matters: of the 16 in 64 bytes, those at 28 and 60 take 3 % longer, those at 0, 16 and 32 1 %
-      // (dense, 43,968 tokens: 6.29, 6.19, and 6.10 ms here); the loops of the other kernels do not care.
-      if constexpr (DUO && BOTH) asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0");
+      // The place of the loop in the code matters, and the bad ones are others after each change of the code before it (dense, 43,968 tokens:
+      // at 8 bytes past a multiple of 64 6,655 us, at 0, 16, 32 and 48 6,573; at another time 28 and 60 were 3 % slower).  A multiple of
+      // 64 has not been one; to be looked at again with the loop or the compiler.
+      if constexpr (DUO && BOTH) asm volatile(".p2align 6");
       for (bool odd = DUO && !BOTH && flip != 0; odd || step(Int<0>{}); odd = false)
         if (!step(Int<1>{})) break;
       // ---- the O update and the last row-sum step of the run's last unit ------------------------------
