@@ -302,8 +302,8 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
   }
 }
 
-// The whole launch order in one workgroup, for up to kOrderOneMax units: 10 us at 1408 rows, where the
-// four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
+// The whole launch order in one workgroup, for up to kOrderOneMax units: 5.4 us at 1,376 rows, 10.2 at 5,504 with the choice, where
+// the four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
 // of a thread are consecutive, so the bulk class keeps its order.  choice: where it leaves whether pairs are taken (or null: as `pair` says).
 constexpr int kOrderOneMax = 8192;
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
@@ -1345,10 +1345,11 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
         ++T;
         return T < ntiles && !tile_ragged(J_cur);
       };
-      // The place of the loop in the code matters, and the bad ones are others after each change of the code before it (dense, 43,968 tokens:
-      // at 8 bytes past a multiple of 64 6,655 us, at 0, 16, 32 and 48 6,573; at another time 28 and 60 were 3 % slower).  A multiple of
-      // 64 has not been one; to be looked at again with the loop or the compiler.
-      if constexpr (DUO && BOTH) asm volatile(".p2align 6");
+      // The place of the loop in the code matters, the same every 32 bytes and not for all lists alike, and changes with the code before
+      // it.  Dense, 43,968 tokens, nine tenths of as many, of 137,400 and, with key blocks of 64, of 43,968: here 6,196, 5,723, 55,695 and
+      // 5,985 us, on a multiple of 32 6,192, 5,761, 56,185 and 5,973 (a scene of 100 frames 2.7 % slower), 8 past one 6,280, 5,737, 55,698,
+      // 5,966, 16 past one 6,192, 5,733, 55,829, 6,034.
+      if constexpr (DUO && BOTH) asm volatile(".p2align 6\n\ts_nop 0");
       for (bool odd = DUO && !BOTH && flip != 0; odd || step(Int<0>{}); odd = false)
         if (!step(Int<1>{})) break;
       // ---- the O update and the last row-sum step of the run's last unit ------------------------------
