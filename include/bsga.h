@@ -184,8 +184,9 @@ size_t bsga_attn_fp32_parts_bytes(int heads, int64_t n_tokens, int head_dim, dou
  * The index lists are trusted to be in range (they come from bsga_select_blocks); block
  * indices are clamped to [0, nb) before use so a corrupt list cannot read out of bounds.
  * A call gives the same bits every time.  Blocks may be computed two at a time (those of 128 in large calls with a
- * workspace and, which changes no bits, in dense calls): a row's sums are then taken in an order that its neighbour's list has a part in, and if one of the two
- * needs the second pass with a running maximum (logits beyond the range of the first), both take it.
+ * workspace and, which changes no bits, in dense calls): a row's sums are then taken in an order that its neighbour's
+ * list has a part in, and if one of the two needs the second pass with a running maximum (logits beyond the range of
+ * the first), both take it.
  * Any order of a row's entries gives the same result up to rounding; the ascending order that
  * bsga_select_blocks writes is the fast one (a ragged block, which is always the last block of the
  * sequence or of its first part, should come last or nearly last in its row: the tiles after it
