@@ -261,6 +261,26 @@ int bsga_dense_attn(const void* q, const void* k, const void* v, int dtype, int 
                     void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The rest of a transformer block around the layer (Sec. 3.1), in bf16; all arrays 16-byte aligned.
+ *
+ * bsga_linear: out[i] = act(weight x[i] + bias), weight [out_features, in_features], fp32 accumulation.
+ *   x          [n_tokens, in_features], or with x_heads [in_features / 64, n_tokens, 64] (what the attention returns)
+ *   activation 0 none, 1 GELU (x Phi(x), on the fp32 sums)
+ *   out        [n_tokens, out_features], or with out_heads [out_features / 64, n_tokens, 64] (what the attention takes)
+ *   row_index  nullable [n_tokens], a permutation: row i goes to out[row_index[i]] (clamped to [0, n_tokens))
+ *   residual   nullable [n_tokens, out_features], may be out: its row is added to the row of out, after the result is rounded to bf16
+ * Features are multiples of 64, x and weight smaller than 2 GiB; row_index and residual without out_heads.
+ *
+ * bsga_layer_norm: out[i] = (x[j] - mean) / sqrt(variance + eps) * weight + bias, j = index[i] (nullable: i; clamped), statistics in fp32.
+ *   features: a multiple of 8, up to 4096.
+ */
+int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features,
+                int out_features, int activation, const int32_t* row_index, const void* residual, int out_heads,
+                void* out, void* stream);
+int bsga_layer_norm(const void* x, const void* weight, const void* bias, double eps, int64_t n_tokens, int features,
+                    const int32_t* index, void* out, void* stream);
+
+/*
  * Measurement aid, not part of the method: the rate the matrix pipes sustain on the MFMA instruction
  * the bf16 attention kernels use (32x32x16 bf16, the products of Eqs. (1)/(2)), with no memory traffic
  * at all, two workgroups of four waves per CU.  The part lowers its clock with the switching activity

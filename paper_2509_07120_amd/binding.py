@@ -44,6 +44,8 @@ EXPORTED_SYMBOLS = (
     "bsga_sparse_attn_qk",
     "bsga_sparse_attn_split",
     "bsga_dense_attn",
+    "bsga_linear",
+    "bsga_layer_norm",
     "bsga_probe_mfma",
 )
 
@@ -106,6 +108,11 @@ def _load() -> ctypes.CDLL:
     lib.bsga_dense_attn.restype = c_int
     lib.bsga_dense_attn.argtypes = [c_void_p, c_void_p, c_void_p, c_int, c_int, c_int64, c_int, c_float,
                                     c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
+    lib.bsga_linear.restype = c_int
+    lib.bsga_linear.argtypes = [c_void_p, c_int, c_void_p, c_void_p, c_int64, c_int, c_int, c_int, c_void_p, c_void_p, c_int,
+                                c_void_p, c_void_p]
+    lib.bsga_layer_norm.restype = c_int
+    lib.bsga_layer_norm.argtypes = [c_void_p, c_void_p, c_void_p, c_double, c_int64, c_int, c_void_p, c_void_p, c_void_p]
     lib.bsga_probe_mfma.restype = c_int
     lib.bsga_probe_mfma.argtypes = [c_int, c_int, c_int, c_void_p, c_size_t, ctypes.POINTER(c_double), c_void_p]
     return lib
@@ -458,6 +465,42 @@ def bsga_merge_heads(x: torch.Tensor, index: Optional[torch.Tensor] = None) -> t
     _require_order(index, x, N)
     out = torch.empty((N, H * d), dtype=x.dtype, device=x.device)
     _check(lib.bsga_merge_heads(_ptr(x), _dtype_code(x), H, N, d, _ptr(index), _ptr(out), _stream(x)))
+    return out
+
+
+def bsga_layer_norm(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, eps: float = 1e-5,
+                    index: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Layer norm of x [N, D] (bfloat16, D a multiple of 8 up to 4096), row i of the result from row index[i] if an index is given."""
+    _require(x, "x", torch.bfloat16); _require(weight, "weight", torch.bfloat16); _require(bias, "bias", torch.bfloat16)
+    if x.dim() != 2 or tuple(weight.shape) != (x.shape[1],) or tuple(bias.shape) != (x.shape[1],):
+        raise ValueError("x must be [n_tokens, features], weight and bias [features]")
+    N, D = x.shape
+    _require_order(index, x, N)
+    out = torch.empty_like(x)
+    _check(lib.bsga_layer_norm(_ptr(x), _ptr(weight), _ptr(bias), float(eps), N, D, _ptr(index), _ptr(out), _stream(x)))
+    return out
+
+
+def bsga_linear(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, gelu: bool = False,
+                residual: Optional[torch.Tensor] = None, row_index: Optional[torch.Tensor] = None,
+                out_heads: bool = False) -> torch.Tensor:
+    """weight x + bias in bfloat16 with its neighbours folded in (features are multiples of 64).  x is [N, K], or [K/64, N, 64]
+    as the attention returns it.  gelu: applied to the fp32 sums.  row_index, residual: row i of the result is row row_index[i] of
+    the output (a permutation) and has that row of the residual added.  out_heads: the output is [F/64, N, 64], not [N, F]."""
+    _require(x, "x", torch.bfloat16); _require(weight, "weight", torch.bfloat16); _require(bias, "bias", torch.bfloat16)
+    F_out, K = weight.shape
+    heads = x.dim() == 3
+    N = x.shape[1] if heads else x.shape[0]
+    if tuple(x.shape) != ((K // 64, N, 64) if heads else (N, K)) or tuple(bias.shape) != (F_out,):
+        raise ValueError("x must be [n_tokens, in_features] or [in_features / 64, n_tokens, 64], bias [out_features]")
+    _require_order(row_index, x, N)
+    if residual is not None:
+        _require(residual, "residual", torch.bfloat16)
+        if tuple(residual.shape) != (N, F_out):
+            raise ValueError("residual must be [n_tokens, out_features]")
+    out = torch.empty((F_out // 64, N, 64) if out_heads else (N, F_out), dtype=x.dtype, device=x.device)
+    _check(lib.bsga_linear(_ptr(x), int(heads), _ptr(weight), _ptr(bias), N, K, F_out, int(gelu), _ptr(row_index),
+                           _ptr(residual), int(out_heads), _ptr(out), _stream(x)))
     return out
 
 

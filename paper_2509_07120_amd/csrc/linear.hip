@@ -1,0 +1,481 @@
+// The parts of a transformer block around the attention (Sec. 3.1; the appendix "Theoretical FLOPs Reduction" for what
+// they are): linear layers in bf16 with their neighbours folded in, and the layer norm.
+//
+// linear_kernel: y[i][f] = sum_k x[i][k] w[f][k] + b[f] on v_mfma_f32_32x32x16_bf16, fp32 accumulation, the sum started from the bias.
+//
+// Tile and split.  A workgroup of four waves, one to a SIMD, takes 64 FU features x 64 TU tokens; each wave a quarter, 32 FU x 32 TU,
+// so an operand read from LDS feeds TU (FU) products.  At 256 x 256 a step of 64 in k reads 128 KB of LDS and writes 64 KB
+// under 2048 cycles of matrix products, of 3072 that would be LDS-bound at 64 x 64 per wave.
+// The features are the products' rows, so a lane holds one token and four consecutive features.
+//
+// Data movement.  Both operands go from global memory straight to LDS (direct-to-LDS loads, 16 bytes per lane), in steps of 64 in k,
+// S buffers; rows of 128 bytes, chunks swizzled (swz_k) so that the operand reads are free of bank conflicts.
+// Workgroups are persistent and take the steps of all their tiles as one sequence: the loads of the next tile's first steps are under
+// way while the last step and the epilogue of this one run.  One barrier per step, a quarter step before its end: by then every
+// wave has the operands of the last quarter in registers, so the buffer is free for the step S later, whose loads are
+// issued over the next half step (over a quarter: 10,992 tokens, 1024 -> 3072 features 87 us and not 80, 4096 -> 1024 85 and not
+// 80; over a whole step 83 and 88.  Steps of 32 in k with four buffers, rows of 64 bytes: 84 and 85).
+// Few tiles are bound by the latency of a step's loads, 0.85 us with two buffers, and the smaller tiles have room for more: 128 x 64,
+// five buffers instead of two, 800 tokens 4096 -> 1024 54 -> 22 us.
+//
+// x is [tokens][k], or (step_bytes = tokens * 128) [k / 64][tokens][64], as the attention leaves its heads: a step is then a head, and the
+// heads need not be merged first.  The result is [tokens][features], row i optionally at row_index[i] and added to that row
+// of `residual`, or [features / 64][tokens][64], as the attention wants them.
+// The epilogue turns 32 tokens at a time through a piece of LDS of the wave's own, so that stores (and the residual's loads) are
+// whole rows of up to 256 bytes.
+#include <utility>
+
+#include "bf16_tile.h"
+#include "bsga_internal.h"
+
+namespace bsga {
+namespace {
+
+constexpr int kTokenGroup = 8;  // token tiles that neighbouring workgroups take before the next feature tile
+
+struct LinearArgs {
+  const unsigned char* x;
+  const unsigned char* w;
+  const unsigned char* bias;
+  const unsigned char* residual;
+  unsigned char* out;
+  const int32_t* row_index;
+  unsigned x_bytes, x_row, x_step;  // bytes of x, of a row, from one step of 64 in k to the next
+  unsigned w_bytes, w_row;
+  int n_tokens, features, steps;
+  int token_tiles, feature_tiles;
+  bool heads;  // result as [features / 64][tokens][64]
+};
+
+// x Phi(x) = max(x, 0) - |x| h(|x|), h(a) = erfc(a / sqrt 2) / 2 = exp(-a^2 / 2) t P(t), t = 1 / (1 + 0.385 a): a form of erfc that goes
+// back to Hastings, here with P of degree 4 fitted by weighted least squares to the relative error of h over [0, 30], 5.7e-5, a
+// thirtieth of the rounding to bf16 that follows.
+// Infinities and NaN come out as x Phi(x) does.
+__device__ __forceinline__ float gelu(float x) {
+  const float a = __builtin_fabsf(x);
+  const float ac = fminf(a, 30.f);  // h is 0 from there on
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.385f, ac, 1.f));
+  float p = -0.08739237f;
+  p = fmaf(p, t, 0.17426558f);
+  p = fmaf(p, t, 0.10218015f);
+  p = fmaf(p, t, 0.15753566f);
+  p = fmaf(p, t, 0.15341043f);
+  const float e = __builtin_amdgcn_exp2f(ac * ac * -0.72134752f);
+  return fmaf(-ac, p * t * e, fmaf(0.5f, a, 0.5f * x));
+}
+
+__device__ __forceinline__ float low_bf16(unsigned x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float high_bf16(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
+
+template <int FU, int TU, int S>
+constexpr int kLinearLds = S * (64 * FU + 64 * TU) * 128 + 4 * 32 * FU * 64;
+template <int FU, int TU, int S>
+constexpr int kLinearPerCu = 2 * kLinearLds<FU, TU, S> <= 160 * 1024 ? 2 : 1;  // workgroups to a CU
+
+template <typename Fn, int... I>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, Fn&& fn) {
+  (fn(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename Fn>  // fn(0) .. fn(N - 1), the number as a constant
+__device__ __forceinline__ void each(Fn&& fn) {
+  each_of(std::make_integer_sequence<int, N>{}, fn);
+}
+
+template <int FU, int TU, int S, bool GELU>
+__global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(LinearArgs a) {
+  constexpr int FT = 64 * FU, TT = 64 * TU;  // tile
+  constexpr int STAGE = (FT + TT) * 128;
+  constexpr int SPAN = 2 * FU;  // places in the code over which a step's loads are spread
+  constexpr int LOADS = 2 * (FU + TU);  // of a wave for a step
+  constexpr int ROW = FU * 64;  // bytes of a wave's features of one token
+  constexpr int RC = ROW / 16;  // chunks of 16 bytes
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wf = wave & 1, wt = wave >> 1;
+  const int n = lane & 31, g = lane >> 5;
+
+  // which tiles: round r of this workgroup is tile r * gridDim.x + me; consecutive numbers to one XCD (workgroup w runs on XCD w % 8),
+  // eight token tiles by four feature tiles there at a time
+  const int grid = static_cast<int>(gridDim.x), w_id = static_cast<int>(blockIdx.x);
+  const int me = (grid & 7) == 0 ? (w_id & 7) * (grid >> 3) + (w_id >> 3) : w_id;
+  const int tiles = a.token_tiles * a.feature_tiles;
+  auto place = [&](int tile, int& f0, int& t0) {
+    const int per = kTokenGroup * a.feature_tiles;
+    const int group = tile / per, rest = tile - group * per;
+    const int wide = min(kTokenGroup, a.token_tiles - group * kTokenGroup);
+    const int f = rest / wide;
+    f0 = f * FT;
+    t0 = (group * kTokenGroup + rest - f * wide) * TT;
+  };
+
+  // ---- loads: wave-load i of a tensor's tile covers rows 8 wave + 32 i .. +7 ----------------------------------------
+  const unsigned smem_addr = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) unsigned char*)smem));
+  const i32x4 wrsrc = make_rsrc(a.w, a.w_bytes), xrsrc = make_rsrc(a.x, a.x_bytes);
+  unsigned w_off[2], x_off[2];
+  {
+    const int r0 = wave * 8 + (lane >> 3);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const unsigned chunk = ((lane & 7) ^ swz_k(r0 + 32 * p)) << 4;
+      w_off[p] = r0 * a.w_row + chunk;
+      x_off[p] = r0 * a.x_row + chunk;
+    }
+  }
+  auto load = [&](auto ic, unsigned wsoff, unsigned xsoff, unsigned lds) {
+    constexpr int i = decltype(ic)::value, j = i - 2 * FU;
+    if constexpr (j < 0) dma16<i * 4096>(wrsrc, w_off[i & 1], wsoff + i * 32 * a.w_row, lds);
+    else dma16<FT * 128 + j * 4096>(xrsrc, x_off[j & 1], xsoff + j * 32 * a.x_row, lds);
+  };
+
+  // ---- operand reads: row r0 + 32 u of the wave's, chunk 2c + g; swz_k(r + 32) = swz_k(r) ^ 4 ------------------------
+  int f_addr[4], x_addr[4];
+  {
+    const int rf = wf * 32 * FU + n, rx = wt * 32 * TU + n;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      f_addr[c] = rf * 128 + (((2 * c + g) ^ swz_k(rf)) << 4);
+      x_addr[c] = FT * 128 + rx * 128 + (((2 * c + g) ^ swz_k(rx)) << 4);
+    }
+  }
+  auto read_f = [&](int buf, int c, int u) { return *LDS_PTR(bf16x8, smem + buf + f_addr[(u & 1) ? c ^ 2 : c] + u * 4096); };
+  auto read_x = [&](int buf, int c, int u) { return *LDS_PTR(bf16x8, smem + buf + x_addr[(u & 1) ? c ^ 2 : c] + u * 4096); };
+
+  f32x16 acc[FU][TU];
+  bf16x8 fa[2][FU], fx[2][TU];
+
+  // the steps of all tiles in a row; (lf, lt, ls): what is loaded next
+  int tile = me;
+  if (tile >= tiles) return;
+  int load_tile = me, ls = 0;
+  unsigned wsoff, xsoff;
+  {
+    int f0, t0;
+    place(tile, f0, t0);
+    wsoff = f0 * a.w_row;
+    xsoff = t0 * a.x_row;
+  }
+  auto advance = [&]() {  // to the step after the one that was just loaded
+    wsoff += 128;
+    xsoff += a.x_step;
+    if (++ls == a.steps) {
+      ls = 0;
+      load_tile += grid;
+      int f0, t0;
+      place(load_tile < tiles ? load_tile : me, f0, t0);  // past the end: loaded again and not used
+      wsoff = f0 * a.w_row;
+      xsoff = t0 * a.x_row;
+    }
+  };
+
+  u32x2 bias_raw[FU][4];
+  auto load_bias = [&](int f0) {
+#pragma unroll
+    for (int u = 0; u < FU; ++u)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        bias_raw[u][r4] = *reinterpret_cast<const u32x2*>(a.bias + 2 * min(f0 + wf * 32 * FU + 32 * u + 8 * r4 + 4 * g, a.features - 4));
+  };
+  auto start_sums = [&]() {
+#pragma unroll
+    for (int u = 0; u < FU; ++u)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+        for (int t = 0; t < TU; ++t) {
+          acc[u][t][4 * r4] = low_bf16(bias_raw[u][r4].x);
+          acc[u][t][4 * r4 + 1] = high_bf16(bias_raw[u][r4].x);
+          acc[u][t][4 * r4 + 2] = low_bf16(bias_raw[u][r4].y);
+          acc[u][t][4 * r4 + 3] = high_bf16(bias_raw[u][r4].y);
+        }
+  };
+
+  const unsigned lds_wave = smem_addr + wave * 1024;
+#pragma unroll
+  for (int i = 0; i < S - 1; ++i) {
+    each<LOADS>([&](auto l) { load(l, wsoff, xsoff, lds_wave + i * STAGE); });
+    advance();
+  }
+  each<LOADS>([&](auto l) {
+    if constexpr (decltype(l)::value * SPAN / LOADS < FU) load(l, wsoff, xsoff, lds_wave + (S - 1) * STAGE);
+  });
+  {
+    int f0, t0;
+    place(tile, f0, t0);
+    load_bias(f0);
+  }
+  start_sums();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  int buf = 0, load_buf = (S - 1) * STAGE;
+#pragma unroll
+  for (int u = 0; u < FU; ++u) fa[0][u] = read_f(buf, 0, u);
+#pragma unroll
+  for (int t = 0; t < TU; ++t) fx[0][t] = read_x(buf, 0, t);
+
+  for (;;) {
+    for (int s = 0; s < a.steps; ++s) {
+      each<4>([&](auto cc) {
+        constexpr int c = decltype(cc)::value, c1 = (c + 1) & 3;
+        if constexpr (c == 3) {
+          // the operands of this quarter are in registers and the next step's loads have arrived, everywhere after the barrier
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * LOADS) : "memory");
+          __builtin_amdgcn_s_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+          load_buf = buf;
+          buf = buf == (S - 1) * STAGE ? 0 : buf + STAGE;
+          advance();
+        }
+        each<FU>([&](auto uc) {
+          constexpr int u = decltype(uc)::value;
+          fa[c1 & 1][u] = read_f(buf, c1, u);
+#pragma unroll
+          for (int t = u; t < TU; t += FU) fx[c1 & 1][t] = read_x(buf, c1, t);
+          each<LOADS>([&](auto l) {
+            constexpr int i = decltype(l)::value;
+            if constexpr (i * SPAN / LOADS == c1 * FU + u) load(l, wsoff, xsoff, lds_wave + load_buf);
+          });
+#pragma unroll
+          for (int t = 0; t < TU; ++t)
+            acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c & 1][u], fx[c & 1][t], acc[u][t], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      });
+    }
+
+    // ---- epilogue -----------------------------------------------------------------------------------------
+    int f0, t0;
+    place(tile, f0, t0);
+    tile += grid;
+    const bool last = tile >= tiles;
+    {
+      int nf, nt;
+      place(last ? me : tile, nf, nt);
+      load_bias(nf);
+    }
+    unsigned char* const turn = smem + S * STAGE + wave * (32 * ROW);
+    const int fw = f0 + wf * 32 * FU, tw = t0 + wt * 32 * TU;
+    constexpr int PASS = 64 / RC;       // tokens that the wave reads back at a time
+    constexpr int PASSES = 32 / PASS;
+    const int rc = lane % RC, rr = lane / RC;
+    const int f = fw + rc * 8;  // the lane's eight features
+#pragma unroll
+    for (int t = 0; t < TU; ++t) {
+      int64_t at[PASSES];  // byte offset in the output, negative: nothing to store
+      u32x4 res[PASSES];
+#pragma unroll
+      for (int p = 0; p < PASSES; ++p) {
+        const int i = tw + 32 * t + p * PASS + rr;
+        const bool in = i < a.n_tokens && f < a.features;
+        if (a.heads) {
+          at[p] = (int64_t(f >> 6) * a.n_tokens + i) * 128 + (f & 63) * 2;
+        } else {
+          const int row = a.row_index != nullptr ? min(max(a.row_index[min(i, a.n_tokens - 1)], 0), a.n_tokens - 1) : i;
+          at[p] = (int64_t(row) * a.features + f) * 2;
+        }
+        if (!in) at[p] = -1;
+        res[p] = u32x4{0, 0, 0, 0};
+        if (a.residual != nullptr && in) res[p] = *reinterpret_cast<const u32x4*>(a.residual + at[p]);
+      }
+#pragma unroll
+      for (int u = 0; u < FU; ++u)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          float y[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            y[r] = acc[u][t][4 * r4 + r];
+            if constexpr (GELU) y[r] = gelu(y[r]);
+          }
+          const u32x2 two = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+          *reinterpret_cast<u32x2 __attribute__((address_space(3)))*>(
+              (__attribute__((address_space(3))) unsigned char*)(turn + n * ROW + (((4 * u + r4) ^ (n & (RC - 1))) << 4) + 8 * g)) = two;
+        }
+      // (LDS operations of one wave run in order; the fence keeps the compiler from moving the reads up)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int p = 0; p < PASSES; ++p) {
+        const int r = p * PASS + rr;
+        u32x4 y = *LDS_PTR(u32x4, turn + r * ROW + ((rc ^ (r & (RC - 1))) << 4));
+        if (a.residual != nullptr) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            y[e] = pack_bf16(low_bf16(y[e]) + low_bf16(res[p][e]), high_bf16(y[e]) + high_bf16(res[p][e]));
+        }
+        if (at[p] >= 0) *reinterpret_cast<u32x4*>(a.out + at[p]) = y;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    if (last) break;
+    start_sums();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // loads that nobody uses have arrived before the LDS is given back
+}
+
+// out[i] = layer norm of x[index[i]] (or of x[i]), a row to a wave, the row in registers: mean, then the mean of squared
+// distances from it, in fp32.  Bound by memory: one pass over either.
+template <int SLOTS>  // chunks of eight values per lane
+__global__ __launch_bounds__(256) void layer_norm_kernel(const unsigned char* __restrict__ x, const unsigned char* __restrict__ weight,
+                                                         const unsigned char* __restrict__ bias, const int32_t* __restrict__ index,
+                                                         unsigned char* __restrict__ out, int n, int d, float eps) {
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i >= n) return;  // whole wave; the kernel has no barriers
+  const int row = index != nullptr ? min(max(index[i], 0), n - 1) : i;
+  const int chunks = d >> 3;
+  const u32x4* src = reinterpret_cast<const u32x4*>(x + int64_t(row) * d * 2);
+  float v[SLOTS][8];
+  float sum = 0.f;
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int c = s * 64 + lane;
+    const u32x4 raw = src[min(c, chunks - 1)];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[s][2 * e] = low_bf16(raw[e]);
+      v[s][2 * e + 1] = high_bf16(raw[e]);
+      sum += c < chunks ? v[s][2 * e] + v[s][2 * e + 1] : 0.f;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  const float mean = sum / d;
+  float squares = 0.f;
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[s][e] -= mean;
+      squares += s * 64 + lane < chunks ? v[s][e] * v[s][e] : 0.f;
+    }
+  for (int o = 32; o > 0; o >>= 1) squares += __shfl_xor(squares, o);
+  const float scale = 1.f / sqrtf(squares / d + eps);
+  u32x4* dst = reinterpret_cast<u32x4*>(out + int64_t(i) * d * 2);
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int c = s * 64 + lane;
+    if (c >= chunks) continue;
+    u32x4 w = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+    w = reinterpret_cast<const u32x4*>(weight)[c];
+    b = reinterpret_cast<const u32x4*>(bias)[c];
+    u32x4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      y[e] = pack_bf16(fmaf(v[s][2 * e] * scale, low_bf16(w[e]), low_bf16(b[e])),
+                       fmaf(v[s][2 * e + 1] * scale, high_bf16(w[e]), high_bf16(b[e])));
+    dst[c] = y;
+  }
+}
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+template <int FU, int TU, int S>
+int launch_linear(LinearArgs a, bool with_gelu, hipStream_t stream) {
+  a.token_tiles = static_cast<int>(ceil_div(a.n_tokens, 64 * TU));
+  a.feature_tiles = static_cast<int>(ceil_div(a.features, 64 * FU));
+  constexpr int places = 256 * kLinearPerCu<FU, TU, S>;
+  const dim3 grid(static_cast<unsigned>(min(int64_t(a.token_tiles) * a.feature_tiles, int64_t(places))));
+  constexpr size_t lds = kLinearLds<FU, TU, S>;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a); };
+  if (with_gelu) launch(linear_kernel<FU, TU, S, true>);
+  else launch(linear_kernel<FU, TU, S, false>);
+  return check_hip(hipGetLastError(), "bsga_linear launch");
+}
+
+}  // namespace
+}  // namespace bsga
+
+using namespace bsga;
+
+extern "C" {
+
+int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features,
+                int activation, const int32_t* row_index, const void* residual, int out_heads, void* out, void* stream) {
+  const char* fn = "bsga_linear";
+  clear_error();
+  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
+  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out) || !aligned16(residual))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
+  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
+  if (in_features < 64 || in_features % 64 != 0 || out_features < 64 || out_features % 64 != 0)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be multiples of 64, got %d -> %d", fn, in_features, out_features);
+  if (activation != 0 && activation != 1) return fail(BSGA_ERR_INVALID_ARG, "%s: activation must be 0 (none) or 1 (GELU), got %d", fn, activation);
+  if (out_heads && (row_index || residual))
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: row_index and residual go with rows of tokens", fn);
+  // byte offsets into x and the weight are 32 bits, and go up to a tile past the end
+  const int64_t limit = int64_t(1) << 31;
+  if ((n_tokens + 256) * in_features * 2 >= limit || (int64_t(out_features) + 256) * in_features * 2 >= limit)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: x and weight must be below 2 GiB", fn);
+  LinearArgs a = {};
+  a.x = static_cast<const unsigned char*>(x);
+  a.w = static_cast<const unsigned char*>(weight);
+  a.bias = static_cast<const unsigned char*>(bias);
+  a.residual = static_cast<const unsigned char*>(residual);
+  a.out = static_cast<unsigned char*>(out);
+  a.row_index = row_index;
+  a.x_bytes = static_cast<unsigned>(n_tokens * in_features * 2);
+  a.x_row = x_heads ? 128 : in_features * 2;
+  a.x_step = x_heads ? static_cast<unsigned>(n_tokens * 128) : 128;
+  a.w_bytes = static_cast<unsigned>(int64_t(out_features) * in_features * 2);
+  a.w_row = in_features * 2;
+  a.n_tokens = static_cast<int>(n_tokens);
+  a.features = out_features;
+  a.steps = in_features / 64;
+  a.heads = out_heads != 0;
+  // The kernel with the least rounds of the chip times time of a tile, (steps * step + rest) ns as fitted to sequences of 800 to 33,000
+  // tokens at 1024 features.  Wide tiles move least, narrow ones with many buffers hide the latency of a launch of one round and leave
+  // less of the last round idle.  us, 256 x 192 / 128 x 192 / 128 x 128, two to a CU / 128 x 128, four buffers / 128 x 64, five:
+  // 10,992 tokens 1024 -> 3072 78 / 85 / 89 / 85 / 109, 4096 -> 1024 82 / 97 / 134 / 102 / 129; 4,122 45 / 39 / 39 / 38 / 45, 69 / 44 / 64 /
+  // 59 / 61; 1,374 24 / 16 / 19 / 20 / 21, 65 / 39 / 59 / 30 / 23.
+  struct Shape {
+    int features, tokens, places, step, rest;
+    int (*launch)(LinearArgs, bool, hipStream_t);
+  };
+  static const Shape shapes[] = {{256, 192, 256, 1000, 10000, launch_linear<4, 3, 2>},
+                                 {128, 192, 256, 560, 6000, launch_linear<2, 3, 3>},
+                                 {128, 128, 512, 950, 3000, launch_linear<2, 2, 2>},
+                                 {128, 128, 256, 480, 2500, launch_linear<2, 2, 4>},
+                                 {128, 64, 256, 310, 2000, launch_linear<2, 1, 5>}};
+  const Shape* best = nullptr;
+  int64_t least = 0;
+  for (const Shape& c : shapes) {
+    const int64_t tiles = ceil_div(n_tokens, c.tokens) * ceil_div(out_features, c.features);
+    const int64_t ns = ceil_div(tiles, c.places) * (int64_t(a.steps) * c.step + c.rest);
+    if (best != nullptr && ns >= least) continue;
+    best = &c;
+    least = ns;
+  }
+  return best->launch(a, activation == 1, static_cast<hipStream_t>(stream));
+}
+
+int bsga_layer_norm(const void* x, const void* weight, const void* bias, double eps, int64_t n_tokens, int features,
+                    const int32_t* index, void* out, void* stream) {
+  const char* fn = "bsga_layer_norm";
+  clear_error();
+  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
+  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
+  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
+  if (features < 8 || features % 8 != 0 || features > 4096)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be a multiple of 8 up to 4096, got %d", fn, features);
+  const dim3 grid(static_cast<unsigned>(ceil_div(n_tokens, 4)));
+  const unsigned char *xp = static_cast<const unsigned char*>(x), *wp = static_cast<const unsigned char*>(weight),
+                      *bp = static_cast<const unsigned char*>(bias);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, xp, wp, bp, index, static_cast<unsigned char*>(out), static_cast<int>(n_tokens),
+                       features, static_cast<float>(eps));
+  };
+  if (features <= 512) launch(layer_norm_kernel<1>);
+  else if (features <= 1024) launch(layer_norm_kernel<2>);
+  else if (features <= 2048) launch(layer_norm_kernel<4>);
+  else launch(layer_norm_kernel<8>);
+  return check_hip(hipGetLastError(), "bsga_layer_norm launch");
+}
+
+}  // extern "C"
