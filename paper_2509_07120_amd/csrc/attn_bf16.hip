@@ -12,7 +12,7 @@
 // merged once at the end.  Two workgroups share a CU (two waves per SIMD).
 // Which workgroup computes which row: see the end of the kernel (launch order, 64 consecutive rows
 // per XCD, the last eighth of a large launch handed out at run time).  Launches of few long rows,
-// blocks of 64 rows and large launches of blocks of 128 divide the work otherwise: STREAM, PAIR and SOLO, DUO below.
+// blocks of 64 rows and large launches of blocks of 128 divide the work otherwise: STREAM, PAIR, DUO below; launches of few short rows go to attn_few.hip.
 //
 // Data movement.  K and V tiles go HBM/L2 -> LDS with direct-to-LDS loads (16 bytes per lane, no
 // staging registers), double buffered, with one workgroup barrier per tile.  Tiles stay row-major
@@ -62,14 +62,6 @@ using Int = std::integral_constant<int, V>;
 
 // chunk swizzle of V tiles (of K tiles: swz_k): 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
 __device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
-
-// the lane's number, through an instruction that the compiler does not see through: nothing that is computed from it can be
-// made ahead of it and kept in registers
-__device__ __forceinline__ int fresh_lane() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
 
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32); }
 
@@ -475,11 +467,8 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // 2,752 rows of 172 blocks, nine tenths kept: 515 -> 434 us; 5,504 of 344 1,910 -> 1,590.
 // While the rest of the longer list runs, the waves of the other block idle.  A pair whose lists differ in length by
 // more than what they share (and a dozen steps, about what another row's start and merge cost) is therefore taken
-// row by row, four waves to each as in SOLO, and so is the odd block at the end of a head.  Lists of nine tenths
+// row by row, four waves to each (ONE: its list dealt to the two halves in turn), and so is the odd block at the end of a head.  Lists of nine tenths
 // and a twentieth in turn, 5,504 rows of 344: 1,080 us with two waves to a row, 1,500 in pairs only, 1,115 so.
-//
-// SOLO: the same kernel with one block of 64 rows and one list, its entries dealt to the two halves in turn: four
-// waves, not two, share a row, which is then half as many steps long.  For launches that do not fill the chip.
 //
 // DUO: eight waves, one workgroup to a CU, take two neighbouring blocks of 128 rows (four waves to each, as above).  The part lowers its
 // clock under large launches, and with no tiles moved at all the kernel is 10 % faster, half of that by a higher clock (loads left out
@@ -493,7 +482,7 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // Nothing runs beside the start and the end of a pair, 13 us: Q is loaded while the lists are sorted, the first own tiles
 // under the common ones, and every wave finishes 32 rows.
 enum { kDone = -1, kByOne = -2 };  // what a workgroup of a pair has left to do
-template <int B, int KB, bool STREAM, bool PAIR, bool SOLO, bool DUO>
+template <int B, int KB, bool STREAM, bool PAIR, bool DUO>
 __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     const unsigned char* __restrict__ q, const unsigned char* __restrict__ k, const unsigned char* __restrict__ v,
     unsigned short* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ kv_idx,
@@ -502,7 +491,6 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     const int32_t* choice, StreamTable* __restrict__ tab) {
   static_assert(KB == B || (2 * KB == B && B == 128), "key blocks are whole tiles or half tiles of 128");
   static_assert(!PAIR || (B == 128 && KB == 64 && !STREAM), "pairs of blocks of 64");
-  static_assert(PAIR || !SOLO, "one block instead of a pair");
   static_assert(!DUO || (B == 128 && !STREAM && !PAIR), "pairs of blocks of 128");
   constexpr int NT = DUO ? 512 : 2 * B;   // threads
   constexpr int QB = PAIR ? 64 : B;       // query block size
@@ -526,7 +514,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   const int kh = gw / WQ;
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
-  // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, in a SOLO launch or as
+  // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, as
   // one of a pair that is taken row by row; listed >= 0: its list is in LDS already, with that many blocks.
   // A pair: listed >= 0 means block `listed` of the two alone.  Returns kDone, or, with nothing done, kByOne if the row
   // or rows are to be run by ONE, or the length of the list that it has sorted into LDS for one row.
@@ -1723,7 +1711,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   //    first come, first served, through one atomic counter, and leave at once when none is left.
   //    Under load the XCDs of a part run at clocks that differ by several per cent; an XCD that is
   //    through with its static share early thus takes more of the remaining rows than a slow one.
-  const int units = (PAIR && !SOLO) || DUO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
+  const int units = PAIR || DUO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
   const int64_t total = int64_t(heads) * units;
   const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
   int64_t pos;
@@ -1742,7 +1730,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     pos = n_static + t;
   }
   int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
-  if constexpr ((PAIR && !SOLO) || DUO) {
+  if constexpr (PAIR || DUO) {
     const bool single = order == nullptr && pos >= n_pairs;  // positions from n_pairs on are rows, two of each unit
     if (single) row = n_pairs + ((pos - n_pairs) >> 1);
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
@@ -1767,7 +1755,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
       run(std::true_type{}, h * nb + i, 0, 0, 0, 0, 0, listed, false);
     }
   } else {
-    run(std::bool_constant<SOLO>{}, row, 0, 0, 0, 0, 0, -1, false);
+    run(std::false_type{}, row, 0, 0, 0, 0, 0, -1, false);
   }
 }
 
@@ -1860,6 +1848,8 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     order = ord;
   }
   const float scale_log2 = softmax_scale * kLog2e;
+  if (!share && !pair && few_rows(block, int64_t(heads) * nb))
+    return launch_attn_few(q, k, v, heads, n_tokens, n_first, scale_log2, kv_idx, kv_cnt, idx_stride, out, lse, stream);
   const unsigned char* qp = static_cast<const unsigned char*>(q);
   const unsigned char* kp = static_cast<const unsigned char*>(k);
   const unsigned char* vp = static_cast<const unsigned char*>(v);
@@ -1869,8 +1859,8 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   const size_t lds64 = 4 * 64 * 128, lds128 = 4 * 128 * 128;
   if (getenv("BSGA_DEBUG") != nullptr) {
     int n64 = -1, n128 = -1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false, false, false>, 128, lds64);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false, false, false>, 256, lds128);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n64, attn_bf16_kernel<64, 64, false, false, false>, 128, lds64);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n128, attn_bf16_kernel<128, 128, false, false, false>, 256, lds128);
     fprintf(stderr, "[bsga] attention occupancy (workgroups per CU): block 64 -> %d, block 128 -> %d\n", n64, n128);
   }
   auto launch = [&](auto kernel, const Spread& to, int threads, size_t lds, StreamTable* tab) {
@@ -1885,25 +1875,23 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
                        block_k == block ? 1 : 2, places, block == 64 || kv_idx == nullptr, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
-    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false, false>, all, 128, lds64, tab);
-    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false, false>, all, 256, lds128, tab);
-    else launch(attn_bf16_kernel<128, 64, true, false, false, false>, all, 256, lds128, tab);
+    if (block == 64) launch(attn_bf16_kernel<64, 64, true, false, false>, all, 128, lds64, tab);
+    else if (block_k == 128) launch(attn_bf16_kernel<128, 128, true, false, false>, all, 256, lds128, tab);
+    else launch(attn_bf16_kernel<128, 64, true, false, false>, all, 256, lds128, tab);
     return check_hip(hipGetLastError(), "bsga bf16 attention launch");
   }
   if (duo || choice != nullptr) {
     const Spread pairs = spread(true, true);
     const size_t lds = 2 * lds128 + (kv_idx != nullptr ? 4 * size_t(nbk) : 0);
-    if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false, true>, pairs, 512, lds, nullptr);
-    else launch(attn_bf16_kernel<128, 64, false, false, false, true>, pairs, 512, lds, nullptr);
+    if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, true>, pairs, 512, lds, nullptr);
+    else launch(attn_bf16_kernel<128, 64, false, false, true>, pairs, 512, lds, nullptr);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention launch")) return rc;
     if (duo) return BSGA_OK;
   }
-  if (pair) launch(attn_bf16_kernel<128, 64, false, true, false, false>, plan, 256, lds128 + 4 * size_t(nbk), nullptr);
-  else if (solo_rows(block, int64_t(heads) * nb, nbk))
-    launch(attn_bf16_kernel<128, 64, false, true, true, false>, plan, 256, lds128 + 4 * size_t(nbk), nullptr);
-  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false, false, false>, plan, 128, lds64, nullptr);
-  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false, false>, plan, 256, lds128, nullptr);
-  else launch(attn_bf16_kernel<128, 64, false, false, false, false>, plan, 256, lds128, nullptr);
+  if (pair) launch(attn_bf16_kernel<128, 64, false, true, false>, plan, 256, lds128 + 4 * size_t(nbk), nullptr);
+  else if (block == 64) launch(attn_bf16_kernel<64, 64, false, false, false>, plan, 128, lds64, nullptr);
+  else if (block_k == 128) launch(attn_bf16_kernel<128, 128, false, false, false>, plan, 256, lds128, nullptr);
+  else launch(attn_bf16_kernel<128, 64, false, false, false>, plan, 256, lds128, nullptr);
   return check_hip(hipGetLastError(), "bsga bf16 attention launch");
 }
 

@@ -28,6 +28,14 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(two, bf16x2));
 }
 
+// the lane's number, through an instruction that the compiler does not see through: nothing that is computed from it can be
+// made ahead of it and kept in registers
+__device__ __forceinline__ int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 // 16 bytes per lane from a raw buffer straight into LDS (buffer_load_dwordx4 ... lds): lane i's
 // data lands at LDS byte address lds_base + lds_imm + 16 i.  voff is the per-lane byte offset, soff a
 // wave-uniform one; lanes whose offset is past the buffer's size get zeros.  Written as inline

@@ -35,7 +35,7 @@ constexpr int kStreamMaxRows = 1024;  // rows of a launch that shares them betwe
 // Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
 // partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
 // idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
-//  - Blocks of 64 otherwise run four waves to a row (SOLO): 344 rows of 344 tiles 230 / 160 us (63 / 56), but
+//  - Blocks of 64 otherwise run four waves to a row: 344 rows of 344 tiles 230 / 160 us (63 / 56), but
 //    129 of 129 57 / 41 (21 / 30).
 //  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
 //    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
@@ -66,12 +66,11 @@ inline bool attn_stream_shape(int heads, int64_t n_tokens) {
 }
 
 constexpr int kPairMaxBlocks = 4096;  // key blocks of which two lists fit the LDS beside the tiles
-// Whether blocks of 64 rows run with four waves to a block (see SOLO): up to two workgroups per CU.  Two waves / four, nine
-// tenths kept (a quarter): 352 rows of 22 tiles 26 / 21 us (12 / 12), 172 of 43 33 / 23 (13 / 11), 22 of 22 19 / 15
-// (11 / 9); 516 of 43 44 / 48 (17 / 21).
-inline bool solo_rows(int block, int64_t rows, int nbk) {
-  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
-}
+// Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip): wherever they are not paired.  Four waves that share
+// their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.5 us (7.8 / 7.5),
+// 172 of 43 24.1 / 17.7 (8.6 / 7.4), 352 of 22 21.8 / 17.5 (9.5 / 7.6), 512 of 128 80 / 70 (16.0 / 13.2), 688 of 43 46.5 / 38.1 (11.2 / 12.1),
+// 880 of 55 62 / 58 (16.1 / 15.6), 1,008 of 63 76 / 73 (18.5 / 16.9).
+inline bool few_rows(int block, int64_t rows) { return block == 64 && rows < 1024; }
 // Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
 // workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
 inline bool pairs_rows(int block, int heads, int nb, int nbk) {
@@ -161,6 +160,8 @@ int launch_gather(const void* src, int dtype, int heads, int64_t n_src, const in
                   int64_t n_dst, void* dst, hipStream_t stream);
 
 // workspace_bytes: of the call's workspace, 0 without one; the launch order alone or more (see attn_order_bytes).
+int launch_attn_few(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first, float scale_log2,
+                    const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, void* out, float* lse, hipStream_t stream);
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
                      int idx_stride, void* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream);
