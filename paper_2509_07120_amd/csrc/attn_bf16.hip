@@ -323,6 +323,7 @@ __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restri
   }
   __syncthreads();
   const int c_bulk = c_bulk_s;
+  if (t == 0) next_row[-1] = next[c_bulk];  // where the bulk class starts: from there on the order depends on the counts alone
   int bulk = 0;
 #pragma unroll
   for (int i = 0; i < MAX; ++i) bulk += cls[i] >= c_bulk;
@@ -1714,6 +1715,9 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   const int units = PAIR || DUO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
   const int64_t total = int64_t(heads) * units;
   const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
+  int64_t pairs_to = n_pairs;  // positions from here on are rows, two of each unit
+  if constexpr (PAIR)
+    if (order != nullptr && n_pairs < total) pairs_to = max(n_pairs, int64_t(__builtin_amdgcn_readfirstlane(next_row[-1])));
   int64_t pos;
   if (w < n_static) {
     constexpr int PLACES = DUO ? 256 : 512;  // workgroups that the chip holds
@@ -1726,16 +1730,16 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane(*slot);
     __syncthreads();  // the slot lies where the first K tile goes
-    if (t >= total - n_static) return;  // the whole workgroup leaves, before any other barrier
+    if (t >= (PAIR ? 2 * total - pairs_to : total) - n_static) return;  // the whole workgroup leaves, before any other barrier
     pos = n_static + t;
   }
-  int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
+  const bool single = PAIR && pos >= pairs_to;
+  const int64_t unit = single ? pairs_to + ((pos - pairs_to) >> 1) : pos;
+  int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[unit])) : unit;
   if constexpr (PAIR || DUO) {
-    const bool single = order == nullptr && pos >= n_pairs;  // positions from n_pairs on are rows, two of each unit
-    if (single) row = n_pairs + ((pos - n_pairs) >> 1);
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
     const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
-    const int first = single ? I + static_cast<int>((pos - n_pairs) & 1) : I, last = min(single ? first + 1 : I + 2, nb);
+    const int first = single ? I + static_cast<int>((pos - pairs_to) & 1) : I, last = min(single ? first + 1 : I + 2, nb);
     if (first >= nb) return;
     if constexpr (DUO) {
       for (int next = single ? first : -1;;) {  // -1: the pair
@@ -1801,6 +1805,13 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
       const int64_t dynamic = rows / 8;
       n_static = (rows - dynamic) / 512 * 512;
       extra = (rows - n_static) / 2 + 512;
+      // Up to half as many pairs as CUs left over after whole rounds of one per CU go row by row, so that a CU has half a pair more
+      // to do than another and not a whole one: the layer of 1,376 pairs of 172 blocks 469 -> 458 us.  With more left over there is
+      // a pair for most CUs anyway.  They are the last ones of the order, of the bulk class only (see pairs_to in the kernel).
+      if (two && !eight_waves && kv_idx != nullptr && rows <= kOrderOneMax && rows % 256 <= 128) {
+        n_pairs = rows - rows % 256;
+        extra += rows % 256;
+      }
     }
     if (two && !eight_waves && rows < 1024 && heads + ceil_div(128, nu) <= 65535) {
       // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
