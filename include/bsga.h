@@ -265,11 +265,11 @@ int bsga_dense_attn(const void* q, const void* k, const void* v, int dtype, int 
  *
  * bsga_linear: out[i] = act(weight x[i] + bias), weight [out_features, in_features], fp32 accumulation.
  *   x          [n_tokens, in_features], or with x_heads [in_features / 64, n_tokens, 64] (what the attention returns)
- *   activation 0 none, 1 GELU (x Phi(x), on the fp32 sums)
+ *   activation 0 none, 1 GELU (x Phi(x); large calls round the sums to bf16 first)
  *   out        [n_tokens, out_features], or with out_heads [out_features / 64, n_tokens, 64] (what the attention takes)
  *   row_index  nullable [n_tokens], a permutation: row i goes to out[row_index[i]] (clamped to [0, n_tokens))
  *   residual   nullable [n_tokens, out_features], may be out: its row is added to the row of out, after the result is rounded to bf16
- * Features are multiples of 64, x and weight smaller than 2 GiB; row_index and residual without out_heads.
+ * Features are multiples of 64, x, weight and out smaller than 2 GiB; row_index and residual without out_heads.
  *
  * bsga_layer_norm: out[i] = (x[j] - mean) / sqrt(variance + eps) * weight + bias, j = index[i] (nullable: i; clamped), statistics in fp32.
  *   features: a multiple of 8, up to 4096.

@@ -22,7 +22,9 @@
 // heads need not be merged first.  The result is [tokens][features], row i optionally at row_index[i] and added to that row
 // of `residual`, or [features / 64][tokens][64], as the attention wants them.
 // The epilogue turns 32 tokens at a time through a piece of LDS of the wave's own, so that stores (and the residual's loads) are
-// whole rows of up to 256 bytes.
+// whole rows of up to 256 bytes.  LATER: with another tile to follow, the finished one waits in registers as bf16, and a piece of it is
+// turned, and put through GELU, between the products of each of the next tile's first steps.  The stores of all CUs at once take 14 of
+// 87 us (10,992 tokens, 1024 -> 3072), GELU another 25 of 126 (1024 -> 4096), with the matrix pipes idle; now 72 and 113.
 #include <utility>
 
 #include "bf16_tile.h"
@@ -41,7 +43,7 @@ struct LinearArgs {
   unsigned char* out;
   const int32_t* row_index;
   unsigned x_bytes, x_row, x_step;  // bytes of x, of a row, from one step of 64 in k to the next
-  unsigned w_bytes, w_row;
+  unsigned w_bytes, w_row, out_bytes;
   int n_tokens, features, steps;
   int token_tiles, feature_tiles;
   bool heads;  // result as [features / 64][tokens][64]
@@ -67,6 +69,13 @@ __device__ __forceinline__ float gelu(float x) {
 __device__ __forceinline__ float low_bf16(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float high_bf16(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
 
+// LDS operations of one wave run in order; this keeps the compiler from moving them past each other
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int FU, int TU, int S>
 constexpr int kLinearLds = S * (64 * FU + 64 * TU) * 128 + 4 * 32 * FU * 64;
 template <int FU, int TU, int S>
@@ -81,7 +90,7 @@ __device__ __forceinline__ void each(Fn&& fn) {
   each_of(std::make_integer_sequence<int, N>{}, fn);
 }
 
-template <int FU, int TU, int S, bool GELU>
+template <int FU, int TU, int S, bool GELU, bool LATER>
 __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(LinearArgs a) {
   constexpr int FT = 64 * FU, TT = 64 * TU;  // tile
   constexpr int STAGE = (FT + TT) * 128;
@@ -213,36 +222,128 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
 #pragma unroll
   for (int t = 0; t < TU; ++t) fx[0][t] = read_x(buf, 0, t);
 
-  for (;;) {
-    for (int s = 0; s < a.steps; ++s) {
-      each<4>([&](auto cc) {
-        constexpr int c = decltype(cc)::value, c1 = (c + 1) & 3;
-        if constexpr (c == 3) {
-          // the operands of this quarter are in registers and the next step's loads have arrived, everywhere after the barrier
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * LOADS) : "memory");
-          __builtin_amdgcn_s_barrier();
-          __builtin_amdgcn_sched_barrier(0);
-          load_buf = buf;
-          buf = buf == (S - 1) * STAGE ? 0 : buf + STAGE;
-          advance();
-        }
-        each<FU>([&](auto uc) {
-          constexpr int u = decltype(uc)::value;
-          fa[c1 & 1][u] = read_f(buf, c1, u);
-#pragma unroll
-          for (int t = u; t < TU; t += FU) fx[c1 & 1][t] = read_x(buf, c1, t);
-          each<LOADS>([&](auto l) {
-            constexpr int i = decltype(l)::value;
-            if constexpr (i * SPAN / LOADS == c1 * FU + u) load(l, wsoff, xsoff, lds_wave + load_buf);
-          });
-#pragma unroll
-          for (int t = 0; t < TU; ++t)
-            acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c & 1][u], fx[c & 1][t], acc[u][t], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      });
+  // LATER: the finished tile waits in registers as bf16, piece by piece (32 tokens x 32 PU features), see above
+  constexpr int PU = GELU ? 1 : 2, NP = TU * FU / PU, UN = NP % 4 == 0 ? 4 : NP % 3 == 0 ? 3 : 2;  // pieces; those that the code names
+  constexpr int CH = 4 * PU, R = 64 / CH;  // chunks of 16 bytes of a piece's rows, rows that the wave reads back at a time
+  u32x2 wait[LATER ? NP : 1][CH];
+  u32x4 back[32 / R];
+  float y[4];
+  int wf0 = 0, wt0 = a.n_tokens;  // the waiting tile: none
+  const auto orsrc = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, static_cast<int>(a.out_bytes), 0x00020000);
+  unsigned char* const turn_piece = smem + S * STAGE + wave * (32 * PU * 64);
+  auto piece_value = [&](auto ic, auto vc) {  // value v of a lane's 16 PU, into LDS by fours
+    constexpr int i = decltype(ic)::value, v = decltype(vc)::value, k = v >> 2, r = v & 3;
+    if constexpr (GELU) y[r] = gelu(r & 1 ? high_bf16(wait[i][k][r >> 1]) : low_bf16(wait[i][k][r >> 1]));
+    if constexpr (r == 3) {
+      u32x2 two = wait[i][k];
+      if constexpr (GELU) two = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+      *reinterpret_cast<u32x2 __attribute__((address_space(3)))*>(
+          (__attribute__((address_space(3))) unsigned char*)(turn_piece + n * (CH * 16) + ((k ^ (n & (CH - 1))) << 4) + 8 * g)) = two;
     }
+  };
+  auto piece_back = [&]() {
+    wave_lds_fence();
+#pragma unroll
+    for (int p = 0; p < 32 / R; ++p) {
+      const int r = p * R + lane / CH;
+      back[p] = *LDS_PTR(u32x4, turn_piece + r * (CH * 16) + (((lane & (CH - 1)) ^ (r & (CH - 1))) << 4));
+    }
+    wave_lds_fence();
+  };
+  auto piece_store = [&](int piece) {
+    const int t = piece / (FU / PU), f = wf0 + wf * 32 * FU + (piece - t * (FU / PU)) * 32 * PU + (lane & (CH - 1)) * 8;
+#pragma unroll
+    for (int p = 0; p < 32 / R; ++p) {
+      const int i = wt0 + wt * 32 * TU + 32 * t + p * R + lane / CH;
+      unsigned at = a.heads ? (static_cast<unsigned>(f >> 6) * a.n_tokens + i) * 128u + (f & 63) * 2 : (static_cast<unsigned>(i) * a.features + f) * 2u;
+      if (i >= a.n_tokens || f >= a.features) at = 0xffffffffu;  // past the buffer's end: not stored
+      __builtin_amdgcn_raw_buffer_store_b128(back[p], orsrc, at, 0, 0);
+    }
+  };
+  auto pieces_move = [&]() {
+#pragma unroll
+    for (int i = 0; i + UN < (LATER ? NP : 0); ++i)
+#pragma unroll
+      for (int k = 0; k < CH; ++k) wait[i][k] = wait[i + UN][k];
+  };
 
+  // A step; with a piece of the waiting tile (piecec >= 0, number `piece`): its values between the products of the first three quarters, its
+  // stores where the last loads have just arrived, so that the next wait for loads finds them a step old.
+  auto step = [&](auto piecec, int piece) {
+    constexpr int pi = decltype(piecec)::value;
+    each<4>([&](auto cc) {
+      constexpr int c = decltype(cc)::value, c1 = (c + 1) & 3;
+      if constexpr (c == 3) {
+        if constexpr (pi >= 0) piece_back();
+        // the operands of this quarter are in registers and the next step's loads have arrived, everywhere after the barrier
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * LOADS) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        load_buf = buf;
+        buf = buf == (S - 1) * STAGE ? 0 : buf + STAGE;
+        advance();
+        if constexpr (pi >= 0) piece_store(piece);
+      }
+      each<FU>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        fa[c1 & 1][u] = read_f(buf, c1, u);
+#pragma unroll
+        for (int t = u; t < TU; t += FU) fx[c1 & 1][t] = read_x(buf, c1, t);
+        each<LOADS>([&](auto l) {
+          constexpr int i = decltype(l)::value;
+          if constexpr (i * SPAN / LOADS == c1 * FU + u) load(l, wsoff, xsoff, lds_wave + load_buf);
+        });
+#pragma unroll
+        for (int t = 0; t < TU; ++t)
+          acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[c & 1][u], fx[c & 1][t], acc[u][t], 0, 0, 0);
+        if constexpr (pi >= 0 && c < 3)
+          each<16 * PU>([&](auto v) {
+            if constexpr (decltype(v)::value * 3 * FU / (16 * PU) == c * FU + u) piece_value(piecec, v);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+  constexpr std::integral_constant<int, -1> none;
+
+  for (;;) {
+    int s = 0;
+    if constexpr (LATER)
+      for (; s < NP; s += UN) {  // (the launcher sees to it that a tile has as many steps)
+        each<UN>([&](auto i) { step(i, s + decltype(i)::value); });
+        pieces_move();
+      }
+    for (; s < a.steps; ++s) step(none, 0);
+
+    if constexpr (LATER) {
+      place(tile, wf0, wt0);
+      tile += grid;
+      const bool last = tile >= tiles;
+      int nf, nt;
+      place(last ? me : tile, nf, nt);
+      load_bias(nf);
+#pragma unroll
+      for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+          const f32x16& x = acc[i % (FU / PU) * PU + (k >> 2)][i / (FU / PU)];
+          const int e = 4 * (k & 3);
+          wait[i][k] = u32x2{pack_bf16(x[e], x[e + 1]), pack_bf16(x[e + 2], x[e + 3])};
+        }
+      if (last) {
+        for (int p = 0; p < NP; p += UN) {
+          each<UN>([&](auto i) {
+            each<16 * PU>([&](auto v) { piece_value(i, v); });
+            piece_back();
+            piece_store(p + decltype(i)::value);
+          });
+          pieces_move();
+        }
+        break;
+      }
+      start_sums();
+      continue;
+    }
     // ---- epilogue -----------------------------------------------------------------------------------------
     int f0, t0;
     place(tile, f0, t0);
@@ -291,10 +392,7 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
           *reinterpret_cast<u32x2 __attribute__((address_space(3)))*>(
               (__attribute__((address_space(3))) unsigned char*)(turn + n * ROW + (((4 * u + r4) ^ (n & (RC - 1))) << 4) + 8 * g)) = two;
         }
-      // (LDS operations of one wave run in order; the fence keeps the compiler from moving the reads up)
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_fence();
 #pragma unroll
       for (int p = 0; p < PASSES; ++p) {
         const int r = p * PASS + rr;
@@ -306,9 +404,7 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
         }
         if (at[p] >= 0) *reinterpret_cast<u32x4*>(a.out + at[p]) = y;
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_fence();
     }
     if (last) break;
     start_sums();
@@ -377,11 +473,20 @@ int launch_linear(LinearArgs a, bool with_gelu, hipStream_t stream) {
   a.token_tiles = static_cast<int>(ceil_div(a.n_tokens, 64 * TU));
   a.feature_tiles = static_cast<int>(ceil_div(a.features, 64 * FU));
   constexpr int places = 256 * kLinearPerCu<FU, TU, S>;
-  const dim3 grid(static_cast<unsigned>(min(int64_t(a.token_tiles) * a.feature_tiles, int64_t(places))));
+  const int64_t tiles = int64_t(a.token_tiles) * a.feature_tiles;
+  const dim3 grid(static_cast<unsigned>(min(tiles, int64_t(places))));
   constexpr size_t lds = kLinearLds<FU, TU, S>;
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a); };
-  if (with_gelu) launch(linear_kernel<FU, TU, S, true>);
-  else launch(linear_kernel<FU, TU, S, false>);
+  if constexpr (S == 2) {
+    // another tile to store the result under, with a step for each of its pieces
+    if (tiles > places && a.residual == nullptr && a.row_index == nullptr && a.steps >= (with_gelu ? TU * FU : TU * FU / 2)) {
+      if (with_gelu) launch(linear_kernel<FU, TU, S, true, true>);
+      else launch(linear_kernel<FU, TU, S, false, true>);
+      return check_hip(hipGetLastError(), "bsga_linear launch");
+    }
+  }
+  if (with_gelu) launch(linear_kernel<FU, TU, S, true, false>);
+  else launch(linear_kernel<FU, TU, S, false, false>);
   return check_hip(hipGetLastError(), "bsga_linear launch");
 }
 
@@ -408,8 +513,8 @@ int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias
     return fail(BSGA_ERR_UNSUPPORTED, "%s: row_index and residual go with rows of tokens", fn);
   // byte offsets into x and the weight are 32 bits, and go up to a tile past the end
   const int64_t limit = int64_t(1) << 31;
-  if ((n_tokens + 256) * in_features * 2 >= limit || (int64_t(out_features) + 256) * in_features * 2 >= limit)
-    return fail(BSGA_ERR_UNSUPPORTED, "%s: x and weight must be below 2 GiB", fn);
+  if ((n_tokens + 256) * in_features * 2 >= limit || (int64_t(out_features) + 256) * in_features * 2 >= limit || n_tokens * out_features * 2 >= limit)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: x, weight and out must be below 2 GiB", fn);
   LinearArgs a = {};
   a.x = static_cast<const unsigned char*>(x);
   a.w = static_cast<const unsigned char*>(weight);
@@ -422,6 +527,7 @@ int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias
   a.x_step = x_heads ? static_cast<unsigned>(n_tokens * 128) : 128;
   a.w_bytes = static_cast<unsigned>(int64_t(out_features) * in_features * 2);
   a.w_row = in_features * 2;
+  a.out_bytes = static_cast<unsigned>(n_tokens * out_features * 2);
   a.n_tokens = static_cast<int>(n_tokens);
   a.features = out_features;
   a.steps = in_features / 64;

@@ -35,12 +35,13 @@ def _close(got, want, slack, roundings=1):
 
 
 @pytest.mark.parametrize("N,K,F", [(1, 64, 64), (70, 192, 192), (700, 128, 3008), (1374, 1024, 3008), (2748, 1024, 3136), (5000, 64, 4032),
-                                   (193, 4096, 1024)])
+                                   (193, 4096, 1024), (5000, 256, 4032), (5170, 1024, 4288)])
 def test_linear(B, N, K, F):
     x, w, b, res, perm, want, slack = _draw(N, K, F)
     _close(B.bsga_linear(x, w, b), want, slack)
     gelu = torch.nn.functional.gelu(want)
-    _close(B.bsga_linear(x, w, b, gelu=True), gelu, slack + 6e-5 * gelu.abs())
+    # launches of more tiles than the chip holds round to bf16 before the GELU as well as after it
+    _close(B.bsga_linear(x, w, b, gelu=True), gelu, slack + 6e-5 * gelu.abs() + 1.13 * 2.0 ** -8 * want.abs())
     xh = x.view(N, K // 64, 64).transpose(0, 1).contiguous()
     _close(B.bsga_linear(xh, w, b, out_heads=True), want.view(N, F // 64, 64).transpose(0, 1), slack.view(N, F // 64, 64).transpose(0, 1))
     placed, placed_slack = torch.empty_like(want), torch.empty_like(slack)
