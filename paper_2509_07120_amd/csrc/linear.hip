@@ -24,7 +24,7 @@
 // The epilogue turns 32 tokens at a time through a piece of LDS of the wave's own, so that stores (and the residual's loads) are
 // whole rows of up to 256 bytes.  LATER: with another tile to follow, the finished one waits in registers as bf16, and a piece of it is
 // turned, and put through GELU, between the products of each of the next tile's first steps.  The stores of all CUs at once take 14 of
-// 87 us (10,992 tokens, 1024 -> 3072), GELU another 25 of 126 (1024 -> 4096), with the matrix pipes idle; now 72 and 113.
+// 87 us (10,992 tokens, 1024 -> 3072), GELU another 25 of 126 (1024 -> 4096), with the matrix pipes idle; now 71 and 106.
 #include <utility>
 
 #include "bf16_tile.h"
@@ -49,21 +49,21 @@ struct LinearArgs {
   bool heads;  // result as [features / 64][tokens][64]
 };
 
-// x Phi(x) = max(x, 0) - |x| h(|x|), h(a) = erfc(a / sqrt 2) / 2 = exp(-a^2 / 2) t P(t), t = 1 / (1 + 0.385 a): a form of erfc that goes
-// back to Hastings, here with P of degree 4 fitted by weighted least squares to the relative error of h over [0, 30], 5.7e-5, a
-// thirtieth of the rounding to bf16 that follows.
-// Infinities and NaN come out as x Phi(x) does.
+// x Phi(x) = max(x, 0) - |x| h(|x|) with h(a) = Phi(-a), and h = 2^Q, Q a polynomial of degree 7 fitted to log2 Phi(-a) over [0, 7.5] (minimax, by
+// reweighted least squares): h is off by 2.2e-5 of itself there, a hundredth of the rounding to bf16 that follows; beyond, below 2^-43, Q goes
+// on falling and h ends as 0.  One exponential and no reciprocal: GELU shares the cycles of the products (62 a value; 94 with h = t P(t) exp(-a^2 / 2),
+// t = 1 / (1 + c a)).  Infinities and NaN come out as x Phi(x) does, -inf as its limit 0.
 __device__ __forceinline__ float gelu(float x) {
   const float a = __builtin_fabsf(x);
-  const float ac = fminf(a, 30.f);  // h is 0 from there on
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.385f, ac, 1.f));
-  float p = -0.08739237f;
-  p = fmaf(p, t, 0.17426558f);
-  p = fmaf(p, t, 0.10218015f);
-  p = fmaf(p, t, 0.15753566f);
-  p = fmaf(p, t, 0.15341043f);
-  const float e = __builtin_amdgcn_exp2f(ac * ac * -0.72134752f);
-  return fmaf(-ac, p * t * e, fmaf(0.5f, a, 0.5f * x));
+  float q = -1.4221640e-6f;
+  q = fmaf(q, a, 5.2221996e-5f);
+  q = fmaf(q, a, -8.4678171e-4f);
+  q = fmaf(q, a, 8.1363982e-3f);
+  q = fmaf(q, a, -5.3110495e-2f);
+  q = fmaf(q, a, -0.45939937f);
+  q = fmaf(q, a, -1.1508543f);
+  q = fmaf(q, a, -1.0000257f);
+  return fmaf(-fminf(a, 30.f), __builtin_amdgcn_exp2f(q), fmaxf(x, 0.f));
 }
 
 __device__ __forceinline__ float low_bf16(unsigned x) { return __uint_as_float(x << 16); }
@@ -76,10 +76,10 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+template <int FU, int TU, int S, bool LATER>
+constexpr int kLinearLds = S * (64 * FU + 64 * TU) * 128 + 4 * 32 * (LATER ? 2 : FU) * 64;
 template <int FU, int TU, int S>
-constexpr int kLinearLds = S * (64 * FU + 64 * TU) * 128 + 4 * 32 * FU * 64;
-template <int FU, int TU, int S>
-constexpr int kLinearPerCu = 2 * kLinearLds<FU, TU, S> <= 160 * 1024 ? 2 : 1;  // workgroups to a CU
+constexpr int kLinearPerCu = 2 * kLinearLds<FU, TU, S, false> <= 160 * 1024 ? 2 : 1;  // workgroups to a CU
 
 template <typename Fn, int... I>
 __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, Fn&& fn) {
@@ -96,8 +96,6 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
   constexpr int STAGE = (FT + TT) * 128;
   constexpr int SPAN = 2 * FU;  // places in the code over which a step's loads are spread
   constexpr int LOADS = 2 * (FU + TU);  // of a wave for a step
-  constexpr int ROW = FU * 64;  // bytes of a wave's features of one token
-  constexpr int RC = ROW / 16;  // chunks of 16 bytes
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -344,6 +342,7 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
       start_sums();
       continue;
     }
+    if constexpr (!LATER) {
     // ---- epilogue -----------------------------------------------------------------------------------------
     int f0, t0;
     place(tile, f0, t0);
@@ -355,6 +354,8 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
       load_bias(nf);
     }
     const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(a.residual), 0, static_cast<int>(a.out_bytes), 0x00020000);
+    constexpr int ROW = FU * 64;  // bytes of a wave's features of one token
+    constexpr int RC = ROW / 16;  // chunks of 16 bytes
     unsigned char* const turn = smem + S * STAGE + wave * (32 * ROW);
     const int fw = f0 + wf * 32 * FU, tw = t0 + wt * 32 * TU;
     constexpr int PASS = 64 / RC;       // tokens that the wave reads back at a time
@@ -414,6 +415,7 @@ __global__ __launch_bounds__(256, (kLinearPerCu<FU, TU, S>)) void linear_kernel(
     }
     if (last) break;
     start_sums();
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // loads that nobody uses have arrived before the LDS is given back
 }
@@ -484,18 +486,17 @@ int launch_linear(LinearArgs a, bool with_gelu, hipStream_t stream) {
   constexpr int places = 256 * kLinearPerCu<FU, TU, S>;
   const int64_t tiles = int64_t(a.token_tiles) * a.feature_tiles;
   const dim3 grid(static_cast<unsigned>(min(tiles, int64_t(places))));
-  constexpr size_t lds = kLinearLds<FU, TU, S>;
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a); };
+  auto launch = [&](auto kernel, size_t lds) { hipLaunchKernelGGL(kernel, grid, dim3(256), lds, stream, a); };
   if constexpr (S == 2) {
     // another tile to store the result under, with a step for each of its pieces
     if (tiles > places && a.residual == nullptr && a.row_index == nullptr && a.steps >= (with_gelu ? TU * FU : TU * FU / 2)) {
-      if (with_gelu) launch(linear_kernel<FU, TU, S, true, true>);
-      else launch(linear_kernel<FU, TU, S, false, true>);
+      if (with_gelu) launch(linear_kernel<FU, TU, S, true, true>, kLinearLds<FU, TU, S, true>);
+      else launch(linear_kernel<FU, TU, S, false, true>, kLinearLds<FU, TU, S, true>);
       return check_hip(hipGetLastError(), "bsga_linear launch");
     }
   }
-  if (with_gelu) launch(linear_kernel<FU, TU, S, true, false>);
-  else launch(linear_kernel<FU, TU, S, false, false>);
+  if (with_gelu) launch(linear_kernel<FU, TU, S, true, false>, kLinearLds<FU, TU, S, false>);
+  else launch(linear_kernel<FU, TU, S, false, false>, kLinearLds<FU, TU, S, false>);
   return check_hip(hipGetLastError(), "bsga_linear launch");
 }
 

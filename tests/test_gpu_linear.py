@@ -2,7 +2,7 @@
 128 x 128 with two and four buffers, 128 x 64) with ragged edges in tokens and features, and one step in k.
 
 Bounds.  The sums are fp32: at most K roundings of 2^-24 of the running sum, which |x| |w| sums bound; then one rounding to bf16 (eight
-significant bits: 2^-8 of the value at most, half an ulp just above a power of two) and, with a residual, a second one of the sum.  GELU's slope is at most 1.13 and its own error 6e-5."""
+significant bits: 2^-8 of the value at most, half an ulp just above a power of two) and, with a residual, a second one of the sum.  GELU's slope is at most 1.13 and its own error 3e-5."""
 import pytest
 import torch
 
@@ -41,7 +41,7 @@ def test_linear(B, N, K, F):
     _close(B.bsga_linear(x, w, b), want, slack)
     gelu = torch.nn.functional.gelu(want)
     # launches of more tiles than the chip holds round to bf16 before the GELU as well as after it
-    _close(B.bsga_linear(x, w, b, gelu=True), gelu, slack + 6e-5 * gelu.abs() + 1.13 * 2.0 ** -8 * want.abs())
+    _close(B.bsga_linear(x, w, b, gelu=True), gelu, slack + 3e-5 * gelu.abs() + 1.13 * 2.0 ** -8 * want.abs())
     xh = x.view(N, K // 64, 64).transpose(0, 1).contiguous()
     _close(B.bsga_linear(xh, w, b, out_heads=True), want.view(N, F // 64, 64).transpose(0, 1), slack.view(N, F // 64, 64).transpose(0, 1))
     placed, placed_slack = torch.empty_like(want), torch.empty_like(slack)
