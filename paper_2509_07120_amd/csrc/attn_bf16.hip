@@ -1859,7 +1859,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     order = ord;
   }
   const float scale_log2 = softmax_scale * kLog2e;
-  if (!share && !pair && few_rows(block, int64_t(heads) * nb))
+  if (!share && !pair && few_rows(block, int64_t(heads) * nb, nbk))
     return launch_attn_few(q, k, v, heads, n_tokens, n_first, scale_log2, kv_idx, kv_cnt, idx_stride, out, lse, stream);
   const unsigned char* qp = static_cast<const unsigned char*>(q);
   const unsigned char* kp = static_cast<const unsigned char*>(k);

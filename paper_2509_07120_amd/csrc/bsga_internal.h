@@ -66,11 +66,15 @@ inline bool attn_stream_shape(int heads, int64_t n_tokens) {
 }
 
 constexpr int kPairMaxBlocks = 4096;  // key blocks of which two lists fit the LDS beside the tiles
-// Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip): wherever they are not paired.  Four waves that share
-// their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.5 us (7.8 / 7.5),
-// 172 of 43 24.1 / 17.7 (8.6 / 7.4), 352 of 22 21.8 / 17.5 (9.5 / 7.6), 512 of 128 80 / 70 (16.0 / 13.2), 688 of 43 46.5 / 38.1 (11.2 / 12.1),
-// 880 of 55 62 / 58 (16.1 / 15.6), 1,008 of 63 76 / 73 (18.5 / 16.9).
-inline bool few_rows(int block, int64_t rows) { return block == 64 && rows < 1024; }
+// Rows of 64 that the chip holds all at once, four waves to each and two to a CU.
+inline bool solo_rows(int block, int64_t rows, int nbk) {
+  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
+}
+// Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip): these, and those that are not paired.  Four waves that
+// share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.5 us
+// (7.8 / 7.5), 172 of 43 24.1 / 17.7 (8.6 / 7.4), 352 of 22 21.8 / 17.5 (9.5 / 7.6), 512 of 128 80 / 70 (16.0 / 13.2), 688 of 43
+// 46.5 / 38.1 (11.2 / 12.1), 880 of 55 62 / 58 (16.1 / 15.6), 1,008 of 63 76 / 73 (18.5 / 16.9).
+inline bool few_rows(int block, int64_t rows, int nbk) { return solo_rows(block, rows, nbk) || (block == 64 && rows < 1024); }
 // Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
 // workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
 inline bool pairs_rows(int block, int heads, int nb, int nbk) {
