@@ -127,6 +127,15 @@ int bsga_gather_tokens(const void* src, int dtype, int heads, int64_t n_src, int
                        const int32_t* index, int64_t n_dst, void* dst, void* stream);
 
 /*
+ * bsga_gather_tokens of q, k and v (index [n_tokens]) and bsga_pool_qk_split of what it makes of q and k, in one pass:
+ *   q, k, v [heads, n_src, 64] -> q_out, k_out, v_out [heads, n_tokens, 64] (must not overlap q, k, v), q_pool, k_pool [heads, nb, 64]
+ * with the same results.
+ */
+int bsga_gather_pool(const void* q, const void* k, const void* v, int dtype, int heads, int64_t n_src, int head_dim,
+                     const int32_t* index, int64_t n_tokens, int64_t n_first, int block, void* q_out, void* k_out,
+                     void* v_out, double* q_pool, double* k_pool, void* stream);
+
+/*
  * Heads of a projection's output made contiguous, and back, with an optional reordering of the tokens in
  * the same pass (the token orders of Sec. 4.2):
  *   bsga_split_heads:  dst[p, h, i, :] = src[index[i], p, h, :]    src [n_tokens, parts, heads, 64]

@@ -35,6 +35,7 @@ EXPORTED_SYMBOLS = (
     "bsga_select_workspace_bytes",
     "bsga_select_blocks",
     "bsga_gather_tokens",
+    "bsga_gather_pool",
     "bsga_split_heads",
     "bsga_merge_heads",
     "bsga_attn_workspace_bytes", "bsga_attn_fp32_parts_bytes",
@@ -82,6 +83,9 @@ def _load() -> ctypes.CDLL:
     lib.bsga_select_workspace_bytes.argtypes = [c_int, c_int, c_int]
     lib.bsga_gather_tokens.restype = c_int
     lib.bsga_gather_tokens.argtypes = [c_void_p, c_int, c_int, c_int64, c_int, c_void_p, c_int64, c_void_p, c_void_p]
+    lib.bsga_gather_pool.restype = c_int
+    lib.bsga_gather_pool.argtypes = [c_void_p, c_void_p, c_void_p, c_int, c_int, c_int64, c_int, c_void_p, c_int64, c_int64, c_int,
+                                     c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
     lib.bsga_split_heads.restype = c_int
     lib.bsga_split_heads.argtypes = [c_void_p, c_int, c_int64, c_int, c_int, c_int, c_void_p, c_void_p, c_void_p]
     lib.bsga_merge_heads.restype = c_int
@@ -533,13 +537,29 @@ class SpecialTokenPlan:
         self.force_k = (dense.to(torch.uint8) * 2).to(device)
 
 
+def _gather_pool(q, k, v, plan: SpecialTokenPlan):
+    """q, k, v in working order and the pooled q and k of that."""
+    perm, n = plan.perm, plan.perm.numel()
+    alike = all(x.is_cuda and x.is_contiguous() and x.shape == q.shape and x.dtype == q.dtype and x.device == perm.device for x in (q, k, v))
+    if not alike or q.dim() != 3 or q.shape[2] != 64 or q.shape[0] < 1 or q.shape[1] < 1 or n < 1:  # let the single steps say what is wrong
+        qw, kw, vw = (bsga_gather_tokens(x, perm) for x in (q, k, v))
+        return (qw, kw, vw) + bsga_pool_qk_split(qw, kw, plan.block, plan.n_patch)
+    _require(perm, "index", torch.int32)
+    H = q.shape[0]
+    qw, kw, vw = (torch.empty((H, n, 64), dtype=q.dtype, device=q.device) for _ in range(3))
+    nb = split_blocks(n, plan.n_patch, plan.block)
+    q_pool, k_pool = (torch.empty((H, nb, 64), dtype=torch.float64, device=q.device) for _ in range(2))
+    _check(lib.bsga_gather_pool(_ptr(q), _ptr(k), _ptr(v), _dtype_code(q), H, q.shape[1], 64, _ptr(perm), n, plan.n_patch, plan.block,
+                                _ptr(qw), _ptr(kw), _ptr(vw), _ptr(q_pool), _ptr(k_pool), _stream(q)))
+    return qw, kw, vw, q_pool, k_pool
+
+
 def sparse_global_attention_special(q, k, v, plan: SpecialTokenPlan, tau: float, rho: float = 1.0,
                                     score_scale: Optional[float] = None, softmax_scale: Optional[float] = None):
     """The layer with the special-token split: gather into the working order, pool, select on the
     patch blocks only, block-sparse attention, gather back.  Returns (O in the caller's token order,
     kv_idx, kv_cnt, mask_bits); the lists refer to blocks of the working order."""
-    qw, kw, vw = (bsga_gather_tokens(x, plan.perm) for x in (q, k, v))
-    q_pool, k_pool = bsga_pool_qk_split(qw, kw, plan.block, plan.n_patch)
+    qw, kw, vw, q_pool, k_pool = _gather_pool(q, k, v, plan)
     mask_bits, kv_idx, kv_cnt = bsga_select_blocks(q_pool, k_pool, tau, rho, score_scale, force_q=plan.force_q,
                                                    force_k=plan.force_k)
     ow = bsga_sparse_attn_split(qw, kw, vw, plan.block, plan.n_patch, kv_idx, kv_cnt, softmax_scale)
