@@ -55,9 +55,6 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
   int mine = fetch(0);
   const int cnt = __builtin_amdgcn_readfirstlane(min(max(kv_cnt[row], 0), nb));
   const int steps = (cnt - first + 1) >> 1;
-  // Short rows start at different places of their lists: lists of neighbouring rows are alike, and rows that walk them together all wait for
-  // every key that is not in the L2 yet (the layer of one frame 29.2 -> 28.8 us).
-  const int turn = steps > 0 && steps <= 64 ? row % steps : 0;
 
   const unsigned head_size = static_cast<unsigned>(n_tokens) * 128u;
   const i32x4 krsrc = make_rsrc(k + head_bytes, head_size), vrsrc = make_rsrc(v + head_bytes, head_size);
@@ -71,9 +68,7 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
   int limits[2];  // keys of the pieces in flight, by buffer
   auto issue = [&](int j, int b) {
     if (j > 0 && (j & 63) == 0) mine = fetch(j);
-    int at = j + turn;
-    at = at >= steps ? at - steps : at;
-    const int J = min(max(__builtin_amdgcn_readlane(mine, at & 63), 0), nb - 1);
+    const int J = min(max(__builtin_amdgcn_readlane(mine, j & 63), 0), nb - 1);
     const int start = block_start(J), left = block_count(J) - kPiece * half;
     limits[b] = left;
     const unsigned soff = static_cast<unsigned>(start + (left > 0 ? kPiece * half : 0)) * 128u;  // of a piece with no keys, the block's first
