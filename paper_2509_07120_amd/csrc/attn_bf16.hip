@@ -12,7 +12,8 @@
 // merged once at the end.  Two workgroups share a CU (two waves per SIMD).
 // Which workgroup computes which row: see the end of the kernel (launch order, 64 consecutive rows
 // per XCD, the last eighth of a large launch handed out at run time).  Launches of few long rows,
-// blocks of 64 rows and large launches of blocks of 128 divide the work otherwise: STREAM, PAIR, DUO below; launches of few short rows go to attn_few.hip.
+// blocks of 64 rows and large launches of blocks of 128 divide the work otherwise: STREAM, PAIR, DUO below;
+// launches of few short rows go to attn_few.hip.
 //
 // Data movement.  K and V tiles go HBM/L2 -> LDS with direct-to-LDS loads (16 bytes per lane, no
 // staging registers), double buffered, with one workgroup barrier per tile.  Tiles stay row-major
@@ -468,7 +469,8 @@ __global__ __launch_bounds__(kStreamMaxRows) void stream_plan_kernel(const int32
 // 2,752 rows of 172 blocks, nine tenths kept: 515 -> 434 us; 5,504 of 344 1,910 -> 1,590.
 // While the rest of the longer list runs, the waves of the other block idle.  A pair whose lists differ in length by
 // more than what they share (and a dozen steps, about what another row's start and merge cost) is therefore taken
-// row by row, four waves to each (ONE: its list dealt to the two halves in turn), and so is the odd block at the end of a head.  Lists of nine tenths
+// row by row, four waves to each (ONE: its list dealt to the two halves in turn), and so is the odd block at the end of a head.  Lists of
+// nine tenths
 // and a twentieth in turn, 5,504 rows of 344: 1,080 us with two waves to a row, 1,500 in pairs only, 1,115 so.
 //
 // DUO: eight waves, one workgroup to a CU, take two neighbouring blocks of 128 rows (four waves to each, as above).  The part lowers its
@@ -515,8 +517,8 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   const int kh = gw / WQ;
 
   // One row (or pair of rows), or (STREAM) its tiles [tile0, tile1); the row's tiles are those of workgroups w0 .. w1, of which
-  // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, as
-  // one of a pair that is taken row by row; listed >= 0: its list is in LDS already, with that many blocks.
+  // this is number `me`.  ONE: the row is a single block of 64 that all four waves share, one of a
+  // pair that is taken row by row; listed >= 0: its list is in LDS already, with that many blocks.
   // A pair: listed >= 0 means block `listed` of the two alone.  Returns kDone, or, with nothing done, kByOne if the row
   // or rows are to be run by ONE, or the length of the list that it has sorted into LDS for one row.
   // (Everything up to the dispatch at the end; not indented.)
@@ -1806,8 +1808,11 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
       n_static = (rows - dynamic) / 512 * 512;
       extra = (rows - n_static) / 2 + 512;
       // Up to half as many pairs as CUs left over after whole rounds of one per CU go row by row, so that a CU has half a pair more
-      // to do than another and not a whole one: the layer of 1,376 pairs of 172 blocks 469 -> 458 us.  With more left over there is
-      // a pair for most CUs anyway.  They are the last ones of the order, of the bulk class only (see pairs_to in the kernel).
+      // to do than another and not a whole one.  With more left over there is a pair for most CUs anyway.  They are the last ones
+      // of the order, of the bulk class only (see pairs_to in the kernel).  us before / now, nine tenths kept (half, a quarter, a tenth,
+      // lengths uniform): 1,088 pairs 298 / 291 (203 / 185, 120 / 110, 63 / 61, 244 / 235), 1,152, of which 128 are left over,
+      // 310 / 310 (212 / 201, 126 / 118, 66 / 68, 266 / 249), 1,376 433 / 430 (294 / 274, 169 / 157, 83 / 79, 356 / 344), 1,552
+      // 546 / 532 (367 / 340, 213 / 197, 103 / 98, 434 / 430).
       if (two && !eight_waves && kv_idx != nullptr && rows <= kOrderOneMax && rows % 256 <= 128) {
         n_pairs = rows - rows % 256;
         extra += rows % 256;
