@@ -13,6 +13,7 @@ from typing import Optional
 
 import torch
 import torch.nn.functional as F
+from torch.autograd import forward_ad
 
 from . import binding as B
 
@@ -54,10 +55,12 @@ class GlobalAttentionBlock(torch.nn.Module):
 
     def _folds(self, x: torch.Tensor) -> bool:
         """Whether a pass takes this library's linear layers and layer norms, which fold in the reorderings, the residuals and the GELU
-        (transformer block of 10,992 tokens: 597 -> 492 us), and not torch's: bf16 on one device, rows and sizes as these need them,
+        (transformer block of 10,992 tokens: 599 -> 486 us), and not torch's: bf16 on one device, rows and sizes as these need them,
         and nothing attached to the layer norms that calling them would run."""
         D, N = self.d_model, x.shape[0] if x.dim() == 2 else 0
         if type(x) is not torch.Tensor or not x.is_cuda or N < 1 or x.shape[1] != D or D > 4096 or torch.is_autocast_enabled():
+            return False
+        if forward_ad._current_level >= 0:  # tangents go with torch's operations
             return False
         tensors = [x, self.w_qkv, self.b_qkv, self.w_out, self.b_out]
         norms = [self.ln1]

@@ -80,6 +80,8 @@ def test_block_passes_agree(B):
     blk = B.GlobalAttentionBlock(256, 4, 64, 0.9, 1.0, special=special, seed=1)
     x = torch.randn((N, 256), generator=torch.Generator().manual_seed(2)).bfloat16().cuda()
     assert blk._folds(x) and not blk._folds(x.float())
+    with torch.autograd.forward_ad.dual_level():
+        assert not blk._folds(x)
     y = blk(x)
     seen = []
     handle = blk.ln1.register_forward_hook(lambda *a: seen.append(1))
