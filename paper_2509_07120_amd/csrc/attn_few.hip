@@ -7,10 +7,11 @@
 // time, moves them into LDS of its own with direct-to-LDS loads two pieces ahead (reissued as soon as a piece's operands are
 // in registers) and waits for nobody.  Then the waves' states are summed through the same LDS, a quarter of the row by each.
 // Rows go to the XCDs in consecutive parts, so that an L2 holds the keys of few heads.
-// A step is now 0.55 us with one workgroup to a CU and about 1 us with two: its products and exponentials, one after the other.  The
-// layer of one frame (352 rows of 20 of 22 blocks) 21.8 -> 17.5 us.  Interleaving the products of one half of the queries with the
-// exponentials of the other (as the pipelined loop of attn_bf16.hip does), operands read a piece ahead, three buffers of K: 18.2 to
-// 19.0 us, and 44 to 46 where this takes 39 (128 rows of 115 of 128 blocks).
+// A step is now 0.52 us with one workgroup to a CU and 1.0 us with two: its products and exponentials, one after the other.  The layer of
+// one frame (352 rows of 20 of 22 blocks) 21.7 -> 16.7 us, of which 0.8 by asking for the next piece under the products and not before
+// them (128 rows of 115 of 128 blocks 39.1 -> 37.5).  Tried: the products of one half of the queries between the exponentials
+// of the other, within a piece 17.7 us, across pieces with three buffers of K 18.2 to 19.0; K of the next piece read under the last
+// products 17.4.
 #include <type_traits>
 
 #include "bf16_tile.h"
@@ -153,9 +154,7 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
           const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
           va[db][cp] = __builtin_bit_cast(bf16x8, u32x4{lo2[0], lo2[1], hi2[0], hi2[1]});
         }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the operands are in registers: the buffer is free
       const int limit = limits[b];
-      if (j + 2 < steps) issue(j + 2, b);
       f32x16 sc[2];
       float base[2];
 #pragma unroll
@@ -166,6 +165,11 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
 #pragma unroll
         for (int c = 0; c < 4; ++c) sc[b2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], qf[b2][c], sc[b2], 0, 0, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the operands are in registers: the buffer is free.  Its
+      // loads go out under the products
+      if (j + 2 < steps) issue(j + 2, b);
+      __builtin_amdgcn_sched_barrier(0);
       if (limit < kPiece) {
 #pragma unroll
         for (int b2 = 0; b2 < 2; ++b2)

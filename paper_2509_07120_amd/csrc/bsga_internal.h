@@ -71,9 +71,9 @@ inline bool solo_rows(int block, int64_t rows, int nbk) {
   return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
 }
 // Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip): these, and those that are not paired.  Four waves that
-// share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.5 us
-// (7.8 / 7.5), 172 of 43 24.1 / 17.7 (8.6 / 7.4), 352 of 22 21.8 / 17.5 (9.5 / 7.6), 512 of 128 80 / 70 (16.0 / 13.2), 688 of 43
-// 46.5 / 38.1 (11.2 / 12.1), 880 of 55 62 / 58 (16.1 / 15.6), 1,008 of 63 76 / 73 (18.5 / 16.9).
+// share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.2 us
+// (7.8 / 7.4), 172 of 43 24.0 / 17.1 (8.7 / 7.4), 352 of 22 21.7 / 16.7 (9.7 / 7.8), 512 of 128 82 / 68 (15.9 / 12.7), 688 of 43
+// 48 / 38.6 (11.2 / 12.1), 880 of 55 62 / 57 (15.4 / 15.6), 1,008 of 63 75 / 68 (18.0 / 17.0).
 inline bool few_rows(int block, int64_t rows, int nbk) { return solo_rows(block, rows, nbk) || (block == 64 && rows < 1024); }
 // Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
 // workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
