@@ -4,8 +4,8 @@
 // linear_kernel: y[i][f] = sum_k x[i][k] w[f][k] + b[f] on v_mfma_f32_32x32x16_bf16, fp32 accumulation, the sum started from the bias.
 //
 // Tile and split.  A workgroup of four waves, one to a SIMD, takes 64 FU features x 64 TU tokens; each wave a quarter, 32 FU x 32 TU,
-// so an operand read from LDS feeds TU (FU) products.  At 256 x 256 a step of 64 in k reads 128 KB of LDS and writes 64 KB
-// under 2048 cycles of matrix products, of 3072 that would be LDS-bound at 64 x 64 per wave.
+// so an operand read from LDS feeds TU (FU) products: at 256 x 192 a step of 64 in k reads 112 KB of LDS and writes 56 KB, 1,350 cycles of
+// its time, under 1,536 of matrix products.
 // The features are the products' rows, so a lane holds one token and four consecutive features.
 //
 // Data movement.  Both operands go from global memory straight to LDS (direct-to-LDS loads, 16 bytes per lane), in steps of 64 in k,
@@ -18,7 +18,7 @@
 // Few tiles are bound by the latency of a step's loads, 0.85 us with two buffers, and the smaller tiles have room for more: 128 x 64,
 // five buffers instead of two, 800 tokens 4096 -> 1024 54 -> 22 us.
 //
-// x is [tokens][k], or (step_bytes = tokens * 128) [k / 64][tokens][64], as the attention leaves its heads: a step is then a head, and the
+// x is [tokens][k], or (x_step = tokens * 128) [k / 64][tokens][64], as the attention leaves its heads: a step is then a head, and the
 // heads need not be merged first.  The result is [tokens][features], row i optionally at row_index[i] and added to that row
 // of `residual`, or [features / 64][tokens][64], as the attention wants them.
 // The epilogue turns 32 tokens at a time through a piece of LDS of the wave's own, so that stores (and the residual's loads) are
@@ -33,7 +33,9 @@
 namespace bsga {
 namespace {
 
-constexpr int kTokenGroup = 8;  // token tiles that neighbouring workgroups take before the next feature tile
+// Token tiles that neighbouring workgroups take before the next feature tile, so that an XCD reads few rows of either operand.  4 / 8 / 16 / 32, us:
+// 33,000 tokens 4096 -> 1024 266 / 262 / 265 / 272, 1024 -> 3072 195 / 192 / 194 / 205; 16,488 4096 -> 1024 135 / 135 / 138 / 162.
+constexpr int kTokenGroup = 8;
 
 struct LinearArgs {
   const unsigned char* x;
