@@ -43,9 +43,10 @@
 //
 // In both, consecutive units run on one XCD (workgroup w runs on XCD w % 8), so that an L2 holds the keys of two heads and
 // not of all of them.
-#include "bsga_internal.h"
-
 #include <type_traits>
+
+#include "bf16_tile.h"
+#include "bsga_internal.h"
 
 namespace bsga {
 namespace {
@@ -56,18 +57,7 @@ constexpr int kPiece = 32;                      // keys a wave takes at a time o
 constexpr int kPlane = kTile * kD * 2;          // one of the three parts of a K or V tile, bytes
 constexpr int kRowWords = 18 * 64;              // what a wave leaves for its neighbour: 16 accumulators, maximum, sum of 64 lanes
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-
-// chunk swizzles: 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
-__device__ __forceinline__ int swz_k(int row) { return (row ^ (row >> 3)) & 7; }
+// chunk swizzle of V tiles (of K tiles: swz_k): 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
 __device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
 
 // the three parts of a and b, packed in pairs.  The first is rounded to nearest, so that the rest has either sign; the others
@@ -107,31 +97,6 @@ __device__ __forceinline__ unsigned split_chunk(f32x4 x0, f32x4 x1, u32x4 (&y)[3
 // The unit then starts over on fp32 instructions, see unit_fp32.
 constexpr unsigned kCutOff = 0xffffu;  // bits of `left` that the third parts have no room for
 __device__ __forceinline__ void mark(u32x4 (&y)[3]) { y[2][0] |= 0x7fffu; }
-
-// 16 bytes per lane from a raw buffer straight into the LDS, and the descriptor of such a buffer; see attn_bf16.hip
-template <unsigned LDS_IMM>
-__device__ __forceinline__ void dma16(i32x4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
-  asm volatile(
-      "s_add_u32 m0, %0, %4\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-      :
-      : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(LDS_IMM)
-      : "memory", "m0", "scc");
-}
-__device__ __forceinline__ i32x4 make_rsrc(const void* base, unsigned bytes) {
-  const unsigned long long a = reinterpret_cast<unsigned long long>(base);
-  return i32x4{__builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a))),
-               __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(a >> 32) & 0xffffu)),
-               __builtin_amdgcn_readfirstlane(static_cast<int>(bytes)), 0x00020000};
-}
-
-// the lane's number, through an instruction that the compiler does not see through; see attn_bf16.hip
-__device__ __forceinline__ int fresh_lane() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
 
 // c + x y of two split operands, the small products first
 __device__ __forceinline__ f32x16 products(const bf16x8 (&x)[3], const bf16x8 (&y)[3], f32x16 c) {
