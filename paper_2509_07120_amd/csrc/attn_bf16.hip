@@ -89,6 +89,13 @@ __device__ __forceinline__ int unit_count(const int32_t* __restrict__ kv_cnt, in
   return pair ? max(c[2 * I], c[min(2 * I + 1, nb - 1)]) : c[I];
 }
 
+// A launch of pairs whose last ones go row by row has n_pairs units that are pairs, then the rows of the others, two units to each: the
+// pair that unit u is of, and which of its rows (-1: both).  An odd head's last pair has a unit with nothing to do.
+__device__ __forceinline__ int64_t pair_of(int64_t u, int64_t n_pairs, int& which) {
+  which = u < n_pairs ? -1 : static_cast<int>((u - n_pairs) & 1);
+  return u < n_pairs ? u : n_pairs + ((u - n_pairs) >> 1);
+}
+
 // Whether a large sparse launch of blocks of 128 takes them two to a workgroup (DUO) or one by one is known on the card only,
 // because it depends on the lists, see pairs_pay.  The kernels below look at them (above kOrderOneMax rows the order is
 // counted both ways and order_merge_kernel goes on with one of them) and leave which in `choice` (else null); both
@@ -253,10 +260,11 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int32_t* __restr
 // The whole launch order in one workgroup, for up to kOrderOneMax units: 5.4 us at 1,376 rows, 10.2 at 5,504 with the choice, where
 // the four kernels above take 5 us each whatever the size, a fifth of an 8-frame layer at high sparsity.  The units
 // of a thread are consecutive, so the bulk class keeps its order.  choice: where it leaves whether pairs are taken (or null: as `pair` says).
+// singly: of the last so many pairs each row is a unit of its own (numbered as the attention kernel does, see pair_of).
 constexpr int kOrderOneMax = 8192;
 __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restrict__ kv_cnt, int nb, int nu, bool pair, int nbk,
-                                                         int heads, int per_tile, int32_t* choice, int32_t* __restrict__ order,
-                                                         int32_t* __restrict__ next_row) {
+                                                         int heads, int singly, int per_tile, int32_t* choice,
+                                                         int32_t* __restrict__ order, int32_t* __restrict__ next_row) {
   constexpr int MAX = kOrderOneMax / 1024;
   __shared__ int total[kOrderClasses], next[kOrderClasses];
   __shared__ int c_bulk_s, wave_bulk[16], sum[2];
@@ -291,7 +299,7 @@ __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restri
     if (pair) nu = half;
     if (t == 0) *choice = pair;
   }
-  const int units = heads * nu;
+  const int n_pairs = heads * nu - singly, units = n_pairs + 2 * singly;
   const int per = (units + 1023) >> 10;
   __syncthreads();
   int cls[MAX];
@@ -300,8 +308,10 @@ __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restri
     const int u = t * per + i;
     cls[i] = -1;
     if (i < per && u < units) {
-      const int h = u / nu;
-      cls[i] = order_class(unit_count(kv_cnt, h, nb, u - h * nu, pair), nbk);
+      int which;
+      const int p = static_cast<int>(pair_of(u, n_pairs, which)), h = p / nu, I = p - h * nu;
+      const int cnt = which < 0 ? unit_count(kv_cnt, h, nb, I, pair) : 2 * I + which < nb ? kv_cnt[int64_t(h) * nb + 2 * I + which] : 0;
+      cls[i] = order_class(cnt, nbk);
       atomicAdd(&total[cls[i]], 1);
     }
   }
@@ -324,7 +334,6 @@ __global__ __launch_bounds__(1024) void order_one_kernel(const int32_t* __restri
   }
   __syncthreads();
   const int c_bulk = c_bulk_s;
-  if (t == 0) next_row[-1] = next[c_bulk];  // where the bulk class starts: from there on the order depends on the counts alone
   int bulk = 0;
 #pragma unroll
   for (int i = 0; i < MAX; ++i) bulk += cls[i] >= c_bulk;
@@ -1717,9 +1726,6 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   const int units = PAIR || DUO ? (nb + 1) >> 1 : nb;  // workgroups' worth of rows per head
   const int64_t total = int64_t(heads) * units;
   const int64_t w = int64_t(blockIdx.y) * units + blockIdx.x;
-  int64_t pairs_to = n_pairs;  // positions from here on are rows, two of each unit
-  if constexpr (PAIR)
-    if (order != nullptr && n_pairs < total) pairs_to = max(n_pairs, int64_t(__builtin_amdgcn_readfirstlane(next_row[-1])));
   int64_t pos;
   if (w < n_static) {
     constexpr int PLACES = DUO ? 256 : 512;  // workgroups that the chip holds
@@ -1732,16 +1738,17 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane(*slot);
     __syncthreads();  // the slot lies where the first K tile goes
-    if (t >= (PAIR ? 2 * total - pairs_to : total) - n_static) return;  // the whole workgroup leaves, before any other barrier
+    if (t >= (PAIR ? 2 * total - n_pairs : total) - n_static) return;  // the whole workgroup leaves, before any other barrier
     pos = n_static + t;
   }
-  const bool single = PAIR && pos >= pairs_to;
-  const int64_t unit = single ? pairs_to + ((pos - pairs_to) >> 1) : pos;
-  int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[unit])) : unit;
+  int64_t row = order != nullptr ? int64_t(__builtin_amdgcn_readfirstlane(order[pos])) : pos;
   if constexpr (PAIR || DUO) {
+    int which = -1;
+    if constexpr (PAIR) row = pair_of(row, n_pairs, which);
+    const bool single = which >= 0;
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
     const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
-    const int first = single ? I + static_cast<int>((pos - pairs_to) & 1) : I, last = min(single ? first + 1 : I + 2, nb);
+    const int first = single ? I + which : I, last = min(single ? first + 1 : I + 2, nb);
     if (first >= nb) return;
     if constexpr (DUO) {
       for (int next = single ? first : -1;;) {  // -1: the pair
@@ -1789,14 +1796,33 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
   struct Spread {
     dim3 grid;
     int64_t n_static;  // units taken by workgroup number
-    int64_t n_pairs;   // units that go in pairs; those after them go row by row (none if there is a launch order)
+    int64_t n_pairs;   // units that are pairs, see pair_of
+    int singly;        // pairs after them that go row by row
     bool big;          // the other units are handed out at run time
   };
   auto spread = [&](bool two, bool eight_waves) {
     const int nu = two ? (nb + 1) >> 1 : nb;
     const int64_t rows = int64_t(heads) * nu;
-    int64_t n_static = rows, n_pairs = rows;  // without a workspace every row is taken by workgroup number
-    int64_t extra = 0;                        // workgroups beyond one per row
+    // Pairs of blocks of 64: the last `singly` ones go row by row.  How many depends on the shape alone, not on the lists nor on whether
+    // there is a launch order, for a row that is taken by itself is summed in another order than one that is taken in a pair.
+    int64_t singly = 0;
+    if (two && !eight_waves && heads + ceil_div(128, nu) <= 65535) {
+      const int64_t rest = rows - 512;
+      // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
+      // 1,064 rows of 532 blocks, nine tenths, a quarter kept, a band: 655 -> 610, 252 -> 204, 216 -> 179 us.  Where more
+      // are left the last 64 do, which evens out the end: 1,600 rows of 100 blocks 176 -> 164, 69 -> 61, 62 -> 60 us.  With
+      // 400 and more there is no room for them: 1,840 rows of 115 205 -> 207 us, 2,032 of 127 242 -> 261.
+      if (rows < 1024) singly = rest <= 128 ? rest : rest < 400 ? 64 : 0;
+      // Of larger launches up to half as many pairs as CUs that are left over after whole rounds of one per CU, so that a CU has half
+      // a pair more to do than another and not a whole one; with more left over there is a pair for most CUs anyway.  In the launch order they
+      // are units like the others.  us, in pairs only / so, nine tenths kept (half, a quarter, a tenth, lengths uniform): 1,040 pairs 283 / 269
+      // (202 / 182, 127 / 111, 71 / 65, 229 / 222), 1,152, of which 128 are left over, 322 / 318 (228 / 214, 146 / 133, 79 / 76, 269 / 254), 1,376
+      // 444 / 436 (307 / 285, 188 / 180, 98 / 93, 361 / 349), 1,552 562 / 544 (384 / 366, 230 / 221, 114 / 112, 446 / 436).
+      else if (rows % 256 <= 128 && rows + rows % 256 <= kOrderOneMax) singly = rows % 256;
+    }
+    const int64_t n_pairs = rows - singly, items = rows + singly;
+    int64_t n_static = items;  // without a workspace every unit is taken by workgroup number
+    int64_t extra = singly;    // workgroups beyond one per row or pair
     // ordering and balancing matter only when the grid does not fit the chip at once
     // (and only while the extra workgroups fit the grid's second dimension)
     const bool big = workspace != nullptr && rows >= 1024 && rows < (int64_t(1) << 30) &&
@@ -1806,31 +1832,9 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
       // are launched for it, so that an XCD can take up to 1.5 times its even share of those rows.
       const int64_t dynamic = rows / 8;
       n_static = (rows - dynamic) / 512 * 512;
-      extra = (rows - n_static) / 2 + 512;
-      // Up to half as many pairs as CUs left over after whole rounds of one per CU go row by row, so that a CU has half a pair more
-      // to do than another and not a whole one.  With more left over there is a pair for most CUs anyway.  They are the last ones
-      // of the order, of the bulk class only (see pairs_to in the kernel).  us before / now, nine tenths kept (half, a quarter, a tenth,
-      // lengths uniform): 1,088 pairs 298 / 291 (203 / 185, 120 / 110, 63 / 61, 244 / 235), 1,152, of which 128 are left over,
-      // 310 / 310 (212 / 201, 126 / 118, 66 / 68, 266 / 249), 1,376 433 / 430 (294 / 274, 169 / 157, 83 / 79, 356 / 344), 1,552
-      // 546 / 532 (367 / 340, 213 / 197, 103 / 98, 434 / 430).
-      if (two && !eight_waves && kv_idx != nullptr && rows <= kOrderOneMax && rows % 256 <= 128) {
-        n_pairs = rows - rows % 256;
-        extra += rows % 256;
-      }
+      extra = singly + (rows - n_static) / 2 + 512;
     }
-    if (two && !eight_waves && rows < 1024 && heads + ceil_div(128, nu) <= 65535) {
-      // The chip holds 512 workgroups.  Up to 128 pairs that are left after the first 512 go row by row, a CU to each:
-      // 1,064 rows of 532 blocks, nine tenths, a quarter kept, a band: 655 -> 610, 252 -> 204, 216 -> 179 us.  Where more
-      // are left the last 64 do, which evens out the end: 1,600 rows of 100 blocks 176 -> 164, 69 -> 61, 62 -> 60 us.  With
-      // 400 and more there is no room for them: 1,840 rows of 115 205 -> 207 us, 2,032 of 127 242 -> 261.  Only here, where
-      // the launch has no order: which rows go which way must not depend on one.
-      const int64_t rest = rows - 512;
-      const int64_t singly = rest <= 128 ? rest : rest < 400 ? 64 : 0;
-      n_pairs = rows - singly;
-      extra = singly;
-      n_static = rows + singly;
-    }
-    return Spread{dim3(nu, heads + static_cast<int>(ceil_div(extra, nu))), n_static, n_pairs, big};
+    return Spread{dim3(nu, heads + static_cast<int>(ceil_div(extra, nu))), n_static, n_pairs, static_cast<int>(singly), big};
   };
   const Spread plan = spread(pair, block == 128);
   int* next_row = nullptr;
@@ -1840,19 +1844,20 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     hipLaunchKernelGGL(zero_word_kernel, dim3(1), dim3(64), 0, stream, next_row);
   }
   if (plan.big && kv_idx != nullptr) {
-    // workspace: launch order of the rows or pairs, then the [classes][heads] table, the number of the merged
+    // workspace: launch order of the units, then the [classes][heads] table, the number of the merged
     // class, the counter of the rows handed out at run time (cleared by order_one_kernel or order_merge_kernel) and, where
     // pairs are thought of, the choice and the pairs' table (there is room: it is sized for blocks of 64, and has nb - 2 words a head left)
     const int nu = static_cast<int>(plan.grid.x);
     const int64_t rows = int64_t(heads) * nu;
     int32_t* ord = static_cast<int32_t*>(workspace);
-    int32_t* table = ord + rows;
+    int32_t* table = ord + rows + plan.singly;
     next_row = table + int64_t(kOrderClasses) * heads + 1;
     const int per_tile = block_k == block ? 1 : 2;
     int32_t* const chosen = choose ? table + int64_t(kOrderClasses) * heads + 2 : nullptr;
     choice = chosen;
     if (rows <= kOrderOneMax) {
-      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, per_tile, chosen, ord, next_row);
+      hipLaunchKernelGGL(order_one_kernel, dim3(1), dim3(1024), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, plan.singly, per_tile,
+                         chosen, ord, next_row);
     } else {
       int32_t* const pairs = choose ? chosen + 1 : nullptr;
       hipLaunchKernelGGL(order_hist_kernel, dim3(heads), dim3(256), 0, stream, kv_cnt, nb, nu, pair, nbk, heads, table, pairs);
@@ -1887,7 +1892,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     const uintptr_t at = reinterpret_cast<uintptr_t>(workspace) + order_bytes;
     StreamTable* tab = reinterpret_cast<StreamTable*>((at + 255) & ~uintptr_t(255));
     const int places = block == 64 ? kStreamPlaces<64> : kStreamPlaces<128>;
-    const Spread all = {dim3(max(places, heads * nb)), 0, 0, false};
+    const Spread all = {dim3(max(places, heads * nb)), 0, 0, 0, false};
     hipLaunchKernelGGL(stream_plan_kernel, dim3(1), dim3(kStreamMaxRows), 0, stream, kv_cnt, heads * nb, nbk,
                        block_k == block ? 1 : 2, places, block == 64 || kv_idx == nullptr, tab);
     if (int rc = check_hip(hipGetLastError(), "bsga bf16 attention (plan)")) return rc;
