@@ -56,7 +56,7 @@ class GlobalAttentionBlock(torch.nn.Module):
     def _folds(self, x: torch.Tensor) -> bool:
         """Whether a pass takes this library's linear layers and layer norms, which fold in the reorderings, the residuals and the GELU
         (transformer block of 10,992 tokens: 599 -> 486 us), and not torch's: bf16 on one device, rows and sizes as these need them,
-        and nothing attached to the layer norms that calling them would run."""
+        plain tensors, and nothing attached to the layer norms that calling them would run."""
         D, N = self.d_model, x.shape[0] if x.dim() == 2 else 0
         if type(x) is not torch.Tensor or not x.is_cuda or N < 1 or x.shape[1] != D or D > 4096 or torch.is_autocast_enabled():
             return False
@@ -73,6 +73,9 @@ class GlobalAttentionBlock(torch.nn.Module):
                     or torch.nn.modules.module._global_forward_hooks or torch.nn.modules.module._global_forward_pre_hooks):
                 return False
             tensors += [ln.weight, ln.bias]
+        # (weights of a subclass have a say in what is done with them, and may have no storage of their own: quantised, sharded)
+        if any(type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter for t in tensors):
+            return False
         if any(t.dtype != torch.bfloat16 or t.device != x.device or not t.is_contiguous() or t.data_ptr() % 16 for t in tensors):
             return False
         if self.w_qkv.shape != (3 * D, D) or self.w_out.shape != (D, D) or self.b_qkv.numel() != 3 * D or self.b_out.numel() != D:

@@ -1,0 +1,65 @@
+"""Which passes of the transformer block take its own linear layers and layer norms: none that something attached to it would then
+miss.  Every case has to see what it is there to see, and give what the plain pass gives."""
+import pytest
+import torch
+from torch.utils._pytree import tree_map
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import paper_2509_07120_amd as pkg
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return pkg
+
+
+class _Wrapped(torch.Tensor):
+    """A weight with no storage of its own (as quantised and sharded ones are)."""
+
+    @staticmethod
+    def __new__(cls, inner):
+        return torch.Tensor._make_wrapper_subclass(cls, inner.shape, strides=inner.stride(), dtype=inner.dtype, device=inner.device)
+
+    def __init__(self, inner):
+        self.inner = inner
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        _Seen.calls += 1
+        args, kwargs = tree_map(lambda t: t.inner if isinstance(t, cls) else t, (args, kwargs or {}))
+        return func(*args, **kwargs)
+
+
+class _Seen(torch.Tensor):
+    """A weight with storage that watches what is done with it."""
+    calls = 0
+
+    @classmethod
+    def __torch_function__(cls, func, types, args=(), kwargs=None):
+        if func is torch.nn.functional.linear:
+            cls.calls += 1
+        return super().__torch_function__(func, types, args, kwargs or {})
+
+
+def _block(B):
+    blk = B.GlobalAttentionBlock(256, 4, 64, 0.9, 1.0, seed=1)
+    x = torch.randn((700, 256), generator=torch.Generator().manual_seed(2)).bfloat16().cuda()
+    assert blk._folds(x)
+    folds, blk._folds = blk._folds, lambda x: False
+    plain = blk(x)
+    blk._folds = folds
+    return blk, x, plain
+
+
+@pytest.mark.parametrize("kind", [_Wrapped, _Seen])
+@pytest.mark.parametrize("name", ["w_qkv", "b_out", "w_fc2", "b_fc1"])
+def test_weights_of_other_types(B, kind, name):
+    blk, x, plain = _block(B)
+    w = getattr(blk, name).data
+    delattr(blk, name)
+    setattr(blk, name, kind(w) if kind is _Wrapped else w.as_subclass(kind))
+    _Seen.calls = 0
+    y = blk(x)
+    assert _Seen.calls > 0
+    assert torch.equal(torch.Tensor(y) if kind is _Wrapped else y.as_subclass(torch.Tensor), plain)
