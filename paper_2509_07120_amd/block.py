@@ -13,9 +13,23 @@ from typing import Optional
 
 import torch
 import torch.nn.functional as F
+import torch.utils._device
 from torch.autograd import forward_ad
 
 from . import binding as B
+
+# Torch has no public names for these: without one of them no pass is taken past torch's operations.
+_function_modes = getattr(torch.overrides, "_get_current_function_mode_stack", None)
+_dispatch_modes = getattr(torch._C, "_len_torch_dispatch_stack", None)
+_DeviceContext = getattr(torch.utils._device, "DeviceContext", None)
+
+
+def _calls_are_watched() -> bool:
+    """Whether torch's operations are more than their results just now: forward-mode tangents, function and dispatch modes (FLOP
+    counters, fake tensors; a default device is a function mode as well, but one that asks for nothing here)."""
+    if _function_modes is None or _dispatch_modes is None or getattr(forward_ad, "_current_level", 0) >= 0:
+        return True
+    return _dispatch_modes() > 0 or any(type(m) is not _DeviceContext for m in _function_modes())
 
 
 class GlobalAttentionBlock(torch.nn.Module):
@@ -60,7 +74,7 @@ class GlobalAttentionBlock(torch.nn.Module):
         D, N = self.d_model, x.shape[0] if x.dim() == 2 else 0
         if type(x) is not torch.Tensor or not x.is_cuda or N < 1 or x.shape[1] != D or D > 4096 or torch.is_autocast_enabled():
             return False
-        if forward_ad._current_level >= 0:  # tangents go with torch's operations
+        if _calls_are_watched():
             return False
         tensors = [x, self.w_qkv, self.b_qkv, self.w_out, self.b_out]
         norms = [self.ln1]

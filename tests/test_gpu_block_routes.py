@@ -2,6 +2,8 @@
 miss.  Every case has to see what it is there to see, and give what the plain pass gives."""
 import pytest
 import torch
+from torch.overrides import TorchFunctionMode
+from torch.utils._python_dispatch import TorchDispatchMode
 from torch.utils._pytree import tree_map
 
 pytestmark = pytest.mark.gpu
@@ -46,9 +48,9 @@ def _block(B):
     blk = B.GlobalAttentionBlock(256, 4, 64, 0.9, 1.0, seed=1)
     x = torch.randn((700, 256), generator=torch.Generator().manual_seed(2)).bfloat16().cuda()
     assert blk._folds(x)
-    folds, blk._folds = blk._folds, lambda x: False
+    blk._folds = lambda x: False
     plain = blk(x)
-    blk._folds = folds
+    del blk._folds
     return blk, x, plain
 
 
@@ -63,3 +65,29 @@ def test_weights_of_other_types(B, kind, name):
     y = blk(x)
     assert _Seen.calls > 0
     assert torch.equal(torch.Tensor(y) if kind is _Wrapped else y.as_subclass(torch.Tensor), plain)
+
+
+def test_modes_see_the_linear_layers(B):
+    blk, x, plain = _block(B)
+    seen = []
+
+    class Calls(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    class Products(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            seen.append(func.overloadpacket)
+            return func(*args, **(kwargs or {}))
+
+    with Calls():
+        y = blk(x)
+    assert seen.count(torch.nn.functional.linear) == 4 and torch.equal(y, plain)
+    seen.clear()
+    with Products():
+        y = blk(x)
+    assert seen.count(torch.ops.aten.addmm) == 4 and torch.equal(y, plain)
+    assert blk._folds(x)
+    with torch.device("cuda"):  # a default device is such a mode too, and misses nothing
+        assert blk._folds(x)
