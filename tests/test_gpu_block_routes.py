@@ -91,3 +91,11 @@ def test_modes_see_the_linear_layers(B):
     assert blk._folds(x)
     with torch.device("cuda"):  # a default device is such a mode too, and misses nothing
         assert blk._folds(x)
+
+
+def test_a_method_put_in_its_place(B, monkeypatch):
+    blk, x, plain = _block(B)
+    seen = []
+    attention = B.GlobalAttentionBlock.attention
+    monkeypatch.setattr(B.GlobalAttentionBlock, "attention", lambda self, x: (seen.append(1), attention(self, x))[1])
+    assert torch.equal(blk(x), plain) and seen == [1]
