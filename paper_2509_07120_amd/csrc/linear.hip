@@ -454,7 +454,15 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const unsigned char* __
     }
   }
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  const float mean = sum / d;
+  float mean = sum / d;
+  if (!(fabsf(mean) < INFINITY)) {  // the whole wave: the sum of values that fit may not, but their mean does
+    mean = 0.f;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mean += s * 64 + lane < chunks ? v[s][e] / d : 0.f;
+    for (int o = 32; o > 0; o >>= 1) mean += __shfl_xor(mean, o);
+  }
   float squares = 0.f;
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s)

@@ -73,6 +73,19 @@ def test_layer_norm(B, N, D):
     _close(B.bsga_layer_norm(x, w, b, 1e-5, perm), want[perm.long()], slack[perm.long()])
 
 
+@pytest.mark.parametrize("D", [8, 1000, 1024, 4096])
+def test_layer_norm_of_values_whose_sum_is_too_large(B, D):
+    """Rows whose values, but not their sum, fit fp32: the mean is finite, the variance is not, and what is left is the bias."""
+    x = torch.full((6, D), 2.0 ** 127, device="cuda").bfloat16()
+    x[1] = -x[1]
+    x[2, ::2] = 2.0 ** 126
+    x[3] = 1.0
+    x[4, 0] = float("nan")
+    w, b = (torch.randn((D,), generator=torch.Generator(device="cuda").manual_seed(D), device="cuda").bfloat16() for _ in range(2))
+    y = B.bsga_layer_norm(x, w, b)
+    assert bool((y[[0, 1, 2, 3, 5]] == b).all()) and bool(y[4].isnan().all())
+
+
 def test_block_passes_agree(B):
     """The folded pass of the transformer block against its plain one on the same weights: roundings differ, by the bf16 ones."""
     N = 3 * 300
