@@ -99,3 +99,13 @@ def test_a_method_put_in_its_place(B, monkeypatch):
     attention = B.GlobalAttentionBlock.attention
     monkeypatch.setattr(B.GlobalAttentionBlock, "attention", lambda self, x: (seen.append(1), attention(self, x))[1])
     assert torch.equal(blk(x), plain) and seen == [1]
+
+
+@pytest.mark.parametrize("D,N,own", [(64, 1, True), (1280, 33000, True), (1344, 4096, True), (1344, 4097, False), (2048, 4096, True), (2048, 4097, False),
+                                     (2112, 64, False), (4096, 64, False)])
+def test_widths(B, D, N, own):
+    """Wide blocks, and long sequences of fairly wide ones, are faster with torch's products; either way the pass runs."""
+    blk = B.GlobalAttentionBlock(D, D // 64, 64, 0.0, 0.9, mlp=False, seed=1)
+    x = torch.randn((N, D), generator=torch.Generator(device="cuda").manual_seed(2), device="cuda").bfloat16()
+    assert blk._folds(x) == own
+    assert bool(torch.isfinite(blk(x).float()).all())
