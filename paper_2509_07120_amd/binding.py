@@ -472,12 +472,20 @@ def bsga_merge_heads(x: torch.Tensor, index: Optional[torch.Tensor] = None) -> t
     return out
 
 
+def _require_beside(x: torch.Tensor, **others: Optional[torch.Tensor]) -> None:
+    at = x.get_device()
+    for name, t in others.items():
+        if t is not None and t.get_device() != at:
+            raise ValueError(f"{name} must be on the same device as x")
+
+
 def bsga_layer_norm(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, eps: float = 1e-5,
                     index: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Layer norm of x [N, D] (bfloat16, D a multiple of 8 up to 4096), row i of the result from row index[i] if an index is given."""
     _require(x, "x", torch.bfloat16); _require(weight, "weight", torch.bfloat16); _require(bias, "bias", torch.bfloat16)
     if x.dim() != 2 or tuple(weight.shape) != (x.shape[1],) or tuple(bias.shape) != (x.shape[1],):
         raise ValueError("x must be [n_tokens, features], weight and bias [features]")
+    _require_beside(x, weight=weight, bias=bias)
     N, D = x.shape
     _require_order(index, x, N)
     out = torch.empty_like(x)
@@ -502,6 +510,7 @@ def bsga_linear(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, gelu:
         _require(residual, "residual", torch.bfloat16)
         if tuple(residual.shape) != (N, F_out):
             raise ValueError("residual must be [n_tokens, out_features]")
+    _require_beside(x, weight=weight, bias=bias, residual=residual)
     out = torch.empty((F_out // 64, N, 64) if out_heads else (N, F_out), dtype=x.dtype, device=x.device)
     _check(lib.bsga_linear(_ptr(x), int(heads), _ptr(weight), _ptr(bias), N, K, F_out, int(gelu), _ptr(row_index),
                            _ptr(residual), int(out_heads), _ptr(out), _stream(x)))
