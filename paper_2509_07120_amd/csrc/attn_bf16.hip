@@ -61,9 +61,6 @@ constexpr float kRaise = 8.0f;  // SAFE pass: raise the reference maximum when a
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-// chunk swizzle of V tiles (of K tiles: swz_k): 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
-__device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
-
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32); }
 
 // Launch order of the (head, query block) rows.  Rows much longer than the average (more kept key
@@ -1869,7 +1866,7 @@ int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int
     order = ord;
   }
   const float scale_log2 = softmax_scale * kLog2e;
-  if (!share && !pair && few_rows(block, int64_t(heads) * nb, nbk))
+  if (!share && !pair && few_rows(block, int64_t(heads) * nb))
     return launch_attn_few(q, k, v, heads, n_tokens, n_first, scale_log2, kv_idx, kv_cnt, idx_stride, out, lse, stream);
   const unsigned char* qp = static_cast<const unsigned char*>(q);
   const unsigned char* kp = static_cast<const unsigned char*>(k);

@@ -1,4 +1,4 @@
-// bf16 attention over kept key blocks for launches of few short rows: blocks of 64 queries of which the chip holds all at once.
+// bf16 attention over kept key blocks for launches of few short rows: fewer than 1024 blocks of 64 queries, of which the chip holds 512 at once.
 // Products, operand layouts, softmax and range check are those of attn_bf16.hip; what differs is the split.
 //
 // Such a launch is a chain of latencies: a workgroup has one row of a few key blocks.  With tiles that all four waves share
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
   unsigned koff[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) koff[i] = r0 * 128 + ((pos ^ r0 ^ i) << 4) + i * 1024;
-  const unsigned voff = r0 * 128 + ((pos ^ ((r0 & 3) << 1)) << 4);
+  const unsigned voff = r0 * 128 + ((pos ^ swz_v(r0)) << 4);
   int limits[2];  // keys of the pieces in flight, by buffer
   auto issue = [&](int j, int b) {
     if (j > 0 && (j & 63) == 0) mine = fetch(j);
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256, 2) void attn_few_kernel(const unsigned char* _
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
       const int cc = db * 4 + 2 * (G & 1) + (j >> 1);
-      vaddr[db] = wave * kWaveLds + kPiece * 128 + key * 128 + ((cc ^ ((key & 3) << 1)) << 4) + (j & 1) * 8;
+      vaddr[db] = wave * kWaveLds + kPiece * 128 + key * 128 + ((cc ^ swz_v(key)) << 4) + (j & 1) * 8;
     }
   }
 

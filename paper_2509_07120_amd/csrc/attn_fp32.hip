@@ -57,9 +57,6 @@ constexpr int kPiece = 32;                      // keys a wave takes at a time o
 constexpr int kPlane = kTile * kD * 2;          // one of the three parts of a K or V tile, bytes
 constexpr int kRowWords = 18 * 64;              // what a wave leaves for its neighbour: 16 accumulators, maximum, sum of 64 lanes
 
-// chunk swizzle of V tiles (of K tiles: swz_k): 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r)
-__device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
-
 // the three parts of a and b, packed in pairs.  The first is rounded to nearest, so that the rest has either sign; the others
 // are cut off, which is a byte permutation instead of a conversion of twice the time.  `left`: what the third parts are cut from, ORed.
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3, unsigned& left) {

@@ -20,8 +20,10 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(T, p) ((const T __attribute__((address_space(3)))*)(p))
 
-// chunk swizzle of tiles whose rows are read whole: 16-byte chunk c of tile row r is stored at chunk position c ^ swz_k(r)
+// chunk swizzles: 16-byte chunk c of tile row r is stored at chunk position c ^ swz(r), swz_k in tiles whose rows are read whole (K, and both
+// operands of a linear layer), swz_v in those that are read transposed (V)
 __device__ __forceinline__ int swz_k(int row) { return (row ^ (row >> 3)) & 7; }
+__device__ __forceinline__ int swz_v(int row) { return (row & 3) << 1; }
 
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   const f32x2 two = {a, b};

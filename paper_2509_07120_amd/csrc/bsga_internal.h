@@ -35,8 +35,9 @@ constexpr int kStreamMaxRows = 1024;  // rows of a launch that shares them betwe
 // Whether a launch of `rows` rows of at most `tiles` key tiles shares its rows out by tiles.  The plan, the
 // partial results and their sum cost 15 to 20 us, so the work must be worth it; what there is to gain is
 // idle CUs.  One workgroup per row / rows shared, all tiles kept (a quarter kept):
-//  - Blocks of 64 otherwise run four waves to a row: 344 rows of 344 tiles 230 / 160 us (63 / 56), but
-//    129 of 129 57 / 41 (21 / 30).
+//  - Blocks of 64 (one workgroup: attn_few.hip): lists of unequal length gain, lists of one length lose.  Lengths uniform, a tenth of the rows full and
+//    the rest a tenth, nine tenths kept, a quarter, a tenth: 313 rows of 313 tiles 118 / 80, 123 / 49, 125 / 122, 43 / 48, 24 / 31 us; 400 of 400 153 / 120,
+//    157 / 62, 176 / 190, 57 / 67, 29 / 40; with fewer tiles less evens out, 256 of 256 74 / 62, 76 / 46, 77 / 87, 31 / 40, 16 / 28.
 //  - Blocks of 128: a CU is busy with one workgroup, so 688 rows (2.7 per CU) gain nothing if they are equal,
 //    876 / 897 us at 344 tiles, but 274 / 233 with a quarter kept in lists of unequal length; 344 rows (1.3 per CU)
 //    521 / 468 (156 / 134) at 344 tiles, 139 / 131 (47 / 50) at 86; 172 rows of 172 148 / 134 (54 / 52), of 86
@@ -66,15 +67,12 @@ inline bool attn_stream_shape(int heads, int64_t n_tokens) {
 }
 
 constexpr int kPairMaxBlocks = 4096;  // key blocks of which two lists fit the LDS beside the tiles
-// Rows of 64 that the chip holds all at once, four waves to each and two to a CU.
-inline bool solo_rows(int block, int64_t rows, int nbk) {
-  return block == 64 && rows <= 512 && nbk <= kPairMaxBlocks;
-}
-// Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip): these, and those that are not paired.  Four waves that
-// share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.2 us
-// (7.8 / 7.4), 172 of 43 24.0 / 17.1 (8.7 / 7.4), 352 of 22 21.7 / 16.7 (9.7 / 7.8), 512 of 128 82 / 68 (15.9 / 12.7), 688 of 43
-// 48 / 38.6 (11.2 / 12.1), 880 of 55 62 / 57 (15.4 / 15.6), 1,008 of 63 75 / 68 (18.0 / 17.0).
-inline bool few_rows(int block, int64_t rows, int nbk) { return solo_rows(block, rows, nbk) || (block == 64 && rows < 1024); }
+// Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip).  Larger launches go in pairs, or with two waves to a block
+// where there are none (heads of one block, more key blocks than pairs take).
+// Four waves that share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.2 us (7.8 / 7.4), 172 of 43 24.0 / 17.1 (8.7 / 7.4), 352 of 22 21.7 / 16.7 (9.7 / 7.8), 512 of 128 82 / 68 (15.9 / 12.7), 688 of
+// 43 45 / 38 (11.5 / 12.4), 688 of 86 82 / 66.5 (15.5 / 14.6), 880 of 55 61 / 56.5 (14.2 / 15.6), 1,008 of 63 74 / 66.5 (16.3 / 16.1).  More than 512 rows
+// of lists of a few blocks lose a microsecond, since the chip holds 512; how long the lists are the host does not know.
+inline bool few_rows(int block, int64_t rows) { return block == 64 && rows < 1024; }
 // Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
 // workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
 inline bool pairs_rows(int block, int heads, int nb, int nbk) {
@@ -159,13 +157,12 @@ int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_
                   const uint8_t* force_k, uint32_t* mask_bits, int32_t* kv_idx, int32_t* kv_cnt,
                   int idx_stride, void* workspace, hipStream_t stream);
 size_t select_workspace_bytes(int heads, int nb_q, int nb_k);
-
 int launch_gather(const void* src, int dtype, int heads, int64_t n_src, const int32_t* index,
                   int64_t n_dst, void* dst, hipStream_t stream);
 
-// workspace_bytes: of the call's workspace, 0 without one; the launch order alone or more (see attn_order_bytes).
 int launch_attn_few(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first, float scale_log2,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int idx_stride, void* out, float* lse, hipStream_t stream);
+// workspace_bytes: of the call's workspace, 0 without one; the launch order alone or more (see attn_order_bytes).
 int launch_attn_bf16(const void* q, const void* k, const void* v, int heads, int64_t n_tokens, int64_t n_first,
                      int block, int block_k, float softmax_scale, const int32_t* kv_idx, const int32_t* kv_cnt,
                      int idx_stride, void* out, float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream);

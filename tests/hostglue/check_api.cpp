@@ -227,14 +227,19 @@ int main() {
   CHECK(bsga_sparse_attn_qk(A, A, A, 1, 4, 1000, 64, 128, 64, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_UNSUPPORTED);
   CHECK(bsga_sparse_attn_split(A, A, A, 0, 4, 1000, 1001, 64, 128, 128, 0.125f, (int32_t*)A, (int32_t*)A, 16, A, nullptr, nullptr, 0, nullptr) == BSGA_ERR_INVALID_ARG);
 
-  // ---- which kernel blocks of 64 go to: the lines that the GPU tests of the four ways choose their sizes by
-  CHECK(bsga::solo_rows(64, 1, 1) && bsga::solo_rows(64, 512, 4096));
-  CHECK(!bsga::solo_rows(64, 513, 32) && !bsga::solo_rows(64, 512, 4097) && !bsga::solo_rows(128, 16, 4));
+  // ---- which kernel blocks of 64 go to: the lines that the GPU tests of the ways choose their sizes by
+  CHECK(bsga::few_rows(64, 1) && bsga::few_rows(64, 1023) && !bsga::few_rows(64, 1024) && !bsga::few_rows(128, 16));
   CHECK(bsga::pairs_rows(64, 512, 2, 2) && bsga::pairs_rows(64, 1, 4096, 4096) && bsga::pairs_rows(64, 16, 64, 64));
   CHECK(!bsga::pairs_rows(64, 1, 1023, 1023) && !bsga::pairs_rows(64, 1, 4097, 4097) && !bsga::pairs_rows(64, 2000, 1, 1) &&
         !bsga::pairs_rows(128, 16, 172, 172));
-  for (int64_t rows = 1; rows < 3000; ++rows)  // never two of them
-    CHECK(bsga::solo_rows(64, rows, 300) + bsga::pairs_rows(64, 1, int(rows), 300) + (bsga::shares_rows(rows, 64, 300, false) && rows > 512) <= 1);
+  CHECK(bsga::shares_rows(313, 64, 313, false) && !bsga::shares_rows(255, 64, 255, false) && !bsga::shares_rows(401, 64, 401, false));
+  for (int nb : {1, 2, 300, 4096, 4097})
+    for (int heads = 1; heads < 3000; ++heads) {
+      const int64_t rows = int64_t(heads) * nb;
+      CHECK(bsga::few_rows(64, rows) + bsga::pairs_rows(64, heads, nb, nb) <= 1);                                   // never two of them
+      CHECK((bsga::few_rows(64, rows) || bsga::pairs_rows(64, heads, nb, nb)) == !(rows >= 1024 && (nb == 1 || nb > 4096)));  // else two waves to a block
+      CHECK(!bsga::shares_rows(rows, 64, nb, false) || bsga::few_rows(64, rows));                                   // rows are shared out of these alone
+    }
 
   // ---- the room for partial results is asked for where some call of the shape can use it, and nowhere else
   for (int heads : {1, 2, 3, 5, 8, 12, 16, 25, 40, 200})
