@@ -215,6 +215,63 @@ int bsga_gather_tokens(const void* src, int dtype, int heads, int64_t n_src, int
   return launch_gather(src, dtype, heads, n_src, index, n_dst, dst, static_cast<hipStream_t>(stream));
 }
 
+int bsga_gather_pool(const void* q, const void* k, const void* v, int dtype, int heads, int64_t n_src, int head_dim, const int32_t* index,
+                     int64_t n_tokens, int64_t n_first, int block, void* q_out, void* k_out, void* v_out, double* q_pool, double* k_pool,
+                     void* stream) {
+  const char* fn = "bsga_gather_pool";
+  clear_error();
+  const void* const in[3] = {q, k, v};
+  void* const out[3] = {q_out, k_out, v_out};
+  double* const pooled[3] = {q_pool, k_pool, nullptr};
+  if (!index || !q_pool || !k_pool) return fail(BSGA_ERR_INVALID_ARG, "%s: index, q_pool and k_pool must be non-null", fn);
+  for (int i = 0; i < 3; ++i)
+    if (!in[i] || !out[i] || !aligned16(in[i]) || !aligned16(out[i]))
+      return fail(BSGA_ERR_INVALID_ARG, "%s: q, k, v and their outputs must be non-null and 16-byte aligned", fn);
+  if (int rc = check_shape(fn, dtype, heads, n_tokens, head_dim)) return rc;
+  if (int rc = check_block(fn, block)) return rc;
+  if (n_src < 1 || n_src > (int64_t(1) << 24))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_src must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_src));
+  if (n_first < 0 || n_first > n_tokens)
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_first must be in [0, n_tokens], got %lld", fn, static_cast<long long>(n_first));
+  return launch_gather_pool(in, dtype, heads, n_src, index, n_tokens, n_first, block, out, pooled, static_cast<hipStream_t>(stream));
+}
+
+int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features,
+                int activation, const int32_t* row_index, const void* residual, int out_heads, void* out, void* stream) {
+  const char* fn = "bsga_linear";
+  clear_error();
+  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
+  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out) || !aligned16(residual))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
+  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
+  if (in_features < 64 || in_features % 64 != 0 || out_features < 64 || out_features % 64 != 0)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be multiples of 64, got %d -> %d", fn, in_features, out_features);
+  if (activation != 0 && activation != 1) return fail(BSGA_ERR_INVALID_ARG, "%s: activation must be 0 (none) or 1 (GELU), got %d", fn, activation);
+  if (out_heads && (row_index || residual))
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: row_index and residual go with rows of tokens", fn);
+  // byte offsets into x and the weight are 32 bits, and go up to a tile past the end
+  const int64_t limit = int64_t(1) << 31;
+  if ((n_tokens + 256) * in_features * 2 >= limit || (int64_t(out_features) + 256) * in_features * 2 >= limit || n_tokens * out_features * 2 >= limit)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: x, weight and out must be below 2 GiB", fn);
+  return launch_linear(x, x_heads != 0, weight, bias, n_tokens, in_features, out_features, activation == 1, row_index, residual, out_heads != 0, out,
+                       static_cast<hipStream_t>(stream));
+}
+
+int bsga_layer_norm(const void* x, const void* weight, const void* bias, double eps, int64_t n_tokens, int features, const int32_t* index,
+                    void* out, void* stream) {
+  const char* fn = "bsga_layer_norm";
+  clear_error();
+  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
+  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
+  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
+    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
+  if (features < 8 || features % 8 != 0 || features > 4096)
+    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be a multiple of 8 up to 4096, got %d", fn, features);
+  return launch_layer_norm(x, weight, bias, static_cast<float>(eps), n_tokens, features, index, out, static_cast<hipStream_t>(stream));
+}
+
 size_t bsga_attn_workspace_bytes(int dtype, int heads, int64_t n_tokens, int head_dim) {
   if ((dtype != BSGA_BF16 && dtype != BSGA_FP32) || heads < 1 || n_tokens < 1 || head_dim != 64) return 0;
   const size_t order = attn_workspace(dtype, heads, n_tokens);

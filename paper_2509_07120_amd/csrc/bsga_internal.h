@@ -157,6 +157,13 @@ int launch_select(const double* q_pool, const double* k_pool, int heads, int nb_
                   const uint8_t* force_k, uint32_t* mask_bits, int32_t* kv_idx, int32_t* kv_cnt,
                   int idx_stride, void* workspace, hipStream_t stream);
 size_t select_workspace_bytes(int heads, int nb_q, int nb_k);
+int launch_gather_pool(const void* const (&x)[3], int dtype, int heads, int64_t n_src, const int32_t* index, int64_t n_tokens, int64_t n_first,
+                       int block, void* const (&ordered)[3], double* const (&pooled)[3], hipStream_t stream);
+int launch_linear(const void* x, bool x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features, bool gelu,
+                  const int32_t* row_index, const void* residual, bool out_heads, void* out, hipStream_t stream);
+int launch_layer_norm(const void* x, const void* weight, const void* bias, float eps, int64_t n_tokens, int features, const int32_t* index, void* out,
+                      hipStream_t stream);
+
 int launch_gather(const void* src, int dtype, int heads, int64_t n_src, const int32_t* index,
                   int64_t n_dst, void* dst, hipStream_t stream);
 

@@ -487,10 +487,8 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const unsigned char* __
   }
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 template <int FU, int TU, int S>
-int launch_linear(LinearArgs a, bool with_gelu, hipStream_t stream) {
+int launch_tiles(LinearArgs a, bool with_gelu, hipStream_t stream) {
   a.token_tiles = static_cast<int>(ceil_div(a.n_tokens, 64 * TU));
   a.feature_tiles = static_cast<int>(ceil_div(a.features, 64 * FU));
   constexpr int places = 256 * kLinearPerCu<FU, TU, S>;
@@ -511,30 +509,9 @@ int launch_linear(LinearArgs a, bool with_gelu, hipStream_t stream) {
 }
 
 }  // namespace
-}  // namespace bsga
 
-using namespace bsga;
-
-extern "C" {
-
-int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features,
-                int activation, const int32_t* row_index, const void* residual, int out_heads, void* out, void* stream) {
-  const char* fn = "bsga_linear";
-  clear_error();
-  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
-  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out) || !aligned16(residual))
-    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
-  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
-    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
-  if (in_features < 64 || in_features % 64 != 0 || out_features < 64 || out_features % 64 != 0)
-    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be multiples of 64, got %d -> %d", fn, in_features, out_features);
-  if (activation != 0 && activation != 1) return fail(BSGA_ERR_INVALID_ARG, "%s: activation must be 0 (none) or 1 (GELU), got %d", fn, activation);
-  if (out_heads && (row_index || residual))
-    return fail(BSGA_ERR_UNSUPPORTED, "%s: row_index and residual go with rows of tokens", fn);
-  // byte offsets into x and the weight are 32 bits, and go up to a tile past the end
-  const int64_t limit = int64_t(1) << 31;
-  if ((n_tokens + 256) * in_features * 2 >= limit || (int64_t(out_features) + 256) * in_features * 2 >= limit || n_tokens * out_features * 2 >= limit)
-    return fail(BSGA_ERR_UNSUPPORTED, "%s: x, weight and out must be below 2 GiB", fn);
+int launch_linear(const void* x, bool x_heads, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features, bool gelu,
+                  const int32_t* row_index, const void* residual, bool out_heads, void* out, hipStream_t stream) {
   LinearArgs a = {};
   a.x = static_cast<const unsigned char*>(x);
   a.w = static_cast<const unsigned char*>(weight);
@@ -551,7 +528,7 @@ int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias
   a.n_tokens = static_cast<int>(n_tokens);
   a.features = out_features;
   a.steps = in_features / 64;
-  a.heads = out_heads != 0;
+  a.heads = out_heads;
   // The kernel with the least rounds of the chip times time of a tile, (steps * step + rest) ns as fitted to sequences of 800 to 33,000
   // tokens at 1024 features.  Wide tiles move least, narrow ones with many buffers hide the latency of a launch of one round and leave
   // less of the last round idle.  us, 256 x 192 / 128 x 192 / 128 x 128, two to a CU / 128 x 128, four buffers / 128 x 64, five:
@@ -561,11 +538,11 @@ int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias
     int features, tokens, places, step, rest;
     int (*launch)(LinearArgs, bool, hipStream_t);
   };
-  static const Shape shapes[] = {{256, 192, 256, 1000, 10000, launch_linear<4, 3, 2>},
-                                 {128, 192, 256, 560, 6000, launch_linear<2, 3, 3>},
-                                 {128, 128, 512, 950, 3000, launch_linear<2, 2, 2>},
-                                 {128, 128, 256, 480, 2500, launch_linear<2, 2, 4>},
-                                 {128, 64, 256, 310, 2000, launch_linear<2, 1, 5>}};
+  static const Shape shapes[] = {{256, 192, 256, 1000, 10000, launch_tiles<4, 3, 2>},
+                                 {128, 192, 256, 560, 6000, launch_tiles<2, 3, 3>},
+                                 {128, 128, 512, 950, 3000, launch_tiles<2, 2, 2>},
+                                 {128, 128, 256, 480, 2500, launch_tiles<2, 2, 4>},
+                                 {128, 64, 256, 310, 2000, launch_tiles<2, 1, 5>}};
   const Shape* best = nullptr;
   int64_t least = 0;
   for (const Shape& c : shapes) {
@@ -575,27 +552,17 @@ int bsga_linear(const void* x, int x_heads, const void* weight, const void* bias
     best = &c;
     least = ns;
   }
-  return best->launch(a, activation == 1, static_cast<hipStream_t>(stream));
+  return best->launch(a, gelu, stream);
 }
 
-int bsga_layer_norm(const void* x, const void* weight, const void* bias, double eps, int64_t n_tokens, int features,
-                    const int32_t* index, void* out, void* stream) {
-  const char* fn = "bsga_layer_norm";
-  clear_error();
-  if (!x || !weight || !bias || !out) return fail(BSGA_ERR_INVALID_ARG, "%s: x, weight, bias and out must be non-null", fn);
-  if (!aligned16(x) || !aligned16(weight) || !aligned16(bias) || !aligned16(out))
-    return fail(BSGA_ERR_INVALID_ARG, "%s: pointers must be 16-byte aligned", fn);
-  if (n_tokens < 1 || n_tokens > (int64_t(1) << 24))
-    return fail(BSGA_ERR_INVALID_ARG, "%s: n_tokens must be in [1, 2^24], got %lld", fn, static_cast<long long>(n_tokens));
-  if (features < 8 || features % 8 != 0 || features > 4096)
-    return fail(BSGA_ERR_UNSUPPORTED, "%s: features must be a multiple of 8 up to 4096, got %d", fn, features);
+int launch_layer_norm(const void* x, const void* weight, const void* bias, float eps, int64_t n_tokens, int features, const int32_t* index, void* out,
+                      hipStream_t stream) {
   const dim3 grid(static_cast<unsigned>(ceil_div(n_tokens, 4)));
   const unsigned char *xp = static_cast<const unsigned char*>(x), *wp = static_cast<const unsigned char*>(weight),
                       *bp = static_cast<const unsigned char*>(bias);
-  hipStream_t s = static_cast<hipStream_t>(stream);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, xp, wp, bp, index, static_cast<unsigned char*>(out), static_cast<int>(n_tokens),
-                       features, static_cast<float>(eps));
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, xp, wp, bp, index, static_cast<unsigned char*>(out), static_cast<int>(n_tokens),
+                       features, eps);
   };
   if (features <= 512) launch(layer_norm_kernel<1>);
   else if (features <= 1024) launch(layer_norm_kernel<2>);
@@ -604,4 +571,4 @@ int bsga_layer_norm(const void* x, const void* weight, const void* bias, double 
   return check_hip(hipGetLastError(), "bsga_layer_norm launch");
 }
 
-}  // extern "C"
+}  // namespace bsga

@@ -122,8 +122,6 @@ void launch(const PoolTensors& a, int tensors, int dtype, int heads, int64_t n_t
   }
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 }  // namespace
 
 int launch_pool(const void* x0, double* pooled0, const void* x1, double* pooled1, int dtype, int heads, int64_t n_tokens, int64_t n_first,
@@ -137,39 +135,18 @@ int launch_pool(const void* x0, double* pooled0, const void* x1, double* pooled1
   return check_hip(hipGetLastError(), "bsga_pool_qk launch");
 }
 
-}  // namespace bsga
-
-using namespace bsga;
-
-extern "C" int bsga_gather_pool(const void* q, const void* k, const void* v, int dtype, int heads, int64_t n_src, int head_dim,
-                                const int32_t* index, int64_t n_tokens, int64_t n_first, int block, void* q_out, void* k_out, void* v_out,
-                                double* q_pool, double* k_pool, void* stream) {
-  const char* fn = "bsga_gather_pool";
-  clear_error();
-  const void* const in[3] = {q, k, v};
-  void* const out[3] = {q_out, k_out, v_out};
-  if (!index || !q_pool || !k_pool) return fail(BSGA_ERR_INVALID_ARG, "%s: index, q_pool and k_pool must be non-null", fn);
-  for (int i = 0; i < 3; ++i)
-    if (!in[i] || !out[i] || !aligned16(in[i]) || !aligned16(out[i]))
-      return fail(BSGA_ERR_INVALID_ARG, "%s: q, k, v and their outputs must be non-null and 16-byte aligned", fn);
-  if (dtype != BSGA_BF16 && dtype != BSGA_FP32) return fail(BSGA_ERR_INVALID_ARG, "%s: unknown dtype %d", fn, dtype);
-  if (heads < 1 || heads > 65535) return fail(BSGA_ERR_INVALID_ARG, "%s: heads must be in [1, 65535], got %d", fn, heads);
-  if (head_dim != 64) return fail(BSGA_ERR_UNSUPPORTED, "%s: head_dim must be 64, got %d", fn, head_dim);
-  if (block != 64 && block != 128) return fail(BSGA_ERR_UNSUPPORTED, "%s: block must be 64 or 128, got %d", fn, block);
-  if (n_src < 1 || n_src > (int64_t(1) << 24) || n_tokens < 1 || n_tokens > (int64_t(1) << 24))
-    return fail(BSGA_ERR_INVALID_ARG, "%s: n_src and n_tokens must be in [1, 2^24], got %lld and %lld", fn, static_cast<long long>(n_src),
-                static_cast<long long>(n_tokens));
-  if (n_first < 0 || n_first > n_tokens)
-    return fail(BSGA_ERR_INVALID_ARG, "%s: n_first must be in [0, n_tokens], got %lld", fn, static_cast<long long>(n_first));
+int launch_gather_pool(const void* const (&x)[3], int dtype, int heads, int64_t n_src, const int32_t* index, int64_t n_tokens, int64_t n_first,
+                       int block, void* const (&ordered)[3], double* const (&pooled)[3], hipStream_t stream) {
   PoolTensors a = {};
   for (int i = 0; i < 3; ++i) {
-    a.x[i] = static_cast<const uint4*>(in[i]);
-    a.ordered[i] = static_cast<uint4*>(out[i]);
+    a.x[i] = static_cast<const uint4*>(x[i]);
+    a.ordered[i] = static_cast<uint4*>(ordered[i]);
+    a.pooled[i] = pooled[i];
   }
-  a.pooled[0] = q_pool;
-  a.pooled[1] = k_pool;
   a.index = index;
   a.n_src = n_src;
-  launch<true>(a, 3, dtype, heads, n_tokens, n_first, block, static_cast<hipStream_t>(stream));
+  launch<true>(a, 3, dtype, heads, n_tokens, n_first, block, stream);
   return check_hip(hipGetLastError(), "bsga_gather_pool launch");
 }
+
+}  // namespace bsga

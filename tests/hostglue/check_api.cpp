@@ -52,6 +52,30 @@ int launch_gather(const void* src, int, int heads, int64_t n_src, const int32_t*
   CHECK(src && index && dst && heads >= 1 && n_src >= 1 && n_dst >= 1);
   return BSGA_OK;
 }
+int launch_gather_pool(const void* const (&x)[3], int dtype, int heads, int64_t n_src, const int32_t* index, int64_t n_tokens, int64_t n_first,
+                       int block, void* const (&ordered)[3], double* const (&pooled)[3], hipStream_t) {
+  ++g_calls;
+  for (int i = 0; i < 3; ++i) CHECK(x[i] && ordered[i] && (pooled[i] != nullptr) == (i < 2));
+  CHECK((dtype == BSGA_BF16 || dtype == BSGA_FP32) && (block == 64 || block == 128) && heads >= 1 && n_src >= 1 && index);
+  CHECK(n_tokens >= 1 && n_first >= 0 && n_first <= n_tokens);
+  return BSGA_OK;
+}
+int launch_linear(const void* x, bool, const void* weight, const void* bias, int64_t n_tokens, int in_features, int out_features, bool,
+                  const int32_t* row_index, const void* residual, bool out_heads, void* out, hipStream_t) {
+  ++g_calls;
+  CHECK(x && weight && bias && out && n_tokens >= 1 && in_features >= 64 && in_features % 64 == 0 && out_features >= 64 && out_features % 64 == 0);
+  CHECK(!out_heads || (!row_index && !residual));
+  // offsets go up to a tile of 256 features or 192 tokens past the end, in 32 bits
+  CHECK((n_tokens + 191) * in_features * 2 < (int64_t(1) << 31) && (int64_t(out_features) + 255) * in_features * 2 < (int64_t(1) << 31));
+  CHECK(n_tokens * out_features * 2 < (int64_t(1) << 31));
+  return BSGA_OK;
+}
+int launch_layer_norm(const void* x, const void* weight, const void* bias, float, int64_t n_tokens, int features, const int32_t*, void* out,
+                      hipStream_t) {
+  ++g_calls;
+  CHECK(x && weight && bias && out && n_tokens >= 1 && n_tokens <= (1 << 24) && features >= 8 && features % 8 == 0 && features <= 4096);
+  return BSGA_OK;
+}
 static void check_attn(int heads, int64_t n_tokens, int64_t n_first, int block, int block_k, const int32_t* kv_idx,
                        const int32_t* kv_cnt, int idx_stride) {
   CHECK(heads >= 1 && n_tokens >= 1 && n_first >= 0 && n_first <= n_tokens);
@@ -240,6 +264,59 @@ int main() {
       CHECK((bsga::few_rows(64, rows) || bsga::pairs_rows(64, heads, nb, nb)) == !(rows >= 1024 && (nb == 1 || nb > 4096)));  // else two waves to a block
       CHECK(!bsga::shares_rows(rows, 64, nb, false) || bsga::few_rows(64, rows));                                   // rows are shared out of these alone
     }
+
+  // ---- token order and pooling in one pass, linear layer, layer norm
+  {
+    const int before = g_calls;
+    int refused = 0;
+    void *Z = nullptr, *O = buf + 8;  // null, misaligned
+    struct GP { const void* q = nullptr; int dt = 0, h = 3; int64_t src = 100; int d = 64; const void* ix = nullptr; int64_t n = 90, first = 80; int b = 64; void *qo, *vo; double *qp, *kp; };
+    auto pool = [&](auto change) {
+      GP a{A, 0, 3, 100, 64, A, 90, 80, 64, A, A, static_cast<double*>(A), static_cast<double*>(A)};
+      change(a);
+      const int rc = bsga_gather_pool(a.q, A, A, a.dt, a.h, a.src, a.d, static_cast<const int32_t*>(a.ix), a.n, a.first, a.b, a.qo, A, a.vo, a.qp, a.kp, nullptr);
+      refused += rc != BSGA_OK;
+      return rc;
+    };
+    CHECK(pool([](GP&) {}) == BSGA_OK && pool([](GP& a) { a.first = 0; }) == BSGA_OK && pool([](GP& a) { a.first = 90; a.b = 128; a.dt = 1; }) == BSGA_OK);
+    CHECK(pool([&](GP& a) { a.q = Z; }) == BSGA_ERR_INVALID_ARG && pool([&](GP& a) { a.q = O; }) == BSGA_ERR_INVALID_ARG && err_has("aligned"));
+    CHECK(pool([&](GP& a) { a.vo = Z; }) == BSGA_ERR_INVALID_ARG && pool([&](GP& a) { a.qo = O; }) == BSGA_ERR_INVALID_ARG);
+    CHECK(pool([&](GP& a) { a.ix = Z; }) == BSGA_ERR_INVALID_ARG && pool([](GP& a) { a.kp = nullptr; }) == BSGA_ERR_INVALID_ARG && err_has("k_pool"));
+    CHECK(pool([](GP& a) { a.dt = 2; }) == BSGA_ERR_INVALID_ARG && pool([](GP& a) { a.h = 0; }) == BSGA_ERR_INVALID_ARG && err_has("heads"));
+    CHECK(pool([](GP& a) { a.d = 32; }) == BSGA_ERR_UNSUPPORTED && pool([](GP& a) { a.b = 32; }) == BSGA_ERR_UNSUPPORTED);
+    CHECK(pool([](GP& a) { a.src = 0; }) == BSGA_ERR_INVALID_ARG && err_has("n_src") && pool([](GP& a) { a.n = 0; }) == BSGA_ERR_INVALID_ARG);
+    CHECK(pool([](GP& a) { a.first = 91; }) == BSGA_ERR_INVALID_ARG && err_has("n_first") && pool([](GP& a) { a.first = -1; }) == BSGA_ERR_INVALID_ARG);
+
+    struct LN { const void *x, *w; int64_t n; int d; void* out; };
+    auto norm = [&](LN a) {
+      const int rc = bsga_layer_norm(a.x, a.w, A, 1e-5, a.n, a.d, nullptr, a.out, nullptr);
+      refused += rc != BSGA_OK;
+      return rc;
+    };
+    CHECK(norm({A, A, 1, 8, A}) == BSGA_OK && norm({A, A, 1 << 24, 4096, A}) == BSGA_OK);
+    CHECK(norm({Z, A, 1, 8, A}) == BSGA_ERR_INVALID_ARG && norm({A, O, 1, 8, A}) == BSGA_ERR_INVALID_ARG && norm({A, A, 1, 8, Z}) == BSGA_ERR_INVALID_ARG);
+    CHECK(norm({A, A, 0, 8, A}) == BSGA_ERR_INVALID_ARG && norm({A, A, (1 << 24) + 1, 8, A}) == BSGA_ERR_INVALID_ARG && err_has("n_tokens"));
+    CHECK(norm({A, A, 1, 12, A}) == BSGA_ERR_UNSUPPORTED && norm({A, A, 1, 4104, A}) == BSGA_ERR_UNSUPPORTED && norm({A, A, 1, 0, A}) == BSGA_ERR_UNSUPPORTED);
+
+    struct Lin { const void *x, *w, *b; int64_t n; int k, f, act; const void *ix, *res; int heads; void* out; };
+    auto linear = [&](Lin a) {
+      const int rc = bsga_linear(a.x, 0, a.w, a.b, a.n, a.k, a.f, a.act, static_cast<const int32_t*>(a.ix), a.res, a.heads, a.out, nullptr);
+      refused += rc != BSGA_OK;
+      return rc;
+    };
+    CHECK(linear({A, A, A, 1, 64, 64, 0, Z, Z, 0, A}) == BSGA_OK && linear({A, A, A, 100, 1024, 3072, 1, Z, Z, 1, A}) == BSGA_OK);
+    CHECK(linear({A, A, A, 100, 64, 128, 0, A, A, 0, A}) == BSGA_OK);
+    CHECK(linear({Z, A, A, 1, 64, 64, 0, Z, Z, 0, A}) == BSGA_ERR_INVALID_ARG && linear({A, Z, A, 1, 64, 64, 0, Z, Z, 0, A}) == BSGA_ERR_INVALID_ARG);
+    CHECK(linear({A, A, O, 1, 64, 64, 0, Z, Z, 0, A}) == BSGA_ERR_INVALID_ARG && linear({A, A, A, 1, 64, 64, 0, Z, O, 0, A}) == BSGA_ERR_INVALID_ARG && err_has("aligned"));
+    CHECK(linear({A, A, A, 0, 64, 64, 0, Z, Z, 0, A}) == BSGA_ERR_INVALID_ARG && linear({A, A, A, 1, 64, 64, 2, Z, Z, 0, A}) == BSGA_ERR_INVALID_ARG && err_has("activation"));
+    CHECK(linear({A, A, A, 1, 96, 64, 0, Z, Z, 0, A}) == BSGA_ERR_UNSUPPORTED && linear({A, A, A, 1, 64, 32, 0, Z, Z, 0, A}) == BSGA_ERR_UNSUPPORTED && err_has("multiples of 64"));
+    CHECK(linear({A, A, A, 1, 64, 64, 0, A, Z, 1, A}) == BSGA_ERR_UNSUPPORTED && linear({A, A, A, 1, 64, 64, 0, Z, A, 1, A}) == BSGA_ERR_UNSUPPORTED && err_has("row_index"));
+    // just below 2 GiB with a tile to spare, and at it: x, weight, out
+    CHECK(linear({A, A, A, (1 << 18) - 257, 4096, 64, 0, Z, Z, 0, A}) == BSGA_OK && linear({A, A, A, (1 << 18) - 256, 4096, 64, 0, Z, Z, 0, A}) == BSGA_ERR_UNSUPPORTED);
+    CHECK(linear({A, A, A, 1, 4096, (1 << 18) - 320, 0, Z, Z, 0, A}) == BSGA_OK && linear({A, A, A, 1, 4096, (1 << 18) - 256, 0, Z, Z, 0, A}) == BSGA_ERR_UNSUPPORTED);
+    CHECK(linear({A, A, A, (1 << 18) - 1, 64, 4096, 0, Z, Z, 0, A}) == BSGA_OK && linear({A, A, A, 1 << 18, 64, 4096, 0, Z, Z, 0, A}) == BSGA_ERR_UNSUPPORTED && err_has("2 GiB"));
+    CHECK(g_calls - before == 11 && refused == 35);
+  }
 
   // ---- the room for partial results is asked for where some call of the shape can use it, and nowhere else
   for (int heads : {1, 2, 3, 5, 8, 12, 16, 25, 40, 200})

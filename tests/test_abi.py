@@ -135,6 +135,33 @@ def test_split_argument_errors(B):
     assert L.bsga_sparse_attn_split(*args, 130, 64, 128, 128, 0.125, None, A, 16, A, None, None, 0, None) == 1
 
 
+def test_block_argument_errors(B):
+    L = B.lib
+
+    def linear(x=A, w=A, b=A, n=100, k=64, f=64, act=0, ix=None, res=None, heads=0, out=A):
+        return L.bsga_linear(x, 0, w, b, n, k, f, act, ix, res, heads, out, None)
+
+    for bad in (dict(x=None), dict(w=None), dict(b=None), dict(out=None)):
+        assert linear(**bad) == 1 and "non-null" in _err(B)
+    assert linear(res=A + 8) == 1 and "aligned" in _err(B)
+    assert linear(n=0) == 1 and "n_tokens" in _err(B)
+    assert linear(k=65) == 2 and linear(f=0) == 2 and "multiples of 64" in _err(B)
+    assert linear(act=2) == 1 and "activation" in _err(B)
+    assert linear(ix=A, heads=1) == 2 and linear(res=A, heads=1) == 2 and "row_index" in _err(B)
+    assert linear(n=1 << 18, k=4096) == 2 and "2 GiB" in _err(B)
+    assert L.bsga_layer_norm(A, A, None, 1e-5, 10, 64, None, A, None) == 1 and "non-null" in _err(B)
+    assert L.bsga_layer_norm(A, A, A, 1e-5, 10, 65, None, A, None) == 2 and "multiple of 8" in _err(B)
+    assert L.bsga_layer_norm(A, A, A, 1e-5, 0, 64, None, A, None) == 1 and "n_tokens" in _err(B)
+
+    def pool(q=A, d=64, b=64, ix=A, n=90, first=80, kp=A):
+        return L.bsga_gather_pool(q, A, A, 0, 3, 100, d, ix, n, first, b, A, A, A, A, kp, None)
+
+    assert pool(q=None) == 1 and pool(ix=None) == 1 and pool(kp=None) == 1 and "k_pool" in _err(B)
+    assert pool(d=32) == 2 and pool(b=32) == 2 and "block" in _err(B)
+    assert pool(first=91) == 1 and "n_first" in _err(B)
+    assert pool(n=0) == 1 and "n_tokens" in _err(B)
+
+
 def test_probe_argument_errors(B):
     L = B.lib
     assert L.bsga_probe_mfma(2, 0, 10, A, 1 << 20, None, None) == 1 and "operands" in _err(B)

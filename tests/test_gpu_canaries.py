@@ -75,6 +75,40 @@ def test_no_entry_point_writes_outside_its_outputs(B, dtype, block, N):
     assert int(c.min()) >= 1 and int(c.max()) <= nb
 
 
+@pytest.mark.parametrize("dtype,block,n,n_first", [(torch.bfloat16, 64, 333, 200), (torch.float32, 128, 129, 129), (torch.bfloat16, 128, 77, 0)])
+def test_token_order_and_pooling_stay_in_bounds(B, dtype, block, n, n_first):
+    H, n_src = 3, 150
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn((H, n_src, 64), device="cuda", generator=g).to(dtype) for _ in range(3))
+    index = torch.randint(0, n_src, (n,), device="cuda", generator=g).int()
+    out = [Guarded((H, n, 64), dtype) for _ in range(3)]
+    pools = [Guarded((H, B.split_blocks(n, n_first, block), 64), torch.float64) for _ in range(2)]
+    assert B.lib.bsga_gather_pool(q.data_ptr(), k.data_ptr(), v.data_ptr(), int(dtype == torch.float32), H, n_src, 64, index.data_ptr(), n, n_first,
+                                  block, *(x.view.data_ptr() for x in out + pools), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert all(x.intact() and bool(torch.isfinite(x.view.double()).all()) for x in out + pools)
+
+
+@pytest.mark.parametrize("N,K,F", [(1, 64, 64), (193, 128, 192), (700, 128, 3008), (2749, 1024, 3136), (5001, 64, 4032), (5171, 1024, 4288),
+                                   (13001, 64, 1088)])
+def test_linear_layers_and_layer_norms_stay_in_bounds(B, N, K, F):
+    """Ragged tiles in tokens and features, in every layout of the result, of every kernel."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x, w, b, res = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((N, K), (F, K), (F,), (N, F)))
+    perm = torch.randperm(N, device="cuda", generator=g).int()
+    st = torch.cuda.current_stream().cuda_stream
+    outs = []
+    for act, index, residual, heads in ((0, None, None, 0), (1, None, None, 0), (0, None, None, 1), (0, perm, res, 0)):
+        out = Guarded((N, F), torch.bfloat16)
+        assert B.lib.bsga_linear(x.data_ptr(), 0, w.data_ptr(), b.data_ptr(), N, K, F, act, None if index is None else index.data_ptr(),
+                                 None if residual is None else residual.data_ptr(), heads, out.view.data_ptr(), st) == 0
+        outs.append(out)
+    norm = Guarded((N, K), torch.bfloat16)
+    assert B.lib.bsga_layer_norm(x.data_ptr(), x.data_ptr(), x.data_ptr(), 1e-5, N, K, perm.data_ptr(), norm.view.data_ptr(), st) == 0
+    torch.cuda.synchronize()
+    assert all(x.intact() and bool(torch.isfinite(x.view.float()).all()) for x in outs + [norm])
+
+
 def test_half_tile_key_blocks_stay_in_bounds(B):
     H, N = 2, 777
     g = torch.Generator(device="cuda").manual_seed(1)
