@@ -50,6 +50,28 @@ def test_linear(B, N, K, F):
     _close(B.bsga_linear(xh, w, b, residual=res, row_index=perm), placed + res.double(), placed_slack + 2.0 ** -8 * 1.01 * placed.abs())
 
 
+# sizes of which the narrow tiles with three, four and five buffers take several rounds: loads of the next tile are then on their way across the
+# epilogue's stores and the loads of residuals and row numbers
+@pytest.mark.parametrize("N,K,F", [(13000, 4096, 1024), (13985, 512, 832), (20000, 1024, 1024), (21961, 256, 320), (1333, 256, 3072), (5440, 256, 704)])
+def test_residuals_of_several_rounds(B, N, K, F):
+    x, w, b, res, perm, want, slack = _draw(N, K, F)
+    placed, placed_slack = torch.empty_like(want), torch.empty_like(slack)
+    placed[perm.long()], placed_slack[perm.long()] = want, slack
+    xh = x.view(N, K // 64, 64).transpose(0, 1).contiguous()
+    y = B.bsga_linear(xh, w, b, residual=res, row_index=perm)
+    _close(y, placed + res.double(), placed_slack + 2.0 ** -8 * 1.01 * placed.abs())
+    for _ in range(3):
+        assert torch.equal(B.bsga_linear(xh, w, b, residual=res, row_index=perm), y)
+    _close(B.bsga_linear(x, w, b, residual=res), want + res.double(), slack + 2.0 ** -8 * 1.01 * want.abs())
+    # the residual's place is the result's
+    st = torch.cuda.current_stream().cuda_stream
+    for index, ref in ((None, B.bsga_linear(x, w, b, residual=res)), (perm, y)):
+        out = res.clone()
+        assert B.lib.bsga_linear(x.data_ptr(), 0, w.data_ptr(), b.data_ptr(), N, K, F, 0, None if index is None else index.data_ptr(),
+                                 out.data_ptr(), 0, out.data_ptr(), st) == 0
+        assert torch.equal(out, ref)
+
+
 def test_gelu_of_values_that_are_not_numbers(B):
     x = torch.zeros((8, 64), device="cuda").bfloat16()
     x[0, 0], x[1, 0], x[2, 0], x[3, 0] = float("inf"), -3e38, 3e38, float("nan")
