@@ -99,8 +99,8 @@ def test_shapes_and_list_orders(B, N, n_first, density):
 
 
 @pytest.mark.parametrize("N,n_first", [(1, 1), (64, 64), (65, 65), (190, 190), (1000, 300), (1700, 1700)])
-def test_four_waves_to_a_block(B, N, n_first):
-    """Up to 512 rows: one list, dealt to the two halves of a workgroup; counts 0, 1, 2, 3, ... and all."""
+def test_up_to_512_rows(B, N, n_first):
+    """Four independent waves to a block, as many blocks as the chip holds at once; counts 0, 1, 2, 3, ... and all."""
     nb = len(O.block_ranges(N, 64, n_first))
     H = max(1, min(8, 512 // nb))
     rng = np.random.default_rng(N)
@@ -207,8 +207,8 @@ def test_pairs_that_go_row_by_row(B, H, N):
 
 @pytest.mark.parametrize("density", [0.1, 0.9])
 @pytest.mark.parametrize("H,N,n_first", [(513, 64, 64), (300, 65, 40), (60, 700, 700), (47, 700, 333), (10, 5100, 5037), (33, 1000, 64)])
-def test_two_waves_to_a_block(B, H, N, n_first, density):
-    """513 to 1023 rows: a workgroup of two waves to a block of 64 and its list as it is; empty rows, ragged and split
+def test_513_to_1023_rows(B, H, N, n_first, density):
+    """Four independent waves to a block, more blocks than the chip holds at once; empty rows, ragged and split
     sequences, any order of the list."""
     nb = len(O.block_ranges(N, 64, n_first))
     assert 512 < H * nb < 1024
@@ -225,7 +225,7 @@ def test_two_waves_to_a_block(B, H, N, n_first, density):
 
 
 @pytest.mark.parametrize("sign", [1.0, -1.0])
-def test_two_waves_out_of_range(B, sign):
+def test_513_to_1023_rows_out_of_range(B, sign):
     """As test_rows_out_of_range for the launches between."""
     H, N = 60, 700
     q, k, v = _qkv(H, N, 13, 27.0 * sign)
@@ -238,6 +238,38 @@ def test_two_waves_out_of_range(B, sign):
     assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
     seen = ~np.isnan(want_lse)
     assert abs(np.median(want_lse[seen])) > 70.0 and np.abs(lse.cpu().numpy() - want_lse)[seen].max() <= 0.25
+
+
+def _heads_of_one_block(H, N, seed, shift=0.0):
+    q, k, v = _qkv(H, N, seed, shift)
+    mask = np.ones((H, 1, 1), bool)
+    mask[::7] = False
+    return q, k, v, mask
+
+
+@pytest.mark.parametrize("H,N", [(1024, 64), (1030, 37), (1500, 1)])
+def test_two_waves_to_a_block(B, H, N):
+    """1024 heads of a single block and more, which has no neighbour: a workgroup of two waves each; the block kept or not."""
+    q, k, v, mask = _heads_of_one_block(H, N, N)
+    out, lse = _run(B, q, k, v, mask, N)
+    _check(out, lse, q, k, v, mask, N, heads=None)
+    again, _ = _run(B, q, k, v, mask, N)
+    assert torch.equal(out, again)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("N", [64, 37])
+def test_two_waves_out_of_range(B, sign, N):
+    """As test_rows_out_of_range, for two waves to a block."""
+    q, k, v, mask = _heads_of_one_block(1024, N, 14, 27.0 * sign)
+    out, lse = _run(B, q, k, v, mask, N)
+    kept = mask[:, 0, 0]
+    assert (out[torch.from_numpy(~kept)].float() == 0).all() and torch.isneginf(lse[torch.from_numpy(~kept)]).all()
+    want, want_lse = O.sparse_attention(q, k, v, np.ones_like(mask), 64, return_lse=True)
+    want[~kept] = np.nan
+    mx, mean = attn_errors(out, want)
+    assert mx <= 5e-2 and mean <= 5e-3, (mx, mean)
+    assert abs(np.median(want_lse)) > 70.0 and np.abs(lse.cpu().numpy() - want_lse)[kept].max() <= 0.25
 
 
 @pytest.mark.parametrize("n_first", [4097 * 64 - 20, 700])

@@ -20,8 +20,8 @@ def B():
     return pkg
 
 
-# rows of the launch, and how it divides them: pairs of blocks; two waves to a block; four waves; shared by tiles
-@pytest.mark.parametrize("H,N", [(140, 1000), (94, 700), (48, 1000), (16, 1374), (1, 16400)])
+# how the launch divides its rows: pairs of blocks, twice; four waves to a block, more rows than the chip holds and fewer; shared by tiles; two waves
+@pytest.mark.parametrize("H,N", [(140, 1000), (94, 700), (48, 1000), (16, 1374), (1, 16400), (1024, 50)])
 @pytest.mark.parametrize("density", [1.0, 0.6, 0.15])
 def test_lse_of_blocks_of_64(B, H, N, density):
     g = torch.Generator(device="cuda").manual_seed(N + H)
