@@ -497,7 +497,8 @@ def bsga_linear(x: torch.Tensor, weight: torch.Tensor, bias: torch.Tensor, gelu:
                 residual: Optional[torch.Tensor] = None, row_index: Optional[torch.Tensor] = None,
                 out_heads: bool = False) -> torch.Tensor:
     """weight x + bias in bfloat16 with its neighbours folded in (features are multiples of 64).  x is [N, K], or [K/64, N, 64]
-    as the attention returns it.  gelu: applied to the fp32 sums.  row_index, residual: row i of the result is row row_index[i] of
+    as the attention returns it.  gelu: applied to the fp32 sums; large calls round them to bf16 first, so a row's bits depend on how many
+    tokens the call has.  row_index, residual: row i of the result is row row_index[i] of
     the output (a permutation) and has that row of the residual added.  out_heads: the output is [F/64, N, 64], not [N, F]."""
     _require(x, "x", torch.bfloat16); _require(weight, "weight", torch.bfloat16); _require(bias, "bias", torch.bfloat16)
     F_out, K = weight.shape
