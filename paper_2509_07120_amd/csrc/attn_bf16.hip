@@ -1742,13 +1742,12 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
   if constexpr (PAIR || DUO) {
     int which = -1;
     if constexpr (PAIR) row = pair_of(row, n_pairs, which);
-    const bool single = which >= 0;
     const int64_t h = min(max(row / units, int64_t(0)), int64_t(heads - 1));
     const int I = 2 * static_cast<int>(min(max(row - h * units, int64_t(0)), int64_t(units - 1)));
-    const int first = single ? I + which : I, last = min(single ? first + 1 : I + 2, nb);
+    const int first = which < 0 ? I : I + which, last = min(which < 0 ? I + 2 : first + 1, nb);
     if (first >= nb) return;
     if constexpr (DUO) {
-      for (int next = single ? first : -1;;) {  // -1: the pair
+      for (int next = -1;;) {  // -1: the pair
         const bool deal = next >= 0;
         const int left = run(std::false_type{}, deal ? h * nb + next : row, 0, 0, 0, 0, 0, -1, deal);
         if (!deal && left == kDone) return;
@@ -1757,7 +1756,7 @@ __global__ __launch_bounds__(DUO ? 512 : 2 * B, 2) void attn_bf16_kernel(
         __syncthreads();  // whatever the end of the row before still reads
       }
     }
-    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, single ? first - I : -1, false);
+    const int listed = run(std::false_type{}, row, 0, 0, 0, 0, 0, which, false);
     if (listed == kDone) return;
 #pragma unroll 1
     for (int i = first; i < last; ++i) {

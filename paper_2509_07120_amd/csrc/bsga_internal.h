@@ -69,9 +69,10 @@ inline bool attn_stream_shape(int heads, int64_t n_tokens) {
 constexpr int kPairMaxBlocks = 4096;  // key blocks of which two lists fit the LDS beside the tiles
 // Whether blocks of 64 rows run with four independent waves to a block (attn_few.hip).  Larger launches go in pairs, or with two waves to a block
 // where there are none (heads of one block, more key blocks than pairs take).
-// Four waves that share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.2 us (7.8 / 7.4), 172 of 43 24.0 / 17.1 (8.7 / 7.4), 352 of 22 21.7 / 16.7 (9.7 / 7.8), 512 of 128 82 / 68 (15.9 / 12.7), 688 of
-// 43 45 / 38 (11.5 / 12.4), 688 of 86 82 / 66.5 (15.5 / 14.6), 880 of 55 61 / 56.5 (14.2 / 15.6), 1,008 of 63 74 / 66.5 (16.3 / 16.1).  More than 512 rows
-// of lists of a few blocks lose a microsecond, since the chip holds 512; how long the lists are the host does not know.
+// Four waves that share their tiles up to 512 rows, two waves from there on / now, nine tenths kept (a tenth): 22 rows of 22 blocks 15.0 / 10.2 us
+// (7.8 / 7.4), 172 of 43 24.0 / 17.1 (8.7 / 7.4), 352 of 22 21.7 / 16.7 (9.7 / 7.8), 512 of 128 82 / 68 (15.9 / 12.7), 688 of 43 45 / 38
+// (11.5 / 12.4), 688 of 86 82 / 66.5 (15.5 / 14.6), 880 of 55 61 / 56.5 (14.2 / 15.6), 1,008 of 63 74 / 66.5 (16.3 / 16.1).  More than 512 rows of lists
+// of a few blocks lose a microsecond, since the chip holds 512; how long the lists are the host does not know.
 inline bool few_rows(int block, int64_t rows) { return block == 64 && rows < 1024; }
 // Whether they are taken two to a workgroup (see PAIR).  Fewer than four rows per CU are better off with a
 // workgroup each: 688 rows of 43 tiles, nine tenths kept, 49 us, paired 53; a quarter kept 18 and 25.
