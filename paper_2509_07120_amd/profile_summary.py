@@ -6,6 +6,7 @@ Usage (from the repository root, after the rocprofv3 runs listed in each summary
     python -m paper_2509_07120_amd.profile_summary traffic <dir FETCH_SIZE run> <dir WRITE_SIZE run> <dir TCC run>
     python -m paper_2509_07120_amd.profile_summary pipes   <dir of counter run A> <dir of counter run B> ...
     python -m paper_2509_07120_amd.profile_summary topk    <dir TCC run at rho 0.9> <dir pipe-counter run at rho 0.9>
+    python -m paper_2509_07120_amd.profile_summary case    <name in perf/cases.py> <dir of --kernel-trace --stats run> <dir of counter run>
 
 Each sub-command reads the `*_kernel_stats.csv`, `*_kernel_trace.csv` or `*_counter_collection.csv`
 files rocprofv3 wrote with `--output-format csv`, prints what it found, and rewrites the matching
@@ -21,6 +22,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -322,6 +324,48 @@ needed over a window of about +-50 tiles, many times what 4 MB of L2 hold.
     print(open(path).read())
 
 
+# ---------------------------------------------------------------------------------------------- case
+def cmd_case(name: str, d_stats: str, d_pipes: str) -> None:
+    """Time and pipe counters of every library kernel of one of the performance cases, means over 20 passes after 5."""
+    passes, skip = 25, 5
+
+    def kernels(rows):  # (name, value) in order -> {name: the launches of the last passes}
+        found = collections.OrderedDict()
+        for n, v in rows:
+            hit = re.search(r"bsga::.*?(\w+_kernel(?:<[^>]*>)?)\(", n)
+            if hit:
+                found.setdefault(hit.group(1), []).append(v)
+        return {n: v[len(v) * skip // passes:] for n, v in found.items() if len(v) % passes == 0}
+
+    trace = sorted(csv.DictReader(open(one(d_stats, "kernel_trace.csv"))), key=lambda r: int(r["Start_Timestamp"]))
+    times = kernels((r["Kernel_Name"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3) for r in trace)
+    pipes = kernels((x["name"], x) for x in dispatches(d_pipes))
+    counters = "SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_MFMA SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_LDS_BANK_CONFLICT"
+    run = (f"python3 -c \"import sys; sys.path.insert(0, '<repo>'); import perf.cases as C; c = [x for x in C.listed() if x['name'] == '{name}'][0]; "
+           f"s = C.prepare(c, 1); [C.run(s) for _ in range({passes})]; C.torch.cuda.synchronize()\"")
+    path = os.path.join(PROFILES, f"{name}_kernels.md")
+    with open(path, "w") as f:
+        f.write(f"# Kernels of the performance case {name}: time and pipe counters\n\n"
+                f"Commands (the summary is written by `python -m paper_2509_07120_amd.profile_summary case {name} <out>/stats <out>/pipes`):\n\n"
+                f"    cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats -d <out>/stats -o stats --output-format csv -- {run}\n"
+                f"    cd /tmp && export TMPDIR=/tmp && rocprofv3 --pmc {counters} -d <out>/pipes -o pmc --output-format csv -- {run}\n\n"
+                f"Means over the last {passes - skip} of {passes} passes; times of the first command.  Columns as in attention_cfg4_mfma_utilisation.md; MFMA pipe "
+                "busy is of the time that CUs are busy, the wave time columns are shares of the time that waves are resident.\n\n"
+                "| kernel | launches a pass | us a launch | MFMA pipe busy | wave time waiting | ready but not issued | issuing VALU | LDS bank conflict cycles |\n"
+                "|---|---|---|---|---|---|---|---|\n")
+        for n, us in times.items():
+            p = pipes.get(n, [])
+
+            def mean(k):
+                return sum(x.get(k, 0.0) for x in p) / max(1, len(p))
+
+            wave = mean("SQ_WAVE_CYCLES") or float("nan")
+            f.write(f"| `{n}` | {len(us) / (passes - skip):g} | {sum(us) / len(us):.2f} | "
+                    f"{mean('SQ_VALU_MFMA_BUSY_CYCLES') / (4.0 * mean('SQ_BUSY_CU_CYCLES') or float('nan')):.3f} | {mean('SQ_WAIT_ANY') / wave:.3f} | "
+                    f"{mean('SQ_WAIT_INST_ANY') / wave:.3f} | {mean('SQ_ACTIVE_INST_VALU') / wave:.3f} | {mean('SQ_LDS_BANK_CONFLICT'):.4g} |\n")
+    print(open(path).read())
+
+
 def main(argv) -> int:
     if len(argv) >= 4 and argv[1] == "stats":
         cmd_stats(argv[2], argv[3])
@@ -331,6 +375,8 @@ def main(argv) -> int:
         cmd_pipes(*argv[2:])
     elif len(argv) >= 4 and argv[1] == "topk":
         cmd_topk(argv[2], argv[3])
+    elif len(argv) >= 5 and argv[1] == "case":
+        cmd_case(argv[2], argv[3], argv[4])
     else:
         print(__doc__)
         return 2
