@@ -7,7 +7,8 @@
 // time, moves them into LDS of its own with direct-to-LDS loads two pieces ahead (reissued as soon as a piece's operands are
 // in registers) and waits for nobody.  Then the waves' states are summed through the same LDS, a quarter of the row by each.
 // Rows go to the XCDs in consecutive parts, so that an L2 holds the keys of few heads.
-// A step is now 0.52 us with one workgroup to a CU and 1.0 us with two: its products and exponentials, one after the other.  The layer of
+// A step is now 0.6 us with one workgroup to a CU and 1.1 us with two (57 steps a wave, 128 rows of 115 of 128 blocks 37.5 us, 512 rows 68): its products
+// and exponentials, one after the other.  The attention of
 // one frame (352 rows of 20 of 22 blocks) 21.7 -> 16.7 us, of which 0.8 by asking for the next piece under the products and not before
 // them (128 rows of 115 of 128 blocks 39.1 -> 37.5).  Tried: the products of one half of the queries between the exponentials
 // of the other, within a piece 17.7 us, across pieces with three buffers of K 18.2 to 19.0; K of the next piece read under the last
