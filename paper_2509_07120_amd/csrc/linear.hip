@@ -54,7 +54,8 @@ struct LinearArgs {
 // x Phi(x) = max(x, 0) - |x| h(|x|) with h(a) = Phi(-a), and h = 2^Q, Q a polynomial of degree 7 fitted to log2 Phi(-a) over [0, 7.5] (minimax, by
 // reweighted least squares): h is off by 2.2e-5 of itself there, a hundredth of the rounding to bf16 that follows; beyond, below 2^-43, Q goes
 // on falling and h ends as 0.  One exponential and no reciprocal: GELU shares the cycles of the products (62 a value; 94 with h = t P(t) exp(-a^2 / 2),
-// t = 1 / (1 + c a)).  Infinities and NaN come out as x Phi(x) does, -inf as its limit 0.
+// t = 1 / (1 + c a)).  Infinities and NaN come out as the product x Phi(x) does: -inf 0 is NaN, so that a sum
+// that has overflowed stays to be seen (inf is kept by clamping x from above alone).
 __device__ __forceinline__ float gelu(float x) {
   const float a = __builtin_fabsf(x);
   float q = -1.4221640e-6f;
@@ -65,7 +66,7 @@ __device__ __forceinline__ float gelu(float x) {
   q = fmaf(q, a, -0.45939937f);
   q = fmaf(q, a, -1.1508543f);
   q = fmaf(q, a, -1.0000257f);
-  return fmaf(-fminf(a, 30.f), __builtin_amdgcn_exp2f(q), fmaxf(x, 0.f));
+  return fmaf(-__builtin_fabsf(fminf(x, 30.f)), __builtin_amdgcn_exp2f(q), fmaxf(x, 0.f));
 }
 
 __device__ __forceinline__ float low_bf16(unsigned x) { return __uint_as_float(x << 16); }

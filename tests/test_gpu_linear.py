@@ -82,6 +82,17 @@ def test_gelu_of_values_that_are_not_numbers(B):
     assert bool(y[3].isnan().all()) and bool((y[4:] == 0).all())
 
 
+@pytest.mark.parametrize("N,K,F", [(8, 64, 64), (5170, 1024, 4288)])  # from the sums; from tiles that wait in registers
+def test_gelu_of_minus_infinity(B, N, K, F):
+    """NaN, as the product of x and Phi(x) and as torch's: the limit 0 would hide that a sum has overflowed."""
+    x, w = torch.zeros((N, K), device="cuda").bfloat16(), torch.zeros((F, K), device="cuda").bfloat16()
+    w[:, 0] = 1
+    x[0, 0], x[1, 0], x[2, 0] = -float("inf"), float("inf"), -30.5
+    y = B.bsga_linear(x, w, torch.zeros(F, device="cuda").bfloat16(), gelu=True)
+    assert bool(torch.nn.functional.gelu(x[0, 0]).isnan())
+    assert bool(y[0].isnan().all()) and bool((y[1] == float("inf")).all()) and bool((y[2:] == 0).all())
+
+
 @pytest.mark.parametrize("N,D", [(1, 8), (5, 512), (33, 520), (101, 1024), (7, 1536), (9, 4096)])
 def test_layer_norm(B, N, D):
     g = torch.Generator(device="cuda").manual_seed(N + D)
