@@ -77,3 +77,28 @@ def test_layer_replays_from_a_graph(B, use_noalloc):
         # eager work between replays (another stream of launches through the same library state)
         B.bsga_dense_attn(q[:1, :4096], k[:1, :4096], v[:1, :4096])
         torch.cuda.synchronize()
+
+
+def test_transformer_block_replays_from_a_graph(B):
+    """The block's own linear layers, layer norms, token order and residuals in a graph: every replay is bitwise the eager pass."""
+    N = 4 * 300
+    special = (torch.arange(N) % 300) < 5
+    blk = B.GlobalAttentionBlock(256, 4, 64, 0.9, 1.0, special=special, seed=1)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    data = [torch.randn((N, 256), generator=g, device="cuda").bfloat16() for _ in range(2)]
+    x = data[0].clone()
+    assert blk._folds(x)
+    want = [blk(d) for d in data]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = blk(x)
+    for rep, which in enumerate((0, 1, 1, 0, 1)):
+        x.copy_(data[which])
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[which]), rep
+        assert torch.equal(blk(data[1 - which]), want[1 - which])  # eager work between replays
+        torch.cuda.synchronize()
